@@ -1,15 +1,13 @@
-// Step 3 of the generalized sparse convolution (Eq. 2) and its input gradient, as one gather-GEMM kernel.
+// Step 3 of the generalized sparse convolution (Eq. 2) and its input gradient: dispatch over the gather-GEMM kernels,
+// the wavefront-private link-list kernel and the plain one.
 //
-// One workgroup owns a tile of destination rows (output rows for the forward pass, input rows for the data
-// gradient) and a slice of destination channels.  It keeps the tile's fp32 accumulator in LDS.  For every
-// kernel offset it takes the tile's compacted link list (source row, destination row), gathers the source
-// feature rows into LDS, multiplies 16-link blocks with the offset's weight matrix on the matrix cores and
-// adds each result row into the accumulator row of its destination.  A destination row belongs to exactly
-// one workgroup and appears at most once per offset, so nothing is atomic and the summation order is
-// fixed (results are reproducible run to run).  The accumulator is written once, rounded once.
+// All of them are destination stationary: a destination row (output row for the forward pass, input row for the
+// data gradient) belongs to exactly one workgroup, its fp32 accumulator stays on the chip, links are added in a
+// fixed order without atomics (results are reproducible run to run), and the result is written once, rounded once.
 #include <mutex>
 #include <type_traits>
 
+#include "sp_conv_tile.h"
 #include "sp_internal.h"
 
 namespace sp {
@@ -41,147 +39,10 @@ struct GatherArgs {
     int lds_per_wave;  // bytes of LDS of one wavefront in gather_wave_kernel
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, src_bytes, row_bytes;  // sizes of f / w / tl_src / tl_row for buffer addressing (< 4 GiB)
-    int wave_ok;       // host-side only: buffers small enough for 32-bit buffer addressing
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
 };
-
-// ---------------------------------------------------------------------------------------------------------
-// T: float or bf16_t.  CC: contraction channels.  COT: destination channels per workgroup (16, 32 or 64).
-// TR: destination rows per workgroup (64, 128 or 256).  4 wavefronts: COT/16 of them side by side over the
-// channel slice, the rest over alternating 16-link blocks.
-// ---------------------------------------------------------------------------------------------------------
-template <typename T, int CC, int COT, int TR>
-struct GatherCfg {
-    static constexpr int kElt = sizeof(T);
-    static constexpr int kNCS = COT / 16;            // wavefronts across channels
-    static constexpr int kNBS = 4 / kNCS;            // wavefronts across link blocks
-    static constexpr int kRowBytes = CC * kElt + 32; // staged row + 32 B pad (measured: b128 fragment reads then run at the full LDS rate)
-    static constexpr int kChunkRaw = (32 * 1024) / kRowBytes;
-    static constexpr int kChunk0 = kChunkRaw > TR ? TR : kChunkRaw;
-    static constexpr int kChunk = (kChunk0 / (16 * kNBS)) * (16 * kNBS) > 0 ? (kChunk0 / (16 * kNBS)) * (16 * kNBS) : 16 * kNBS;
-    static constexpr int kAccStride = COT + 4;       // floats
-    static constexpr int kPiecesPerRow = CC * kElt / 16;
-    static constexpr size_t kLds = (size_t)TR * kAccStride * 4 + (size_t)kChunk * kRowBytes + (size_t)kChunk * 2;
-};
-
-template <typename T, int CC, int COT, int TR>
-__global__ __launch_bounds__(256) void gather_mma_kernel(GatherArgs a) {
-    using Cfg = GatherCfg<T, CC, COT, TR>;
-    constexpr bool kIsF32 = std::is_same<T, float>::value;
-    constexpr int kGroup = kIsF32 ? 16 : 32;  // contraction channels consumed per A/B fragment load
-    constexpr int kGroups = CC / kGroup;
-    static_assert(CC % kGroup == 0, "contraction channels must fill whole fragment groups");
-    static_assert(COT == 16 || COT == 32 || COT == 64, "bad channel tile");
-
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* acc = reinterpret_cast<float*>(smem);
-    unsigned char* abuf = smem + (size_t)TR * Cfg::kAccStride * 4;
-    uint16_t* s_row = reinterpret_cast<uint16_t*>(abuf + (size_t)Cfg::kChunk * Cfg::kRowBytes);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cs = wave % Cfg::kNCS, bs = wave / Cfg::kNCS;
-    const int n16 = lane & 15, g = lane >> 4;
-    constexpr int kPerTile = kTileRows / TR;             // workgroups per 256-row tile
-    const int64_t tile = blockIdx.x / kPerTile;
-    const int q0 = (blockIdx.x % kPerTile) * (TR / 64);  // first 64-row sub-tile inside the 256-row tile
-    constexpr int kNQ = TR / 64;
-    const int co0 = blockIdx.y * COT;
-
-    for (int i = tid; i < TR * Cfg::kAccStride; i += 256) acc[i] = 0.f;
-
-    const T* __restrict__ F = static_cast<const T*>(a.f);
-    const T* __restrict__ W = static_cast<const T*>(a.w);
-
-    const int64_t wt0 = (int64_t)blockIdx.x * kNQ;       // first 64-row sub-tile of this workgroup
-    for (int kk = 0; kk < a.kvol; ++kk) {
-        // the lists are sub-tile-major: this workgroup's links of offset kk are kNQ separate segments
-        int sb[kNQ], sl[kNQ], mtot = 0;
-#pragma unroll
-        for (int q = 0; q < kNQ; ++q) {
-            sb[q] = a.tl_off[((wt0 + q) * a.kvol + kk) * kHalves];
-            sl[q] = a.tl_off[((wt0 + q) * a.kvol + kk + 1) * kHalves] - sb[q];
-            mtot += sl[q];
-        }
-        if (mtot == 0) continue;
-        auto entry = [&](int p) {
-            int q = 0;
-#pragma unroll
-            for (int j = 0; j < kNQ - 1; ++j)
-                if (q == j && p >= sl[j]) { p -= sl[j]; ++q; }
-            return sb[q] + p;
-        };
-        const int wk = a.flip ? a.kvol - 1 - kk : kk;
-        // this wavefront's weight slice: B[cc][n16] = W[wk][co0 + cs*16 + n16][cc]
-        const T* wrow = W + ((size_t)wk * a.co_total + co0 + cs * 16 + n16) * CC;
-        f32x4 bf[kIsF32 ? kGroups : 1];
-        bf16x8 bh[kIsF32 ? 1 : kGroups];
-#pragma unroll
-        for (int s = 0; s < kGroups; ++s) {
-            if constexpr (kIsF32)
-                bf[s] = *reinterpret_cast<const f32x4*>(wrow + s * 16 + g * 4);
-            else
-                bh[s] = *reinterpret_cast<const bf16x8*>(wrow + s * 32 + g * 8);
-        }
-        for (int c0 = 0; c0 < mtot; c0 += Cfg::kChunk) {
-            const int m = min(Cfg::kChunk, mtot - c0);
-            __syncthreads();  // everyone is done with the previous staging buffer and its accumulator updates
-            for (int idx = tid; idx < m * Cfg::kPiecesPerRow; idx += 256) {
-                const int p = idx / Cfg::kPiecesPerRow, piece = idx % Cfg::kPiecesPerRow;
-                const int32_t src = a.tl_src[entry(c0 + p)];
-                const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(F) +
-                                                                ((size_t)src * CC * Cfg::kElt + piece * 16));
-                *reinterpret_cast<uint4*>(abuf + (size_t)p * Cfg::kRowBytes + piece * 16) = v;
-            }
-            if (tid < m) s_row[tid] = (uint16_t)(a.tl_row[entry(c0 + tid)] - q0 * 64);
-            __syncthreads();
-            const int nblk = (m + 15) >> 4;
-            for (int blk = bs; blk < nblk; blk += Cfg::kNBS) {
-                f32x4 d = {0.f, 0.f, 0.f, 0.f};
-                const unsigned char* arow = abuf + (size_t)(blk * 16 + n16) * Cfg::kRowBytes;
-#pragma unroll
-                for (int s = 0; s < kGroups; ++s) {
-                    if constexpr (kIsF32) {
-                        const f32x4 av = *reinterpret_cast<const f32x4*>(arow + (s * 16 + g * 4) * 4);
-                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0], bf[s][0], d, 0, 0, 0);
-                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[1], bf[s][1], d, 0, 0, 0);
-                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[2], bf[s][2], d, 0, 0, 0);
-                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[3], bf[s][3], d, 0, 0, 0);
-                    } else {
-                        const bf16x8 av = *reinterpret_cast<const bf16x8*>(arow + (s * 32 + g * 8) * 2);
-                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bh[s], d, 0, 0, 0);
-                    }
-                }
-                // d[j] is link blk*16 + 4*g + j, channel n16 of this wavefront's slice
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int p = blk * 16 + g * 4 + j;
-                    if (p < m) acc[(int)s_row[p] * Cfg::kAccStride + cs * 16 + n16] += d[j];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const int64_t row0 = tile * kTileRows + q0 * 64;
-    constexpr int kQuads = COT / 4;
-    for (int idx = tid; idx < TR * kQuads; idx += 256) {
-        const int r = idx / kQuads, c4 = (idx % kQuads) * 4;
-        const int64_t row = row0 + r;
-        if (row >= a.n_rows) continue;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(acc + r * Cfg::kAccStride + c4);
-        if constexpr (kIsF32) {
-            *reinterpret_cast<f32x4*>(static_cast<float*>(a.g) + row * a.co_total + co0 + c4) = v;
-        } else {
-            ushort4 o;
-            o.x = f32_to_bf16(v[0]);
-            o.y = f32_to_bf16(v[1]);
-            o.z = f32_to_bf16(v[2]);
-            o.w = f32_to_bf16(v[3]);
-            *reinterpret_cast<ushort4*>(static_cast<bf16_t*>(a.g) + row * a.co_total + co0 + c4) = o;
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------------------------------------
 // Narrow-channel variant: every wavefront owns 64 destination rows (one sub-tile) and all COT channels of a
@@ -600,7 +461,7 @@ int launch_wave(GatherArgs a, hipStream_t s) {
     return SP_OK;  // wf goes back to the pool; later users are ordered behind this launch on the stream
 }
 
-// Plain kernel for channel counts the matrix-core kernel does not take: one thread per (row, channel),
+// Plain kernel for what the other kernels' 32-bit buffer offsets cannot address: one thread per (row, channel),
 // walking the neighbour table.  Weights as stored, W[kvol][cout][cin]; (w_cc, w_co) are the element strides
 // of the contraction / destination channel inside one offset's matrix.
 template <typename T>
@@ -648,42 +509,11 @@ __global__ __launch_bounds__(256) void transpose_w_kernel(const T* __restrict__ 
     wt[idx] = w[(size_t)k * per + (size_t)co * cin + ci];
 }
 
-template <typename T, int CC, int COT, int TR>
-int launch_gather(GatherArgs a, hipStream_t s) {
-    using Cfg = GatherCfg<T, CC, COT, TR>;
-    auto kern = gather_mma_kernel<T, CC, COT, TR>;
-    {
-        static std::mutex mu;
-        static bool attr_set = false;  // one-time opt-in to > 64 KB of dynamic LDS
-        std::lock_guard<std::mutex> lk(mu);
-        if (!attr_set) {
-            SP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)Cfg::kLds));
-            attr_set = true;
-        }
-    }
-    Buf wt;
-    if (a.w_transposed) {  // stored matrix is [cout = cc][cin = co]; the kernel wants [co][cc]
-        const int64_t n = (int64_t)a.kvol * CC * a.co_total;
-        wt = dev_alloc((size_t)n * sizeof(T), s);
-        if (!wt) return SP_ERR_ALLOC;
-        hipLaunchKernelGGL(transpose_w_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           static_cast<const T*>(a.w), ptr<T>(wt), a.kvol, CC, a.co_total);
-        a.w = wt->p;
-    }
-    const int64_t ntiles = (a.n_rows + kTileRows - 1) / kTileRows;
-    dim3 grid((unsigned)(ntiles * (kTileRows / TR)), (unsigned)(a.co_total / COT));
-    hipLaunchKernelGGL(kern, grid, dim3(256), Cfg::kLds, s, a);
-    SP_HIP(hipGetLastError());
-    return SP_OK;
-}
-
 // Narrow layers take the wavefront-private kernel, with the widest channel tile whose weight matrix fits in
 // 32 fragment registers (CC/group * COT/16 fragments of 4 registers each).  Returns that tile, or 0 when the
 // workgroup-cooperative kernel takes the layer.
-int wave_tile(int cc, int co, bool is_f32, bool wave_ok) {
+int wave_tile(int cc, int co, bool is_f32) {
     const int groups = cc / (is_f32 ? 16 : 32);
-    if (!wave_ok) return 0;
     if (groups * 4 <= 16 && co % 64 == 0) return 64;  // more than 8 fragments per lane: the matrix is held in two halves
     if (groups * 2 <= 8 && co % 32 == 0) return 32;
     if (groups <= 2 && (co == 16 || co == 48)) return 16;
@@ -693,18 +523,14 @@ int wave_tile(int cc, int co, bool is_f32, bool wave_ok) {
 template <typename T, int CC>
 int dispatch_co(const GatherArgs& a, hipStream_t s) {
     constexpr int kGroups = CC / (std::is_same<T, float>::value ? 16 : 32);
-    const int cot = wave_tile(CC, a.co_total, std::is_same<T, float>::value, a.wave_ok != 0);
+    const int cot = wave_tile(CC, a.co_total, std::is_same<T, float>::value);
     if constexpr (kGroups * 4 <= 16)
         if (cot == 64) return launch_wave<T, CC, 64>(a, s);
     if constexpr (kGroups * 2 <= 8)
         if (cot == 32) return launch_wave<T, CC, 32>(a, s);
     if constexpr (kGroups <= 2)
         if (cot == 16) return launch_wave<T, CC, 16>(a, s);
-    // Wide layers: workgroup-cooperative kernel; rows per workgroup keep accumulator + staging within
-    // ~64 KB so two workgroups share a CU
-    if (a.co_total % 64 == 0) return launch_gather<T, CC, 64, 128>(a, s);
-    if (a.co_total % 32 == 0) return launch_gather<T, CC, 32, 128>(a, s);
-    return launch_gather<T, CC, 16, 128>(a, s);
+    return fail(SP_ERR_UNSUPPORTED, "internal: no wavefront kernel for %d -> %d channels", CC, a.co_total);
 }
 
 template <typename T>
@@ -716,23 +542,129 @@ int dispatch_cc(int cc, const GatherArgs& a, hipStream_t s) {
         case 32: return dispatch_co<T, 32>(a, s);
         case 64: return dispatch_co<T, 64>(a, s);
         case 128: return dispatch_co<T, 128>(a, s);
-        case 256: return dispatch_co<T, 256>(a, s);
         default: break;
     }
     return SP_ERR_UNSUPPORTED;
 }
 
-bool mma_shape_ok(int cc, int co, sp_dtype dt) {
+bool wave_shape_ok(int cc, int co, sp_dtype dt) {
     if (co % 16 != 0) return false;
-    if (dt == SP_F32) return cc == 16 || cc == 32 || cc == 64 || cc == 128 || cc == 256;
-    return cc == 32 || cc == 64 || cc == 128 || cc == 256;
+    if (dt == SP_F32) return cc == 16 || cc == 32 || cc == 64;
+    return cc == 32 || cc == 64 || cc == 128;
+}
+
+// Slices of the contraction and channel tiles of gather_tile_kernel: the cut with the least padding, where a further
+// slice (another accumulator update per link) or channel tile (the rows are gathered again) counts as 8 more padded
+// channels (80 fp32 channels: 2 x 48 measured faster than 5 x 16).
+TileShape tile_shape(int cc, int co, bool is_f32) {
+    TileShape t{0, 0, 0, 0};
+    const int kcs[] = {64, 48, 32, 16}, ncss[] = {8, 4, 3, 2, 1};
+    int best = 1 << 30;
+    for (int kc : kcs) {
+        if (!is_f32 && kc % 32) continue;
+        const int n = (cc + kc - 1) / kc, cost = n * kc + 8 * (n - 1);
+        if (cost < best) {
+            best = cost;
+            t.kc = kc;
+            t.nsl = n;
+        }
+    }
+    best = 1 << 30;
+    for (int n : ncss) {
+        const int ny = (co + 16 * n - 1) / (16 * n), cost = ny * 16 * n + 8 * (ny - 1);
+        if (cost < best) {
+            best = cost;
+            t.ncs = n;
+            t.ny = ny;
+        }
+    }
+    return t;
+}
+
+size_t tile_weight_bytes(const TileShape& t, int kvol, size_t elt) {
+    return (size_t)kvol * t.ny * t.ncs * 16 * t.nsl * t.kc * elt;
+}
+
+// scratch (the allocation-free entry point): the weight copy goes there if it fits; if it does not, whole
+// fragments of wide layers are read from the stored weights in place (a fragment load is then 16 stretches of 64
+// bytes instead of 1 KB in a row), and narrow layers are refused, as they always were.
+int conv_gather_tile(const MapSide& side, int kvol, int64_t total_links, const void* d_f, const void* d_w, bool w_transposed,
+                     void* d_g, int cc, int co, sp_dtype dt, hipStream_t s, void* scratch, size_t scratch_bytes) {
+    const bool f32 = dt == SP_F32;
+    const int elt = f32 ? 4 : 2;
+    const TileShape t = tile_shape(cc, co, f32);
+    TileArgs a{};
+    a.tl_off = ptr<int32_t>(side.tl_off);
+    a.tl_src = ptr<int32_t>(side.tl_src);
+    a.tl_row = ptr<uint16_t>(side.tl_row);
+    a.f = d_f;
+    a.g = d_g;
+    a.n_rows = side.n_rows;
+    a.kvol = kvol;
+    a.cc = cc;
+    a.co = co;
+    a.flip = side.flip ? 1 : 0;
+    a.nsl = t.nsl;
+    a.row_bytes = (uint32_t)(cc * elt);
+    a.f_bytes = (uint32_t)((uint64_t)side.n_src * cc * elt);
+    a.src_bytes = (uint32_t)((uint64_t)total_links * 4);
+    a.dst_bytes = (uint32_t)((uint64_t)total_links * 2);
+    const size_t copy = tile_weight_bytes(t, kvol, elt);
+    const int groups = t.kc / (f32 ? 16 : 32);
+    Buf wf;
+    void* d_wf = scratch;
+    if (!scratch) {
+        wf = dev_alloc(copy, s);
+        if (!wf) return SP_ERR_ALLOC;
+        d_wf = wf->p;
+    } else if (copy > scratch_bytes) {
+        if (w_transposed || cc % t.kc || (cc < 64 && co % 32 == 0))
+            return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch", (long long)copy,
+                        scratch_bytes);
+        d_wf = nullptr;
+    }
+    if (d_wf) {
+        a.w = d_wf;
+        a.w_bytes = (uint32_t)copy;
+        a.w_s = 1024;
+        a.w_slice = (uint32_t)groups * a.w_s;
+        a.w_cs = (uint32_t)t.nsl * a.w_slice;
+        a.w_y = (uint32_t)t.ncs * a.w_cs;
+        a.w_k = (uint32_t)t.ny * a.w_y;
+        a.w_n16 = 16;
+        a.w_g = 256;
+        const int s_co = w_transposed ? 1 : cc, s_cc = w_transposed ? co : 1;
+        const dim3 grid((unsigned)((copy / 16 + 255) / 256));
+        if (f32)
+            hipLaunchKernelGGL(tile_weights_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(d_w),
+                               static_cast<float*>(d_wf), kvol, co, cc, s_co, s_cc, t.ny, t.ncs, t.nsl, groups);
+        else
+            hipLaunchKernelGGL(tile_weights_kernel<bf16_t>, grid, dim3(256), 0, s, static_cast<const bf16_t*>(d_w),
+                               static_cast<bf16_t*>(d_wf), kvol, co, cc, s_co, s_cc, t.ny, t.ncs, t.nsl, groups);
+    } else {
+        a.w = d_w;
+        a.w_bytes = (uint32_t)((uint64_t)kvol * cc * co * elt);
+        a.w_s = 64;
+        a.w_slice = (uint32_t)(t.kc * elt);
+        a.w_n16 = (uint32_t)(cc * elt);
+        a.w_cs = 16 * a.w_n16;
+        a.w_y = (uint32_t)t.ncs * a.w_cs;
+        a.w_k = (uint32_t)co * a.w_n16;
+        a.w_g = 16;
+    }
+    // 128-row tiles fill the 16-link blocks better, 64-row tiles give twice the workgroups and leave more LDS to
+    // the tiles with several accumulators (ncs < 3)
+    const int tr = t.ncs >= 3 && (side.n_rows + 127) / 128 * t.ny >= 512 ? 128 : 64;
+    return f32 ? conv_tile_f32(a, t.kc, t.ncs, tr, s) : conv_tile_bf16(a, t.kc, t.ncs, tr, s);
 }
 
 }  // namespace
 
 namespace {
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,
-// 2 workgroup-cooperative link lists, 3 plain.
+// 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain.  The wavefront-private kernel keeps the whole
+// weight matrix of a narrow layer in registers and is 5-20 % faster there (fp32 64 -> 64 on 5 M links: 620-680 us
+// against 665-710); everything else, wide or not a multiple of its tiles, takes the tile kernel.
 int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
     // Row-stationary kernel: it multiplies all kvol offsets of every row, the link-list kernels only the links
@@ -745,11 +677,12 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
         (side.tile_mask || (double)total_links >= dense_min_fill(cc) * (double)side.n_rows * kvol) &&
         (uint64_t)side.n_src * cc * elt < lim && (uint64_t)side.n_rows * kvol * 4 < lim && (uint64_t)kvol * cc * co * elt < lim)
         return 0;
-    if (mma_shape_ok(cc, co, dt)) {
-        const bool wave_ok = (uint64_t)side.n_src * cc * elt < 0xffffffffull && (uint64_t)total_links * 4 < 0xffffffffull;
-        return wave_tile(cc, co, dt == SP_F32, wave_ok) ? 1 : 2;
-    }
-    return 3;
+    // the link-list kernels address their buffers with 32-bit offsets
+    const uint64_t lim32 = 0xffffff00ull;
+    if ((uint64_t)side.n_src * cc * elt >= lim32 || (uint64_t)total_links * 4 >= lim32) return 3;
+    if (wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
+    if (tile_weight_bytes(tile_shape(cc, co, dt == SP_F32), kvol, elt) >= lim32) return 3;
+    return 2;
 }
 }  // namespace
 
@@ -774,7 +707,8 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         }
         return conv_gather_dense(side, kvol, d_f, w, d_g, cc, co, s);
     }
-    if (kind == 1 || kind == 2) {
+    if (kind == 2) return conv_gather_tile(side, kvol, total_links, d_f, d_w, w_transposed, d_g, cc, co, dt, s, scratch, scratch_bytes);
+    if (kind == 1) {
         GatherArgs a;
         a.tl_off = ptr<int32_t>(side.tl_off);
         a.tl_src = ptr<int32_t>(side.tl_src);
@@ -785,7 +719,6 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         a.scratch = scratch;
         a.scratch_bytes = scratch_bytes;
         const uint64_t fb = (uint64_t)side.n_src * cc * elt, sb = (uint64_t)total_links * 4;
-        a.wave_ok = fb < 0xffffffffull && sb < 0xffffffffull;
         a.f_bytes = (uint32_t)fb;
         a.src_bytes = (uint32_t)sb;
         a.row_bytes = (uint32_t)((uint64_t)total_links * 2);
@@ -875,7 +808,7 @@ int sp_conv_bwd_data(const sp_kmap_t* m, const void* d_dy, const void* d_w, void
 }
 
 const char* sp_conv_kernel_name(const sp_kmap_t* m, int32_t cin, int32_t cout, sp_dtype dt, int32_t direction) {
-    static const char* const names[] = {"gather_dense_kernel", "gather_wave_kernel", "gather_mma_kernel",
+    static const char* const names[] = {"gather_dense_kernel", "gather_wave_kernel", "gather_tile_kernel",
                                         "gather_plain_kernel"};
     if (!m || cin < 1 || cout < 1 || (dt != SP_F32 && dt != SP_BF16) || kmap_resolve(m) != SP_OK) return "";
     return direction == 0 ? names[select_gather(m->out_side, m->kvol, m->total, cin, cout, dt)]

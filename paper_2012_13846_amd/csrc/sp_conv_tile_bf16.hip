@@ -1,0 +1,23 @@
+// gather_tile_kernel for bf16 features.
+#include "sp_conv_tile.h"
+
+namespace sp {
+
+int conv_tile_bf16(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s) {
+#define SP_TILE(KC, NCS)                                                     \
+    if (kc == KC && ncs == NCS)                                              \
+    return tr == 128 ? launch_tile<uint16_t, KC, NCS, 128>(a, s) : launch_tile<uint16_t, KC, NCS, 64>(a, s)
+#define SP_TILES(KC)  \
+    SP_TILE(KC, 1);   \
+    SP_TILE(KC, 2);   \
+    SP_TILE(KC, 3);   \
+    SP_TILE(KC, 4);   \
+    SP_TILE(KC, 8)
+    SP_TILES(32);
+    SP_TILES(64);
+#undef SP_TILES
+#undef SP_TILE
+    return fail(SP_ERR_UNSUPPORTED, "internal: no bf16 tile kernel for slices of %d x %d", kc, ncs);
+}
+
+}  // namespace sp

@@ -1,0 +1,25 @@
+// gather_tile_kernel for fp32 features.
+#include "sp_conv_tile.h"
+
+namespace sp {
+
+int conv_tile_f32(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s) {
+#define SP_TILE(KC, NCS)                                                     \
+    if (kc == KC && ncs == NCS)                                              \
+    return tr == 128 ? launch_tile<float, KC, NCS, 128>(a, s) : launch_tile<float, KC, NCS, 64>(a, s)
+#define SP_TILES(KC)  \
+    SP_TILE(KC, 1);   \
+    SP_TILE(KC, 2);   \
+    SP_TILE(KC, 3);   \
+    SP_TILE(KC, 4);   \
+    SP_TILE(KC, 8)
+    SP_TILES(16);
+    SP_TILES(32);
+    SP_TILES(48);
+    SP_TILES(64);
+#undef SP_TILES
+#undef SP_TILE
+    return fail(SP_ERR_UNSUPPORTED, "internal: no fp32 tile kernel for slices of %d x %d", kc, ncs);
+}
+
+}  // namespace sp

@@ -183,6 +183,10 @@ bool dense_shape_ok(int cc, int co, sp_dtype dt);
 double dense_min_fill(int cc);
 int conv_gather_dense(const MapSide& side, int kvol, const void* d_f, const void* d_w, void* d_g, int cc, int co,
                       hipStream_t s);
+// link lists, any channel counts (sp_conv_tile.h): kc-wide slices of the contraction, ncs * 16 channels and tr rows a workgroup
+struct TileArgs;
+int conv_tile_f32(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s);
+int conv_tile_bf16(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s);
 int conv_wgrad(const sp_kmap* m, const void* d_x, const void* d_dy, float* d_dw, int cin, int cout, sp_dtype dt,
                hipStream_t s);
 }  // namespace sp
