@@ -139,10 +139,8 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
  * (SP_BF16: 16-bit bfloat16, results rounded to nearest even once); accumulation is always fp32.
  * Outputs are overwritten (rows / offsets without pairs become zero).  No host synchronisation.
  * All feature / weight / gradient pointers must be 16-byte aligned (SP_ERR_INVALID_ARG otherwise).
- * Matrix-core kernels exist for: forward / data gradient with a contraction width (cin for the forward pass,
- * cout for the data gradient) of 16 (fp32 only), 32, 64, 128 or 256 and the other width a multiple of 16;
- * weight gradient with both widths multiples of 16.  Every other channel count runs on a plain
- * one-thread-per-output kernel (correct, slow).
+ * Every channel count runs on the matrix cores; multiples of 16 (fp32) or 32 (bf16) without padding, 16-byte
+ * multiples of a row without element-wise loads.
  *
  *   sp_conv_fwd:        y[o,:]  = sum_k sum_{(i,o) in M_k} W_k   x[i,:]      x [n_in][cin]   -> y  [n_out][cout]
  *   sp_conv_bwd_data:   dx[i,:] = sum_k sum_{(i,o) in M_k} W_k^T dy[o,:]     dy [n_out][cout] -> dx [n_in][cin]

@@ -10,6 +10,10 @@
 // coalesced 16-byte loads into LDS (double buffered, one barrier per step) and reads MFMA fragments from
 // there: fp32 with one 4-byte read per lane (lane = channel, links in lane groups), bf16 with the LDS
 // transpose read, which hands a lane 4 consecutive links of one channel out of row-major storage.
+//
+// Channel counts that the tiles do not divide: a tile reaches past the last channel, loads there return zeros and the
+// reduction leaves the padding out (48 x 48 on 0.61 M links as one 48 x 48 tile instead of nine 16 x 16: 175 -> 59 us;
+// 32 x 3, which ran one thread per weight over the whole list: 24.5 ms -> 33 us).
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -102,12 +106,12 @@ __device__ __forceinline__ StripPlan strip_plan(const PlanArgs& pa, int s, int c
 // x 4 elements each x 16 block slices.
 // P: type of the partial blocks and of the sums (double on the fp32 path, see wgrad_staged_kernel).
 // first / count [S8][kvol]: number of offset k's first partial block in strip s and how many it has (written by
-// the staged kernel).
+// the staged kernel).  A block is cout_p x cin_p (per elements), the real cout x cin channels of it are written.
 template <typename P>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const P* __restrict__ part,
                                                            const int32_t* __restrict__ first,
                                                            const int32_t* __restrict__ count, int S8, int kvol, int per,
-                                                           float* __restrict__ dw) {
+                                                           int cin_p, int cin, int cout, float* __restrict__ dw) {
     typedef P Px4 __attribute__((ext_vector_type(4)));
     constexpr int kMaxStrips = 64;
     __shared__ int s_first[kMaxStrips], s_count[kMaxStrips];
@@ -134,7 +138,18 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const P* __restrict__
         Px4 t = red[0][el];
 #pragma unroll
         for (int i = 1; i < 16; ++i) t += red[i][el];
-        *reinterpret_cast<f32x4*>(dw + (size_t)k * per + e) = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+        // 4 elements of one row: padded rows are whole multiples of 16 channels
+        const int co = e / cin_p, ci = e - co * cin_p;
+        float* out = dw + (size_t)k * cin * cout + (size_t)co * cin + ci;
+        if (co < cout) {
+            if (cin % 4 == 0) {
+                if (ci < cin) *reinterpret_cast<f32x4*>(out) = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (ci + i < cin) out[i] = (float)t[i];
+            }
+        }
     }
 }
 
@@ -157,7 +172,8 @@ struct StagedCfg {
     static constexpr int kTA = COB / WCO / 16, kTB = CIB / WCI / 16;  // 16x16 tiles per wavefront
     // Row pad so that a fragment read (4 link rows x 16 lanes) hits disjoint banks: bf16 transpose reads take
     // 32 bytes per row, fp32 reads 64 * kT bytes per row (a lane reads its kT channels at once).
-    static constexpr int pad_f32(int kt) { return kt >= 4 ? 0 : 64 * kt; }
+    // (3 channels are read one by one, 12 bytes apart in the lanes: conflict-free with rows of 192 bytes in a row.)
+    static constexpr int pad_f32(int kt) { return kt >= 3 ? 0 : 64 * kt; }
     static constexpr int kPA = COB * kElt + (kIsF32 ? pad_f32(kTA) : 32);  // staged row pitch of dY rows
     static constexpr int kPB = CIB * kElt + (kIsF32 ? pad_f32(kTB) : 32);  // and of X rows
     static constexpr int kPiecesA = COB * kElt / 16, kPiecesB = CIB * kElt / 16;  // 16-byte pieces per row
@@ -177,15 +193,17 @@ struct StagedArgs {
     const int32_t* pair_out;
     const void* x;
     const void* dy;
-    void* part;   // partial blocks [slot][cout][cin], double (fp32 path) or float (bf16 path)
-    int cin, cout;
+    void* part;   // partial blocks [slot][cout_p][cin_p], double (fp32 path) or float (bf16 path)
+    int cin_p, cout_p;                     // channels, rounded up to whole tiles
+    uint32_t rowbytes_a, rowbytes_b;       // one row of dY, of X (multiples of 16)
     uint32_t x_bytes, dy_bytes, pair_bytes;  // buffer sizes (< 2 GiB each)
     PlanArgs plan;
     int32_t* first;   // [S8][kvol], for the reduction: written here by the workgroup in whose chunk a stretch starts
     int32_t* count;
 };
 
-template <typename T, int COB, int CIB, int WCO, int WCI, int WK, int kD>
+// kPad: the channel counts are not multiples of the tile; pieces past the end of a row are zeros.
+template <typename T, int COB, int CIB, int WCO, int WCI, int WK, int kD, bool kPad>
 __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(StagedArgs a) {
     using Cfg = StagedCfg<T, COB, CIB, WCO, WCI, WK>;
     constexpr bool kIsF32 = Cfg::kIsF32;
@@ -201,7 +219,7 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wk = wave % WK, wci = (wave / WK) % WCI, wco = wave / (WK * WCI);
     const int n16 = lane & 15, g = lane >> 4;
-    const int co0 = (tile / (a.cin / CIB)) * COB, ci0 = (tile % (a.cin / CIB)) * CIB;
+    const int co0 = (tile / (a.cin_p / CIB)) * COB, ci0 = (tile % (a.cin_p / CIB)) * CIB;
 
     // Buffer addressing: a lane whose link lies past the piece's end asks for an offset outside the buffer
     // and gets zeros, so the loop body has no branch around a load.
@@ -213,7 +231,7 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.pair_in), 0, (int)a.pair_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rPO =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.pair_out), 0, (int)a.pair_bytes, kRsrcFlags);
-    const uint32_t rowbytes_a = (uint32_t)a.cout * Cfg::kElt, rowbytes_b = (uint32_t)a.cin * Cfg::kElt;
+    const uint32_t rowbytes_a = a.rowbytes_a, rowbytes_b = a.rowbytes_b;
 
     // Loading: thread = (row of the step, sub); it loads the 16-byte pieces sub, sub + kTPR, ... of that row of
     // dY and of X: one row number and one address per operand, the pieces differ by constant offsets; four
@@ -248,12 +266,14 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
     auto issue_rows = [&](Regs& r, const RowAddr& ra) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kLoadsA; ++j) {
-            const bool mine = Cfg::kPiecesA % kTPR == 0 || ld_sub + j * kTPR < Cfg::kPiecesA;
+            const bool mine = (Cfg::kPiecesA % kTPR == 0 || ld_sub + j * kTPR < Cfg::kPiecesA) &&
+                              (!kPad || col_a + j * kTPR * 16 < rowbytes_a);
             r.va[j] = __builtin_amdgcn_raw_buffer_load_b128(rDY, mine ? ra.a + j * kTPR * 16 : kOutside, 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < kLoadsB; ++j) {
-            const bool mine = Cfg::kPiecesB % kTPR == 0 || ld_sub + j * kTPR < Cfg::kPiecesB;
+            const bool mine = (Cfg::kPiecesB % kTPR == 0 || ld_sub + j * kTPR < Cfg::kPiecesB) &&
+                              (!kPad || col_b + j * kTPR * 16 < rowbytes_b);
             r.vb[j] = __builtin_amdgcn_raw_buffer_load_b128(rX, mine ? ra.b + j * kTPR * 16 : kOutside, 0, 0);
         }
     };
@@ -296,18 +316,22 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
         if constexpr (kIsF32) {
             // MFMA 16x16x4: lane (index n16 in the tile, link g) of both operands; the fragments of the next 4
             // links are read while the current ones are multiplied
-            typedef float fvA __attribute__((ext_vector_type(kTA == 3 ? 4 : kTA)));
-            typedef float fvB __attribute__((ext_vector_type(kTB == 3 ? 4 : kTB)));
+            typedef float fvA __attribute__((ext_vector_type(kTA == 3 ? 1 : kTA)));
+            typedef float fvB __attribute__((ext_vector_type(kTB == 3 ? 1 : kTB)));
             float av[2][kTA], bv[2][kTB];
             auto read = [&](int j, float (&x)[kTA], float (&y)[kTB]) __attribute__((always_inline)) {
-                if constexpr (kTA == 1) x[0] = *reinterpret_cast<const float*>(A + 4 * j * kPA);
-                else {
+                if constexpr (kTA == 1 || kTA == 3) {
+#pragma unroll
+                    for (int ta = 0; ta < kTA; ++ta) x[ta] = *reinterpret_cast<const float*>(A + 4 * j * kPA + ta * 4);
+                } else {
                     const fvA v = *reinterpret_cast<const fvA*>(A + 4 * j * kPA);
 #pragma unroll
                     for (int ta = 0; ta < kTA; ++ta) x[ta] = v[ta];
                 }
-                if constexpr (kTB == 1) y[0] = *reinterpret_cast<const float*>(B + 4 * j * kPB);
-                else {
+                if constexpr (kTB == 1 || kTB == 3) {
+#pragma unroll
+                    for (int tb = 0; tb < kTB; ++tb) y[tb] = *reinterpret_cast<const float*>(B + 4 * j * kPB + tb * 4);
+                } else {
                     const fvB v = *reinterpret_cast<const fvB*>(B + 4 * j * kPB);
 #pragma unroll
                     for (int tb = 0; tb < kTB; ++tb) y[tb] = v[tb];
@@ -456,7 +480,7 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
         // slice.  The WK link slices are added in order.
         auto chan = [&](int t, int m, int kt) { return kIsF32 ? m * kt + t : t * 16 + m; };
         typedef Part Partx4 __attribute__((ext_vector_type(4)));
-        Part* dst = static_cast<Part*>(a.part) + (size_t)slot * a.cout * a.cin;
+        Part* dst = static_cast<Part*>(a.part) + (size_t)slot * a.cout_p * a.cin_p;
         // Large tiles: the lane's position is made opaque here, or the store addresses below are computed before the
         // main loop, where the registers that hold them get spilled and reloaded between the gathers (a reload waits
         // for every load issued before it; 256 x 256) or cost two thirds of the wavefronts per SIMD (128 x 128).
@@ -483,7 +507,7 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
             }
             for (int e = tid * 4; e < COB * CIB; e += kThreads * 4) {
                 const int co = e / CIB, ci = e % CIB;
-                *reinterpret_cast<Partx4*>(dst + (size_t)(co0 + co) * a.cin + ci0 + ci) = *reinterpret_cast<const Partx4*>(red + e);
+                *reinterpret_cast<Partx4*>(dst + (size_t)(co0 + co) * a.cin_p + ci0 + ci) = *reinterpret_cast<const Partx4*>(red + e);
             }
         } else {
 #pragma unroll
@@ -492,14 +516,32 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
                 for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        dst[(size_t)(co0 + wco * kTA * 16 + chan(ta, g_here * 4 + j, kTA)) * a.cin + ci0 + wci * kTB * 16 +
+                        dst[(size_t)(co0 + wco * kTA * 16 + chan(ta, g_here * 4 + j, kTA)) * a.cin_p + ci0 + wci * kTB * 16 +
                             chan(tb, n16_here, kTB)] = piece_val(ta, tb, j);
         }
         __syncthreads();  // the next piece reuses the staging buffers
     }
 }
 
-// Plain kernel for channel counts that are not multiples of 16: one thread per weight element.
+// Rows of c channels -> rows of cp channels (cp * sizeof(T) a multiple of 16), zeros behind: for rows that 16-byte
+// loads cannot take apart.  One pass over a few channels per row, a small part of the weight gradient's time.
+template <typename T>
+__global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ src, T* __restrict__ dst, int64_t n, int c, int cp) {
+    constexpr int kN = 16 / (int)sizeof(T);
+    const int pieces = cp / kN;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n * pieces) return;
+    const int64_t r = i / pieces;
+    const int c0 = (int)(i - r * pieces) * kN;
+    T v[kN];
+#pragma unroll
+    for (int j = 0; j < kN; ++j) v[j] = c0 + j < c ? src[r * c + c0 + j] : (T)0;
+    uint4 raw;
+    __builtin_memcpy(&raw, v, 16);
+    *reinterpret_cast<uint4*>(dst + r * cp + c0) = raw;
+}
+
+// Plain kernel for what the staged kernel's 32-bit offsets cannot address: one thread per weight element.
 template <typename T>
 __global__ __launch_bounds__(256) void wgrad_plain_kernel(const int32_t* __restrict__ pair_in,
                                                           const int32_t* __restrict__ pair_out,
@@ -517,10 +559,12 @@ __global__ __launch_bounds__(256) void wgrad_plain_kernel(const int32_t* __restr
     dw[(size_t)k * cin * cout + e] = s;
 }
 
-template <typename T, int COB, int CIB, int WCO, int WCI, int WK, int kD>
-int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int cout, float* dw, hipStream_t s) {
+// x / dy: rows of cin_row / cout_row channels (whole 16-byte pieces; channels past cin / cout are zeros)
+template <typename T, int COB, int CIB, int WCO, int WCI, int WK, int kD, bool kPad>
+int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int cout, int cin_row, int cout_row, float* dw,
+                  hipStream_t s) {
     using Cfg = StagedCfg<T, COB, CIB, WCO, WCI, WK>;
-    auto kern = wgrad_staged_kernel<T, COB, CIB, WCO, WCI, WK, kD>;
+    auto kern = wgrad_staged_kernel<T, COB, CIB, WCO, WCI, WK, kD, kPad>;
     static std::mutex mu;  // guards the two one-time queries below
     static bool attr_set = false;  // one-time opt-in to > 64 KB of dynamic LDS
     static int occ = 0;  // workgroups of this kernel that fit a CU: asked once
@@ -537,12 +581,13 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
             occ = q < 1 ? 1 : q;
         }
     }
-    const int kvol = m->kvol, per = cin * cout;
+    const int cin_p = (cin + CIB - 1) / CIB * CIB, cout_p = (cout + COB - 1) / COB * COB;
+    const int kvol = m->kvol, per = cin_p * cout_p;
     StagedArgs a;
     PlanArgs& pa = a.plan;
     pa.kvol = kvol;
     pa.pair_stride = (int)m->pair_stride;
-    pa.tiles = (cout / COB) * (cin / CIB);
+    pa.tiles = (cout_p / COB) * (cin_p / CIB);
     for (int k = 0; k <= kvol; ++k) pa.koff[k] = (int32_t)m->koff[k];
     // Strips: one per XCD.  (More strips, sized so that a strip's rows fit an XCD's L2, were measured slower on
     // every workload, 4-19 %: each strip adds one partial block per offset, and the rows' L2 hits did not pay for
@@ -571,62 +616,109 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
     a.x = x;
     a.dy = dy;
     a.part = part->p;
-    a.cin = cin;
-    a.cout = cout;
-    a.x_bytes = (uint32_t)((uint64_t)m->n_in * cin * sizeof(T));
-    a.dy_bytes = (uint32_t)((uint64_t)m->n_out * cout * sizeof(T));
+    a.cin_p = cin_p;
+    a.cout_p = cout_p;
+    a.rowbytes_a = (uint32_t)(cout_row * sizeof(T));
+    a.rowbytes_b = (uint32_t)(cin_row * sizeof(T));
+    a.x_bytes = (uint32_t)((uint64_t)m->n_in * a.rowbytes_b);
+    a.dy_bytes = (uint32_t)((uint64_t)m->n_out * a.rowbytes_a);
     a.pair_bytes = (uint32_t)((uint64_t)kvol * m->pair_stride * 4);
     const int64_t wgs = (int64_t)pa.S8 * nc * pa.tiles;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(Cfg::kThreads), Cfg::kLds, s, a);
     if constexpr (Cfg::kIsF32)
         hipLaunchKernelGGL(wgrad_reduce_kernel<double>, dim3(per / 64, kvol), dim3(256), 0, s, ptr<double>(part), a.first,
-                           a.count, pa.S8, kvol, per, dw);
+                           a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
     else
         hipLaunchKernelGGL(wgrad_reduce_kernel<float>, dim3(per / 64, kvol), dim3(256), 0, s, ptr<float>(part), a.first,
-                           a.count, pa.S8, kvol, per, dw);
+                           a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
     SP_HIP(hipGetLastError());
     return SP_OK;
 }
 
-// largest of 128, 64, 32, 16 dividing c (c is a multiple of 16)
-int channel_block(int c) { return c % 128 == 0 ? 128 : (c % 64 == 0 ? 64 : (c % 32 == 0 ? 32 : 16)); }
+// Channel tile of c channels: the widest of 128, 64, 48, 32, 16 that divides them, else the one of 64, 48, 32, 16
+// that pads least (a further tile gathers the other operand's rows again, worth about 8 padded channels).
+int channel_block(int c) {
+    for (int b : {128, 64, 48, 32, 16})
+        if (c % b == 0) return b;
+    int best = 0, cost = 1 << 30;
+    for (int b : {64, 48, 32, 16}) {
+        const int t = (c + b - 1) / b, k = t * b + 8 * (t - 1);
+        if (k < cost) {
+            cost = k;
+            best = b;
+        }
+    }
+    return best;
+}
 
 template <typename T>
 int wgrad_typed(const sp_kmap* m, const void* x, const void* dy, float* dw, int cin, int cout, hipStream_t s) {
+    constexpr int kN = 16 / (int)sizeof(T);
     const int kvol = m->kvol;
+    const int cin_row = (cin + kN - 1) / kN * kN, cout_row = (cout + kN - 1) / kN * kN;
     const uint64_t lim = 0x7fffffffull;  // the staged kernel addresses its buffers with 32-bit offsets
-    const bool small = (uint64_t)m->n_in * cin * sizeof(T) < lim && (uint64_t)m->n_out * cout * sizeof(T) < lim &&
+    const bool small = (uint64_t)m->n_in * cin_row * sizeof(T) < lim && (uint64_t)m->n_out * cout_row * sizeof(T) < lim &&
                        (uint64_t)kvol * m->pair_stride * 4 < lim;
-    if (cin % 16 || cout % 16 || !small || m->total == 0 || kvol > 128) {
+    if (!small || m->total == 0 || kvol > 128) {
         hipLaunchKernelGGL(wgrad_plain_kernel<T>, dim3((cin * cout + 255) / 256, kvol), dim3(256), 0, s,
                            ptr<int32_t>(m->pair_in), ptr<int32_t>(m->pair_out), ptr<int32_t>(m->d_koff), m->pair_stride,
                            static_cast<const T*>(x), static_cast<const T*>(dy), cin, cout, dw);
         SP_HIP(hipGetLastError());
         return SP_OK;
     }
+    // rows that are not whole 16-byte pieces: a padded copy
+    Buf px, pdy;
+    auto padded = [&](const void* p, int64_t n, int c, int cp, Buf& b) -> const void* {
+        if (c == cp || n == 0) return p;
+        b = dev_alloc((size_t)n * cp * sizeof(T), s);
+        if (!b) return nullptr;
+        hipLaunchKernelGGL(pad_rows_kernel<T>, dim3((unsigned)((n * (cp / kN) + 255) / 256)), dim3(256), 0, s,
+                           static_cast<const T*>(p), ptr<T>(b), n, c, cp);
+        return b->p;
+    };
+    x = padded(x, m->n_in, cin, cin_row, px);
+    dy = padded(dy, m->n_out, cout, cout_row, pdy);
+    if (!x || !dy) return SP_ERR_ALLOC;
     int cob = channel_block(cout), cib = channel_block(cin);
     if (cob == 128 && cib < 64) cob = 64;  // 128-wide tiles only in the combinations instantiated below
     if (cib == 128 && cob < 64) cib = 64;
+    const bool pad = cin % cib != 0 || cout % cob != 0;
+    if (pad && cob == 128) cob = 64;
+    if (pad && cib == 128) cib = 64;
     // register stages of gathered rows: two for bf16 (a step's arithmetic is short next to the gather latency)
     constexpr int kD = sizeof(T) == 2 ? 2 : 1;
-#define SP_STAGED(COB, CIB, WCO, WCI, WK) \
-    if (cob == COB && cib == CIB) return launch_staged<T, COB, CIB, WCO, WCI, WK, kD>(m, x, dy, cin, cout, dw, s)
+#define SP_EXACT(COB, CIB, WCO, WCI, WK)                                                        \
+    if (!pad && cob == COB && cib == CIB)                                                       \
+    return launch_staged<T, COB, CIB, WCO, WCI, WK, kD, false>(m, x, dy, cin, cout, cin_row, cout_row, dw, s)
+#define SP_STAGED(COB, CIB, WCO, WCI, WK)                                                       \
+    SP_EXACT(COB, CIB, WCO, WCI, WK);                                                           \
+    if (pad && cob == COB && cib == CIB)                                                        \
+    return launch_staged<T, COB, CIB, WCO, WCI, WK, kD, true>(m, x, dy, cin, cout, cin_row, cout_row, dw, s)
     if constexpr (sizeof(T) == 2) {  // bf16: the whole 256 x 256 matrix in one workgroup, every row gathered once
-        if (cout % 256 == 0 && cin % 256 == 0) return launch_staged<T, 256, 256, 2, 4, 1, 1>(m, x, dy, cin, cout, dw, s);
+        if (cout % 256 == 0 && cin % 256 == 0)
+            return launch_staged<T, 256, 256, 2, 4, 1, 1, false>(m, x, dy, cin, cout, cin, cout, dw, s);
     }
-    SP_STAGED(128, 128, 2, 2, 1);
-    SP_STAGED(128, 64, 2, 1, 2);
-    SP_STAGED(64, 128, 1, 2, 2);
+    SP_EXACT(128, 128, 2, 2, 1);
+    SP_EXACT(128, 64, 2, 1, 2);
+    SP_EXACT(64, 128, 1, 2, 2);
     SP_STAGED(64, 64, 2, 1, 2);
+    SP_STAGED(64, 48, 2, 1, 2);
+    SP_STAGED(48, 64, 1, 2, 2);
     SP_STAGED(64, 32, 2, 1, 2);
     SP_STAGED(32, 64, 1, 2, 2);
     SP_STAGED(64, 16, 2, 1, 2);
     SP_STAGED(16, 64, 1, 2, 2);
+    SP_STAGED(48, 48, 1, 1, 2);
+    SP_STAGED(48, 32, 1, 1, 2);
+    SP_STAGED(32, 48, 1, 1, 2);
+    SP_STAGED(48, 16, 1, 1, 4);
+    SP_STAGED(16, 48, 1, 1, 4);
     SP_STAGED(32, 32, 1, 1, 2);
     SP_STAGED(32, 16, 1, 1, 4);
     SP_STAGED(16, 32, 1, 1, 4);
     SP_STAGED(16, 16, 1, 1, 4);
 #undef SP_STAGED
+#undef SP_EXACT
     return fail(SP_ERR_UNSUPPORTED, "no weight-gradient kernel for %d x %d channels", cout, cin);
 }
 

@@ -1,0 +1,36 @@
+"""Channel counts that no 16-, 32- or 64-channel tile divides, and the row counts where tiles of 64 and 128 rows begin and
+end: forward and both gradients against the fp64 oracle.  Tolerances are the parity bounds (fp32 1e-5, bf16 2e-2 of one
+rounding to 8 bits, see util.py): channel counts change nothing about how a term is rounded."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import conv_case, full_cubes, random_coords, sp  # noqa: F401  (sp: the binding fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cin,cout", [(1, 1), (3, 16), (5, 64), (6, 32), (7, 13), (17, 33), (20, 24), (24, 48), (48, 20),
+                                      (48, 48), (65, 40), (80, 40), (100, 130), (300, 31)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_any_channel_count(sp, cin, cout, bf16):  # noqa: F811
+    conv_case(sp, random_coords(31 + cin, 1500, 12, batches=2, lo=-5), 1, 3, 1, 1, cin, cout, bf16, seed=7 * cin + cout)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 257])
+def test_ragged_tiles(sp, n):  # noqa: F811
+    raw = np.unique(random_coords(5 + n, 4 * n, max(2, int(round(n ** (1 / 3))) + 1), batches=2), axis=0)[:n]
+    conv_case(sp, raw, 1, 3, 1, 1, 20, 128, False, seed=n)
+
+
+@pytest.mark.parametrize("K,stride,cin,cout,transposed", [(5, 1, 40, 24, False), (2, 2, 24, 48, False), (2, 2, 48, 24, True),
+                                                          (3, 2, 5, 48, False), (1, 1, 33, 17, False)])
+def test_other_kernels_and_strides(sp, K, stride, cin, cout, transposed):  # noqa: F811
+    for bf16 in (False, True):
+        conv_case(sp, full_cubes(8, 2), 1, K, stride, 1, cin, cout, bf16, seed=K + cin, transposed=transposed)
+
+
+@pytest.mark.parametrize("cin,cout", [(128, 128), (256, 48), (64, 80)])
+def test_128_row_tiles_fp32(sp, cin, cout):  # noqa: F811
+    # enough rows that the 128-row tiles are chosen; rows not a multiple of 64
+    raw = np.unique(random_coords(77, 90000, 60, batches=3), axis=0)[:65601]
+    conv_case(sp, raw[np.random.default_rng(2).permutation(len(raw))], 1, 3, 1, 1, cin, cout, False, seed=cin + cout)
