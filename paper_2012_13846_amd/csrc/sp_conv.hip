@@ -26,9 +26,9 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {  // round to nearest ev
 }
 
 struct GatherArgs {
-    const int32_t* tl_off;
-    const int32_t* tl_src;
-    const uint16_t* tl_row;
+    const int32_t* off;  // the side's lists (MapSide)
+    const int32_t* src;
+    const int32_t* dst;
     const void* f;   // source features [n_src][CC]
     const void* w;   // weights [kvol][co_total][CC] (contraction index fastest)
     void* g;         // destination features [n_rows][co_total]
@@ -38,7 +38,7 @@ struct GatherArgs {
     int flip;        // weight matrix of list k is kvol-1-k
     int lds_per_wave;  // bytes of LDS of one wavefront in gather_wave_kernel
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
-    uint32_t f_bytes, w_bytes, src_bytes, row_bytes;  // sizes of f / w / tl_src / tl_row for buffer addressing (< 4 GiB)
+    uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
@@ -46,8 +46,7 @@ struct GatherArgs {
 
 // ---------------------------------------------------------------------------------------------------------
 // Narrow-channel variant: every wavefront owns 64 destination rows (one sub-tile) and all COT channels of a
-// channel tile, and runs on its own: no workgroup barrier anywhere.  Its links of all offsets are one
-// contiguous stretch of the sub-tile-major lists.
+// channel tile, and runs on its own: no workgroup barrier anywhere.
 //
 //  - The wavefront first cuts its links into blocks of up to 16 links of one offset and writes one packed
 //    descriptor per block into LDS, so that block b+n is addressable without walking a cursor.
@@ -76,9 +75,9 @@ struct WaveCfg {
     static constexpr int kRowBytes = CC * (int)sizeof(T); // one source row
     static constexpr int kPieces = kRowBytes / 16;        // 16-byte pieces per source row
     static constexpr int kXStride = kRowBytes + 32;       // staged row + pad (b128 fragment reads at the full LDS rate)
-    static constexpr int kXBytes = 16 * kXStride;
+    static constexpr int kXBytes = 16 * kXStride - 32;  // the last row needs no pad
     static constexpr int kXLoads = (16 * kPieces + 63) / 64;  // coalesced load instructions per 16-link block
-    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + ((kvol * 4 + 3) / 4) * 16; }
+    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + ((kvol * 5 + 3) / 4) * 16; }  // 4 descriptors and a begin per offset
     // fragment-major weights: [kvol][co_total/COT][kNCT][kGroups][64 lanes][16 bytes]
     static constexpr size_t kWFragBytesPerOffsetTile = (size_t)kNCT * kGroups * 64 * 16;
 };
@@ -121,25 +120,26 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     const int64_t nwt = (a.n_rows + 63) / 64;
     const int half = blockIdx.x >= nwt ? 1 : 0;     // which 32-row half it takes if the sub-tile is split
     const int64_t wt = (int64_t)blockIdx.x - (half ? nwt : 0);  // this wavefront's sub-tile
+    const int kvol = a.kvol;
     unsigned char* base = smem;
     float* acc = reinterpret_cast<float*>(base);
     unsigned char* xbuf = base + Cfg::kAccBytes;
-    int* s_blk = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);
+    int* s_beg = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);  // per offset: where this wavefront's links begin
+    int* s_blk = s_beg + kvol;
     const int n16 = lane & 15, g = lane >> 4;
-    const int kvol = a.kvol;
 
     for (int i = lane; i < Cfg::kAccBytes / 16; i += 64) reinterpret_cast<f32x4*>(acc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // ---- block descriptors: k | (links-1) << 7 | (blocks left in this offset - 1) << 11 | (first link - off0) << 13
+    // ---- block descriptors: k | (links-1) << 7 | (block of the offset) << 11
     // Two wavefronts are launched per sub-tile.  When the launch is small (a.split_blocks set by the host)
     // and the sub-tile is long, each takes one 32-row half, which halves the longest dependent chain of the
     // launch; otherwise the first takes all 64 rows and the second leaves.
-    const int32_t* __restrict__ offp = a.tl_off + wt * kvol * kHalves;
-    const int off0 = offp[0];
+    const int32_t* __restrict__ offp = a.off + wt * kvol * kHalves;
+    const int32_t* __restrict__ offn = offp + kvol * kHalves;  // the next sub-tile's begins: this one's ends
     int nblk_whole = 0;
     for (int kb = 0; kb < kvol; kb += 64) {
         const int k = kb + lane;
-        int nb = k < kvol ? (offp[(k + 1) * kHalves] - offp[k * kHalves] + 15) >> 4 : 0;
+        int nb = k < kvol ? (offn[k * kHalves] - offp[k * kHalves] + 15) >> 4 : 0;
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) nb += __shfl_xor(nb, d, 64);
         nblk_whole += nb;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         int o0 = 0, o1 = 0;
         if (k < kvol) {
             o0 = offp[k * kHalves + (split ? half : 0)];
-            o1 = offp[k * kHalves + (split ? half + 1 : kHalves)];
+            o1 = split && half == 0 ? offp[k * kHalves + 1] : offn[k * kHalves];
         }
         const int cnt = o1 - o0, nb = (cnt + 15) >> 4;
         int inc = nb;
@@ -164,8 +164,9 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
             if (lane >= d) inc += t;
         }
         const int ex = nblk + inc - nb;
+        if (k < kvol) s_beg[k] = o0;
         for (int i = 0; i < nb; ++i)
-            s_blk[ex + i] = k | ((min(16, cnt - 16 * i) - 1) << 7) | ((nb - i - 1) << 11) | ((o0 - off0 + 16 * i) << 13);
+            s_blk[ex + i] = k | ((min(16, cnt - 16 * i) - 1) << 7) | (i << 11);
         nblk += __shfl(inc, 63, 64);
     }
     wave_sync();
@@ -176,9 +177,9 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     const __amdgpu_buffer_rsrc_t rF = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.f), 0, (int)a.f_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.w), 0, (int)a.w_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rSrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.tl_src), 0, (int)a.src_bytes, kRsrcFlags);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.src), 0, (int)a.list_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rRow =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.tl_row), 0, (int)a.row_bytes, kRsrcFlags);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.dst), 0, (int)a.list_bytes, kRsrcFlags);
     const uint32_t w_tile_off = (uint32_t)(blockIdx.y * Cfg::kWFragBytesPerOffsetTile);
     const uint32_t w_offset_stride = (uint32_t)((a.co_total / COT) * Cfg::kWFragBytesPerOffsetTile);
 
@@ -213,11 +214,11 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     // the same weight lines at the same moment, was measured and is slower: in step, they share the lines in L1.)
     auto load_entries = [&](Slot& sl, int b) __attribute__((always_inline)) {
         sl.de = s_blk[min(b, last)];
-        const int cnt = ((sl.de >> 7) & 15) + 1, e0 = off0 + (sl.de >> 13);
+        const int cnt = ((sl.de >> 7) & 15) + 1, e0 = s_beg[sl.de & 127] + ((sl.de >> 11) << 4);
 #pragma unroll
         for (int t = 0; t < kXLoads; ++t)
             sl.esrc[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rSrc, (e0 + min((t * 64 + lane) / kPieces, cnt - 1)) * 4, 0, 0);
-        sl.erow = (int)__builtin_amdgcn_raw_buffer_load_b16(rRow, (e0 + min(n16, cnt - 1)) * 2, 0, 0);
+        sl.erow = (int)__builtin_amdgcn_raw_buffer_load_b32(rRow, (e0 + min(n16, cnt - 1)) * 4, 0, 0);
     };
     auto issue_gather = [&](Slot& sl) __attribute__((always_inline)) {
         sl.dc = sl.de;
@@ -588,15 +589,15 @@ size_t tile_weight_bytes(const TileShape& t, int kvol, size_t elt) {
 // scratch (the allocation-free entry point): the weight copy goes there if it fits; if it does not, whole
 // fragments of wide layers are read from the stored weights in place (a fragment load is then 16 stretches of 64
 // bytes instead of 1 KB in a row), and narrow layers are refused, as they always were.
-int conv_gather_tile(const MapSide& side, int kvol, int64_t total_links, const void* d_f, const void* d_w, bool w_transposed,
+int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed,
                      void* d_g, int cc, int co, sp_dtype dt, hipStream_t s, void* scratch, size_t scratch_bytes) {
     const bool f32 = dt == SP_F32;
     const int elt = f32 ? 4 : 2;
     const TileShape t = tile_shape(cc, co, f32);
     TileArgs a{};
-    a.tl_off = ptr<int32_t>(side.tl_off);
-    a.tl_src = ptr<int32_t>(side.tl_src);
-    a.tl_row = ptr<uint16_t>(side.tl_row);
+    a.off = ptr<int32_t>(side.off);
+    a.src = ptr<int32_t>(side.src);
+    a.dst = ptr<int32_t>(side.dst);
     a.f = d_f;
     a.g = d_g;
     a.n_rows = side.n_rows;
@@ -607,8 +608,7 @@ int conv_gather_tile(const MapSide& side, int kvol, int64_t total_links, const v
     a.nsl = t.nsl;
     a.row_bytes = (uint32_t)(cc * elt);
     a.f_bytes = (uint32_t)((uint64_t)side.n_src * cc * elt);
-    a.src_bytes = (uint32_t)((uint64_t)total_links * 4);
-    a.dst_bytes = (uint32_t)((uint64_t)total_links * 2);
+    a.list_bytes = (uint32_t)((uint64_t)side.pitch * kvol * 4);
     const size_t copy = tile_weight_bytes(t, kvol, elt);
     const int groups = t.kc / (f32 ? 16 : 32);
     Buf wf;
@@ -679,7 +679,7 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
         return 0;
     // the link-list kernels address their buffers with 32-bit offsets
     const uint64_t lim32 = 0xffffff00ull;
-    if ((uint64_t)side.n_src * cc * elt >= lim32 || (uint64_t)total_links * 4 >= lim32) return 3;
+    if ((uint64_t)side.n_src * cc * elt >= lim32 || (uint64_t)side.pitch * kvol * 4 >= lim32) return 3;
     if (wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
     if (tile_weight_bytes(tile_shape(cc, co, dt == SP_F32), kvol, elt) >= lim32) return 3;
     return 2;
@@ -694,7 +694,9 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
     if (scratch && w_transposed) return fail(SP_ERR_UNSUPPORTED, "no allocation-free path for transposed weights");
     const size_t elt = dt == SP_F32 ? 4 : 2;
     const int kind = select_gather(side, kvol, total_links, cc, co, dt);
+    if (kind == 1 || kind == 2) SP_TRY(need_lists(side, kvol, s));
     if (kind == 0) {
+        SP_TRY(need_classes(side, s));
         Buf wt;
         const void* w = d_w;
         if (w_transposed) {  // stored matrix is [cout = cc][cin = co]; the kernel wants [co][cc]
@@ -707,21 +709,20 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         }
         return conv_gather_dense(side, kvol, d_f, w, d_g, cc, co, s);
     }
-    if (kind == 2) return conv_gather_tile(side, kvol, total_links, d_f, d_w, w_transposed, d_g, cc, co, dt, s, scratch, scratch_bytes);
+    if (kind == 2) return conv_gather_tile(side, kvol, d_f, d_w, w_transposed, d_g, cc, co, dt, s, scratch, scratch_bytes);
     if (kind == 1) {
         GatherArgs a;
-        a.tl_off = ptr<int32_t>(side.tl_off);
-        a.tl_src = ptr<int32_t>(side.tl_src);
-        a.tl_row = ptr<uint16_t>(side.tl_row);
+        a.off = ptr<int32_t>(side.off);
+        a.src = ptr<int32_t>(side.src);
+        a.dst = ptr<int32_t>(side.dst);
         a.f = d_f;
         a.w = d_w;
         a.w_transposed = w_transposed ? 1 : 0;
         a.scratch = scratch;
         a.scratch_bytes = scratch_bytes;
-        const uint64_t fb = (uint64_t)side.n_src * cc * elt, sb = (uint64_t)total_links * 4;
+        const uint64_t fb = (uint64_t)side.n_src * cc * elt;
         a.f_bytes = (uint32_t)fb;
-        a.src_bytes = (uint32_t)sb;
-        a.row_bytes = (uint32_t)((uint64_t)total_links * 2);
+        a.list_bytes = (uint32_t)((uint64_t)side.pitch * kvol * 4);
         a.g = d_g;
         a.n_rows = side.n_rows;
         a.kvol = kvol;

@@ -30,9 +30,9 @@
 namespace sp {
 
 struct TileArgs {
-    const int32_t* tl_off;
-    const int32_t* tl_src;
-    const uint16_t* tl_row;
+    const int32_t* off;  // the side's lists (MapSide)
+    const int32_t* src;
+    const int32_t* dst;
     const void* f;   // source features [n_src][cc]
     const void* w;   // weights, see w_k .. w_s
     void* g;         // destination features [n_rows][co]
@@ -41,7 +41,7 @@ struct TileArgs {
     int nsl;                 // slices of KC contraction channels
     int max_blk;             // room for block descriptors
     uint32_t row_bytes;      // one source row
-    uint32_t f_bytes, w_bytes, src_bytes, dst_bytes;  // buffer sizes: f, w, tl_src, tl_row
+    uint32_t f_bytes, w_bytes, list_bytes;  // buffer sizes: f, w, src and dst
     // byte offsets into w: offset k, channel tile y, 16-channel group cs, slice, fragment s of a unit; lane = n16 + 16*g
     uint32_t w_k, w_y, w_cs, w_slice, w_s, w_n16, w_g;
 };
@@ -102,19 +102,15 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
     // sub-tile 0's part}: block i of offset k holds links 16 i .. of the sub-tiles' stretches put end to end
     if (wave == 0) {
         int base = 0;
-        const int64_t nwt = (a.n_rows + 63) / 64;
         for (int kb = 0; kb < kvol; kb += 64) {
             const int k = kb + lane;
             int o0 = 0, l0 = 0, o1 = 0, l1 = 0;
             if (k < kvol) {
-                const int32_t* p = a.tl_off + ((tile * kNSub) * kvol + k) * kHalves;
+                const int32_t* p = a.off + ((tile * kNSub) * kvol + k) * kHalves;
                 o0 = p[0];
-                l0 = p[kHalves] - o0;
-                if (kNSub == 2 && tile * kNSub + 1 < nwt) {
-                    p += (int64_t)kvol * kHalves;
-                    o1 = p[0];
-                    l1 = p[kHalves] - o1;
-                }
+                o1 = p[kvol * kHalves];  // the next sub-tile's begin: this one's end
+                l0 = o1 - o0;
+                if (kNSub == 2) l1 = p[2 * kvol * kHalves] - o1;
             }
             const int cnt = l0 + l1, nb = (cnt + 15) >> 4;
             int inc = nb;
@@ -142,9 +138,9 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
         // ---------------------------------------------------------------- producers
         const __amdgpu_buffer_rsrc_t rF = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.f), 0, (int)a.f_bytes, kRsrcFlags);
         const __amdgpu_buffer_rsrc_t rSrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.tl_src), 0, (int)a.src_bytes, kRsrcFlags);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.src), 0, (int)a.list_bytes, kRsrcFlags);
         const __amdgpu_buffer_rsrc_t rRow =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.tl_row), 0, (int)a.dst_bytes, kRsrcFlags);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.dst), 0, (int)a.list_bytes, kRsrcFlags);
         constexpr int kEN = kSB * 16 / 64;  // links of a step per lane (every producer wavefront looks at all of them)
         const int pt = tid - 64 * Cfg::kCW;
         struct Ent {
@@ -191,7 +187,7 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
 #pragma unroll
             for (int e = 0; e < kEN; ++e) {
                 const Link l = link_of(step, e);
-                r.row[e] = (int)__builtin_amdgcn_raw_buffer_load_b16(rRow, l.live ? l.entry * 2u : kOutside, 0, 0);
+                r.row[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rRow, l.live ? l.entry * 4u : kOutside, 0, 0);
                 if (!l.live) r.row[e] = -1;
                 off[e] = en.add[e] == kOutside ? kOutside : (uint32_t)en.src[e] * a.row_bytes;
             }

@@ -1,12 +1,15 @@
-// Coordinate sets: hash insertion, duplicate merging in first-occurrence order, strided (coarser)
-// coordinate generation.  Sec. III-B: sparse tensor definition and step 1.
+// Coordinate sets: duplicate merging in first-occurrence order through a grid or a hash table (sp_hash.h), strided
+// (coarser) coordinate generation.  Sec. III-B: sparse tensor definition and step 1.
 //
-// Four launches, no host round trip: (1) reset the table and the bookkeeping words; (2) insert every row
-// (slot.first = smallest row carrying the key); (3) number the first occurrences in row order in a single pass
-// (every block of 1024 rows counts its first occurrences, gets the count of all earlier blocks by decoupled
-// look-back, ranks its rows with ballots, writes coordinates + row numbers; the last block writes the row count
-// N to device memory for later kernels and to a mail slot for the host); (4) read the row numbers back per
-// source row (the inverse map).  The host learns N when it first asks (coords_resolve).
+// No host round trip.  Small sets (kGridRows and less, where every launch counts): reset the hash table, insert every
+// row (slot.first = smallest row carrying the key), number, inverse.  Larger sets: the extent of the coordinates (a
+// coarser set takes its parent's), prepare (every workgroup derives the grid's box, or that a hash table is needed, and
+// clears that table), mark the occupied blocks (or insert into the hash table), number the blocks and clear their
+// cells, put the smallest row of each cell into it, number, inverse.
+// number: in a single pass every block of rows counts its first occurrences, gets the count of all earlier blocks by
+// decoupled look-back, ranks its rows with ballots and writes coordinates + row numbers; the last block writes the
+// row count N to device memory for later kernels and to a mail slot for the host.  inverse: the row number of every
+// source row.  The host learns N when it first asks (coords_resolve).
 #include <algorithm>
 
 #include "sp_hash.h"
@@ -18,7 +21,12 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kRowsPerThread = 4;
-constexpr int kBlockRows = kThreads * kRowsPerThread;  // rows numbered by one block
+constexpr int kNumberThreads = 1024;           // most threads of a numbering block
+constexpr int64_t kGridRows = 32768;           // up to here a hash table: four launches instead of seven
+constexpr int kBoxBlocks = 256;                // blocks of the extent kernel = threads of a prepare block
+constexpr int kBoxWords = 12;                  // min and max of b, x, y, z; out of range; off the lattice
+constexpr int kScanThreads = 1024;
+constexpr int kScanWords = 16 * kScanThreads;  // dir words numbered by one block
 
 __device__ __forceinline__ int32_t floor_to_multiple(int32_t v, int32_t s) {
     int32_t q = v / s;
@@ -41,69 +49,297 @@ __device__ __forceinline__ int64_t row_count(int64_t n_host, const int32_t* __re
     return d_n ? (int64_t)*d_n : n_host;
 }
 
+// The table while it is built.
+struct Build {
+    HashSlot* slots;
+    uint32_t cap;
+    int zshift;
+    int32_t* dir;       // grid form; shares the memory of slots
+    int32_t* cells;
+    int64_t dir_words;  // room (whole blocks of the scan); 0: hash form for certain
+    int32_t* meta;
+    int ts;
+};
+__device__ __forceinline__ bool is_grid(const Build& t) { return t.dir_words > 0 && t.meta[kMetaGrid] != 0; }
+
+__device__ __forceinline__ void clear_slot(HashSlot* slot) {
+    uint4 v;
+    v.x = 0xffffffffu;
+    v.y = 0xffffffffu;
+    v.z = (uint32_t)kNoRow;
+    v.w = (uint32_t)-1;
+    *reinterpret_cast<uint4*>(slot) = v;
+}
+
 // table slots <- empty; meta words and look-back words <- 0
 __global__ __launch_bounds__(kThreads) void reset_kernel(HashSlot* __restrict__ tab, uint32_t cap,
                                                          int32_t* __restrict__ meta, unsigned long long* __restrict__ desc,
                                                          int64_t n_desc) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < cap) {
-        uint4 v;
-        v.x = 0xffffffffu;
-        v.y = 0xffffffffu;
-        v.z = (uint32_t)kNoRow;
-        v.w = (uint32_t)-1;
-        *reinterpret_cast<uint4*>(&tab[i]) = v;
-    }
+    if (i < cap) clear_slot(&tab[i]);
     if (i < kMetaWords) meta[i] = 0;
     if (i < n_desc) desc[i] = 0ull;
 }
 
-// Every source row inserts its key; slot.first becomes the smallest source row carrying that key.
-__global__ __launch_bounds__(kThreads) void insert_kernel(const int4* __restrict__ src, int64_t n_host,
-                                                          const int32_t* __restrict__ d_n, int32_t floor_step,
-                                                          HashSlot* __restrict__ tab, uint32_t cap, int zshift,
-                                                          int32_t* __restrict__ slot_of, int32_t* __restrict__ err, int always) {
+// Extent of the source rows, per block: part[block][kBoxWords].
+__global__ __launch_bounds__(kThreads) void box_kernel(const int4* __restrict__ src, int64_t n_host, const int32_t* __restrict__ d_n,
+                                                       int ts, int32_t* __restrict__ part) {
+    __shared__ int s_red[kThreads / 64][10];
     const int64_t n = row_count(n_host, d_n);
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    const int4 c = load_row(src, i, floor_step);
+    int v[10];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        v[a] = 0x7fffffff;
+        v[4 + a] = -0x7fffffff - 1;
+    }
+    v[8] = v[9] = 0;
+    const int4 c0 = n > 0 ? src[0] : int4{0, 0, 0, 0};
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i0 = (int64_t)blockIdx.x * kThreads + threadIdx.x; i0 < n; i0 += 4 * stride) {
+        int4 c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = src[min(i0 + j * stride, n - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int w[4] = {c[j].x, c[j].y, c[j].z, c[j].w};
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                v[a] = min(v[a], w[a]);
+                v[4 + a] = max(v[4 + a], w[a]);
+            }
+            uint64_t key;
+            if (!pack_key(w[0], w[1], w[2], w[3], &key)) v[8] = 1;
+            else if (ts > 1 && ((w[1] - c0.y) % ts != 0 || (w[2] - c0.z) % ts != 0 || (w[3] - c0.w) % ts != 0)) v[9] = 1;
+        }
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+        for (int a = 0; a < 10; ++a) {
+            const int o = __shfl_xor(v[a], d, 64);
+            v[a] = a < 4 ? min(v[a], o) : max(v[a], o);
+        }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int a = 0; a < 10; ++a) s_red[w][a] = v[a];
+    __syncthreads();
+    if (threadIdx.x < 10) {
+        const int a = threadIdx.x;
+        int r = s_red[0][a];
+        for (int j = 1; j < kThreads / 64; ++j) r = a < 4 ? min(r, s_red[j][a]) : max(r, s_red[j][a]);
+        part[blockIdx.x * kBoxWords + a] = r;
+    }
+}
+
+// Every block derives the box and the form of the table for itself and clears its share of it; block 0 writes meta.
+// part: the extents box_kernel left, or null: the parent's box (parent_meta, lattice step parent_ts), floored to t.ts.
+__global__ __launch_bounds__(kBoxBlocks) void prepare_kernel(Build t, int64_t n_host, const int32_t* __restrict__ d_n,
+                                                             const int32_t* __restrict__ part,
+                                                             const int32_t* __restrict__ parent_meta, int parent_ts,
+                                                             unsigned long long* __restrict__ desc, int64_t n_desc) {
+    __shared__ int s_red[kBoxBlocks / 64][10];
+    __shared__ int s_box[10];
+    const int tid = threadIdx.x;
+    const int64_t n = row_count(n_host, d_n);
+    if (part) {
+        int v[10];
+#pragma unroll
+        for (int a = 0; a < 10; ++a) v[a] = part[tid * kBoxWords + a];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+            for (int a = 0; a < 10; ++a) {
+                const int o = __shfl_xor(v[a], d, 64);
+                v[a] = a < 4 ? min(v[a], o) : max(v[a], o);
+            }
+        if ((tid & 63) == 0)
+#pragma unroll
+            for (int a = 0; a < 10; ++a) s_red[tid >> 6][a] = v[a];
+        __syncthreads();
+        if (tid < 10) {
+            int r = s_red[0][tid];
+            for (int j = 1; j < kBoxBlocks / 64; ++j) r = tid < 4 ? min(r, s_red[j][tid]) : max(r, s_red[j][tid]);
+            s_box[tid] = r;
+        }
+    } else if (tid < 10) {
+        const bool grid = parent_meta[kMetaGrid] != 0;
+        int r = tid == 8 ? 0 : (grid ? 0 : 1);  // a parent that is no grid: word 9 sends this set to the hash form too
+        if (grid && tid < 8) {
+            const int a = tid & 3, low = parent_meta[kMetaLow + a];
+            const int cells = parent_meta[kMetaExt + a] * (a == 0 ? 1 : (a == 3 ? 16 : 8));
+            r = tid < 4 ? low : low + (cells - 1) * (a == 0 ? 1 : parent_ts);
+            if (a > 0) r = floor_to_multiple(r, t.ts);
+        }
+        s_box[tid] = r;
+    }
+    __syncthreads();
+    int64_t ext[4], words = 1;
+    bool ok = n > 0 && s_box[8] == 0 && s_box[9] == 0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const int64_t cells = ((int64_t)s_box[4 + a] - s_box[a]) / (a == 0 ? 1 : t.ts) + 1;
+        ext[a] = a == 0 ? cells : (a == 3 ? (cells + 15) / 16 : (cells + 7) / 8);
+        ok = ok && cells >= 1 && cells <= 65536;
+        ok = ok && s_box[a] >= (a == 0 ? 0 : -32768);
+    }
+    if (ok) words = ext[0] * ext[1] * ext[2] * ext[3] * 64;
+    ok = ok && words <= t.dir_words;
+    const int64_t gid = (int64_t)blockIdx.x * kBoxBlocks + tid, stride = (int64_t)gridDim.x * kBoxBlocks;
+    if (gid == 0) {
+        t.meta[kMetaN] = 0;
+        t.meta[kMetaErr] = s_box[8] != 0 ? 1 : 0;
+        t.meta[kMetaGrid] = ok ? 1 : 0;
+        t.meta[kMetaBlocks] = 0;
+        for (int a = 0; a < 4; ++a) {
+            t.meta[kMetaLow + a] = s_box[a];
+            t.meta[kMetaExt + a] = ok ? (int)ext[a] : 0;
+        }
+    }
+    for (int64_t i = gid; i < n_desc; i += stride) desc[i] = 0ull;
+    if (ok) {
+        const int64_t quads = (words + kScanWords - 1) / kScanWords * (kScanWords / 4);
+        for (int64_t i = gid; i < quads; i += stride) reinterpret_cast<int4*>(t.dir)[i] = int4{-1, -1, -1, -1};
+    } else {
+        for (int64_t i = gid; i < (int64_t)t.cap; i += stride) clear_slot(&t.slots[i]);
+    }
+}
+
+// Every source row inserts its key; slot.first becomes the smallest source row carrying that key.
+__device__ __forceinline__ void insert_row(const Build& t, const int4& c, int64_t i, int always, int32_t* __restrict__ at) {
     uint64_t key;
     if (!pack_key(c.x, c.y, c.z, c.w, &key)) {
-        atomicOr(err, 1);
-        slot_of[i] = -1;
+        atomicOr(t.meta + kMetaErr, 1);
+        at[i] = -1;
         return;
     }
     bool fresh;
-    const int64_t slot = hash_insert(tab, cap, zshift, key, &fresh);
+    const int64_t slot = hash_insert(t.slots, t.cap, t.zshift, key, &fresh);
     if (slot < 0) {
-        atomicOr(err, 2);
-        slot_of[i] = -1;
+        atomicOr(t.meta + kMetaErr, 2);
+        at[i] = -1;
         return;
     }
     // A duplicate that sees a smaller row already recorded has nothing to add (the value only ever decreases).
     // Looking first costs a round trip and saves an atomic: measured 5 us slower on 157 k rows, 50 us faster
     // on 4.1 M rows (where the atomics' throughput binds), so the host asks for it from 1 M rows (always = 0).
-    if (always || fresh || __builtin_nontemporal_load(&tab[slot].first) > (int32_t)i) atomicMin(&tab[slot].first, (int32_t)i);
-    slot_of[i] = (int32_t)slot;
+    if (always || fresh || __builtin_nontemporal_load(&t.slots[slot].first) > (int32_t)i) atomicMin(&t.slots[slot].first, (int32_t)i);
+    at[i] = (int32_t)slot;
 }
 
-// Block t numbers the first occurrences among rows [t*1024, t*1024+1024): rank = (first
-// occurrences in earlier blocks, by look-back) + (those before it in this block, row order).  Writes the
-// (floored) coordinates at that rank and the rank into the table slot.  The block holding the last rows
-// delivers the total.
-__global__ __launch_bounds__(kThreads) void number_kernel(const int4* __restrict__ src, int64_t n_host,
-                                                          const int32_t* __restrict__ d_n, int32_t floor_step,
-                                                          HashSlot* __restrict__ tab, const int32_t* __restrict__ slot_of,
-                                                          Chain chain, int32_t* __restrict__ meta, int4* __restrict__ coords,
-                                                          uint32_t* __restrict__ mail, uint32_t mail_seq) {
-    __shared__ int s_own[1], s_excl[1], s_state[2];
-    __shared__ int s_row[kRowsPerThread][kThreads / 64];
+// Hash: insert.  Grid: the row's block is occupied (all rows of a block store the same word), at[i] = its cell.
+__global__ __launch_bounds__(kThreads) void mark_kernel(const int4* __restrict__ src, int64_t n_host,
+                                                        const int32_t* __restrict__ d_n, int32_t floor_step, Build t,
+                                                        int32_t* __restrict__ at, int always) {
     const int64_t n = row_count(n_host, d_n);
-    const int64_t nb = (n + kBlockRows - 1) / kBlockRows;
-    const int t = blockIdx.x;
+    const int64_t tile = xcd_tile(blockIdx.x, (n + kThreads - 1) / kThreads), i = tile * kThreads + threadIdx.x;
+    if (tile < 0 || i >= n) return;
+    const int4 c = load_row(src, i, floor_step);
+    if (!is_grid(t)) {
+        insert_row(t, c, i, always, at);
+        return;
+    }
+    const Grid g = load_grid(t.meta);
+    int qx, qy, qz;
+    lattice(c.y - g.x0, t.ts, &qx);
+    lattice(c.z - g.y0, t.ts, &qy);
+    lattice(c.w - g.z0, t.ts, &qz);
+    const uint32_t blk = grid_block(g, c.x - g.b0, qx, qy, qz >> 2);
+    t.dir[blk] = 0;
+    at[i] = (int32_t)(blk * 16u + (uint32_t)(grid_run(qx, qy) * 4 + (qz & 3)));
+}
+
+// Grid: occupied blocks are numbered, their cells cleared.  16 words a thread.  The numbers need no order (nothing
+// that the build returns depends on them), so a workgroup takes as many as it needs from a counter: 12 ns per
+// workgroup, where a look-back made the launch wait 8 us.
+__global__ __launch_bounds__(kScanThreads) void number_blocks_kernel(Build t) {
+    __shared__ int s_base;
+    __shared__ int s_wave[kScanThreads / 64];
+    if (!is_grid(t)) return;
+    const Grid g = load_grid(t.meta);
+    const int64_t words = (int64_t)g.nb * g.gx * g.gy * g.gz * 64;
+    if ((int64_t)blockIdx.x * kScanWords >= words) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // thread t takes quads t, t + 1024, ...: coalesced; numbers follow quad by quad
+    int4* q = reinterpret_cast<int4*>(t.dir + (int64_t)blockIdx.x * kScanWords);
+    int4 v[4];
+    int pos[4], total = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = q[j * kScanThreads + tid];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int mine = (v[j].x == 0) + (v[j].y == 0) + (v[j].z == 0) + (v[j].w == 0);
+        int inc = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        if (lane == 63) s_wave[w] = inc;
+        __syncthreads();
+        pos[j] = total + inc - mine;
+        for (int ww = 0; ww < kScanThreads / 64; ++ww) {
+            if (ww < w) pos[j] += s_wave[ww];
+            total += s_wave[ww];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) s_base = total ? atomicAdd(t.meta + kMetaBlocks, total) : 0;
+    __syncthreads();
+    const int base = s_base;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        int r = base + pos[j];
+        if ((v[j].x & v[j].y & v[j].z & v[j].w) == -1) continue;  // none of the four is occupied
+        if (v[j].x == 0) v[j].x = r++;
+        if (v[j].y == 0) v[j].y = r++;
+        if (v[j].z == 0) v[j].z = r++;
+        if (v[j].w == 0) v[j].w = r++;
+        q[j * kScanThreads + tid] = v[j];
+    }
+    int4* cells = reinterpret_cast<int4*>(t.cells) + (int64_t)base * 4;
+    for (int i = tid; i < total * 4; i += kScanThreads) cells[i] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
+}
+
+// Grid: at[i] becomes the row's place in cells, and the cell ends up with its smallest row.  A cell's value is one of its
+// rows and only ever decreases, so a row that reads one smaller than itself, however old the copy it reads, can stay
+// away: most duplicates spend no atomic.  (Plain stores followed by a pass of atomics for the rows that lost would
+// be faster still, but two XCDs that store different values to one word are left with an L2 copy each, and later
+// kernels have been seen to read both.)
+__global__ __launch_bounds__(kThreads) void place_kernel(Build t, int64_t n_host, const int32_t* __restrict__ d_n,
+                                                         int32_t* __restrict__ at) {
+    if (!is_grid(t)) return;
+    const int64_t n = row_count(n_host, d_n);
+    // rows in ascending order over time, not dealt to the XCDs: a later row then mostly finds a smaller one in place
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t c = (uint32_t)at[i];
+    const int32_t p = t.dir[c >> 4] * 16 + (int32_t)(c & 15u);
+    if (t.cells[p] > (int32_t)i) atomicMin(&t.cells[p], (int32_t)i);
+    at[i] = p;
+}
+
+// Block b numbers the first occurrences among its rows: rank = (first occurrences in earlier blocks, by look-back) +
+// (those before it in this block, row order).  Writes the (floored) coordinates at that rank and the rank into the
+// table.  The block holding the last rows delivers the total.
+// (Grid: the rank replaces the row in the cell.  It is smaller than every later row of the cell, so none of those
+// takes itself for the first.)
+__global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __restrict__ src, int64_t n_host,
+                                                                const int32_t* __restrict__ d_n, int32_t floor_step, Build t,
+                                                                const int32_t* __restrict__ at, Chain chain,
+                                                                int4* __restrict__ coords, uint32_t* __restrict__ mail,
+                                                                uint32_t mail_seq) {
+    __shared__ int s_own[1], s_excl[1], s_state[2];
+    __shared__ int s_row[kRowsPerThread][kNumberThreads / 64];
+    const int nthreads = blockDim.x, nw = nthreads >> 6;
+    const int rows = nthreads * kRowsPerThread;
+    const int64_t n = row_count(n_host, d_n);
+    const int64_t nb = (n + rows - 1) / rows;
+    const int b = blockIdx.x;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (t >= nb) {
-        if (t == 0 && threadIdx.x == 0) {  // no rows at all: block 0 reports N = 0
+    int32_t* meta = t.meta;
+    if (b >= nb) {
+        if (b == 0 && threadIdx.x == 0) {  // no rows at all: block 0 reports N = 0
             meta[kMetaN] = 0;
             if (mail) {
                 mail[0] = 0u;
@@ -114,19 +350,25 @@ __global__ __launch_bounds__(kThreads) void number_kernel(const int4* __restrict
         }
         return;
     }
-    const int64_t base = (int64_t)t * kBlockRows;
+    const bool grid = is_grid(t);
+    const int64_t base = (int64_t)b * rows;
     bool f[kRowsPerThread];
     int pos[kRowsPerThread];
+    int32_t s[kRowsPerThread], first[kRowsPerThread];
 #pragma unroll
     for (int j = 0; j < kRowsPerThread; ++j) {
-        const int64_t i = base + j * kThreads + threadIdx.x;
-        bool first = false;
-        if (i < n) {
-            const int32_t s = slot_of[i];
-            first = s >= 0 && tab[s].first == (int32_t)i;
-        }
-        const unsigned long long m = __ballot(first);
-        f[j] = first;
+        const int64_t i = base + j * nthreads + threadIdx.x;
+        s[j] = i < n ? at[i] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kRowsPerThread; ++j) {
+        first[j] = -1;
+        if (s[j] >= 0) first[j] = grid ? t.cells[s[j]] : t.slots[s[j]].first;
+    }
+#pragma unroll
+    for (int j = 0; j < kRowsPerThread; ++j) {
+        f[j] = s[j] >= 0 && first[j] == (int32_t)(base + j * nthreads + threadIdx.x);
+        const unsigned long long m = __ballot(f[j]);
         pos[j] = __popcll(m & ((1ull << lane) - 1ull));
         if (lane == 0) s_row[j][w] = __popcll(m);
     }
@@ -134,26 +376,26 @@ __global__ __launch_bounds__(kThreads) void number_kernel(const int4* __restrict
     if (threadIdx.x == 0) {
         int c = 0;
         for (int j = 0; j < kRowsPerThread; ++j)
-            for (int ww = 0; ww < kThreads / 64; ++ww) c += s_row[j][ww];
+            for (int ww = 0; ww < nw; ++ww) c += s_row[j][ww];
         s_own[0] = c;
     }
-    chain_lookback(chain, t, s_own, s_excl, s_state, meta + kMetaErr);
+    chain_lookback(chain, b, s_own, s_excl, s_state, meta + kMetaErr);
     int run = s_excl[0];
 #pragma unroll
     for (int j = 0; j < kRowsPerThread; ++j) {
         int mine = run;
-        for (int ww = 0; ww < kThreads / 64; ++ww) {
+        for (int ww = 0; ww < nw; ++ww) {
             if (ww < w) mine += s_row[j][ww];
             run += s_row[j][ww];
         }
         if (f[j]) {
-            const int64_t i = base + j * kThreads + threadIdx.x;
             const int32_t r = mine + pos[j];
-            coords[r] = load_row(src, i, floor_step);
-            tab[slot_of[i]].row = r;
+            coords[r] = load_row(src, base + j * nthreads + threadIdx.x, floor_step);
+            if (grid) t.cells[s[j]] = r;
+            else t.slots[s[j]].row = r;
         }
     }
-    if (t == nb - 1 && threadIdx.x == 0) {
+    if (b == nb - 1 && threadIdx.x == 0) {
         meta[kMetaN] = run;
         if (mail) {
             mail[0] = (uint32_t)run;
@@ -164,22 +406,34 @@ __global__ __launch_bounds__(kThreads) void number_kernel(const int4* __restrict
     }
 }
 
-__global__ __launch_bounds__(kThreads) void inverse_kernel(const HashSlot* __restrict__ tab,
-                                                           const int32_t* __restrict__ slot_of, int64_t n_host,
+__global__ __launch_bounds__(kThreads) void inverse_kernel(Build t, const int32_t* __restrict__ at, int64_t n_host,
                                                            const int32_t* __restrict__ d_n, int32_t* __restrict__ inverse) {
     const int64_t n = row_count(n_host, d_n);
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    const int32_t s = slot_of[i];
-    inverse[i] = s >= 0 ? tab[s].row : -1;
+    const int64_t tile = xcd_tile(blockIdx.x, (n + kThreads - 1) / kThreads), i = tile * kThreads + threadIdx.x;
+    if (tile < 0 || i >= n) return;
+    const int32_t s = at[i];
+    inverse[i] = s < 0 ? -1 : (is_grid(t) ? t.cells[s] : t.slots[s].row);
 }
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
 
+TableView table_view(const sp_coords* c) {
+    TableView v;
+    v.slots = ptr<HashSlot>(c->tab.mem);
+    v.cap = c->tab.cap;
+    v.zshift = c->tab.zshift;
+    v.meta = ptr<int32_t>(c->meta);
+    v.dir = ptr<int32_t>(c->tab.mem);
+    v.cells = v.dir + c->tab.dir_words;
+    v.ts = c->ts;
+    v.maybe_grid = c->tab.dir_words > 0 ? 1 : 0;
+    return v;
+}
+
 int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_src, int32_t floor_step,
-                      int32_t tensor_stride, hipStream_t s, sp_coords_t** out) {
+                      int32_t tensor_stride, const sp_coords* parent, hipStream_t s, sp_coords_t** out) {
     if (n_src >= (int64_t)1 << 30) return fail(SP_ERR_INVALID_ARG, "too many rows (%lld)", (long long)n_src);
     std::unique_ptr<sp_coords> c(new sp_coords);
     c->n_raw = n_src;
@@ -189,41 +443,73 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     while ((int64_t)cap < 2 * n_src) cap <<= 1;
     c->tab.cap = cap;
     for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
-    const int64_t nb = (n_src + kBlockRows - 1) / kBlockRows;
-    c->tab.slots = dev_alloc((size_t)cap * sizeof(HashSlot), s);
+    // A grid: 32 bytes of dir per source row (128 cells of the box; 4 MB at least), whole scan blocks, and 64 bytes per
+    // block that can be occupied.  Cell numbers have to fit 32 bits, places in cells 31.
+    int64_t dir_words = 0;
+    if (n_src > kGridRows && n_src < ((int64_t)1 << 26) && (!parent || parent->tab.dir_words > 0))
+        dir_words = std::min<int64_t>((std::max<int64_t>(8 * n_src, 1 << 20) + kScanWords - 1) / kScanWords * kScanWords, (int64_t)1 << 28);
+    const bool may_grid = dir_words > 0;
+    c->tab.dir_words = dir_words;
+    const size_t grid_bytes = may_grid ? (size_t)dir_words * 4 + (size_t)n_src * 64 : 0;
+    const int nthreads = n_src >= (1 << 18) ? kNumberThreads : kThreads;
+    const int block_rows = nthreads * kRowsPerThread;
+    const int64_t nb = (n_src + block_rows - 1) / block_rows;
+    c->tab.mem = dev_alloc(std::max((size_t)cap * sizeof(HashSlot), grid_bytes), s);
     c->coords = dev_alloc((size_t)(n_src ? n_src : 1) * 16, s);
     c->inverse = dev_alloc((size_t)(n_src ? n_src : 1) * 4, s);
     c->meta = dev_alloc(kMetaWords * 4, s);
-    Buf slot_of = dev_alloc((size_t)(n_src ? n_src : 1) * 4, s);
-    Buf chain_mem = dev_alloc((size_t)(nb ? nb : 1) * 8, s);  // one look-back word per numbering block
-    if (!c->tab.slots || !c->coords || !c->inverse || !c->meta || !slot_of || !chain_mem) return SP_ERR_ALLOC;
-    HashSlot* tab = ptr<HashSlot>(c->tab.slots);
-    int32_t* meta = ptr<int32_t>(c->meta);
+    // scratch: a slot or cell per source row, the look-back words, the extents
+    const size_t at_bytes = ((size_t)(n_src ? n_src : 1) * 4 + 15) / 16 * 16;
+    const int64_t n_desc = nb ? nb : 1;
+    Buf scratch = dev_alloc(at_bytes + (size_t)n_desc * 8 + (may_grid ? kBoxBlocks * kBoxWords * 4 : 0), s);
+    if (!c->tab.mem || !c->coords || !c->inverse || !c->meta || !scratch) return SP_ERR_ALLOC;
+    int32_t* at = ptr<int32_t>(scratch);
+    unsigned long long* desc = reinterpret_cast<unsigned long long*>(ptr<unsigned char>(scratch) + at_bytes);
+    Build t;
+    t.slots = ptr<HashSlot>(c->tab.mem);
+    t.cap = cap;
+    t.zshift = c->tab.zshift;
+    t.dir = ptr<int32_t>(c->tab.mem);
+    t.cells = t.dir + dir_words;
+    t.dir_words = dir_words;
+    t.meta = ptr<int32_t>(c->meta);
+    t.ts = tensor_stride;
     Chain chain;
-    chain.desc = ptr<unsigned long long>(chain_mem);
+    chain.desc = desc;
     chain.n_tiles = nb ? nb : 1;
     chain.width = 1;
     const bool mailed = mail_acquire(&c->mail);
-
-    hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(std::max<int64_t>(cap, nb), kThreads)), dim3(kThreads), 0, s, tab, cap, meta,
-                       chain.desc, nb);
     const int4* src = reinterpret_cast<const int4*>(d_src);
-    if (n_src > 0)
-        hipLaunchKernelGGL(insert_kernel, dim3(blocks_for(n_src, kThreads)), dim3(kThreads), 0, s, src, n_src, d_n_src,
-                           floor_step, tab, cap, c->tab.zshift, ptr<int32_t>(slot_of), meta + kMetaErr,
-                           n_src < (1 << 20) ? 1 : 0);
-    hipLaunchKernelGGL(number_kernel, dim3((unsigned)(nb ? nb : 1)), dim3(kThreads), 0, s, src, n_src, d_n_src, floor_step, tab,
-                       ptr<int32_t>(slot_of), chain, meta, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr,
-                       c->mail.seq);
+    const dim3 rows(xcd_grid(blocks_for(n_src, kThreads))), threads(kThreads);
+    const int always = n_src < (1 << 20) ? 1 : 0;
+
+    if (may_grid) {
+        int32_t* part = nullptr;
+        if (!parent) {
+            part = reinterpret_cast<int32_t*>(desc + n_desc);
+            hipLaunchKernelGGL(box_kernel, dim3(kBoxBlocks), threads, 0, s, src, n_src, d_n_src, tensor_stride, part);
+        }
+        hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)std::min<int64_t>(2048, dir_words / 4 / kBoxBlocks)), dim3(kBoxBlocks), 0, s,
+                           t, n_src, d_n_src, part, parent ? ptr<int32_t>(parent->meta) : nullptr, parent ? parent->ts : 1, desc,
+                           n_desc);
+        hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
+        hipLaunchKernelGGL(number_blocks_kernel, dim3((unsigned)(dir_words / kScanWords)), dim3(kScanThreads), 0, s, t);
+        hipLaunchKernelGGL(place_kernel, rows, threads, 0, s, t, n_src, d_n_src, at);
+    } else {
+        hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(std::max<int64_t>(cap, n_desc), kThreads)), threads, 0, s, t.slots, cap,
+                           t.meta, desc, n_desc);
+        if (n_src > 0) hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
+    }
+    hipLaunchKernelGGL(number_kernel, dim3((unsigned)(nb ? nb : 1)), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at,
+                       chain, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
     c->mail.armed = mailed;
     c->mail.stream = s;
     if (n_src > 0)
-        hipLaunchKernelGGL(inverse_kernel, dim3(blocks_for(n_src, kThreads)), dim3(kThreads), 0, s, tab, ptr<int32_t>(slot_of),
-                           n_src, d_n_src, ptr<int32_t>(c->inverse));
+        hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, n_src, d_n_src, ptr<int32_t>(c->inverse));
     SP_HIP(hipGetLastError());
     if (!mailed) {  // no mail slot free: wait here, the old way
         int32_t h[2] = {0, 0};
-        SP_TRY(read_back(h, meta, 8, s));
+        SP_TRY(read_back(h, t.meta, 8, s));
         c->n = h[0];
         c->status = (h[1] & 1) ? SP_ERR_RANGE : (h[1] & 2) ? SP_ERR_TABLE_FULL : (h[1] & kErrLookback) ? SP_ERR_HIP : SP_OK;
         c->resolved = true;
@@ -268,7 +554,7 @@ int sp_coords_build(const int32_t* d_raw, int64_t n_raw, int32_t tensor_stride, 
     if (n_raw > 0 && !d_raw) return sp::fail(SP_ERR_INVALID_ARG, "d_raw is NULL");
     if (tensor_stride < 1) return sp::fail(SP_ERR_INVALID_ARG, "tensor_stride < 1");
     if (((uintptr_t)d_raw & 15) != 0) return sp::fail(SP_ERR_INVALID_ARG, "d_raw must be 16-byte aligned");
-    return sp::coords_build_impl(d_raw, n_raw, nullptr, 1, tensor_stride, (hipStream_t)stream, out);
+    return sp::coords_build_impl(d_raw, n_raw, nullptr, 1, tensor_stride, nullptr, (hipStream_t)stream, out);
 }
 
 int sp_coords_size(const sp_coords_t* c, int64_t* n, int32_t* tensor_stride) {

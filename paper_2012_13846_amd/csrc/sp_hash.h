@@ -1,19 +1,32 @@
-// Device-side open-addressing hash table on 64-bit packed coordinates (the GPU hashmap of Sec. III-B,
-// used for the insertions and searches of step 2).  One slot is 16 bytes {key, first, row}, so a search
-// resolves key and row with a single 16-byte access.
+// Coordinate tables: which row has a given (b, x, y, z), the GPU hashmap of Sec. III-B.  Two forms, one chosen on the
+// device by the build (sp_coords.hip) from the extent of the coordinates.
 //
-// The table is made of buckets of 4 slots (64 bytes).  Four coordinates that are neighbours along z (same b,
+// Grid (bounded clouds, at most 128 cells of the bounding box per source row): the box is cut into blocks of 2 x 2 x 4
+// cells (x, y, z); dir[block] is the number of an occupied block or -1, cells[16 * number + cell] the row or kNoRow.
+// dir is laid out in groups of 4 x 4 x 4 blocks, so that the words a surface touches are few lines (four clouds of a
+// 230^3 box: 2.3 MB instead of 5-10, an L2 holds 4).
+// Two dependent loads per search, both from arrays a fraction of a hash table's size, and four z-neighbours share
+// 16 bytes.  Building it takes one atomic per distinct row, non-returning, where a hash table takes two and a chain of
+// dependent ones on every collision: 25 G random atomics a second is the most this chip does, whatever their scope
+// and wherever the line is (0.5 M rows: 21 us, plain stores 2), and that is what bounds the insertion.
+//
+// Hash (everything else): open addressing on the 64-bit packed coordinate.  One slot is 16 bytes {key, first, row}, so a
+// search resolves key and row with a single 16-byte access.
+//
+// The hash table is made of buckets of 4 slots (64 bytes).  Four coordinates that are neighbours along z (same b,
 // x, y, same z / (4 * lattice step)) hash to the same bucket and have the slot given by their position in
 // that group of four as home slot; collisions are resolved by plain linear probing over all slots, so the
 // table fills evenly even when the coordinates use one position only (a plane of constant z).  The kernel-map search
 // asks for a voxel's neighbours along z in one thread, so its 2-3 searches usually fall into one 64-byte line
-// instead of 2-3 random ones: these searches are bound by the rate of random line fetches.
+// instead of 2-3 random ones.
 // zshift = floor(log2(lattice step)): which two bits of z number the four group members.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+
+#include "sp_internal.h"
 
 namespace sp {
 
@@ -85,5 +98,52 @@ __device__ __forceinline__ int32_t hash_find(const HashSlot* __restrict__ tab, u
     }
     return -1;
 }
+
+// ---- grid ----------------------------------------------------------------------------------------------------
+struct TableView {
+    const HashSlot* slots;  // hash form
+    uint32_t cap;
+    int zshift;
+    const int32_t* meta;    // which form, and the grid's box
+    const int32_t* dir;     // grid form
+    const int32_t* cells;
+    int ts;                 // lattice step
+    int maybe_grid;         // 0: the hash form for certain
+};
+
+// The box of a grid, from the set's meta words.
+struct Grid {
+    int b0, x0, y0, z0;
+    int nb, gx, gy, gz;     // clouds, groups of 4 x 4 x 4 blocks along x, y, z
+};
+__device__ __forceinline__ Grid load_grid(const int32_t* __restrict__ meta) {
+    return Grid{meta[kMetaLow], meta[kMetaLow + 1], meta[kMetaLow + 2], meta[kMetaLow + 3],
+                meta[kMetaExt], meta[kMetaExt + 1], meta[kMetaExt + 2], meta[kMetaExt + 3]};
+}
+// Lattice position of d = coordinate - lowest (d may be negative): true if d is on the lattice.
+__device__ __forceinline__ bool lattice(int d, int ts, int* q) {
+    if (ts == 1) {
+        *q = d;
+        return true;
+    }
+    int t = d / ts;
+    if (t * ts > d) --t;
+    *q = t;
+    return t * ts == d;
+}
+// dir word of the block that holds lattice position (qx, qy, 4 bz ..)
+__device__ __forceinline__ uint32_t grid_block(const Grid& g, int qb, int qx, int qy, int bz) {
+    const uint32_t group = ((uint32_t)(qb * g.gx + (qx >> 3)) * (uint32_t)g.gy + (uint32_t)(qy >> 3)) * (uint32_t)g.gz + (uint32_t)(bz >> 2);
+    return group * 64u + (uint32_t)(((qx >> 1) & 3) * 16 + ((qy >> 1) & 3) * 4 + (bz & 3));
+}
+__device__ __forceinline__ int grid_run(int qx, int qy) { return (qx & 1) * 2 + (qy & 1); }  // which 4-cell run of the block
+
+// Workgroup -> tile such that each XCD (workgroup id % 8) walks a contiguous eighth of the rows: clouds lie one behind
+// the other, so an XCD's L2 sees a few clouds' tables instead of all.  -1: nothing left.  Launch a multiple of 8.
+__device__ __forceinline__ int64_t xcd_tile(int64_t wg, int64_t tiles) {
+    const int64_t per = (tiles + 7) / 8, j = wg / 8, t = (wg & 7) * per + j;
+    return j < per && t < tiles ? t : -1;
+}
+inline unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 
 }  // namespace sp

@@ -80,31 +80,36 @@ bool mail_acquire(MailSlot* out);                  // false: none free (the call
 void mail_release(MailSlot* slot);
 int mail_wait(const MailSlot& slot, hipStream_t s);  // blocks until the slot's payload has arrived
 
-// ---- hash table ---------------------------------------------------------------------------------------------
-struct HashTab {
-    Buf slots;         // HashSlot [cap] (sp_hash.h): 16 bytes {key, first source row, row number}
-    uint32_t cap = 0;  // power of two, >= 2 * entries
-    int zshift = 0;    // floor(log2(tensor stride)): see sp_hash.h
+// ---- coordinate table: a cell grid or a hash table, in one buffer; the build decides on the device (sp_hash.h) ----
+struct CoordTab {
+    Buf mem;               // HashSlot [cap], or dir [dir_words] followed by the cells of the occupied blocks
+    uint32_t cap = 0;      // hash: slots, a power of two >= 2 * entries
+    int zshift = 0;        // hash: floor(log2(tensor stride))
+    int64_t dir_words = 0; // grid: room for block numbers; 0: the set is too small to be worth one (hash for certain)
 };
 
 // ---- coords (sp_coords.hip) ---------------------------------------------------------------------------------------
 // Builds a coordinate set from d_src rows; floor_step > 1 floors x,y,z to multiples of it first.  n_src_ub is an
 // upper bound of the row count (sizes every allocation and grid); d_n_src, if not null, points at the true count
 // in device memory (a count that the host has not seen yet), else the count is n_src_ub.  Does not wait.
+// parent: the set whose coordinates d_src are, or null (then their extent is looked up first).
 int coords_build_impl(const int32_t* d_src, int64_t n_src_ub, const int32_t* d_n_src, int32_t floor_step,
-                      int32_t tensor_stride, hipStream_t s, sp_coords_t** out);
+                      int32_t tensor_stride, const sp_coords* parent, hipStream_t s, sp_coords_t** out);
 // Waits (first call only) until the handle's row count has come back; reports device-detected errors.
 int coords_resolve(const sp_coords_t* c);
+struct TableView;
+TableView table_view(const sp_coords* c);
 int kmap_resolve(const sp_kmap_t* m);
 
-constexpr int kTileRows = 256;   // rows per tile of the tile lists (= map-build block size)
-constexpr int kSubTiles = 4;     // 64-row sub-tiles (one wavefront ballot each) per tile
+constexpr int kTileRows = 1024;  // rows per tile of the map build (= its workgroup size)
+constexpr int kSubTiles = 16;    // 64-row sub-tiles (one wavefront ballot each) per tile
 constexpr int kHalves = 2;       // list offsets are kept per 32-row half of a sub-tile
 
 }  // namespace sp
 
-// Words of a coordinate set's device-side `meta` block (int32)
-enum { kMetaN = 0, kMetaErr = 1, kMetaWords = 4 };
+// Words of a coordinate set's device-side `meta` block (int32): row count, error bits, 1 if the table is a grid (0: hash),
+// the grid's occupied blocks, its lowest coordinate per axis (b, x, y, z), its clouds and its groups of blocks per axis.
+enum { kMetaN = 0, kMetaErr = 1, kMetaGrid = 2, kMetaBlocks = 3, kMetaLow = 4, kMetaExt = 8, kMetaWords = 12 };
 
 struct sp_coords {
     std::atomic<int> ref{1};
@@ -113,7 +118,7 @@ struct sp_coords {
     sp::Buf coords;   // int32 [n][4] (allocated for n_raw rows)
     sp::Buf inverse;  // int32 [n_raw]
     sp::Buf meta;     // int32 [kMetaWords]: the row count n, error bits, ...: what kernels of later builds read
-    sp::HashTab tab;
+    sp::CoordTab tab;
     hipStream_t stream = nullptr;
     // the host's copy of n arrives through a mail slot and is read on first demand (coords_resolve)
     mutable std::mutex mu;
@@ -127,15 +132,29 @@ struct sp_coords {
 
 namespace sp {
 
-// One direction of a kernel map, as the gather-GEMM kernel consumes it: `n_rows` destination rows in tiles
-// of kTileRows; for (64-row sub-tile u, offset k, 32-row half h) the entries [off[(u*kvol+k)*2+h], off[(u*kvol+k)*2+h+1])
-// of src/row list the live (source row, destination row within the tile) links, destination rows ascending.
+// What the lists of an input side of its own and the class order are made from, and whether they have been made: they
+// are built on the stream of the first call that needs them (many steps need neither: pooling walks the tables,
+// wide layers the class order).  Their memory is reserved when the map is built.
+struct SideWork {
+    std::mutex mu;
+    bool lists = false, classes = false;             // built
+    hipStream_t lists_on = nullptr, classes_on = nullptr;
+    Buf counts;        // scratch of the list and class builds
+    Buf coords;        // the side's coordinates (classes)
+    int ts = 1, stride = 1, K = 1, nclass = 0;
+};
+
+// One direction of a kernel map, as the gather-GEMM kernels consume it: `n_rows` destination rows in 64-row
+// sub-tiles.  Offset k's links (source row src[e], destination row dst[e]) are the entries [k * pitch, k * pitch + links of k),
+// destination rows ascending; off[(u*kvol + k)*2 + h] is where those of (sub-tile u, offset k, 32-row half h) begin, so that
+// sub-tile u's end where sub-tile u + 1's begin (there is one more sub-tile row than sub-tiles).
 struct MapSide {
     int64_t n_rows = 0, n_src = 0;
     Buf nbr;      // int32 [kvol][n_rows]: source row or -1
-    Buf tl_off;   // int32 [nsub*kvol*2 + 1], nsub = 4*ntiles, index (sub*kvol + k)*2 + half (sub-tile-major)
-    Buf tl_src;   // int32 [total]
-    Buf tl_row;   // uint16 [total]
+    Buf off;      // int32 [(nsub + 1)*kvol*2]
+    Buf src;      // int32 [kvol][pitch]
+    Buf dst;      // int32 [kvol][pitch]
+    int64_t pitch = 0;
     bool flip = false;  // weight offset index = kvol-1-k (side derived by the stride-1 symmetry)
     // Input side of a strided map only: which offsets can link an input row depends on the row's position inside
     // its coarse cell (stride 2, K = 3: 1 to 8 of the 27).  `perm` lists the rows sorted by that position class
@@ -143,6 +162,7 @@ struct MapSide {
     // of word k/32), so that a row-stationary kernel walking perm skips the other offsets of a tile.
     Buf perm;       // int32 [n_rows] or null
     Buf tile_mask;  // uint32 [ceil(n_rows/256)][4] or null
+    std::shared_ptr<SideWork> work;  // null: the lists were built with the map and there are no classes
 };
 
 }  // namespace sp
@@ -155,18 +175,19 @@ struct sp_kmap {
     mutable sp::MapSide out_side;  // destinations = output rows, sources = input rows   (forward)
     mutable sp::MapSide in_side;   // destinations = input rows,  sources = output rows  (data gradient)
     sp::Buf pair_in, pair_out;  // int32 [kvol][pair_stride]: offset k's pairs are the first counts[k] entries of row k
+                                // (the lists of the side whose rows the build walked)
     int64_t pair_stride = 0;
     mutable std::vector<int64_t> counts;   // [kvol]
     mutable std::vector<int64_t> koff;     // [kvol+1] exclusive prefix of counts
-    sp::Buf d_koff;                // int32 [kvol+1], the same prefix on the device
+    sp::Buf d_counts;              // int32 [kvol + 1]: counts on the device, then a word of the build's own
     sp_coords* c_in = nullptr;     // references held
     sp_coords* c_out = nullptr;
     hipStream_t stream = nullptr;
     mutable std::mutex mu;
     mutable bool resolved = false;
     mutable int status = 0;
-    mutable sp::MailSlot mail;     // payload: n_in, n_out, error bits, koff[0..kvol]
-    void set_sizes(int64_t n_in_, int64_t n_out_, const uint32_t* koff_words) const;
+    mutable sp::MailSlot mail;     // payload: n_in, n_out, error bits, counts[0..kvol)
+    void set_sizes(int64_t n_in_, int64_t n_out_, const uint32_t* count_words) const;
     ~sp_kmap() { sp::mail_release(&mail); }
     // filled on first use (average pooling's backward pass): links per output row, int32 [n_out]
     mutable std::mutex cache_mu;
@@ -174,6 +195,11 @@ struct sp_kmap {
 };
 
 namespace sp {
+// The side's lists / class order, if they do not exist yet, on stream s (sp_kmap.hip).
+int need_lists(const MapSide& side, int kvol, hipStream_t s);
+int need_classes(const MapSide& side, hipStream_t s);
+// Orders `to` behind everything enqueued on `from` so far.
+int stream_wait(hipStream_t from, hipStream_t to);
 // conv launchers (sp_conv.hip / sp_wgrad.hip)
 // scratch != null: the call must not allocate; the weight copy of the link-list kernel goes there (forward only)
 int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* d_f, const void* d_w, bool w_transposed,

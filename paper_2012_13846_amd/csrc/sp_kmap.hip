@@ -1,16 +1,18 @@
-// Kernel maps (Sec. III-B step 2): for every kernel offset the (input row, output row) pairs it links,
-// found by probing the input coordinate set's hash table, then compacted with wavefront ballots and
-// prefix sums into (a) per-offset pair lists and (b) tile-major lists for the gather-GEMM kernels.
+// Kernel maps (Sec. III-B step 2): for every kernel offset the (input row, output row) pairs it links, found by
+// searching the input coordinate set's table, then compacted with wavefront ballots and prefix sums into per-offset
+// lists that the gather-GEMM kernels and the weight gradient read.
 //
-// No host round trip and no scan launches: the build is (1) one reset launch, (2) the searches, which fill the
-// neighbour table(s), (3) per map side a count launch (links per 256-row tile and offset), a small prefix launch
-// (one workgroup per offset scans its counts over the tiles) and an emit launch (every tile writes its stretch
-// of the lists); the last tile delivers the per-offset totals
-// to device memory and to a mail slot, which the host reads when it first asks (kmap_resolve).  Row counts that
-// the host has not seen yet (the input set's N, the coarse set's N) are read from device memory by the kernels;
-// grids and allocations use upper bounds.  (A single-pass count + look-back + emit kernel was measured slower:
-// the look-back's device-coherent loads cost ~2 us a round trip and a tile near the end of a launch that starts
-// all at once needs several of them per offset.)
+// No host round trip.  (1) The searches: one thread per output row and column of offsets fills the neighbour table
+// and counts the links per (64-row sub-tile, offset); a workgroup is a tile of 1024 rows, so it also leaves the
+// tile's sum per offset.  (2) emit: every tile adds up the sums of the tiles before it (a few hundred numbers per
+// offset, cheaper than a prefix launch) and writes its stretch of every offset's list; the last tile delivers the
+// counts to device memory and to a mail slot, which the host reads when it first asks (kmap_resolve).  Row counts
+// that the host has not seen yet (the input set's N, the coarse set's N) are read from device memory by the kernels;
+// grids and allocations use upper bounds.  (A single-pass count + look-back + emit kernel was measured slower: the
+// look-back's device-coherent loads cost ~2 us a round trip and a tile near the end of a launch that starts all at
+// once needs several of them per offset.)
+// The lists of an input side of its own (strided maps, even kernels) and its class order are made by the first call
+// that walks them.
 #include <algorithm>
 
 #include "sp_hash.h"
@@ -19,8 +21,7 @@
 namespace sp {
 namespace {
 
-constexpr int kThreads = kTileRows;  // one thread per row of a tile; 4 wavefronts = 4 sub-tiles
-constexpr int kMaxKvol = 125;
+constexpr int kThreads = 256;
 
 // A row count: the host's value, or (d != null) a count in device memory that the host has not seen yet.
 struct Count {
@@ -29,78 +30,78 @@ struct Count {
 };
 __device__ __forceinline__ int64_t get(const Count& c) { return c.d ? (int64_t)*c.d : c.h; }
 
-// table[k][r] <- -1 for k in [k_lo, kvol), r < n (n may live on the device); a second such region
-struct NegRegion {
-    int32_t* table;
-    Count n;
-    int k_lo, kvol;
+// table[0, kvol * n) <- -1 (n may live on the device), 16 bytes a thread
+__global__ __launch_bounds__(kThreads) void reset_kernel(int32_t* __restrict__ table, Count cn, int kvol) {
+    const int64_t total = get(cn) * kvol, i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    if (i + 4 <= total) *reinterpret_cast<int4*>(table + i) = int4{-1, -1, -1, -1};
+    else
+        for (int64_t j = i; j < total; ++j) table[j] = -1;
+}
+
+// Links per (tile, sub-tile, offset, 32-row half) and per (tile, offset): what emit_kernel places its entries by.
+struct Counts {
+    int32_t* cnt;  // [tile][sub][kvol][half]
+    int32_t* agg;  // [tile][kvol]
 };
-__global__ __launch_bounds__(256) void reset_kernel(NegRegion a, NegRegion b) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (a.table) {
-        const int64_t n = get(a.n);
-        if (i < n * (a.kvol - a.k_lo)) a.table[(int64_t)a.k_lo * n + i] = -1;
+
+// A workgroup's share of the counts: offsets k(0) .. k(NO-1) of its tile, v[j] = this row's entry of the j-th.
+template <int NO, class Koff>
+__device__ __forceinline__ void count_rows(const Counts& c, int kvol, int64_t tile, const int32_t (&v)[NO], int (&s_cnt)[kSubTiles][NO][kHalves],
+                                           Koff k_of) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+#pragma unroll
+    for (int j = 0; j < NO; ++j) {
+        const unsigned long long live = __ballot(v[j] >= 0);
+        if (lane == 0) {
+            s_cnt[w][j][0] = __popc((unsigned)live);
+            s_cnt[w][j][1] = __popc((unsigned)(live >> 32));
+        }
     }
-    if (b.table) {
-        const int64_t n = get(b.n);
-        if (i < n * (b.kvol - b.k_lo)) b.table[(int64_t)b.k_lo * n + i] = -1;
+    __syncthreads();
+    if (tid < kSubTiles * NO) {
+        const int ww = tid / NO, j = tid % NO, k = k_of(j);
+        if (k < kvol) {
+            int2 two;
+            two.x = s_cnt[ww][j][0];
+            two.y = s_cnt[ww][j][1];
+            *reinterpret_cast<int2*>(c.cnt + (((tile * kSubTiles + ww) * kvol + k) * kHalves)) = two;
+        }
+    }
+    if (tid >= 512 && tid < 512 + NO) {
+        const int j = tid - 512, k = k_of(j);
+        if (k < kvol) {
+            int sum = 0;
+            for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cnt[ww][j][0] + s_cnt[ww][j][1];
+            c.agg[tile * kvol + k] = sum;
+        }
     }
 }
 
-// grid (tiles of n_out, K*K).  Thread (o, ax, ay) probes the K offsets (ax, ay, 0..K-1): the K searches of
-// one thread are independent, so their memory latencies overlap, and the row's coordinates are read once.
-// Writes nbr_out[k][o]; scatters nbr_in[k][i] = o when nbr_in is given.
-// identity_k >= 0 (stride 1, odd K; input and output rows are the same set): the centre offset is the
-// identity, and link (i, o) at offset k is link (o, i) at offset kvol-1-k, so only the offsets below the
-// centre are searched and each hit is also written to the mirrored entry nbr_out[kvol-1-k][i] = o.  The
-// entries above the centre that stay without a hit were set to -1 beforehand.
+// The K searches of one column (ax, ay) of offsets for one row, in the hash table.  They advance in lockstep: every
+// turn issues the next slot's load of all searches still running and only then looks at the answers, so their memory
+// latencies overlap (run one after the other, each costs as many round trips as the longest probe sequence among
+// the 64 lanes).
 template <int K>
-__global__ __launch_bounds__(kThreads) void probe_kernel(const int4* __restrict__ c_out, Count cn_out,
-                                                         const HashSlot* __restrict__ tab, uint32_t cap, int zshift, int step,
-                                                         int identity_k, int32_t* __restrict__ nbr_out,
-                                                         int32_t* __restrict__ nbr_in, Count cn_in) {
-    constexpr int kvol = K * K * K;
-    const int64_t n_out = get(cn_out);
-    const int ay = blockIdx.y % K, ax = blockIdx.y / K;
-    const int64_t o = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (o >= n_out) return;
-    const int64_t n_in = nbr_in ? get(cn_in) : 0;
+__device__ __forceinline__ void search_hash(const TableView& t, const int4& c, int dx, int dy, int step, int skip, int32_t* v) {
     constexpr int centre = (K & 1) ? (K - 1) / 2 : 0;
-    const int k0 = (ax * K + ay) * K;
-    int32_t v[K];
-#pragma unroll
-    for (int az = 0; az < K; ++az) v[az] = -1;
-    const int4 c = c_out[o];
     uint64_t key[K];
-    bool ok[K];
-#pragma unroll
-    for (int az = 0; az < K; ++az)
-        ok[az] = pack_key(c.x, c.y + (ax - centre) * step, c.z + (ay - centre) * step, c.w + (az - centre) * step, &key[az]);
-    // The K searches advance in lockstep: every turn issues the next slot's load of all searches still
-    // running and only then looks at the answers, so their memory latencies overlap (run one after the
-    // other, each search costs as many round trips as the longest probe sequence among the 64 lanes).
     uint32_t slot[K];
     bool run[K];
     bool any = false;
 #pragma unroll
     for (int az = 0; az < K; ++az) {
-        run[az] = false;
-        slot[az] = 0;
-        if (k0 + az == identity_k) {
-            v[az] = (int32_t)o;
-        } else if (ok[az] && (identity_k < 0 || k0 + az < identity_k)) {
-            uint32_t bucket, pos;
-            hash_home(key[az], cap, zshift, &bucket, &pos);
-            slot[az] = bucket * 4 + pos;
-            run[az] = true;
-            any = true;
-        }
+        v[az] = -1;
+        run[az] = pack_key(c.x, c.y + dx * step, c.z + dy * step, c.w + (az - centre) * step, &key[az]) && az != skip;
+        uint32_t bucket, pos;
+        hash_home(key[az], t.cap, t.zshift, &bucket, &pos);
+        slot[az] = bucket * 4 + pos;
+        any = any || run[az];
     }
-    for (uint32_t turn = 0; any && turn < cap; ++turn) {
+    for (uint32_t turn = 0; any && turn < t.cap; ++turn) {
         uint4 raw[K];
 #pragma unroll
         for (int az = 0; az < K; ++az)
-            if (run[az]) raw[az] = *reinterpret_cast<const uint4*>(&tab[slot[az]]);
+            if (run[az]) raw[az] = *reinterpret_cast<const uint4*>(&t.slots[slot[az]]);
         any = false;
 #pragma unroll
         for (int az = 0; az < K; ++az) {
@@ -112,19 +113,105 @@ __global__ __launch_bounds__(kThreads) void probe_kernel(const int4* __restrict_
             } else if (cur == kEmptyKey) {
                 run[az] = false;
             } else {
-                slot[az] = (slot[az] + 1) & (cap - 1);
+                slot[az] = (slot[az] + 1) & (t.cap - 1);
                 any = true;
             }
         }
     }
+}
+
+// grid (tiles, K*K / NC): thread (o, columns) searches the K offsets along z of NC columns (ax, ay).  Writes
+// nbr_out[k][o], scatters nbr_in[k][i] = o when nbr_in is given, and counts the links.
+// identity: input and output rows are the same set, the centre offset links every row to itself.
+// Bound by the rate of scattered loads (a wavefront's 64 lanes touch 64 lines).  In a grid a column is at most two
+// blocks: two loads of dir and two of four cells each, all of the thread's columns requested together.  (0.37 M
+// rows, K = 3: 84 us when the lower half of the offsets was searched in the hash table and mirrored, plus 29 us for
+// resetting the table and counting its entries.)
+template <int K, int NC>
+__global__ __launch_bounds__(kTileRows) void search_kernel(const int4* __restrict__ c_out, Count cn_out, TableView t, int dilation,
+                                                           int identity, int32_t* __restrict__ nbr_out,
+                                                           int32_t* __restrict__ nbr_in, Count cn_in, Counts counts,
+                                                           int32_t* __restrict__ done) {
+    constexpr int kvol = K * K * K, centre = (K & 1) ? (K - 1) / 2 : 0;
+    __shared__ int s_cnt[kSubTiles][NC * K][kHalves];
+    const int64_t n_out = get(cn_out);
+    const int64_t tile = xcd_tile(blockIdx.x, (n_out + kTileRows - 1) / kTileRows);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *done = 0;
+    if (tile < 0) return;
+    const int64_t o = tile * kTileRows + threadIdx.x;
+    const int col0 = blockIdx.y * NC;
+    int32_t v[NC * K];
 #pragma unroll
-    for (int az = 0; az < K; ++az) {
-        if (identity_k >= 0 && k0 + az > identity_k) continue;  // written by the mirrored offset's hits
-        nbr_out[(int64_t)(k0 + az) * n_out + o] = v[az];
-        if (nbr_in && v[az] >= 0) nbr_in[(int64_t)(k0 + az) * n_in + v[az]] = (int32_t)o;
-        if (identity_k >= 0 && k0 + az < identity_k && v[az] >= 0)
-            nbr_out[(int64_t)(kvol - 1 - (k0 + az)) * n_out + v[az]] = (int32_t)o;
+    for (int j = 0; j < NC * K; ++j) v[j] = -1;
+    if (o < n_out) {
+        const int4 c = c_out[o];
+        if (t.maybe_grid && t.meta[kMetaGrid]) {
+            const Grid g = load_grid(t.meta);
+            const int qb = c.x - g.b0;
+            int qx, qy, qz;
+            const bool onx = lattice(c.y - g.x0, t.ts, &qx), ony = lattice(c.z - g.y0, t.ts, &qy), onz = lattice(c.w - g.z0, t.ts, &qz);
+            const bool on = onx && ony && onz && (unsigned)qb < (unsigned)g.nb;
+            const int zl = qz - centre * dilation, zh = qz + (K - 1 - centre) * dilation;
+            const bool narrow = (zh >> 2) - (zl >> 2) <= 1;  // the column's cells lie in at most two blocks: uniform for dilation 1
+            int lo[NC], hi[NC], run[NC];
+#pragma unroll
+            for (int m = 0; m < NC; ++m) {
+                const int x = qx + ((col0 + m) / K - centre) * dilation, y = qy + ((col0 + m) % K - centre) * dilation;
+                const bool in = on && (unsigned)x < (unsigned)(8 * g.gx) && (unsigned)y < (unsigned)(8 * g.gy);
+                const int bl = zl >> 2, bh = zh >> 2, nbz = 4 * g.gz;
+                run[m] = grid_run(x, y);
+                lo[m] = hi[m] = -1;
+                if (in && (unsigned)bl < (unsigned)nbz) lo[m] = t.dir[grid_block(g, qb, x, y, bl)];
+                if (in && bh != bl && (unsigned)bh < (unsigned)nbz) hi[m] = t.dir[grid_block(g, qb, x, y, bh)];
+                if (!narrow && in) {  // wide spacing: one search at a time
+#pragma unroll
+                    for (int az = 0; az < K; ++az) {
+                        const int z = zl + az * dilation;
+                        if ((unsigned)(z >> 2) < (unsigned)nbz) {
+                            const int b = t.dir[grid_block(g, qb, x, y, z >> 2)];
+                            if (b >= 0) v[m * K + az] = t.cells[(int64_t)b * 16 + run[m] * 4 + (z & 3)];
+                        }
+                    }
+                }
+            }
+            if (narrow) {
+                int4 a[NC], b[NC];
+#pragma unroll
+                for (int m = 0; m < NC; ++m) {
+                    a[m] = b[m] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
+                    if (lo[m] >= 0) a[m] = reinterpret_cast<const int4*>(t.cells)[(int64_t)lo[m] * 4 + run[m]];
+                    if (hi[m] >= 0) b[m] = reinterpret_cast<const int4*>(t.cells)[(int64_t)hi[m] * 4 + run[m]];
+                }
+#pragma unroll
+                for (int m = 0; m < NC; ++m)
+#pragma unroll
+                    for (int az = 0; az < K; ++az) {
+                        const int z = zl + az * dilation, e = z & 3;
+                        const bool low = (z >> 2) == (zl >> 2);
+                        const int p0 = low ? a[m].x : b[m].x, p1 = low ? a[m].y : b[m].y, p2 = low ? a[m].z : b[m].z, p3 = low ? a[m].w : b[m].w;
+                        v[m * K + az] = e < 2 ? (e == 0 ? p0 : p1) : (e == 2 ? p2 : p3);
+                    }
+            }
+#pragma unroll
+            for (int j = 0; j < NC * K; ++j) v[j] = v[j] == kNoRow ? -1 : v[j];
+        } else {
+#pragma unroll
+            for (int m = 0; m < NC; ++m) {
+                const int ax = (col0 + m) / K, ay = (col0 + m) % K;
+                const int skip = identity && ax == centre && ay == centre ? centre : -1;
+                search_hash<K>(t, c, ax - centre, ay - centre, dilation * t.ts, skip, v + m * K);
+                if (skip >= 0) v[m * K + centre] = (int32_t)o;
+            }
+        }
+        const int64_t n_in = nbr_in ? get(cn_in) : 0;
+#pragma unroll
+        for (int j = 0; j < NC * K; ++j) {
+            const int64_t k = col0 * K + j;
+            nbr_out[k * n_out + o] = v[j];
+            if (nbr_in && v[j] >= 0) nbr_in[k * n_in + v[j]] = (int32_t)o;
+        }
     }
+    count_rows<NC * K>(counts, kvol, tile, v, s_cnt, [&](int j) { return col0 * K + j; });
 }
 
 // Position class of an input row inside its coarse cell: ((x/ts) mod s, (y/ts) mod s, (z/ts) mod s) as one number.
@@ -137,14 +224,14 @@ __device__ __forceinline__ int cell_class(const int4& c, int ts, int stride) {
 // has exactly one link, to its own coarse cell (parent[i], from the coarse coordinates' merge), at the offset
 // that is its position in the cell.  No searches.
 __global__ __launch_bounds__(kThreads) void child_map_kernel(const int4* __restrict__ c_in, Count cn_in, int ts, int stride,
-                                                             const int32_t* __restrict__ parent, Count cn_out,
+                                                             const int32_t* __restrict__ parent, Count cn_out, int kvol,
                                                              int32_t* __restrict__ nbr_out, int32_t* __restrict__ nbr_in) {
     const int64_t n_in = get(cn_in), n_out = get(cn_out);
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n_in) return;
     const int k = cell_class(c_in[i], ts, stride);
     const int32_t o = parent[i];
-    nbr_in[(int64_t)k * n_in + i] = o;
+    for (int j = 0; j < kvol; ++j) nbr_in[(int64_t)j * n_in + i] = j == k ? o : -1;
     nbr_out[(int64_t)k * n_out + o] = (int32_t)i;
 }
 
@@ -180,186 +267,91 @@ __global__ __launch_bounds__(kThreads) void gen_tables_kernel(const int32_t* __r
     nbr_in[(int64_t)k * n_fine + f] = (int32_t)j;
 }
 
-// ---------------------------------------------------------------------------------------------------------------
-// One side of a map: neighbour table -> lists, in two launches.
-//
-// count_kernel: per tile (256 destination rows) the live entries per (sub-tile, offset, 32-row half) into cnt and
-// the tile's links per offset into agg[tile][*].  On a strided map's input side the rows per position class ride
-// along as extra sums (width = kvol + nclass).
-// prefix_kernel: one workgroup per sum scans it over the tiles: excl[tile][*].
-// emit_kernel: tile t writes
-//   tl_off  list offsets of its 4 sub-tiles: index ((t*4 + sub)*kvol + k)*2 + half, sub-tile-major stretches
-//   tl_src / tl_row  the tile lists (source row, destination row inside the tile), destination rows ascending
-//   pair_in / pair_out (output side only)  offset k's pairs at k*pair_stride + (links of earlier tiles at k) + rank
-//   cls_excl[t][*] (classes)  rows of each position class in earlier tiles, for class_emit_kernel
-// The last tile writes koff (prefix of the per-offset totals) to device memory and the mail slot, and the class
-// bases.
-// ---------------------------------------------------------------------------------------------------------------
-struct Sums {
-    int32_t* agg;   // [tile][width]: the tile's own sums (count_kernel)
-    int32_t* excl;  // [tile][width]: sums of all earlier tiles (prefix_kernel)
-    int width;      // kvol (+ nclass)
-};
-
-struct CountArgs {
-    const int32_t* nbr;
-    Count n_rows;
-    int kvol;
-    int32_t* cnt;   // [tile][sub][k][half]
-    Sums sums;
-    const int4* coords;  // classes (input side of a strided map), else nclass = 0
-    int ts, stride, nclass;
-};
-
 constexpr int kChunk = 9;  // offsets whose table entries a thread requests before it looks at any of them
 
-// grid (tiles, chunks of kChunk offsets): a workgroup counts one chunk of offsets of one tile (one table entry per
-// thread and offset, all requested before any is looked at); the chunk-0 workgroup also counts the classes.
-__global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
+// Counts of a table that no search has counted: grid (tiles, chunks of kChunk offsets).
+__global__ __launch_bounds__(kTileRows) void count_kernel(const int32_t* __restrict__ nbr, Count n_rows, int kvol, Counts counts,
+                                                          int32_t* __restrict__ done) {
     __shared__ int s_cnt[kSubTiles][kChunk][kHalves];
-    __shared__ int s_cls[32][kSubTiles];
-    const int kvol = a.kvol, width = a.sums.width;
-    const int n_ent = kSubTiles * kvol * kHalves;
-    const int64_t n = get(a.n_rows);
-    const int64_t t = blockIdx.x;
+    const int64_t n = get(n_rows), t = blockIdx.x;
+    if (done && t == 0 && blockIdx.y == 0 && threadIdx.x == 0) *done = 0;
     if (t * kTileRows >= n) return;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t r = t * kTileRows + tid;
+    const int64_t r = t * kTileRows + threadIdx.x;
     const int k0 = blockIdx.y * kChunk;
     int32_t v[kChunk];
 #pragma unroll
-    for (int j = 0; j < kChunk; ++j) v[j] = (r < n && k0 + j < kvol) ? a.nbr[(int64_t)(k0 + j) * n + r] : -1;
-#pragma unroll
-    for (int j = 0; j < kChunk; ++j) {
-        const unsigned long long live = __ballot(v[j] >= 0);
-        if (lane == 0) {
-            s_cnt[w][j][0] = __popc((unsigned)live);
-            s_cnt[w][j][1] = __popc((unsigned)(live >> 32));
-        }
-    }
-    const bool classes = a.nclass && blockIdx.y == 0;
-    if (classes) {
-        const int cls = r < n ? cell_class(a.coords[r], a.ts, a.stride) : -1;
-        for (int c = 0; c < a.nclass; ++c) {
-            const unsigned long long m = __ballot(cls == c);
-            if (lane == 0) s_cls[c][w] = __popcll(m);
-        }
-    }
-    __syncthreads();
-    if (tid < kSubTiles * kChunk * kHalves) {
-        const int ww = tid / (kChunk * kHalves), j = tid / kHalves % kChunk, h = tid % kHalves;
-        if (k0 + j < kvol) a.cnt[t * n_ent + (ww * kvol + k0 + j) * kHalves + h] = s_cnt[ww][j][h];
-    }
-    if (tid < kChunk && k0 + tid < kvol) {
-        int sum = 0;
-        for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cnt[ww][tid][0] + s_cnt[ww][tid][1];
-        a.sums.agg[t * width + k0 + tid] = sum;
-    }
-    if (classes && tid >= 64 && tid < 64 + a.nclass) {
-        int sum = 0;
-        for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cls[tid - 64][ww];
-        a.sums.agg[t * width + kvol + tid - 64] = sum;
-    }
-}
-
-// Block i: excl[t][i] = sum of agg[t'][i] over t' < t, for all tiles (1024 tiles a round, running carry).
-__global__ __launch_bounds__(1024) void prefix_kernel(Sums sm, Count n_rows) {
-    __shared__ int s_wave[16];
-    __shared__ int s_carry;
-    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t n = get(n_rows);
-    const int64_t ntiles = (n + kTileRows - 1) / kTileRows;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < ntiles; t0 += 1024) {
-        const int64_t t = t0 + tid;
-        const int v = t < ntiles ? sm.agg[t * sm.width + i] : 0;
-        int inc = v;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int u = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += u;
-        }
-        if (lane == 63) s_wave[w] = inc;
-        __syncthreads();
-        int before = s_carry;
-        for (int ww = 0; ww < w; ++ww) before += s_wave[ww];
-        if (t < ntiles) sm.excl[t * sm.width + i] = before + inc - v;
-        __syncthreads();
-        if (tid == 1023) s_carry = before + inc;
-        __syncthreads();
-    }
+    for (int j = 0; j < kChunk; ++j) v[j] = (r < n && k0 + j < kvol) ? nbr[(int64_t)(k0 + j) * n + r] : -1;
+    count_rows<kChunk>(counts, kvol, t, v, s_cnt, [&](int j) { return k0 + j; });
 }
 
 struct EmitArgs {
     const int32_t* nbr;
     Count n_rows;
     int kvol;
-    const int32_t* cnt;  // count_kernel's counts (the workgroups that share a tile all read them: not tl_off itself)
-    int32_t* tl_off;
-    int32_t* tl_src;
-    uint16_t* tl_row;
-    int32_t* pair_in;   // null on the input side
-    int32_t* pair_out;
-    int64_t pair_stride;
-    Sums sums;
-    int nclass;
-    int32_t* cls_excl;  // [tile][nclass]: rows of class c in earlier tiles
-    int32_t* cls_base;  // [nclass + 1]: first position of class c in the class-sorted order (written by the last tile)
-    // results
-    int32_t* d_koff;    // [kvol + 1] (output side only)
-    uint32_t* mail;     // null or the mail slot: n_in, n_out, error bits, koff[0..kvol]
+    Counts counts;
+    int32_t* off;       // [(sub-tile)][kvol][half], and one row of ends
+    int32_t* src;       // [kvol][pitch]
+    int32_t* dst;
+    int64_t pitch;
+    // results (the side the build walks only)
+    int32_t* d_counts;  // null, or [kvol] and the word that counts the workgroups which have delivered
+    uint32_t* mail;     // null or the mail slot: n_in, n_out, error bits, counts[0..kvol)
     uint32_t mail_seq;
     Count n_in, n_out;  // for the mail
 };
 
-__global__ __launch_bounds__(kThreads) void emit_kernel(EmitArgs a) {
-    __shared__ int s_cnt[kSubTiles * kMaxKvol * kHalves + 2];  // [sub][k][half]: counts, then list offsets
-    __shared__ int s_own[kMaxKvol + 32], s_excl[kMaxKvol + 32];
-    const int kvol = a.kvol, width = a.sums.width;
+// grid (tiles, chunks of kChunk offsets): entries of a tile for one chunk.
+__global__ __launch_bounds__(kTileRows) void emit_kernel(EmitArgs a) {
+    __shared__ int s_start[kSubTiles][kChunk];
+    __shared__ int s_total[kChunk];
+    const int kvol = a.kvol;
     const int64_t n = get(a.n_rows);
     const int64_t ntiles = (n + kTileRows - 1) / kTileRows;
     const int64_t t = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (t >= ntiles && !(t == 0 && ntiles == 0)) return;
-    const bool empty = ntiles == 0;  // tile 0 of an empty side only delivers the (zero) results
+    const int k0 = blockIdx.y * kChunk;
     const int64_t r = t * kTileRows + tid;
-    const int n_ent = kSubTiles * kvol * kHalves;
+    int32_t v[kChunk];
+#pragma unroll
+    for (int j = 0; j < kChunk; ++j) v[j] = (r < n && k0 + j < kvol) ? a.nbr[(int64_t)(k0 + j) * n + r] : -1;
 
-    // ---- this tile's counts, and the sums of everything before it
-    if (!empty) {
-        for (int e = tid; e < n_ent; e += kThreads) s_cnt[e] = a.cnt[t * n_ent + e];
-        for (int i = tid; i < width; i += kThreads) {
-            s_excl[i] = a.sums.excl[t * width + i];
-            s_own[i] = a.sums.agg[t * width + i];
+    // wavefront j: offset k0 + j.  Links of the tiles before this one, then where each sub-tile's begin.
+    if (w < kChunk && k0 + w < kvol) {
+        const int k = k0 + w;
+        int sum = 0;
+        for (int64_t tt = lane; tt < t; tt += 64) sum += a.counts.agg[tt * kvol + k];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+        int2 c = {0, 0};
+        if (ntiles && lane < kSubTiles) c = *reinterpret_cast<const int2*>(a.counts.cnt + ((t * kSubTiles + lane) * kvol + k) * kHalves);
+        int inc = c.x + c.y;
+#pragma unroll
+        for (int d = 1; d < kSubTiles; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
         }
-    } else {
-        for (int i = tid; i < width; i += kThreads) s_own[i] = s_excl[i] = 0;
+        const int start = (int)(k * a.pitch) + sum + inc - (c.x + c.y);
+        if (ntiles && lane < kSubTiles) {
+            s_start[lane][w] = start;
+            *reinterpret_cast<int2*>(a.off + ((t * kSubTiles + lane) * kvol + k) * kHalves) = int2{start, start + c.x};
+        }
+        const int end = (int)(k * a.pitch) + sum + __shfl(inc, kSubTiles - 1, 64);
+        if (t == (ntiles ? ntiles - 1 : 0) && lane == 0) {  // the last tile: the ends, the counts
+            *reinterpret_cast<int2*>(a.off + ((ntiles * kSubTiles) * kvol + k) * kHalves) = int2{end, end};
+            s_total[w] = ntiles ? end - (int)(k * a.pitch) : 0;
+        }
     }
     __syncthreads();
-
-    // ---- the last tile delivers the totals (gridDim.y workgroups share a tile: each emits a chunk of the offsets,
-    // the first one also writes what belongs to the tile as a whole)
-    const bool lead = blockIdx.y == 0;
-    if (lead && t == (empty ? 0 : ntiles - 1) && tid == 0) {
-        if (a.nclass) {
-            int run = 0;
-            for (int c = 0; c < a.nclass; ++c) {
-                a.cls_base[c] = run;
-                run += s_excl[kvol + c] + s_own[kvol + c];
-            }
-            a.cls_base[a.nclass] = run;
+    if (a.d_counts && t == (ntiles ? ntiles - 1 : 0) && tid == 0) {
+        // the workgroups of the last tile each deliver their chunk; the one that finishes last also sends the mail off
+        for (int j = 0; j < kChunk && k0 + j < kvol; ++j) {
+            a.d_counts[k0 + j] = s_total[j];
+            if (a.mail) a.mail[3 + k0 + j] = (uint32_t)s_total[j];
         }
-        if (a.d_koff) {
-            int run = 0;
-            for (int k = 0; k < kvol; ++k) {
-                a.d_koff[k] = run;
-                if (a.mail) a.mail[3 + k] = (uint32_t)run;
-                run += s_excl[k] + s_own[k];
-            }
-            a.d_koff[kvol] = run;
-            if (a.mail) {
-                a.mail[3 + kvol] = (uint32_t)run;
+        if (a.mail) {
+            __threadfence_system();
+            if (atomicAdd(a.d_counts + kvol, 1) == (int)gridDim.y - 1) {
                 a.mail[0] = (uint32_t)get(a.n_in);
                 a.mail[1] = (uint32_t)get(a.n_out);
                 a.mail[2] = 0u;
@@ -368,105 +360,80 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(EmitArgs a) {
             }
         }
     }
-    if (empty) {
-        if (lead && tid == 0) a.tl_off[0] = 0;
-        return;
-    }
-    if (lead && a.nclass)
-        for (int c = tid; c < a.nclass; c += kThreads) a.cls_excl[t * a.nclass + c] = s_excl[kvol + c];
+    if (ntiles == 0) return;
 
-    // ---- list offsets of the tile: links of all earlier tiles + exclusive scan over (sub, k, half).
-    // Wavefront 0: lane l takes the entries [l*per, l*per + per).  s_cnt then holds offsets, with the end of the
-    // tile's stretch in the entry after the last.
-    if (w == 0) {
-        int before = 0;
-        for (int k = 0; k < kvol; ++k) before += s_excl[k];   // the same in every lane: links of all earlier tiles
-        const int per = (n_ent + 63) / 64;
-        int sum = 0;
-        for (int j = 0; j < per; ++j) {
-            const int e = lane * per + j;
-            if (e < n_ent) sum += s_cnt[e];
-        }
-        int inc = sum;
+    // every live (row, k) writes its entry at start + (number of live lanes below it)
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int u = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += u;
+    for (int j = 0; j < kChunk; ++j) {
+        const unsigned long long live = __ballot(v[j] >= 0);
+        if (v[j] >= 0) {
+            const int e = s_start[w][j] + __popcll(live & ((1ull << lane) - 1ull));
+            a.src[e] = v[j];
+            a.dst[e] = (int32_t)r;
         }
-        int run = before + inc - sum;
-        for (int j = 0; j < per; ++j) {
-            const int e = lane * per + j;
-            if (e < n_ent) {
-                const int c = s_cnt[e];
-                s_cnt[e] = run;  // from here on: the entry's list offset
-                if (lead) a.tl_off[t * n_ent + e] = run;
-                run += c;
-            }
-        }
-        if (lane == 63) {
-            s_cnt[n_ent] = run;                                        // all lanes' entries precede: run = end of the tile
-            if (lead && t == ntiles - 1) a.tl_off[ntiles * n_ent] = run;  // end of the last stretch = all links
-        }
+    }
+}
+
+// Rows per position class and tile.
+__global__ __launch_bounds__(kTileRows) void class_count_kernel(const int4* __restrict__ coords, int64_t n, int ts, int stride,
+                                                                int nclass, int32_t* __restrict__ agg) {
+    __shared__ int s_cls[32][kSubTiles];
+    const int64_t t = blockIdx.x, r = t * kTileRows + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int cls = r < n ? cell_class(coords[r], ts, stride) : -1;
+    for (int c = 0; c < nclass; ++c) {
+        const unsigned long long m = __ballot(cls == c);
+        if (lane == 0) s_cls[c][w] = __popcll(m);
     }
     __syncthreads();
-
-    // ---- emit: every live (row, k) writes its entry at offset + (number of live lanes below it)
-    for (int k0 = blockIdx.y * kChunk; k0 < kvol; k0 += gridDim.y * kChunk) {
-      int32_t vv[kChunk];
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) vv[j] = (r < n && k0 + j < kvol) ? a.nbr[(int64_t)(k0 + j) * n + r] : -1;
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-        const int k = k0 + j;
-        const int32_t v = vv[j];
-        const unsigned long long live = __ballot(v >= 0);
-        const int pos = __popcll(live & ((1ull << lane) - 1ull));  // among the wavefront's 64 rows
-        if (v >= 0) {
-            // the two 32-row halves of a sub-tile are adjacent in the list, so the position inside the sub-tile's
-            // stretch is the plain 64-lane rank
-            const int64_t e = (int64_t)s_cnt[(w * kvol + k) * kHalves] + pos;
-            a.tl_src[e] = v;
-            a.tl_row[e] = (uint16_t)tid;
-            if (a.pair_in) {
-                // links of this tile at offset k in the sub-tiles before this one, from the sizes of their stretches
-                int before = 0;
-                for (int ww = 0; ww < w; ++ww)
-                    before += s_cnt[(ww * kvol + k + 1) * kHalves] - s_cnt[(ww * kvol + k) * kHalves];
-                const int64_t p = (int64_t)k * a.pair_stride + s_excl[k] + before + pos;
-                a.pair_in[p] = v;
-                a.pair_out[p] = (int32_t)r;
-            }
-        }
-      }
+    if ((int)threadIdx.x < nclass) {
+        int sum = 0;
+        for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cls[threadIdx.x][ww];
+        agg[t * nclass + threadIdx.x] = sum;
     }
 }
 
 // Rows of a strided map's input side in position-class order, and per 256 entries of that order the offsets
-// that can link them.  perm[cls_base[c] + (rows of class c in earlier tiles) + rank in the tile] = row.
+// that can link them.  perm[(rows of lower classes) + (rows of class c in earlier tiles) + rank in the tile] = row.
 // mask[tile][k / 32] bit k % 32 = offset k can link a row of one of the position classes present in
 // perm[tile*256 .. +255]: offset (ax, ay, az) links an input at class r to an output only if, per axis, the
 // offset's displacement is congruent to r modulo the stride (output coordinates are multiples of the stride).
-__global__ __launch_bounds__(kThreads) void class_emit_kernel(const int4* __restrict__ coords, Count cn, int ts, int stride,
-                                                              int nclass, int K, const int32_t* __restrict__ cls_excl,
-                                                              const int32_t* __restrict__ cls_base,
-                                                              int32_t* __restrict__ perm, uint32_t* __restrict__ mask) {
+__global__ __launch_bounds__(kTileRows) void class_emit_kernel(const int4* __restrict__ coords, int64_t n, int ts, int stride,
+                                                               int nclass, int K, const int32_t* __restrict__ agg,
+                                                               int32_t* __restrict__ perm, uint32_t* __restrict__ mask) {
     __shared__ int s_cnt[32][kSubTiles];
+    __shared__ int s_total[32], s_before[32], s_base[33];
     __shared__ uint32_t s_cm[32][4];  // offsets possible for each class
-    const int64_t n = get(cn);
-    const int64_t t = blockIdx.x;
-    if (t * kTileRows >= n) return;
+    const int64_t t = blockIdx.x, ntiles = (n + kTileRows - 1) / kTileRows;
     const int64_t r = t * kTileRows + threadIdx.x;
     const int cls = r < n ? cell_class(coords[r], ts, stride) : -1;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     int rank = 0;
     for (int c = 0; c < nclass; ++c) {
         const unsigned long long m = __ballot(cls == c);
         if (lane == 0) s_cnt[c][w] = __popcll(m);
         if (cls == c) rank = __popcll(m & ((1ull << lane) - 1ull));
     }
+    for (int c = w; c < nclass; c += kSubTiles) {  // a wavefront per class: rows of the class before this tile, and in all
+        int before = 0, all = 0;
+        for (int64_t tt = lane; tt < ntiles; tt += 64) {
+            const int v = agg[tt * nclass + c];
+            all += v;
+            before += tt < t ? v : 0;
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            before += __shfl_xor(before, d, 64);
+            all += __shfl_xor(all, d, 64);
+        }
+        if (lane == 0) {
+            s_before[c] = before;
+            s_total[c] = all;
+        }
+    }
     const int centre = (K & 1) ? (K - 1) / 2 : 0;
-    if ((int)threadIdx.x < nclass) {
-        const int c = threadIdx.x;
+    if (tid >= 64 && tid < 64 + nclass) {
+        const int c = tid - 64;
         const int rr[3] = {c / (stride * stride), c / stride % stride, c % stride};
         uint32_t m[4] = {0u, 0u, 0u, 0u};
         for (int k = 0; k < K * K * K; ++k) {
@@ -478,145 +445,114 @@ __global__ __launch_bounds__(kThreads) void class_emit_kernel(const int4* __rest
         for (int i = 0; i < 4; ++i) s_cm[c][i] = m[i];
     }
     __syncthreads();
+    if (tid == 0) {
+        int run = 0;
+        for (int c = 0; c < nclass; ++c) {
+            s_base[c] = run;
+            run += s_total[c];
+        }
+        s_base[nclass] = run;
+    }
+    __syncthreads();
     if (cls >= 0) {
         for (int j = 0; j < w; ++j) rank += s_cnt[cls][j];
-        perm[cls_base[cls] + cls_excl[t * nclass + cls] + rank] = (int32_t)r;
+        perm[s_base[cls] + s_before[cls] + rank] = (int32_t)r;
     }
-    if (threadIdx.x < 4) {  // the mask of tile t of the class-sorted order
-        const int64_t lo = t * kTileRows, hi = lo + kTileRows < n ? lo + kTileRows : n;
-        uint32_t m = 0u;
-        for (int c = 0; c < nclass; ++c)
-            if (cls_base[c] < hi && cls_base[c + 1] > lo) m |= s_cm[c][threadIdx.x];
-        mask[t * 4 + threadIdx.x] = m;
+    if (tid < 16) {  // the masks of this tile's four 256-entry stretches of the class-sorted order
+        const int64_t mt = t * 4 + (tid >> 2), lo = mt * 256, hi = lo + 256 < n ? lo + 256 : n;
+        if (lo < n) {
+            uint32_t m = 0u;
+            for (int c = 0; c < nclass; ++c)
+                if (s_base[c] < hi && s_base[c + 1] > lo) m |= s_cm[c][tid & 3];
+            mask[mt * 4 + (tid & 3)] = m;
+        }
     }
 }
 
 inline unsigned blocks256(int64_t n) { return (unsigned)((n + 255) / 256); }
+inline int64_t tiles_of(int64_t n) { return (n + kTileRows - 1) / kTileRows; }
+inline unsigned chunks_of(int kvol) { return (unsigned)((kvol + kChunk - 1) / kChunk); }
 
-// Everything a build needs besides the tables: the tile counts and sums of both sides, the class prefixes of a
-// strided input side.
-struct Work {
-    Buf mem;
-    int32_t *cnt_out = nullptr, *cnt_in = nullptr;
-    Sums sums_out{}, sums_in{};
-    int32_t *cls_excl = nullptr, *cls_base = nullptr;
-};
-
-int make_work(Work& wk, int64_t nt_out, int64_t nt_in, int kvol, int nclass, bool two_sides, hipStream_t s) {
-    const int64_t no = nt_out ? nt_out : 1, ni = two_sides ? (nt_in ? nt_in : 1) : 0;
-    const int w_out = kvol, w_in = kvol + nclass;
-    const int64_t n_ent = (int64_t)kSubTiles * kvol * kHalves;
-    const int64_t words = 2 * no * w_out + 2 * ni * w_in + ni * nclass + nclass + 2 + (no + ni) * n_ent;
-    wk.mem = dev_alloc((size_t)words * 4, s);
-    if (!wk.mem) return SP_ERR_ALLOC;
-    int32_t* q = ptr<int32_t>(wk.mem);
-    wk.sums_out = Sums{q, q + no * w_out, w_out};
-    q += 2 * no * w_out;
-    wk.sums_in = Sums{q, q + ni * w_in, w_in};
-    q += 2 * ni * w_in;
-    wk.cls_excl = q;
-    wk.cls_base = q + ni * nclass;
-    q += ni * nclass + nclass + 2;
-    wk.cnt_out = q;
-    wk.cnt_in = q + no * n_ent;
-    return SP_OK;
+// Memory of a side's lists: `pitch` entries per offset.
+int reserve_lists(MapSide& side, int64_t n_ub, int64_t pitch, int kvol, hipStream_t s) {
+    const size_t entries = (size_t)(pitch ? pitch : 1) * kvol;
+    side.pitch = pitch;
+    side.off = dev_alloc((size_t)(tiles_of(n_ub) * kSubTiles + 1) * kvol * kHalves * 4, s);
+    side.src = dev_alloc(entries * 4, s);
+    side.dst = dev_alloc(entries * 4, s);
+    return side.off && side.src && side.dst ? SP_OK : SP_ERR_ALLOC;
 }
 
-// Second half of a map build, shared by every way of filling the neighbour tables: on entry both tables are
-// complete (on the stream).  One launch per side turns them into lists; a strided input side also gets its
-// position-class order.  n_in_ub / n_out_ub: upper bounds of the row counts, cn_in / cn_out: where the kernels
-// find the true ones.
-int finish_map(sp_kmap* m, bool symmetric, Work& wk, int64_t n_in_ub, int64_t n_out_ub, Count cn_in, Count cn_out,
+size_t counts_bytes(int64_t n_ub, int kvol) {
+    const int64_t nt = tiles_of(n_ub) ? tiles_of(n_ub) : 1;
+    return (size_t)nt * kvol * (kSubTiles * kHalves + 1) * 4;
+}
+Counts counts_in(const Buf& b, int64_t n_ub, int kvol) {
+    const int64_t nt = tiles_of(n_ub) ? tiles_of(n_ub) : 1;
+    int32_t* p = ptr<int32_t>(b);
+    return Counts{p, p + nt * kvol * kSubTiles * kHalves};
+}
+
+EmitArgs emit_args(const MapSide& side, Count n_rows, int kvol, const Counts& counts) {
+    EmitArgs a{};
+    a.nbr = ptr<int32_t>(side.nbr);
+    a.n_rows = n_rows;
+    a.kvol = kvol;
+    a.counts = counts;
+    a.off = ptr<int32_t>(side.off);
+    a.src = ptr<int32_t>(side.src);
+    a.dst = ptr<int32_t>(side.dst);
+    a.pitch = side.pitch;
+    return a;
+}
+
+// Second half of a map build, shared by every way of filling the neighbour tables: on entry both tables and the
+// output side's counts are complete (on the stream).  n_in_ub / n_out_ub: upper bounds of the row counts, cn_in /
+// cn_out: where the kernels find the true ones.  Emits the output side's lists; an input side of its own gets the
+// memory for lists and class order.
+int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub, int64_t n_out_ub, Count cn_in, Count cn_out,
                int nclass, hipStream_t s) {
     MapSide& so = m->out_side;
     MapSide& si = m->in_side;
     const int kvol = m->kvol;
-    const int64_t nt_out = (n_out_ub + kTileRows - 1) / kTileRows, nt_in = (n_in_ub + kTileRows - 1) / kTileRows;
-    const int64_t most = std::min(n_out_ub, n_in_ub) * kvol;  // links there can be
-    m->pair_stride = std::min(n_out_ub, n_in_ub);
-    m->pair_in = dev_alloc((size_t)(most ? most : 1) * 4, s);
-    m->pair_out = dev_alloc((size_t)(most ? most : 1) * 4, s);
-    m->d_koff = dev_alloc((size_t)(kvol + 1) * 4, s);
-    so.tl_src = dev_alloc((size_t)(most ? most : 1) * 4, s);
-    so.tl_row = dev_alloc((size_t)(most ? most : 1) * 2, s);
-    if (!m->pair_in || !m->pair_out || !m->d_koff || !so.tl_src || !so.tl_row) return SP_ERR_ALLOC;
     const bool mailed = mail_acquire(&m->mail);
-    EmitArgs a{};
-    a.nbr = ptr<int32_t>(so.nbr);
-    a.n_rows = cn_out;
-    a.kvol = kvol;
-    a.tl_off = ptr<int32_t>(so.tl_off);
-    a.tl_src = ptr<int32_t>(so.tl_src);
-    a.tl_row = ptr<uint16_t>(so.tl_row);
-    a.pair_in = ptr<int32_t>(m->pair_in);
-    a.pair_out = ptr<int32_t>(m->pair_out);
-    a.pair_stride = m->pair_stride;
-    a.cnt = wk.cnt_out;
-    a.sums = wk.sums_out;
-    a.d_koff = ptr<int32_t>(m->d_koff);
+    EmitArgs a = emit_args(so, cn_out, kvol, counts);
+    a.d_counts = ptr<int32_t>(m->d_counts);
     a.mail = mailed ? m->mail.d : nullptr;
     a.mail_seq = m->mail.seq;
     a.n_in = cn_in;
     a.n_out = cn_out;
-    {
-        CountArgs c{};
-        c.nbr = a.nbr;
-        c.n_rows = cn_out;
-        c.kvol = kvol;
-        c.cnt = wk.cnt_out;
-        c.sums = wk.sums_out;
-        hipLaunchKernelGGL(count_kernel, dim3((unsigned)(nt_out ? nt_out : 1), (unsigned)((kvol + kChunk - 1) / kChunk)), dim3(kThreads), 0, s, c);
-        hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)c.sums.width), dim3(1024), 0, s, c.sums, cn_out);
-    }
-    const unsigned chunks = (unsigned)((kvol + kChunk - 1) / kChunk);
-    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt_out ? nt_out : 1), chunks), dim3(kThreads), 0, s, a);
+    const int64_t nt = tiles_of(n_out_ub);
+    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt ? nt : 1), chunks_of(kvol)), dim3(kTileRows), 0, s, a);
     m->mail.armed = mailed;
     m->mail.stream = s;
+    m->pair_in = so.src;
+    m->pair_out = so.dst;
+    m->pair_stride = so.pitch;
     if (symmetric) {
         si = so;  // same lists; the link (i, o) at offset k is the link (o, i) at offset kvol-1-k
         si.flip = true;
     } else {
-        si.tl_src = dev_alloc((size_t)(most ? most : 1) * 4, s);
-        si.tl_row = dev_alloc((size_t)(most ? most : 1) * 2, s);
-        if (!si.tl_src || !si.tl_row) return SP_ERR_ALLOC;
-        EmitArgs b{};
-        b.nbr = ptr<int32_t>(si.nbr);
-        b.n_rows = cn_in;
-        b.kvol = kvol;
-        b.tl_off = ptr<int32_t>(si.tl_off);
-        b.tl_src = ptr<int32_t>(si.tl_src);
-        b.tl_row = ptr<uint16_t>(si.tl_row);
-        b.cnt = wk.cnt_in;
-        b.sums = wk.sums_in;
-        b.nclass = nclass;
-        b.cls_excl = wk.cls_excl;
-        b.cls_base = wk.cls_base;
-        CountArgs c{};
-        c.nbr = b.nbr;
-        c.n_rows = cn_in;
-        c.kvol = kvol;
-        c.cnt = wk.cnt_in;
-        c.sums = wk.sums_in;
-        c.coords = ptr<int4>(m->c_in->coords);
-        c.ts = m->c_in->ts;
-        c.stride = m->stride;
-        c.nclass = nclass;
-        hipLaunchKernelGGL(count_kernel, dim3((unsigned)(nt_in ? nt_in : 1), chunks), dim3(kThreads), 0, s, c);
-        hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)c.sums.width), dim3(1024), 0, s, c.sums, cn_in);
-        hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt_in ? nt_in : 1), chunks), dim3(kThreads), 0, s, b);
+        SP_TRY(reserve_lists(si, n_in_ub, so.pitch, kvol, s));
+        si.work = std::make_shared<SideWork>();
+        SideWork& w = *si.work;
+        w.counts = dev_alloc(std::max(counts_bytes(n_in_ub, kvol), (size_t)(tiles_of(n_in_ub) + 1) * 32 * 4), s);
+        if (!w.counts) return SP_ERR_ALLOC;
         if (nclass && n_in_ub > 0) {
             si.perm = dev_alloc((size_t)n_in_ub * 4, s);
-            si.tile_mask = dev_alloc((size_t)nt_in * 16, s);
+            si.tile_mask = dev_alloc((size_t)((n_in_ub + 255) / 256) * 16, s);
             if (!si.perm || !si.tile_mask) return SP_ERR_ALLOC;
-            hipLaunchKernelGGL(class_emit_kernel, dim3((unsigned)nt_in), dim3(kThreads), 0, s, ptr<int4>(m->c_in->coords), cn_in,
-                               m->c_in->ts, m->stride, nclass, m->K, wk.cls_excl, wk.cls_base, ptr<int32_t>(si.perm),
-                               ptr<uint32_t>(si.tile_mask));
+            w.coords = m->c_in->coords;
+            w.ts = m->c_in->ts;
+            w.stride = m->stride;
+            w.K = m->K;
+            w.nclass = nclass;
         }
     }
     SP_HIP(hipGetLastError());
     if (!mailed) {  // no mail slot free: wait here
-        std::vector<uint32_t> h(kvol + 1);
-        SP_TRY(read_back(h.data(), ptr<int32_t>(m->d_koff), (size_t)(kvol + 1) * 4, s));
+        std::vector<uint32_t> h(kvol);
+        SP_TRY(read_back(h.data(), ptr<int32_t>(m->d_counts), (size_t)kvol * 4, s));
         SP_TRY(coords_resolve(m->c_in));
         SP_TRY(coords_resolve(m->c_out));
         m->set_sizes(m->c_in->n, m->c_out->n, h.data());
@@ -626,7 +562,55 @@ int finish_map(sp_kmap* m, bool symmetric, Work& wk, int64_t n_in_ub, int64_t n_
     return SP_OK;
 }
 
+// First call that needs it builds on its stream; later calls from another stream wait for that one.  A build that is
+// being captured into a graph runs when the graph does, so it does not count as done.
+template <class Build>
+int once(bool& built, hipStream_t& on, hipStream_t s, Build build) {
+    if (built) return s == on ? SP_OK : stream_wait(on, s);
+    SP_TRY(build());
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap == hipStreamCaptureStatusNone) {
+        built = true;
+        on = s;
+    }
+    return SP_OK;
+}
+
 }  // namespace
+
+int need_lists(const MapSide& side, int kvol, hipStream_t s) {
+    if (!side.work || side.n_rows == 0) return SP_OK;
+    SideWork& w = *side.work;
+    std::lock_guard<std::mutex> lk(w.mu);
+    return once(w.lists, w.lists_on, s, [&]() -> int {
+        // (the class build uses the same scratch; both run on the stream order that `once` keeps)
+        if (w.classes && w.classes_on != s) SP_TRY(stream_wait(w.classes_on, s));
+        const Count n{nullptr, side.n_rows};
+        const Counts c = counts_in(w.counts, side.n_rows, kvol);
+        const dim3 grid((unsigned)tiles_of(side.n_rows), chunks_of(kvol));
+        hipLaunchKernelGGL(count_kernel, grid, dim3(kTileRows), 0, s, ptr<int32_t>(side.nbr), n, kvol, c, (int32_t*)nullptr);
+        hipLaunchKernelGGL(emit_kernel, grid, dim3(kTileRows), 0, s, emit_args(side, n, kvol, c));
+        SP_HIP(hipGetLastError());
+        return SP_OK;
+    });
+}
+
+int need_classes(const MapSide& side, hipStream_t s) {
+    if (!side.tile_mask || !side.work || side.n_rows == 0) return SP_OK;
+    SideWork& w = *side.work;
+    std::lock_guard<std::mutex> lk(w.mu);
+    return once(w.classes, w.classes_on, s, [&]() -> int {
+        if (w.lists && w.lists_on != s) SP_TRY(stream_wait(w.lists_on, s));
+        const dim3 grid((unsigned)tiles_of(side.n_rows));
+        hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
+                           ptr<int32_t>(w.counts));
+        hipLaunchKernelGGL(class_emit_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
+                           w.K, ptr<int32_t>(w.counts), ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
+        SP_HIP(hipGetLastError());
+        return SP_OK;
+    });
+}
 
 int kmap_resolve(const sp_kmap_t* m) {
     std::lock_guard<std::mutex> lk(m->mu);
@@ -646,14 +630,17 @@ int kmap_resolve(const sp_kmap_t* m) {
 
 }  // namespace sp
 
-// host copies of the sizes, once they have arrived: koff = kvol + 1 prefix values
-void sp_kmap::set_sizes(int64_t ni, int64_t no, const uint32_t* koff_words) const {
+// host copies of the sizes, once they have arrived: counts per offset
+void sp_kmap::set_sizes(int64_t ni, int64_t no, const uint32_t* count_words) const {
     n_in = ni;
     n_out = no;
     koff.resize(kvol + 1);
     counts.resize(kvol);
-    for (int k = 0; k <= kvol; ++k) koff[k] = koff_words[k];
-    for (int k = 0; k < kvol; ++k) counts[k] = koff[k + 1] - koff[k];
+    koff[0] = 0;
+    for (int k = 0; k < kvol; ++k) {
+        counts[k] = count_words[k];
+        koff[k + 1] = koff[k] + counts[k];
+    }
     total = koff[kvol];
     out_side.n_rows = no;
     out_side.n_src = ni;
@@ -711,7 +698,7 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
         m->c_out = cin;
     } else {
         sp_coords* co = nullptr;
-        SP_TRY(coords_build_impl(ptr<int32_t>(in->coords), n_in_ub, cn_in.d, in->ts * stride, in->ts * stride, s, &co));
+        SP_TRY(coords_build_impl(ptr<int32_t>(in->coords), n_in_ub, cn_in.d, in->ts * stride, in->ts * stride, in, s, &co));
         cin->ref.fetch_add(1);
         co->src_of = cin;  // its inverse array has one entry per row of `in`
         m->c_out = co;
@@ -719,65 +706,55 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
         if (co->resolved) n_out_ub = co->n;
     }
     const bool symmetric = (stride == 1) && (kernel_size & 1);
-    const int64_t nt_out = (n_out_ub + kTileRows - 1) / kTileRows, nt_in = (n_in_ub + kTileRows - 1) / kTileRows;
-    const int step = dilation * in->ts;
     const int nclass = (stride > 1 && stride * stride * stride <= 32) ? stride * stride * stride : 0;
 
     MapSide& so = m->out_side;
     MapSide& si = m->in_side;
     so.nbr = dev_alloc((size_t)(n_out_ub ? n_out_ub : 1) * kvol * 4, s);
-    so.tl_off = dev_alloc((size_t)(nt_out * kvol * kSubTiles * kHalves + 1) * 4, s);
-    Work wk;
-    SP_TRY(make_work(wk, nt_out, nt_in, kvol, nclass, !symmetric, s));
-    if (!so.nbr || !so.tl_off) return SP_ERR_ALLOC;
+    SP_TRY(reserve_lists(so, n_out_ub, std::min(n_out_ub, n_in_ub), kvol, s));
+    m->d_counts = dev_alloc((size_t)(kvol + 1) * 4, s);
+    Buf work = dev_alloc(counts_bytes(n_out_ub, kvol), s);
+    if (!so.nbr || !m->d_counts || !work) return SP_ERR_ALLOC;
     if (!symmetric) {
         si.nbr = dev_alloc((size_t)(n_in_ub ? n_in_ub : 1) * kvol * 4, s);
-        si.tl_off = dev_alloc((size_t)(nt_in * kvol * kSubTiles * kHalves + 1) * 4, s);
-        if (!si.nbr || !si.tl_off) return SP_ERR_ALLOC;
+        if (!si.nbr) return SP_ERR_ALLOC;
     }
-    const bool children = stride > 1 && kernel_size == stride && kernel_size % 2 == 0;
-    const int identity_k = symmetric ? (kvol - 1) / 2 : -1;
-    // one reset launch: "no link" where the searches will not write, zeros in the bookkeeping words
-    {
-        NegRegion ra{nullptr, cn_out, 0, kvol}, rb{nullptr, cn_in, 0, kvol};
-        int64_t cover = 0;
-        if (symmetric && kvol > 1) {
-            ra = NegRegion{ptr<int32_t>(so.nbr), cn_out, identity_k + 1, kvol};
-            cover = std::max(cover, n_out_ub * (int64_t)(kvol - 1 - identity_k));
+    const Counts counts = counts_in(work, n_out_ub, kvol);
+    int32_t* done = ptr<int32_t>(m->d_counts) + kvol;
+    const unsigned nt = (unsigned)(tiles_of(n_out_ub) ? tiles_of(n_out_ub) : 1);
+    if (stride > 1 && kernel_size == stride && kernel_size % 2 == 0) {
+        if (n_out_ub > 0) {
+            hipLaunchKernelGGL(reset_kernel, dim3(blocks256((n_out_ub * (int64_t)kvol + 3) / 4)), dim3(kThreads), 0, s, ptr<int32_t>(so.nbr),
+                               cn_out, kvol);
+            hipLaunchKernelGGL(child_map_kernel, dim3(blocks256(n_in_ub)), dim3(kThreads), 0, s, ptr<int4>(in->coords), cn_in, in->ts,
+                               stride, ptr<int32_t>(m->c_out->inverse), cn_out, kvol, ptr<int32_t>(so.nbr), ptr<int32_t>(si.nbr));
         }
-        if (!symmetric) {
-            rb = NegRegion{ptr<int32_t>(si.nbr), cn_in, 0, kvol};
-            cover = std::max(cover, n_in_ub * (int64_t)kvol);
-            if (children) {
-                ra = NegRegion{ptr<int32_t>(so.nbr), cn_out, 0, kvol};
-                cover = std::max(cover, n_out_ub * (int64_t)kvol);
-            }
-        }
-        if (cover > 0) hipLaunchKernelGGL(reset_kernel, dim3(blocks256(cover)), dim3(256), 0, s, ra, rb);
-    }
-    if (nt_out > 0 && children) {
-        hipLaunchKernelGGL(child_map_kernel, dim3(blocks256(n_in_ub)), dim3(kThreads), 0, s, ptr<int4>(in->coords), cn_in,
-                           in->ts, stride, ptr<int32_t>(m->c_out->inverse), cn_out, ptr<int32_t>(so.nbr), ptr<int32_t>(si.nbr));
-    } else if (nt_out > 0) {
-        // mirrored table: only the (ax, ay) pairs that hold an offset up to the centre are launched
-        const int pairs_xy = symmetric ? identity_k / kernel_size + 1 : kernel_size * kernel_size;
-        const dim3 grid((unsigned)nt_out, (unsigned)pairs_xy);
-        int32_t* nbr_in_arg = symmetric ? (int32_t*)nullptr : ptr<int32_t>(si.nbr);
-#define SP_LAUNCH_PROBE(KS)                                                                                          \
-    hipLaunchKernelGGL(probe_kernel<KS>, grid, dim3(kThreads), 0, s, ptr<int4>(m->c_out->coords), cn_out,              \
-                       ptr<HashSlot>(in->tab.slots), in->tab.cap, in->tab.zshift, step, identity_k, ptr<int32_t>(so.nbr), \
-                       nbr_in_arg, cn_in)
+        hipLaunchKernelGGL(count_kernel, dim3(nt, chunks_of(kvol)), dim3(kTileRows), 0, s, ptr<int32_t>(so.nbr), cn_out, kvol, counts, done);
+    } else {
+        if (!symmetric && n_in_ub > 0)
+            hipLaunchKernelGGL(reset_kernel, dim3(blocks256((n_in_ub * (int64_t)kvol + 3) / 4)), dim3(kThreads), 0, s, ptr<int32_t>(si.nbr),
+                               cn_in, kvol);
+        const TableView tab = table_view(in);
+        // columns per thread: all K of one ax where the rows alone fill the chip, one where they do not
+        const bool few = n_out_ub < (1 << 17);
+#define SP_SEARCH(KS, NC)                                                                                                   \
+    hipLaunchKernelGGL((search_kernel<KS, NC>), dim3(xcd_grid(nt), KS * KS / NC), dim3(kTileRows), 0, s, ptr<int4>(m->c_out->coords), cn_out, tab, \
+                       dilation, symmetric ? 1 : 0, ptr<int32_t>(so.nbr), symmetric ? (int32_t*)nullptr : ptr<int32_t>(si.nbr), cn_in, \
+                       counts, done)
         switch (kernel_size) {
-            case 1: SP_LAUNCH_PROBE(1); break;
-            case 2: SP_LAUNCH_PROBE(2); break;
-            case 3: SP_LAUNCH_PROBE(3); break;
-            case 4: SP_LAUNCH_PROBE(4); break;
-            default: SP_LAUNCH_PROBE(5); break;
+            case 1: SP_SEARCH(1, 1); break;
+            case 2: SP_SEARCH(2, 1); break;
+            case 3:
+                if (few) SP_SEARCH(3, 1);
+                else SP_SEARCH(3, 3);
+                break;
+            case 4: SP_SEARCH(4, 1); break;
+            default: SP_SEARCH(5, 1); break;
         }
-#undef SP_LAUNCH_PROBE
+#undef SP_SEARCH
     }
     SP_HIP(hipGetLastError());
-    SP_TRY(finish_map(m.get(), symmetric, wk, n_in_ub, n_out_ub, cn_in, cn_out, nclass, s));
+    SP_TRY(finish_map(m.get(), symmetric, counts, n_in_ub, n_out_ub, cn_in, cn_out, nclass, s));
     if (out_coords) {
         m->c_out->ref.fetch_add(1);
         *out_coords = m->c_out;
@@ -810,7 +787,7 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
                            n_coarse, kernel_size, ts_out, ptr<int4>(cand));
     SP_HIP(hipGetLastError());
     sp_coords* fine = nullptr;
-    SP_TRY(coords_build_impl(ptr<int32_t>(cand), n_cand, nullptr, 1, ts_out, s, &fine));
+    SP_TRY(coords_build_impl(ptr<int32_t>(cand), n_cand, nullptr, 1, ts_out, nullptr, s, &fine));
 
     // the stride-s convolution's map from the fine rows (inputs) to the coarse rows (outputs) ...
     std::unique_ptr<sp_kmap, int (*)(sp_kmap*)> m(new sp_kmap, sp_kmap_destroy);
@@ -828,27 +805,26 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
     const Count cn_fine{nullptr, n_fine}, cn_coarse{nullptr, n_coarse};
     if (n_fine * (int64_t)kvol >= ((int64_t)1 << 31) - 4096)
         return fail(SP_ERR_INVALID_ARG, "n * kernel volume exceeds 32-bit list offsets");
-    const int64_t nt_out = (n_coarse + kTileRows - 1) / kTileRows, nt_in = (n_fine + kTileRows - 1) / kTileRows;
     const int nclass = (stride > 1 && stride * stride * stride <= 32) ? stride * stride * stride : 0;
     MapSide& so = m->out_side;
     MapSide& si = m->in_side;
     so.nbr = dev_alloc((size_t)(n_cand ? n_cand : 1) * 4, s);
-    so.tl_off = dev_alloc((size_t)(nt_out * kvol * kSubTiles * kHalves + 1) * 4, s);
     si.nbr = dev_alloc((size_t)(n_fine ? n_fine : 1) * kvol * 4, s);
-    si.tl_off = dev_alloc((size_t)(nt_in * kvol * kSubTiles * kHalves + 1) * 4, s);
-    Work wk;
-    SP_TRY(make_work(wk, nt_out, nt_in, kvol, nclass, true, s));
-    if (!so.nbr || !so.tl_off || !si.nbr || !si.tl_off) return SP_ERR_ALLOC;
-    {
-        NegRegion ra{nullptr, cn_coarse, 0, kvol}, rb{ptr<int32_t>(si.nbr), cn_fine, 0, kvol};
-        const int64_t cover = n_fine * (int64_t)kvol;
-        if (cover > 0) hipLaunchKernelGGL(reset_kernel, dim3(blocks256(cover)), dim3(256), 0, s, ra, rb);
-    }
+    SP_TRY(reserve_lists(so, n_coarse, std::min(n_coarse, n_fine), kvol, s));
+    m->d_counts = dev_alloc((size_t)(kvol + 1) * 4, s);
+    Buf work = dev_alloc(counts_bytes(n_coarse, kvol), s);
+    if (!so.nbr || !si.nbr || !m->d_counts || !work) return SP_ERR_ALLOC;
+    const Counts counts = counts_in(work, n_coarse, kvol);
+    if (n_fine > 0)
+        hipLaunchKernelGGL(reset_kernel, dim3(blocks256((n_fine * (int64_t)kvol + 3) / 4)), dim3(kThreads), 0, s, ptr<int32_t>(si.nbr), cn_fine,
+                           kvol);
     if (n_cand > 0)
         hipLaunchKernelGGL(gen_tables_kernel, dim3(blocks256(n_cand)), dim3(kThreads), 0, s, ptr<int32_t>(fine->inverse),
                            n_coarse, cn_fine, kvol, ptr<int32_t>(so.nbr), ptr<int32_t>(si.nbr));
+    hipLaunchKernelGGL(count_kernel, dim3((unsigned)(tiles_of(n_coarse) ? tiles_of(n_coarse) : 1), chunks_of(kvol)), dim3(kTileRows), 0, s,
+                       ptr<int32_t>(so.nbr), cn_coarse, kvol, counts, ptr<int32_t>(m->d_counts) + kvol);
     SP_HIP(hipGetLastError());
-    SP_TRY(finish_map(m.get(), false, wk, n_fine, n_coarse, cn_fine, cn_coarse, nclass, s));
+    SP_TRY(finish_map(m.get(), false, counts, n_fine, n_coarse, cn_fine, cn_coarse, nclass, s));
     // ... handed out with the roles swapped: inputs = the given (coarse) rows, outputs = the created rows
     sp_kmap_t* t = nullptr;
     SP_TRY(sp_kmap_transpose(m.get(), &t));
@@ -879,7 +855,7 @@ int sp_kmap_transpose(const sp_kmap_t* f, sp_kmap_t** transposed) {
     t->pair_stride = f->pair_stride;
     t->counts = f->counts;
     t->koff = f->koff;
-    t->d_koff = f->d_koff;
+    t->d_counts = f->d_counts;
     t->c_in = f->c_out;
     t->c_out = f->c_in;
     t->stream = f->stream;

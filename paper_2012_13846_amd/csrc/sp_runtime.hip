@@ -216,6 +216,10 @@ Buf dev_alloc(size_t bytes, hipStream_t s) {
     return b;
 }
 
+int stream_wait(hipStream_t from, hipStream_t to) {
+    std::lock_guard<std::mutex> lk(pool().mu);
+    return pool().hand_over(from, to) ? SP_OK : fail(SP_ERR_HIP, "could not make one stream wait for another");
+}
 int pool_trim() { return pool().trim(); }
 int64_t pool_bytes() {
     std::lock_guard<std::mutex> lk(pool().mu);

@@ -545,7 +545,7 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ src
 template <typename T>
 __global__ __launch_bounds__(256) void wgrad_plain_kernel(const int32_t* __restrict__ pair_in,
                                                           const int32_t* __restrict__ pair_out,
-                                                          const int32_t* __restrict__ koff, int64_t pair_stride,
+                                                          const int32_t* __restrict__ counts, int64_t pair_stride,
                                                           const T* __restrict__ X, const T* __restrict__ dY, int cin,
                                                           int cout, float* __restrict__ dw) {
     const int k = blockIdx.y;
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(256) void wgrad_plain_kernel(const int32_t* __restr
     const int co = e / cin, ci = e % cin;
     float s = 0.f;
     const int64_t p0 = (int64_t)k * pair_stride;
-    for (int64_t p = p0; p < p0 + (koff[k + 1] - koff[k]); ++p)
+    for (int64_t p = p0; p < p0 + counts[k]; ++p)
         s = fmaf(load_f32(dY + (size_t)pair_out[p] * cout + co), load_f32(X + (size_t)pair_in[p] * cin + ci), s);
     dw[(size_t)k * cin * cout + e] = s;
 }
@@ -661,7 +661,7 @@ int wgrad_typed(const sp_kmap* m, const void* x, const void* dy, float* dw, int 
                        (uint64_t)kvol * m->pair_stride * 4 < lim;
     if (!small || m->total == 0 || kvol > 128) {
         hipLaunchKernelGGL(wgrad_plain_kernel<T>, dim3((cin * cout + 255) / 256, kvol), dim3(256), 0, s,
-                           ptr<int32_t>(m->pair_in), ptr<int32_t>(m->pair_out), ptr<int32_t>(m->d_koff), m->pair_stride,
+                           ptr<int32_t>(m->pair_in), ptr<int32_t>(m->pair_out), ptr<int32_t>(m->d_counts), m->pair_stride,
                            static_cast<const T*>(x), static_cast<const T*>(dy), cin, cout, dw);
         SP_HIP(hipGetLastError());
         return SP_OK;
