@@ -1,8 +1,9 @@
 // Coordinate sets: duplicate merging in first-occurrence order through a grid or a hash table (sp_hash.h), strided
 // (coarser) coordinate generation.  Sec. III-B: sparse tensor definition and step 1.
 //
-// No host round trip.  Small sets (kGridRows and less, where every launch counts): reset the hash table, insert every
-// row (slot.first = smallest row carrying the key), number, inverse.  Larger sets: the extent of the coordinates (a
+// No host round trip.  Up to kSmallRows one workgroup does everything in one launch, with the hash table in LDS.  Up to
+// kGridRows (where every launch counts): reset the hash table, insert every row (slot.first = smallest row carrying
+// the key), number, inverse.  Larger sets: the extent of the coordinates (a
 // coarser set takes its parent's), prepare (every workgroup derives the grid's box, or that a hash table is needed, and
 // clears that table), mark the occupied blocks (or insert into the hash table), number the blocks and clear their
 // cells, put the smallest row of each cell into it, number, inverse.
@@ -22,6 +23,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kRowsPerThread = 4;
 constexpr int kNumberThreads = 1024;           // most threads of a numbering block
+constexpr int64_t kSmallRows = 8192;           // up to here one workgroup (8 rows a thread, keys and slots in LDS)
+constexpr int kSmallSlots = 16384;             // most slots of its table
 constexpr int64_t kGridRows = 32768;           // up to here a hash table: four launches instead of seven
 constexpr int kBoxBlocks = 256;                // blocks of the extent kernel = threads of a prepare block
 constexpr int kBoxWords = 12;                  // min and max of b, x, y, z; out of range; off the lattice
@@ -79,6 +82,120 @@ __global__ __launch_bounds__(kThreads) void reset_kernel(HashSlot* __restrict__ 
     if (i < cap) clear_slot(&tab[i]);
     if (i < kMetaWords) meta[i] = 0;
     if (i < n_desc) desc[i] = 0ull;
+}
+
+// A small set in one launch: hash, merge, number, inverse, and the table written out as the searches read it.  Bound by
+// latency: the four launches it replaces spent 25 us on 2048 rows, most of it in chains of dependent atomics on the
+// fabric, which are LDS operations here.  Slot: -1, or the smallest source row of its key; once numbered, that row
+// and its rank << 16.
+__global__ __launch_bounds__(kNumberThreads) void small_build_kernel(const int4* __restrict__ src, int64_t n_host,
+                                                                     const int32_t* __restrict__ d_n, int32_t floor_step, Build t,
+                                                                     int4* __restrict__ coords, int32_t* __restrict__ inverse,
+                                                                     uint32_t* __restrict__ mail, uint32_t mail_seq) {
+    constexpr int kPer = (int)(kSmallRows / kNumberThreads);
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int s_row[kPer][kNumberThreads / 64];
+    __shared__ int s_err;
+    const int cap = (int)t.cap;
+    int* slots = reinterpret_cast<int*>(smem);
+    uint64_t* keys = reinterpret_cast<uint64_t*>(smem + (size_t)cap * 4);
+    const int n = (int)row_count(n_host, d_n);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int i = tid; i < cap; i += kNumberThreads) slots[i] = -1;
+    if (tid == 0) s_err = 0;
+    int4 c[kPer];
+    bool ok[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int i = j * kNumberThreads + tid;
+        ok[j] = i < n;
+        if (ok[j]) c[j] = load_row(src, i, floor_step);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (!ok[j]) continue;
+        uint64_t key;
+        ok[j] = pack_key(c[j].x, c[j].y, c[j].z, c[j].w, &key);
+        if (ok[j]) keys[j * kNumberThreads + tid] = key;
+        else s_err = 1;
+    }
+    __syncthreads();
+    int at[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        at[j] = 0;
+        if (!ok[j]) continue;
+        const int i = j * kNumberThreads + tid;
+        const uint64_t key = keys[i];
+        uint32_t bucket, pos;
+        hash_home(key, (uint32_t)cap, t.zshift, &bucket, &pos);
+        int s = (int)(bucket * 4 + pos);
+        for (int probe = 0; probe < cap; ++probe) {  // at most half of the slots are ever taken: an empty one is met
+            int cur = slots[s];
+            if (cur == -1) cur = atomicCAS(&slots[s], -1, i);
+            if (cur == -1) break;
+            if (keys[cur] == key) {
+                if (cur > i) atomicMin(&slots[s], i);
+                break;
+            }
+            s = (s + 1) & (cap - 1);
+        }
+        at[j] = s;
+    }
+    __syncthreads();
+    bool f[kPer];
+    int pos[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        f[j] = ok[j] && slots[at[j]] == j * kNumberThreads + tid;
+        const unsigned long long m = __ballot(f[j]);
+        pos[j] = __popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) s_row[j][w] = __popcll(m);
+    }
+    __syncthreads();
+    int run = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        int mine = run;
+        for (int ww = 0; ww < kNumberThreads / 64; ++ww) {
+            if (ww < w) mine += s_row[j][ww];
+            run += s_row[j][ww];
+        }
+        if (f[j]) {
+            const int r = mine + pos[j];
+            coords[r] = c[j];
+            slots[at[j]] = (j * kNumberThreads + tid) | (r << 16);
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const int err = s_err;
+        t.meta[kMetaN] = run;
+        t.meta[kMetaErr] = err;
+        t.meta[kMetaGrid] = 0;
+        if (mail) {
+            mail[0] = (uint32_t)run;
+            mail[1] = (uint32_t)err;
+            __threadfence_system();
+            __hip_atomic_store(mail + kMailSeqWord, mail_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int i = j * kNumberThreads + tid;
+        if (i < n) inverse[i] = ok[j] ? slots[at[j]] >> 16 : -1;
+    }
+    for (int i = tid; i < cap; i += kNumberThreads) {
+        const int v = slots[i];
+        const uint64_t key = v >= 0 ? keys[v & 0xffff] : kEmptyKey;
+        uint4 o;
+        o.x = (uint32_t)key;
+        o.y = (uint32_t)(key >> 32);
+        o.z = (uint32_t)(v >= 0 ? v & 0xffff : kNoRow);
+        o.w = (uint32_t)(v >= 0 ? v >> 16 : -1);
+        *reinterpret_cast<uint4*>(&t.slots[i]) = o;
+    }
 }
 
 // Extent of the source rows, per block: part[block][kBoxWords].
@@ -439,8 +556,12 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     c->n_raw = n_src;
     c->ts = tensor_stride;
     c->stream = s;
+    // slots: room for every row at half load; small sets, whose builds and searches wait for the longest chain of
+    // collisions and not for memory, get an eighth
+    const bool small = n_src <= kSmallRows;
     uint32_t cap = 1024;
-    while ((int64_t)cap < 2 * n_src) cap <<= 1;
+    while ((int64_t)cap < (n_src <= kGridRows ? 8 : 2) * n_src) cap <<= 1;
+    if (small) cap = std::min<uint32_t>(cap, kSmallSlots);
     c->tab.cap = cap;
     for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
     // A grid: 32 bytes of dir per source row (128 cells of the box; 4 MB at least), whole scan blocks, and 64 bytes per
@@ -461,10 +582,10 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     // scratch: a slot or cell per source row, the look-back words, the extents
     const size_t at_bytes = ((size_t)(n_src ? n_src : 1) * 4 + 15) / 16 * 16;
     const int64_t n_desc = nb ? nb : 1;
-    Buf scratch = dev_alloc(at_bytes + (size_t)n_desc * 8 + (may_grid ? kBoxBlocks * kBoxWords * 4 : 0), s);
-    if (!c->tab.mem || !c->coords || !c->inverse || !c->meta || !scratch) return SP_ERR_ALLOC;
+    Buf scratch = small ? Buf() : dev_alloc(at_bytes + (size_t)n_desc * 8 + (may_grid ? kBoxBlocks * kBoxWords * 4 : 0), s);
+    if (!c->tab.mem || !c->coords || !c->inverse || !c->meta || (!small && !scratch)) return SP_ERR_ALLOC;
     int32_t* at = ptr<int32_t>(scratch);
-    unsigned long long* desc = reinterpret_cast<unsigned long long*>(ptr<unsigned char>(scratch) + at_bytes);
+    unsigned long long* desc = small ? nullptr : reinterpret_cast<unsigned long long*>(ptr<unsigned char>(scratch) + at_bytes);
     Build t;
     t.slots = ptr<HashSlot>(c->tab.mem);
     t.cap = cap;
@@ -483,6 +604,36 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     const dim3 rows(xcd_grid(blocks_for(n_src, kThreads))), threads(kThreads);
     const int always = n_src < (1 << 20) ? 1 : 0;
 
+    auto hand_over = [&]() -> int {  // the last launch is enqueued
+        c->mail.armed = mailed;
+        c->mail.stream = s;
+        SP_HIP(hipGetLastError());
+        if (!mailed) {  // no mail slot free: wait here, the old way
+            int32_t h[2] = {0, 0};
+            SP_TRY(read_back(h, t.meta, 8, s));
+            c->n = h[0];
+            c->status = (h[1] & 1) ? SP_ERR_RANGE : (h[1] & 2) ? SP_ERR_TABLE_FULL : (h[1] & kErrLookback) ? SP_ERR_HIP : SP_OK;
+            c->resolved = true;
+        }
+        *out = c.release();
+        return SP_OK;
+    };
+    if (small) {
+        const int lds = (int)cap * 4 + (int)(n_src ? n_src : 1) * 8;
+        {
+            static std::mutex mu;
+            static bool attr_set = false;  // one-time opt-in to > 64 KB of dynamic LDS
+            std::lock_guard<std::mutex> lk(mu);
+            if (!attr_set) {
+                SP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small_build_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSmallSlots * 4 + kSmallRows * 8)));
+                attr_set = true;
+            }
+        }
+        hipLaunchKernelGGL(small_build_kernel, dim3(1), dim3(kNumberThreads), lds, s, src, n_src, d_n_src, floor_step, t,
+                           ptr<int4>(c->coords), ptr<int32_t>(c->inverse), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
+        return hand_over();
+    }
     if (may_grid) {
         int32_t* part = nullptr;
         if (!parent) {
@@ -498,24 +649,12 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     } else {
         hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(std::max<int64_t>(cap, n_desc), kThreads)), threads, 0, s, t.slots, cap,
                            t.meta, desc, n_desc);
-        if (n_src > 0) hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
+        hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
     }
-    hipLaunchKernelGGL(number_kernel, dim3((unsigned)(nb ? nb : 1)), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at,
+    hipLaunchKernelGGL(number_kernel, dim3((unsigned)nb), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at,
                        chain, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
-    c->mail.armed = mailed;
-    c->mail.stream = s;
-    if (n_src > 0)
-        hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, n_src, d_n_src, ptr<int32_t>(c->inverse));
-    SP_HIP(hipGetLastError());
-    if (!mailed) {  // no mail slot free: wait here, the old way
-        int32_t h[2] = {0, 0};
-        SP_TRY(read_back(h, t.meta, 8, s));
-        c->n = h[0];
-        c->status = (h[1] & 1) ? SP_ERR_RANGE : (h[1] & 2) ? SP_ERR_TABLE_FULL : (h[1] & kErrLookback) ? SP_ERR_HIP : SP_OK;
-        c->resolved = true;
-    }
-    *out = c.release();
-    return SP_OK;
+    hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, n_src, d_n_src, ptr<int32_t>(c->inverse));
+    return hand_over();
 }
 
 static int status_message(int status) {
