@@ -139,7 +139,8 @@ struct SideWork {
     std::mutex mu;
     bool lists = false, classes = false;             // built
     hipStream_t lists_on = nullptr, classes_on = nullptr;
-    Buf counts;        // scratch of the list and class builds
+    Buf counts;        // scratch of the list build
+    Buf class_counts;  // of the class build
     Buf coords;        // the side's coordinates (classes)
     int ts = 1, stride = 1, K = 1, nclass = 0;
 };

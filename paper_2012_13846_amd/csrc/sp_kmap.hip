@@ -536,12 +536,13 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
         SP_TRY(reserve_lists(si, n_in_ub, so.pitch, kvol, s));
         si.work = std::make_shared<SideWork>();
         SideWork& w = *si.work;
-        w.counts = dev_alloc(std::max(counts_bytes(n_in_ub, kvol), (size_t)(tiles_of(n_in_ub) + 1) * 32 * 4), s);
+        w.counts = dev_alloc(counts_bytes(n_in_ub, kvol), s);
         if (!w.counts) return SP_ERR_ALLOC;
         if (nclass && n_in_ub > 0) {
             si.perm = dev_alloc((size_t)n_in_ub * 4, s);
             si.tile_mask = dev_alloc((size_t)((n_in_ub + 255) / 256) * 16, s);
-            if (!si.perm || !si.tile_mask) return SP_ERR_ALLOC;
+            w.class_counts = dev_alloc((size_t)tiles_of(n_in_ub) * nclass * 4, s);
+            if (!si.perm || !si.tile_mask || !w.class_counts) return SP_ERR_ALLOC;
             w.coords = m->c_in->coords;
             w.ts = m->c_in->ts;
             w.stride = m->stride;
@@ -562,15 +563,19 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
     return SP_OK;
 }
 
-// First call that needs it builds on its stream; later calls from another stream wait for that one.  A build that is
-// being captured into a graph runs when the graph does, so it does not count as done.
+// First call that needs it builds on its stream; later calls from another stream wait for that one.  Under graph
+// capture neither holds: the build runs when the graph does, so it does not count as done, and a captured stream
+// cannot wait for one that is not, so a build done elsewhere is repeated in the graph.  A build that finds an earlier
+// one at work is harmless: it writes the same words to the same places.
 template <class Build>
 int once(bool& built, hipStream_t& on, hipStream_t s, Build build) {
-    if (built) return s == on ? SP_OK : stream_wait(on, s);
-    SP_TRY(build());
+    if (built && s == on) return SP_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap == hipStreamCaptureStatusNone) {
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (built && !capturing) return stream_wait(on, s);
+    SP_TRY(build());
+    if (!capturing) {
         built = true;
         on = s;
     }
@@ -584,8 +589,6 @@ int need_lists(const MapSide& side, int kvol, hipStream_t s) {
     SideWork& w = *side.work;
     std::lock_guard<std::mutex> lk(w.mu);
     return once(w.lists, w.lists_on, s, [&]() -> int {
-        // (the class build uses the same scratch; both run on the stream order that `once` keeps)
-        if (w.classes && w.classes_on != s) SP_TRY(stream_wait(w.classes_on, s));
         const Count n{nullptr, side.n_rows};
         const Counts c = counts_in(w.counts, side.n_rows, kvol);
         const dim3 grid((unsigned)tiles_of(side.n_rows), chunks_of(kvol));
@@ -601,12 +604,11 @@ int need_classes(const MapSide& side, hipStream_t s) {
     SideWork& w = *side.work;
     std::lock_guard<std::mutex> lk(w.mu);
     return once(w.classes, w.classes_on, s, [&]() -> int {
-        if (w.lists && w.lists_on != s) SP_TRY(stream_wait(w.lists_on, s));
         const dim3 grid((unsigned)tiles_of(side.n_rows));
         hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
-                           ptr<int32_t>(w.counts));
+                           ptr<int32_t>(w.class_counts));
         hipLaunchKernelGGL(class_emit_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
-                           w.K, ptr<int32_t>(w.counts), ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
+                           w.K, ptr<int32_t>(w.class_counts), ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
         SP_HIP(hipGetLastError());
         return SP_OK;
     });

@@ -1,0 +1,99 @@
+"""The forms of the coordinate table (one workgroup's table in LDS, hash table, cell grid) where one ends and the next
+begins, and what decides between them: row counts, extent, lattice.  Coordinates, maps and their transposes are whole
+numbers: equal to the oracle's, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import dev, random_coords, sp, test_coords_build_matches_oracle, test_kmap_matches_oracle  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+check_set, check_maps = test_coords_build_matches_oracle, test_kmap_matches_oracle
+del test_coords_build_matches_oracle, test_kmap_matches_oracle
+
+
+def scaled(raw, ts, shift=0):
+    return raw * np.array([1, ts, ts, ts], np.int32) + np.array([0, shift, shift, shift], np.int32)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 8191, 8192, 8193, 32768, 32769])
+def test_row_counts_at_which_the_table_changes(sp, n):  # noqa: F811
+    raw = random_coords(n, n, 28, batches=2, lo=-14)
+    check_set(sp, "", raw)
+    check_maps(sp, "", raw, 1, 3, 1, 1)
+    check_maps(sp, "", raw, 1, 3, 2, 1)
+
+
+DENSE = random_coords(11, 40000, 37, batches=3, lo=-19) + np.array([5, 0, 0, 0], np.int32)
+CORNER = random_coords(12, 40000, 40, batches=2, lo=32728) + np.array([65534, 0, 0, 0], np.int32)
+LOW = random_coords(13, 40000, 40, batches=2, lo=-32768)
+FAR = random_coords(14, 40000, 20000, batches=9, lo=-10000)           # a box too large for a grid
+PLANE = DENSE * np.array([1, 9, 1, 0], np.int32)
+CASES = [("grid", DENSE, 1, 3, 1, 1), ("grid_k5", DENSE, 1, 5, 1, 1), ("grid_k4", DENSE, 1, 4, 1, 1), ("grid_k2", DENSE, 1, 2, 1, 1),
+         ("grid_d2", DENSE, 1, 3, 1, 2), ("grid_d5", DENSE, 1, 3, 1, 5), ("grid_k5_d7", DENSE, 1, 5, 1, 7),
+         ("grid_s2", DENSE, 1, 3, 2, 1), ("grid_s3", DENSE, 1, 3, 3, 1), ("grid_k2s2", DENSE, 1, 2, 2, 1), ("grid_k4s2", DENSE, 1, 4, 2, 1),
+         ("plane", PLANE, 1, 3, 1, 1), ("corner_d2", CORNER, 1, 3, 1, 2), ("corner_s2", CORNER, 1, 3, 2, 1), ("low_k5", LOW, 1, 5, 1, 1),
+         ("low_s2", LOW, 1, 3, 2, 1), ("hash", FAR, 1, 3, 1, 1), ("hash_s2", FAR, 1, 3, 2, 1), ("hash_k2s2", FAR, 1, 2, 2, 1),
+         ("ts4", scaled(DENSE, 4), 4, 3, 1, 1), ("ts4_s2", scaled(DENSE, 4), 4, 3, 2, 1), ("ts3_shifted", scaled(DENSE, 3, 1), 3, 3, 1, 1),
+         ("ts2_shifted_s2", scaled(DENSE, 2, 1), 2, 3, 2, 1), ("off_lattice", DENSE, 2, 3, 1, 1), ("off_lattice_s2", DENSE, 2, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_forms_match_oracle(sp, case):  # noqa: F811
+    if case[3:5] == (3, 1):
+        check_set(sp, case[0], case[1])
+    check_maps(sp, *case)
+
+
+def test_out_of_range_row_among_many(sp):  # noqa: F811
+    for bad in ([0, 32768, 0, 0], [0, 0, -32769, 0], [65536, 0, 0, 0], [-1, 0, 0, 0]):
+        raw = DENSE.copy()
+        raw[20000] = bad
+        c = sp.sp_coords_build(dev(raw), 1)
+        with pytest.raises(sp.SpError) as e:
+            _ = c.n
+        assert e.value.code == -2 or "outside" in str(e.value)
+
+
+def test_two_levels_built_without_waiting(sp):  # noqa: F811
+    """A stack of strided maps whose counts the host never asked for: every level's grid comes from its parent's box."""
+    c0 = sp.sp_coords_build(dev(DENSE), 1)
+    k1, c1 = sp.sp_kmap_build(c0, 3, 2, 1)
+    k2, c2 = sp.sp_kmap_build(c1, 3, 2, 1)
+    k3, _ = sp.sp_kmap_build(c2, 3, 1, 1)
+    u, v = np.unique(DENSE, axis=0), lambda a, s: np.unique(a * np.array([1, 0, 0, 0]) + a // s * s * np.array([0, 1, 1, 1]), axis=0)
+    assert (c0.n, c1.n, c2.n) == (len(u), len(v(u, 2)), len(v(u, 4)))
+    top = {tuple(r) for r in v(u, 4)}
+    links = sum((b, x + 4 * i, y + 4 * j, z + 4 * k) in top for b, x, y, z in top for i in (-1, 0, 1) for j in (-1, 0, 1) for k in (-1, 0, 1))
+    assert k3.total == links and k1.n_out == c1.n and k2.n_in == c1.n
+
+
+@pytest.mark.parametrize("cin,cout,bf16", [(32, 32, False), (128, 128, True), (20, 24, False)])
+@pytest.mark.parametrize("warm", [True, False])
+def test_lists_of_the_input_side_under_capture(sp, cin, cout, bf16, warm):  # noqa: F811
+    """The lists and the class order of a strided map's input side are made by the first call that walks them: here on
+    another stream than the captured one, or by the captured call itself."""
+    c = sp.sp_coords_build(dev(DENSE), 1)
+    km, _ = sp.sp_kmap_build(c, 3, 2, 1)
+    kt = sp.sp_kmap_transpose(km)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    xs = [torch.randn((km.n_out, cin), device="cuda", generator=g).to(dt) for _ in range(3)]
+    w = torch.randn((27, cout, cin), device="cuda", generator=g).to(dt)
+    kt2 = sp.sp_kmap_transpose(sp.sp_kmap_build(c, 3, 2, 1)[0])
+    want = [sp.sp_conv_fwd(kt2, x, w) for x in xs]                       # also the one-time set-up of the kernels
+    if warm:
+        sp.sp_conv_fwd(kt, xs[0], w)
+    x, y = torch.empty_like(xs[0]), torch.empty_like(want[0])
+    sp.sp_conv_fwd_noalloc(kt2, xs[0], w, y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp.sp_conv_fwd_noalloc(kt, x, w, y)
+    for i in (0, 1, 2):
+        x.copy_(xs[i])
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[i])
+        assert torch.equal(sp.sp_conv_fwd(kt, xs[i], w), want[i])
