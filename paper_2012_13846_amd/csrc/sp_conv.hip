@@ -557,8 +557,15 @@ bool wave_shape_ok(int cc, int co, sp_dtype dt) {
 // Slices of the contraction and channel tiles of gather_tile_kernel: the cut with the least padding, where a further
 // slice (another accumulator update per link) or channel tile (the rows are gathered again) counts as 8 more padded
 // channels (80 fp32 channels: 2 x 48 measured faster than 5 x 16).
-TileShape tile_shape(int cc, int co, bool is_f32) {
+TileShape tile_shape(int cc, int co, bool is_f32, bool big) {
     TileShape t{0, 0, 0, 0};
+    if (big) {
+        t.kc = cc <= 32 ? 32 : 64;
+        t.nsl = (cc + t.kc - 1) / t.kc;
+        t.ncs = kBigNcs;
+        t.ny = (co + 16 * kBigNcs - 1) / (16 * kBigNcs);
+        return t;
+    }
     const int kcs[] = {64, 48, 32, 16}, ncss[] = {8, 4, 3, 2, 1};
     int best = 1 << 30;
     for (int kc : kcs) {
@@ -586,14 +593,25 @@ size_t tile_weight_bytes(const TileShape& t, int kvol, size_t elt) {
     return (size_t)kvol * t.ny * t.ncs * 16 * t.nsl * t.kc * elt;
 }
 
-// scratch (the allocation-free entry point): the weight copy goes there if it fits; if it does not, whole
-// fragments of wide layers are read from the stored weights in place (a fragment load is then 16 stretches of 64
-// bytes instead of 1 KB in a row), and narrow layers are refused, as they always were.
+constexpr uint64_t kLim32 = 0xffffff00ull;
+bool tile_big(const MapSide& side, int kvol, int cc, sp_dtype dt) {
+    return (uint64_t)side.n_src * cc * (dt == SP_F32 ? 4 : 2) >= kLim32 || (uint64_t)side.pitch * kvol * 4 >= kLim32;
+}
+
+// The allocation-free entry point has room for this much of a weight copy.  Weights larger than that are read from where
+// they are stored if they are whole fragments (a fragment load is then 16 stretches of 64 bytes instead of 1 KB in a
+// row); other widths are left to the plain kernel.
+bool tile_fits_scratch(const MapSide& side, int cc, int co, int kvol, sp_dtype dt, size_t scratch_bytes) {
+    const TileShape t = tile_shape(cc, co, dt == SP_F32, tile_big(side, kvol, cc, dt));
+    return cc % t.kc == 0 || tile_weight_bytes(t, kvol, dt == SP_F32 ? 4 : 2) <= scratch_bytes;
+}
+
 int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed,
                      void* d_g, int cc, int co, sp_dtype dt, hipStream_t s, void* scratch, size_t scratch_bytes) {
     const bool f32 = dt == SP_F32;
     const int elt = f32 ? 4 : 2;
-    const TileShape t = tile_shape(cc, co, f32);
+    const bool big = tile_big(side, kvol, cc, dt);
+    const TileShape t = tile_shape(cc, co, f32, big);
     TileArgs a{};
     a.off = ptr<int32_t>(side.off);
     a.src = ptr<int32_t>(side.src);
@@ -606,6 +624,7 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
     a.co = co;
     a.flip = side.flip ? 1 : 0;
     a.nsl = t.nsl;
+    a.big = big ? 1 : 0;
     a.row_bytes = (uint32_t)(cc * elt);
     a.f_bytes = (uint32_t)((uint64_t)side.n_src * cc * elt);
     a.list_bytes = (uint32_t)((uint64_t)side.pitch * kvol * 4);
@@ -618,9 +637,6 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
         if (!wf) return SP_ERR_ALLOC;
         d_wf = wf->p;
     } else if (copy > scratch_bytes) {
-        if (w_transposed || cc % t.kc || (cc < 64 && co % 32 == 0))
-            return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch", (long long)copy,
-                        scratch_bytes);
         d_wf = nullptr;
     }
     if (d_wf) {
@@ -677,11 +693,11 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
         (side.tile_mask || (double)total_links >= dense_min_fill(cc) * (double)side.n_rows * kvol) &&
         (uint64_t)side.n_src * cc * elt < lim && (uint64_t)side.n_rows * kvol * 4 < lim && (uint64_t)kvol * cc * co * elt < lim)
         return 0;
-    // the link-list kernels address their buffers with 32-bit offsets
-    const uint64_t lim32 = 0xffffff00ull;
-    if ((uint64_t)side.n_src * cc * elt >= lim32 || (uint64_t)side.pitch * kvol * 4 >= lim32) return 3;
-    if (wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
-    if (tile_weight_bytes(tile_shape(cc, co, dt == SP_F32), kvol, elt) >= lim32) return 3;
+    // the link-list kernels address their buffers with 32-bit offsets; the tile kernel takes larger features and lists
+    // too if a row is whole 16-byte pieces
+    const bool big = tile_big(side, kvol, cc, dt);
+    if (!big && wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
+    if ((big && cc * elt % 16) || tile_weight_bytes(tile_shape(cc, co, dt == SP_F32, big), kvol, elt) >= kLim32) return 3;
     return 2;
 }
 }  // namespace
@@ -693,7 +709,8 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
     if (side.n_rows == 0) return SP_OK;
     if (scratch && w_transposed) return fail(SP_ERR_UNSUPPORTED, "no allocation-free path for transposed weights");
     const size_t elt = dt == SP_F32 ? 4 : 2;
-    const int kind = select_gather(side, kvol, total_links, cc, co, dt);
+    int kind = select_gather(side, kvol, total_links, cc, co, dt);
+    if (scratch && kind == 2 && !tile_fits_scratch(side, cc, co, kvol, dt, scratch_bytes)) kind = 3;
     if (kind == 1 || kind == 2) SP_TRY(need_lists(side, kvol, s));
     if (kind == 0) {
         SP_TRY(need_classes(side, s));

@@ -38,6 +38,7 @@ struct TileArgs {
     void* g;         // destination features [n_rows][co]
     int64_t n_rows;
     int kvol, cc, co, flip;
+    int big;                 // features or lists beyond 32-bit byte offsets: the BIG kernels
     int nsl;                 // slices of KC contraction channels
     int max_blk;             // room for block descriptors
     uint32_t row_bytes;      // one source row
@@ -74,7 +75,9 @@ struct TileCfg {
     static_assert(TR == 64 || TR == 128, "one or two sub-tiles");
 };
 
-template <typename T, int KC, int NCS, int TR>
+// A kernel of its own, and for one cut of the channels, because a choice inside the loop slows every launch: at the join the
+// loads of both branches have to have come back (fp32 128 -> 128 under the profiler, 0.66 M links: 614 us).
+template <typename T, int KC, int NCS, int TR, bool BIG>
 __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_tile_kernel(TileArgs a) {
     using Cfg = TileCfg<T, KC, NCS, TR>;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -177,7 +180,8 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
 #pragma unroll
             for (int e = 0; e < kEN; ++e) {
                 const Link l = link_of(step, e);
-                en.src[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rSrc, l.live ? l.entry * 4u : kOutside, 0, 0);
+                if constexpr (BIG) en.src[e] = l.live ? a.src[l.entry] : 0;
+                else en.src[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rSrc, l.live ? l.entry * 4u : kOutside, 0, 0);
                 en.add[e] = l.live ? l.slice_off : kOutside;
             }
         };
@@ -187,9 +191,10 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
 #pragma unroll
             for (int e = 0; e < kEN; ++e) {
                 const Link l = link_of(step, e);
-                r.row[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rRow, l.live ? l.entry * 4u : kOutside, 0, 0);
+                if constexpr (BIG) r.row[e] = l.live ? a.dst[l.entry] : -1;
+                else r.row[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rRow, l.live ? l.entry * 4u : kOutside, 0, 0);
                 if (!l.live) r.row[e] = -1;
-                off[e] = en.add[e] == kOutside ? kOutside : (uint32_t)en.src[e] * a.row_bytes;
+                off[e] = en.add[e] == kOutside ? kOutside : (uint32_t)en.src[e] * (BIG ? 1u : a.row_bytes);
             }
             const uint32_t left0 = a.row_bytes;
 #pragma unroll
@@ -206,7 +211,11 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
                     }
                 }
                 const uint32_t at = sl + piece * 16;  // byte inside the row
-                if (vec) {
+                if constexpr (BIG) {  // o: the row's number
+                    r.x[j] = u32x4{0u, 0u, 0u, 0u};
+                    if (o != kOutside && at < left0)
+                        r.x[j] = *reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(a.f) + (size_t)o * a.row_bytes + at);
+                } else if (vec) {
                     r.x[j] = __builtin_amdgcn_raw_buffer_load_b128(rF, (o != kOutside && at < left0) ? o + at : kOutside, 0, 0);
                 } else if (a.row_bytes % 4 == 0) {
 #pragma unroll
@@ -402,10 +411,10 @@ __global__ __launch_bounds__(256) void tile_weights_kernel(const T* __restrict__
     *reinterpret_cast<uint4*>(wf + idx * kPer) = raw;
 }
 
-template <typename T, int KC, int NCS, int TR>
+template <typename T, int KC, int NCS, int TR, bool BIG = false>
 int launch_tile(TileArgs a, hipStream_t s) {
     using Cfg = TileCfg<T, KC, NCS, TR>;
-    auto kern = gather_tile_kernel<T, KC, NCS, TR>;
+    auto kern = gather_tile_kernel<T, KC, NCS, TR, BIG>;
     a.max_blk = a.kvol * (TR / 16);
     const int lds = Cfg::kFixed + a.max_blk * 16;
     if (lds > 160 * 1024 - 64) return fail(SP_ERR_UNSUPPORTED, "internal: tile does not fit the LDS");
@@ -429,5 +438,6 @@ int launch_tile(TileArgs a, hipStream_t s) {
 struct TileShape {
     int kc, ncs, nsl, ny;
 };
+constexpr int kBigNcs = 4;  // NCS of the BIG kernels; their KC is 32 or 64
 
 }  // namespace sp

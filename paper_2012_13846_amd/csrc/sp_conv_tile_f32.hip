@@ -4,6 +4,11 @@
 namespace sp {
 
 int conv_tile_f32(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s) {
+    if (a.big) {
+        if (ncs == kBigNcs && kc == 64) return launch_tile<float, 64, kBigNcs, 128, true>(a, s);
+        if (ncs == kBigNcs && kc == 32) return launch_tile<float, 32, kBigNcs, 128, true>(a, s);
+        return fail(SP_ERR_UNSUPPORTED, "internal: no tile kernel for slices of %d x %d beyond 32 bits", kc, ncs);
+    }
 #define SP_TILE(KC, NCS)                                                     \
     if (kc == KC && ncs == NCS)                                              \
     return tr == 128 ? launch_tile<float, KC, NCS, 128>(a, s) : launch_tile<float, KC, NCS, 64>(a, s)

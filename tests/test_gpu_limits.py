@@ -1,0 +1,44 @@
+"""Calls at the limits of the convolution kernels: weights beyond the scratch of the allocation-free entry point, features
+beyond 32-bit byte offsets."""
+import pytest
+import torch
+
+from test_gpu_parity import dev, random_coords, sp  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,cin,cout,bf16", [(3, 256, 256, False), (3, 300, 200, False), (5, 48, 512, False), (5, 96, 400, True),
+                                             (5, 65, 300, False)])
+def test_noalloc_takes_weights_beyond_its_scratch(sp, K, cin, cout, bf16):  # noqa: F811
+    """More than 4 MiB of weights: whole fragments are read in place (same bits as sp_conv_fwd), other widths run on the
+    plain kernel (fp32 sums of up to 8125 terms in another order: the parity bounds)."""
+    c = sp.sp_coords_build(dev(random_coords(3, 300, 7)), 1)
+    km, _ = sp.sp_kmap_build(c, K, 1, 1)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((c.n, cin), device="cuda", generator=g).to(dt)
+    w = torch.randn((K ** 3, cout, cin), device="cuda", generator=g).to(dt)
+    assert w.numel() * w.element_size() > 4 << 20
+    y = torch.full((c.n, cout), float("nan"), device="cuda", dtype=dt)
+    sp.sp_conv_fwd_noalloc(km, x, w, y)
+    want = sp.sp_conv_fwd(km, x, w).float()
+    assert float((y.float() - want).norm() / want.norm()) <= (1e-2 if bf16 else 1e-5)
+
+
+def test_features_beyond_32_bit_offsets(sp):  # noqa: F811
+    """4.3 GB of features: the tile kernel with 64-bit addresses, against fp64 products of some of the rows."""
+    side, cin, cout = 257, 64, 64
+    n = side ** 3
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+    raw = torch.stack([torch.zeros_like(i), i // (side * side), i // side % side, i % side], dim=1).contiguous()
+    c = sp.sp_coords_build(raw, 1)
+    km, _ = sp.sp_kmap_build(c, 1, 1, 1)
+    x = torch.randn((n, cin), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    w = torch.randn((1, cout, cin), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+    assert x.numel() * 4 > 1 << 32
+    assert sp.sp_conv_kernel_name(km, cin, cout, torch.float32) == "gather_tile_kernel"
+    y = sp.sp_conv_fwd(km, x, w)
+    at = torch.cat([torch.arange(0, n, 1009, device="cuda"), torch.arange(n - 200, n, device="cuda")])
+    want = x[at].double() @ w[0].double().T
+    assert float((y[at].double() - want).norm() / want.norm()) <= 1e-6
