@@ -75,7 +75,8 @@ struct TileCfg {
     static_assert(TR == 64 || TR == 128, "one or two sub-tiles");
 };
 
-// A kernel of its own, and for one cut of the channels, because a choice inside the loop slows every launch: at the join the
+// BIG: 64-bit addresses for features and lists (rows of whole 16-byte pieces).  A kernel of its own, and for one cut of
+// the channels, because a choice inside the loop slows every launch: at the join the
 // loads of both branches have to have come back (fp32 128 -> 128 under the profiler, 0.66 M links: 614 us).
 template <typename T, int KC, int NCS, int TR, bool BIG>
 __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_tile_kernel(TileArgs a) {

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kScanThreads) void number_blocks_kernel(Build t) {
     for (int i = tid; i < total * 4; i += kScanThreads) cells[i] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
 }
 
-// Grid: at[i] becomes the row's place in cells, and the cell ends up with its smallest row.  A cell's value is one of its
+// Grid: at[i] becomes the row's place in cells (its complement for a row that is not the first of its cell), and the cell ends up with its smallest row.  A cell's value is one of its
 // rows and only ever decreases, so a row that reads one smaller than itself, however old the copy it reads, can stay
 // away: most duplicates spend no atomic.  (Plain stores followed by a pass of atomics for the rows that lost would
 // be faster still, but two XCDs that store different values to one word are left with an L2 copy each, and later
@@ -432,8 +432,9 @@ __global__ __launch_bounds__(kThreads) void place_kernel(Build t, int64_t n_host
     if (i >= n) return;
     const uint32_t c = (uint32_t)at[i];
     const int32_t p = t.dir[c >> 4] * 16 + (int32_t)(c & 15u);
-    if (t.cells[p] > (int32_t)i) atomicMin(&t.cells[p], (int32_t)i);
-    at[i] = p;
+    const bool maybe = t.cells[p] > (int32_t)i;
+    if (maybe) atomicMin(&t.cells[p], (int32_t)i);
+    at[i] = maybe ? p : ~p;
 }
 
 // Block b numbers the first occurrences among its rows: rank = (first occurrences in earlier blocks, by look-back) +
@@ -447,7 +448,8 @@ __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __re
                                                                 int4* __restrict__ coords, uint32_t* __restrict__ mail,
                                                                 uint32_t mail_seq) {
     __shared__ int s_own[1], s_excl[1], s_state[2];
-    __shared__ int s_row[kRowsPerThread][kNumberThreads / 64];
+    __shared__ int s_row[kRowsPerThread * (kNumberThreads / 64)];  // first occurrences in earlier 64-row stretches of the block
+    static_assert(kRowsPerThread * (kNumberThreads / 64) <= 64, "one wavefront scans them");
     const int nthreads = blockDim.x, nw = nthreads >> 6;
     const int rows = nthreads * kRowsPerThread;
     const int64_t n = row_count(n_host, d_n);
@@ -487,32 +489,33 @@ __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __re
         f[j] = s[j] >= 0 && first[j] == (int32_t)(base + j * nthreads + threadIdx.x);
         const unsigned long long m = __ballot(f[j]);
         pos[j] = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) s_row[j][w] = __popcll(m);
+        if (lane == 0) s_row[j * nw + w] = __popcll(m);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int c = 0;
-        for (int j = 0; j < kRowsPerThread; ++j)
-            for (int ww = 0; ww < nw; ++ww) c += s_row[j][ww];
-        s_own[0] = c;
+    if (threadIdx.x < 64) {
+        const int v = lane < kRowsPerThread * nw ? s_row[lane] : 0;
+        int inc = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        if (lane < kRowsPerThread * nw) s_row[lane] = inc - v;
+        if (lane == 63) s_own[0] = inc;
     }
     chain_lookback(chain, b, s_own, s_excl, s_state, meta + kMetaErr);
-    int run = s_excl[0];
+    const int before = s_excl[0];
 #pragma unroll
     for (int j = 0; j < kRowsPerThread; ++j) {
-        int mine = run;
-        for (int ww = 0; ww < nw; ++ww) {
-            if (ww < w) mine += s_row[j][ww];
-            run += s_row[j][ww];
-        }
         if (f[j]) {
-            const int32_t r = mine + pos[j];
+            const int32_t r = before + s_row[j * nw + w] + pos[j];
             coords[r] = load_row(src, base + j * nthreads + threadIdx.x, floor_step);
             if (grid) t.cells[s[j]] = r;
             else t.slots[s[j]].row = r;
         }
     }
     if (b == nb - 1 && threadIdx.x == 0) {
+        const int run = before + s_own[0];
         meta[kMetaN] = run;
         if (mail) {
             mail[0] = (uint32_t)run;
@@ -529,7 +532,7 @@ __global__ __launch_bounds__(kThreads) void inverse_kernel(Build t, const int32_
     const int64_t tile = xcd_tile(blockIdx.x, (n + kThreads - 1) / kThreads), i = tile * kThreads + threadIdx.x;
     if (tile < 0 || i >= n) return;
     const int32_t s = at[i];
-    inverse[i] = s < 0 ? -1 : (is_grid(t) ? t.cells[s] : t.slots[s].row);
+    inverse[i] = is_grid(t) ? t.cells[s < 0 ? ~s : s] : (s < 0 ? -1 : t.slots[s].row);
 }
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -572,7 +575,7 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     const bool may_grid = dir_words > 0;
     c->tab.dir_words = dir_words;
     const size_t grid_bytes = may_grid ? (size_t)dir_words * 4 + (size_t)n_src * 64 : 0;
-    const int nthreads = n_src >= (1 << 18) ? kNumberThreads : kThreads;
+    const int nthreads = n_src >= (1 << 20) ? kNumberThreads : (n_src >= (1 << 18) ? 512 : kThreads);
     const int block_rows = nthreads * kRowsPerThread;
     const int64_t nb = (n_src + block_rows - 1) / block_rows;
     c->tab.mem = dev_alloc(std::max((size_t)cap * sizeof(HashSlot), grid_bytes), s);

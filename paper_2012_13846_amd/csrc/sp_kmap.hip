@@ -41,7 +41,8 @@ __global__ __launch_bounds__(kThreads) void reset_kernel(int32_t* __restrict__ t
 // Links per (tile, sub-tile, offset, 32-row half) and per (tile, offset): what emit_kernel places its entries by.
 struct Counts {
     int32_t* cnt;  // [tile][sub][kvol][half]
-    int32_t* agg;  // [tile][kvol]
+    int32_t* agg;  // [kvol][pitch]: a wavefront sums an offset's row of them
+    int64_t pitch;
 };
 
 // A workgroup's share of the counts: offsets k(0) .. k(NO-1) of its tile, v[j] = this row's entry of the j-th.
@@ -72,7 +73,7 @@ __device__ __forceinline__ void count_rows(const Counts& c, int kvol, int64_t ti
         if (k < kvol) {
             int sum = 0;
             for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cnt[ww][j][0] + s_cnt[ww][j][1];
-            c.agg[tile * kvol + k] = sum;
+            c.agg[k * c.pitch + tile] = sum;
         }
     }
 }
@@ -320,7 +321,13 @@ __global__ __launch_bounds__(kTileRows) void emit_kernel(EmitArgs a) {
     if (w < kChunk && k0 + w < kvol) {
         const int k = k0 + w;
         int sum = 0;
-        for (int64_t tt = lane; tt < t; tt += 64) sum += a.counts.agg[tt * kvol + k];
+        const int32_t* agg = a.counts.agg + k * a.counts.pitch;
+        for (int64_t t0 = lane; t0 < t; t0 += 256) {  // four loads at a time
+            int v4[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v4[i] = t0 + 64 * i < t ? agg[t0 + 64 * i] : 0;
+            sum += (v4[0] + v4[1]) + (v4[2] + v4[3]);
+        }
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
         int2 c = {0, 0};
@@ -490,7 +497,7 @@ size_t counts_bytes(int64_t n_ub, int kvol) {
 Counts counts_in(const Buf& b, int64_t n_ub, int kvol) {
     const int64_t nt = tiles_of(n_ub) ? tiles_of(n_ub) : 1;
     int32_t* p = ptr<int32_t>(b);
-    return Counts{p, p + nt * kvol * kSubTiles * kHalves};
+    return Counts{p, p + nt * kvol * kSubTiles * kHalves, nt};
 }
 
 EmitArgs emit_args(const MapSide& side, Count n_rows, int kvol, const Counts& counts) {
