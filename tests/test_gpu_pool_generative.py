@@ -83,6 +83,29 @@ def test_pool_matches_oracle(sp, case):
         assert torch.count_nonzero(y[torch.from_numpy(dead).cuda()]).item() == 0
 
 
+@pytest.mark.parametrize("K,stride", [(1, 1), (2, 2), (3, 1), (3, 2), (4, 2)])    # kernel volumes 1, 8, 27, 64
+@pytest.mark.parametrize("ch,bf16", [(8, True), (4, False), (520, True), (6, False)])    # 520: a workgroup starts inside a row
+def test_pool_offset_batches_and_records_at_odd_addresses(sp, K, stride, ch, bf16):
+    raw = spgen.coords_config(0)
+    want = oracle_steps(raw, K, stride, 1, 1)
+    pin, pout, counts = want["pair_in"], want["pair_out"], want["counts"]
+    n_in, n_out = len(want["c_in"]), len(want["c_out"])
+    c = sp.sp_coords_build(dev(raw), 1)
+    km, _ = sp.sp_kmap_build(c, K, stride, 1)
+    X, dY = spgen.features(K, n_in, ch, bf16), spgen.features(10 + K, n_out, ch, bf16)
+    X[X > 0.8] = 0.75                              # ties
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    Y, ARG = opool.pool_fwd(pin, pout, counts, X, n_out, "max")
+    DX = opool.pool_bwd(pin, pout, counts, dY, ARG, n_in, "max")
+    y, arg = sp.sp_pool_fwd(km, dev(X, tdt), "max")
+    assert np.array_equal(host(y), Y.astype(np.float32))
+    assert np.array_equal(arg.cpu().numpy().astype(np.int8), ARG.astype(np.int8))
+    odd = torch.empty(arg.numel() + 1, dtype=torch.uint8, device="cuda")[1:].view_as(arg).copy_(arg)
+    dx = sp.sp_pool_bwd(km, dev(dY, tdt), arg, "max")
+    assert rel_err(host(dx), DX) <= (TOL_BF16 if bf16 else TOL_F32)
+    assert torch.equal(dx, sp.sp_pool_bwd(km, dev(dY, tdt), odd, "max"))
+
+
 def test_pool_empty_and_bad_arguments(sp):
     c = sp.sp_coords_build(torch.empty((0, 4), dtype=torch.int32, device="cuda"), 1)
     km, _ = sp.sp_kmap_build(c, 2, 2, 1)
