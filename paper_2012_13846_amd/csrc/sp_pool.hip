@@ -7,9 +7,10 @@
 // Memory bound: a row of c channels is gathered once per link.  Two round trips per kBatch offsets, whatever their number:
 // a thread requests the entries of kBatch offsets, then the rows that exist, and only then reduces.  (One offset at a
 // time is a chain of two dependent loads per offset, and a 64-bit division per thread beside it.)
-// 2 x 2 x 2, stride 2, 64 bf16 channels, 0.37 M input rows: forward 37.7 -> 24.5 us, backward 42.9 -> 33.3 us (compulsory
-// bytes at a large copy's rate: 13 and 16 us).  Backward: each of a wavefront's 8 rows has another offset, so its loads go
-// out one row at a time.
+// Backward, the rows of a wavefront have their links at different offsets (one of 8 at 2 x 2 x 2, stride 2): a thread's
+// u-th link goes out with the other rows' u-th, kSlots at a time, not one offset and so one row after the other.
+// 2 x 2 x 2, stride 2, 64 bf16 channels, 0.37 M input rows: forward 37.7 -> 24.6 us; backward 42.9 -> 33.3 us by the batches,
+// -> 25.4 us by the slots (compulsory bytes at a large copy's rate: 13 and 16 us).
 #include <mutex>
 
 #include "sp_internal.h"
@@ -20,6 +21,7 @@ namespace {
 typedef uint16_t bf16_t;
 constexpr int kThreads = 256;
 constexpr uint8_t kNoArg = 255;
+constexpr int kSlots = 4;  // links of a row that the backward pass has in flight
 constexpr int kBatch = 8;  // offsets whose entries, then rows, a thread has in flight (the whole of a 2 x 2 x 2 kernel)
 
 __device__ __forceinline__ float to_f32(float v) { return v; }
@@ -194,34 +196,44 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_kernel(const int32_t* __res
     for (int k0 = 0; k0 < kvol; k0 += kBatch) {
         int32_t o[kBatch];
         load_entries(nbr, n_rows, row, kvol, flip, k0, o);
-        Vec<T, V> g[kBatch] = {};
-        typename ArgWord<V>::type a[kBatch] = {};
-        int32_t links[kBatch] = {};
+        uint32_t live = 0;
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (o[j] < 0) continue;
-            const size_t e = (size_t)o[j] * c + c0;
-            g[j] = load_vec<T, V>(dy + e);
-            if constexpr (MODE == SP_POOL_MAX) __builtin_memcpy(&a[j], arg + e, V);
-            if constexpr (MODE == SP_POOL_AVG) links[j] = link_cnt[o[j]];  // o has at least this link
-        }
+        for (int j = 0; j < kBatch; ++j) live |= o[j] >= 0 ? 1u << j : 0u;
+        while (live) {
+            Vec<T, V> g[kSlots] = {};
+            typename ArgWord<V>::type a[kSlots] = {};
+            int32_t links[kSlots] = {}, at[kSlots];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            arrive(g[j]);
-            if constexpr (MODE == SP_POOL_MAX) arrive(a[j]);
-        }
+            for (int u = 0; u < kSlots; ++u) {  // the next link of this row, whatever its offset
+                at[u] = live ? __ffs(live) - 1 : -1;
+                live &= live - 1;
+                int32_t src = o[0];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (o[j] < 0) continue;
-            const float scale = MODE == SP_POOL_AVG ? 1.f / (float)links[j] : 1.f;
+                for (int j = 1; j < kBatch; ++j) src = at[u] == j ? o[j] : src;
+                if (at[u] < 0) continue;
+                const size_t e = (size_t)src * c + c0;
+                g[u] = load_vec<T, V>(dy + e);
+                if constexpr (MODE == SP_POOL_MAX) __builtin_memcpy(&a[u], arg + e, V);
+                if constexpr (MODE == SP_POOL_AVG) links[u] = link_cnt[src];  // the output has at least this link
+            }
 #pragma unroll
-            for (int i = 0; i < V; ++i) {
-                if constexpr (MODE == SP_POOL_MAX) {
-                    if ((uint8_t)(a[j] >> (8 * i)) == (uint8_t)(k0 + j)) acc[i] += to_f32(g[j].v[i]);
-                } else if constexpr (MODE == SP_POOL_AVG) {
-                    acc[i] += to_f32(g[j].v[i]) * scale;
-                } else {
-                    acc[i] += to_f32(g[j].v[i]);
+            for (int u = 0; u < kSlots; ++u) {
+                arrive(g[u]);
+                if constexpr (MODE == SP_POOL_MAX) arrive(a[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kSlots; ++u) {
+                if (at[u] < 0) continue;
+                const float scale = MODE == SP_POOL_AVG ? 1.f / (float)links[u] : 1.f;
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    if constexpr (MODE == SP_POOL_MAX) {
+                        if ((uint8_t)(a[u] >> (8 * i)) == (uint8_t)(k0 + at[u])) acc[i] += to_f32(g[u].v[i]);
+                    } else if constexpr (MODE == SP_POOL_AVG) {
+                        acc[i] += to_f32(g[u].v[i]) * scale;
+                    } else {
+                        acc[i] += to_f32(g[u].v[i]);
+                    }
                 }
             }
         }
