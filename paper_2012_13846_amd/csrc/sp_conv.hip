@@ -554,45 +554,6 @@ bool wave_shape_ok(int cc, int co, sp_dtype dt) {
     return cc == 32 || cc == 64 || cc == 128;
 }
 
-// Slices of the contraction and channel tiles of gather_tile_kernel: the cut with the least padding, where a further
-// slice (another accumulator update per link) or channel tile (the rows are gathered again) counts as 8 more padded
-// channels (80 fp32 channels: 2 x 48 measured faster than 5 x 16).
-TileShape tile_shape(int cc, int co, bool is_f32, bool big) {
-    TileShape t{0, 0, 0, 0};
-    if (big) {
-        t.kc = cc <= 32 ? 32 : 64;
-        t.nsl = (cc + t.kc - 1) / t.kc;
-        t.ncs = kBigNcs;
-        t.ny = (co + 16 * kBigNcs - 1) / (16 * kBigNcs);
-        return t;
-    }
-    const int kcs[] = {64, 48, 32, 16}, ncss[] = {8, 4, 3, 2, 1};
-    int best = 1 << 30;
-    for (int kc : kcs) {
-        if (!is_f32 && kc % 32) continue;
-        const int n = (cc + kc - 1) / kc, cost = n * kc + 8 * (n - 1);
-        if (cost < best) {
-            best = cost;
-            t.kc = kc;
-            t.nsl = n;
-        }
-    }
-    best = 1 << 30;
-    for (int n : ncss) {
-        const int ny = (co + 16 * n - 1) / (16 * n), cost = ny * 16 * n + 8 * (ny - 1);
-        if (cost < best) {
-            best = cost;
-            t.ncs = n;
-            t.ny = ny;
-        }
-    }
-    return t;
-}
-
-size_t tile_weight_bytes(const TileShape& t, int kvol, size_t elt) {
-    return (size_t)kvol * t.ny * t.ncs * 16 * t.nsl * t.kc * elt;
-}
-
 constexpr uint64_t kLim32 = 0xffffff00ull;
 bool tile_big(const MapSide& side, int kvol, int cc, sp_dtype dt) {
     return (uint64_t)side.n_src * cc * (dt == SP_F32 ? 4 : 2) >= kLim32 || (uint64_t)side.pitch * kvol * 4 >= kLim32;
@@ -603,7 +564,7 @@ bool tile_big(const MapSide& side, int kvol, int cc, sp_dtype dt) {
 // row); other widths are left to the plain kernel.
 bool tile_fits_scratch(const MapSide& side, int cc, int co, int kvol, sp_dtype dt, size_t scratch_bytes) {
     const TileShape t = tile_shape(cc, co, dt == SP_F32, tile_big(side, kvol, cc, dt));
-    return cc % t.kc == 0 || tile_weight_bytes(t, kvol, dt == SP_F32 ? 4 : 2) <= scratch_bytes;
+    return tile_in_place_ok(t, cc) || tile_copy_bytes(t, kvol, dt == SP_F32 ? 4 : 2) <= scratch_bytes;
 }
 
 int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed,
@@ -620,7 +581,6 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
     a.g = d_g;
     a.n_rows = side.n_rows;
     a.kvol = kvol;
-    a.cc = cc;
     a.co = co;
     a.flip = side.flip ? 1 : 0;
     a.nsl = t.nsl;
@@ -628,7 +588,7 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
     a.row_bytes = (uint32_t)(cc * elt);
     a.f_bytes = (uint32_t)((uint64_t)side.n_src * cc * elt);
     a.list_bytes = (uint32_t)((uint64_t)side.pitch * kvol * 4);
-    const size_t copy = tile_weight_bytes(t, kvol, elt);
+    const size_t copy = tile_copy_bytes(t, kvol, elt);
     const int groups = t.kc / (f32 ? 16 : 32);
     Buf wf;
     void* d_wf = scratch;
@@ -641,14 +601,7 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
     }
     if (d_wf) {
         a.w = d_wf;
-        a.w_bytes = (uint32_t)copy;
-        a.w_s = 1024;
-        a.w_slice = (uint32_t)groups * a.w_s;
-        a.w_cs = (uint32_t)t.nsl * a.w_slice;
-        a.w_y = (uint32_t)t.ncs * a.w_cs;
-        a.w_k = (uint32_t)t.ny * a.w_y;
-        a.w_n16 = 16;
-        a.w_g = 256;
+        a.wt = tile_weights_copied(t, kvol, elt);
         const int s_co = w_transposed ? 1 : cc, s_cc = w_transposed ? co : 1;
         const dim3 grid((unsigned)((copy / 16 + 255) / 256));
         if (f32)
@@ -659,14 +612,7 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
                                static_cast<bf16_t*>(d_wf), kvol, co, cc, s_co, s_cc, t.ny, t.ncs, t.nsl, groups);
     } else {
         a.w = d_w;
-        a.w_bytes = (uint32_t)((uint64_t)kvol * cc * co * elt);
-        a.w_s = 64;
-        a.w_slice = (uint32_t)(t.kc * elt);
-        a.w_n16 = (uint32_t)(cc * elt);
-        a.w_cs = 16 * a.w_n16;
-        a.w_y = (uint32_t)t.ncs * a.w_cs;
-        a.w_k = (uint32_t)co * a.w_n16;
-        a.w_g = 16;
+        a.wt = tile_weights_in_place(t, kvol, cc, co, elt);
     }
     // 128-row tiles fill the 16-link blocks better, 64-row tiles give twice the workgroups and leave more LDS to
     // the tiles with several accumulators (ncs < 3)
@@ -697,7 +643,7 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
     // too if a row is whole 16-byte pieces
     const bool big = tile_big(side, kvol, cc, dt);
     if (!big && wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
-    if ((big && cc * elt % 16) || tile_weight_bytes(tile_shape(cc, co, dt == SP_F32, big), kvol, elt) >= kLim32) return 3;
+    if ((big && cc * elt % 16) || tile_copy_bytes(tile_shape(cc, co, dt == SP_F32, big), kvol, (int)elt) >= kLim32) return 3;
     return 2;
 }
 }  // namespace

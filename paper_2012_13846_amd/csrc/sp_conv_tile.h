@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "sp_internal.h"
+#include "sp_tile_shape.h"
 
 namespace sp {
 
@@ -34,17 +35,16 @@ struct TileArgs {
     const int32_t* src;
     const int32_t* dst;
     const void* f;   // source features [n_src][cc]
-    const void* w;   // weights, see w_k .. w_s
+    const void* w;   // weights
     void* g;         // destination features [n_rows][co]
     int64_t n_rows;
-    int kvol, cc, co, flip;
+    int kvol, co, flip;
     int big;                 // features or lists beyond 32-bit byte offsets: the BIG kernels
     int nsl;                 // slices of KC contraction channels
     int max_blk;             // room for block descriptors
     uint32_t row_bytes;      // one source row
-    uint32_t f_bytes, w_bytes, list_bytes;  // buffer sizes: f, w, src and dst
-    // byte offsets into w: offset k, channel tile y, 16-channel group cs, slice, fragment s of a unit; lane = n16 + 16*g
-    uint32_t w_k, w_y, w_cs, w_slice, w_s, w_n16, w_g;
+    uint32_t f_bytes, list_bytes;  // buffer sizes: f, src and dst
+    TileWeights wt;          // where w's elements are
 };
 
 template <typename T, int KC, int NCS, int TR>
@@ -174,7 +174,7 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
             l.entry = (uint32_t)(p < d.w ? d.y + p : d.z + p);
             l.slice_off = (uint32_t)sl * Cfg::kRow;
             const int k = d.x & 255;
-            l.k_off = (int)((uint32_t)(a.flip ? kvol - 1 - k : k) * a.w_k + (uint32_t)sl * a.w_slice);
+            l.k_off = (int)((uint32_t)(a.flip ? kvol - 1 - k : k) * a.wt.k + (uint32_t)sl * a.wt.slice);
             return l;
         };
         auto load_ent = [&](int step, Ent& en) __attribute__((always_inline)) {
@@ -286,17 +286,17 @@ __global__ __launch_bounds__((TileCfg<T, KC, NCS, TR>::kThreads)) void gather_ti
         }
     } else {
         // ---------------------------------------------------------------- consumers
-        const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.w), 0, (int)a.w_bytes, kRsrcFlags);
+        const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.w), 0, (int)a.wt.bytes, kRsrcFlags);
         const int n16 = lane & 15, g = lane >> 4;
         const int cs = wave % NCS, bs = wave / NCS;
-        const uint32_t w_lane = (uint32_t)n16 * a.w_n16 + (uint32_t)g * a.w_g;
-        const uint32_t w_base = blockIdx.y * a.w_y + (uint32_t)cs * a.w_cs;
+        uint32_t w_base, w_lane;
+        tile_weight_at(a.wt, NCS, (int)blockIdx.y, cs, n16, g, &w_base, &w_lane);
         float* my_acc = acc + bs * (TR + 1) * Cfg::kAccStride + cs * 16 + g * 4;
         auto load_w = [&](Frag (&w)[kGroups], int woff) __attribute__((always_inline)) {
             const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane(woff) + w_base;
 #pragma unroll
             for (int s = 0; s < kGroups; ++s)
-                w[s] = __builtin_bit_cast(Frag, __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane, (int)(so + s * a.w_s), 0));
+                w[s] = __builtin_bit_cast(Frag, __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane, (int)(so + s * a.wt.s), 0));
         };
         constexpr int kUPW = Cfg::kUPW;
         constexpr int kChains = kIsF32 ? 2 : 1;  // independent MFMA chains per unit
@@ -434,11 +434,5 @@ int launch_tile(TileArgs a, hipStream_t s) {
     SP_HIP(hipGetLastError());
     return SP_OK;
 }
-
-// How a layer is cut: KC contraction channels a slice, NCS * 16 destination channels a workgroup.
-struct TileShape {
-    int kc, ncs, nsl, ny;
-};
-constexpr int kBigNcs = 4;  // NCS of the BIG kernels; their KC is 32 or 64
 
 }  // namespace sp
