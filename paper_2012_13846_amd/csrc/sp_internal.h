@@ -79,6 +79,8 @@ bool mail_acquire(MailSlot* out);                  // false: none free (the call
 // a late write must not land in a slot that another build already owns.
 void mail_release(MailSlot* slot);
 int mail_wait(const MailSlot& slot, hipStream_t s);  // blocks until the slot's payload has arrived
+void mail_send(MailSlot* slot, hipStream_t s);     // enqueues a kernel that delivers the slot without a payload
+bool mail_arrived(const MailSlot& slot);
 
 // ---- coordinate table: a cell grid or a hash table, in one buffer; the build decides on the device (sp_hash.h) ----
 struct CoordTab {
@@ -132,13 +134,22 @@ struct sp_coords {
 
 namespace sp {
 
+// Something built by the first call that needs it.  Until the host has seen the build's word in its mail slot, only the
+// stream it was enqueued on can rely on it; other streams repeat it (every build writes the same words to the same
+// places).  No stream ever waits for another, and a stream handle is only compared, never used again.
+struct Once {
+    bool ready = false;
+    hipStream_t on = nullptr;  // while mail is held: where the last build was enqueued
+    MailSlot mail;
+    ~Once() { mail_release(&mail); }
+};
+
 // What the lists of an input side of its own and the class order are made from, and whether they have been made: they
-// are built on the stream of the first call that needs them (many steps need neither: pooling walks the tables,
-// wide layers the class order).  Their memory is reserved when the map is built.
+// are built by the first call that needs them (many steps need neither: pooling walks the tables, wide layers the class
+// order).  Their memory is reserved when the map is built.
 struct SideWork {
     std::mutex mu;
-    bool lists = false, classes = false;             // built
-    hipStream_t lists_on = nullptr, classes_on = nullptr;
+    Once lists, classes;
     Buf counts;        // scratch of the list build
     Buf class_counts;  // of the class build
     Buf coords;        // the side's coordinates (classes)
@@ -199,8 +210,6 @@ namespace sp {
 // The side's lists / class order, if they do not exist yet, on stream s (sp_kmap.hip).
 int need_lists(const MapSide& side, int kvol, hipStream_t s);
 int need_classes(const MapSide& side, hipStream_t s);
-// Orders `to` behind everything enqueued on `from` so far.
-int stream_wait(hipStream_t from, hipStream_t to);
 // conv launchers (sp_conv.hip / sp_wgrad.hip)
 // scratch != null: the call must not allocate; the weight copy of the link-list kernel goes there (forward only)
 int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* d_f, const void* d_w, bool w_transposed,

@@ -522,24 +522,8 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
     MapSide& so = m->out_side;
     MapSide& si = m->in_side;
     const int kvol = m->kvol;
-    const bool mailed = mail_acquire(&m->mail);
-    EmitArgs a = emit_args(so, cn_out, kvol, counts);
-    a.d_counts = ptr<int32_t>(m->d_counts);
-    a.mail = mailed ? m->mail.d : nullptr;
-    a.mail_seq = m->mail.seq;
-    a.n_in = cn_in;
-    a.n_out = cn_out;
-    const int64_t nt = tiles_of(n_out_ub);
-    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt ? nt : 1), chunks_of(kvol)), dim3(kTileRows), 0, s, a);
-    m->mail.armed = mailed;
-    m->mail.stream = s;
-    m->pair_in = so.src;
-    m->pair_out = so.dst;
-    m->pair_stride = so.pitch;
-    if (symmetric) {
-        si = so;  // same lists; the link (i, o) at offset k is the link (o, i) at offset kvol-1-k
-        si.flip = true;
-    } else {
+    // All memory first: whoever has seen the counts then knows that the stream is past every wait for a block's last user.
+    if (!symmetric) {
         SP_TRY(reserve_lists(si, n_in_ub, so.pitch, kvol, s));
         si.work = std::make_shared<SideWork>();
         SideWork& w = *si.work;
@@ -557,6 +541,24 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
             w.nclass = nclass;
         }
     }
+    const bool mailed = mail_acquire(&m->mail);
+    EmitArgs a = emit_args(so, cn_out, kvol, counts);
+    a.d_counts = ptr<int32_t>(m->d_counts);
+    a.mail = mailed ? m->mail.d : nullptr;
+    a.mail_seq = m->mail.seq;
+    a.n_in = cn_in;
+    a.n_out = cn_out;
+    const int64_t nt = tiles_of(n_out_ub);
+    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt ? nt : 1), chunks_of(kvol)), dim3(kTileRows), 0, s, a);
+    m->mail.armed = mailed;
+    m->mail.stream = s;
+    m->pair_in = so.src;
+    m->pair_out = so.dst;
+    m->pair_stride = so.pitch;
+    if (symmetric) {
+        si = so;  // same lists; the link (i, o) at offset k is the link (o, i) at offset kvol-1-k
+        si.flip = true;
+    }
     SP_HIP(hipGetLastError());
     if (!mailed) {  // no mail slot free: wait here
         std::vector<uint32_t> h(kvol);
@@ -570,22 +572,52 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
     return SP_OK;
 }
 
-// First call that needs it builds on its stream; later calls from another stream wait for that one.  Under graph
-// capture neither holds: the build runs when the graph does, so it does not count as done, and a captured stream
-// cannot wait for one that is not, so a build done elsewhere is repeated in the graph.  A build that finds an earlier
-// one at work is harmless: it writes the same words to the same places.
+// Calls of this thread that a capture under way elsewhere would forbid (making a stream, waiting for it).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// build(stream) enqueues the work; what s runs from here on finds it done.
+// (Events would not do: the runtime refuses an event, and draws who waits for it into the capture, while the stream it
+// was recorded on is being captured, also if it was recorded before.)
+// Under graph capture the work stays out of the graph, or every replay would repeat it: it runs on a stream of its own and
+// the host waits for it.  All that it reads is complete: the host has had the map's counts.
 template <class Build>
-int once(bool& built, hipStream_t& on, hipStream_t s, Build build) {
-    if (built && s == on) return SP_OK;
+int once(Once& o, hipStream_t s, Build build) {
+    if (o.ready) return SP_OK;
+    if (o.mail.index >= 0 && mail_arrived(o.mail)) {
+        mail_release(&o.mail);
+        o.ready = true;
+        return SP_OK;
+    }
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    const bool capturing = cap != hipStreamCaptureStatusNone;
-    if (built && !capturing) return stream_wait(on, s);
-    SP_TRY(build());
-    if (!capturing) {
-        built = true;
-        on = s;
+    if (cap != hipStreamCaptureStatusNone) {
+        RelaxedCapture relaxed;
+        hipStream_t own = nullptr;
+        SP_HIP(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
+        const int rc = build(own);
+        const hipError_t e = hipStreamSynchronize(own);
+        (void)hipStreamDestroy(own);
+        SP_TRY(rc);
+        SP_HIP(e);
+        mail_release(&o.mail);
+        o.ready = true;
+        return SP_OK;
     }
+    if (o.mail.index >= 0 && o.on == s) return SP_OK;
+    SP_TRY(build(s));
+    mail_release(&o.mail);
+    if (!mail_acquire(&o.mail)) {  // no mail slot free: wait here
+        SP_HIP(hipStreamSynchronize(s));
+        o.ready = true;
+        return SP_OK;
+    }
+    mail_send(&o.mail, s);
+    SP_HIP(hipGetLastError());
+    o.on = s;
     return SP_OK;
 }
 
@@ -595,12 +627,12 @@ int need_lists(const MapSide& side, int kvol, hipStream_t s) {
     if (!side.work || side.n_rows == 0) return SP_OK;
     SideWork& w = *side.work;
     std::lock_guard<std::mutex> lk(w.mu);
-    return once(w.lists, w.lists_on, s, [&]() -> int {
+    return once(w.lists, s, [&](hipStream_t on) -> int {
         const Count n{nullptr, side.n_rows};
         const Counts c = counts_in(w.counts, side.n_rows, kvol);
         const dim3 grid((unsigned)tiles_of(side.n_rows), chunks_of(kvol));
-        hipLaunchKernelGGL(count_kernel, grid, dim3(kTileRows), 0, s, ptr<int32_t>(side.nbr), n, kvol, c, (int32_t*)nullptr);
-        hipLaunchKernelGGL(emit_kernel, grid, dim3(kTileRows), 0, s, emit_args(side, n, kvol, c));
+        hipLaunchKernelGGL(count_kernel, grid, dim3(kTileRows), 0, on, ptr<int32_t>(side.nbr), n, kvol, c, (int32_t*)nullptr);
+        hipLaunchKernelGGL(emit_kernel, grid, dim3(kTileRows), 0, on, emit_args(side, n, kvol, c));
         SP_HIP(hipGetLastError());
         return SP_OK;
     });
@@ -610,11 +642,11 @@ int need_classes(const MapSide& side, hipStream_t s) {
     if (!side.tile_mask || !side.work || side.n_rows == 0) return SP_OK;
     SideWork& w = *side.work;
     std::lock_guard<std::mutex> lk(w.mu);
-    return once(w.classes, w.classes_on, s, [&]() -> int {
+    return once(w.classes, s, [&](hipStream_t on) -> int {
         const dim3 grid((unsigned)tiles_of(side.n_rows));
-        hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
+        hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, on, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
                            ptr<int32_t>(w.class_counts));
-        hipLaunchKernelGGL(class_emit_kernel, grid, dim3(kTileRows), 0, s, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
+        hipLaunchKernelGGL(class_emit_kernel, grid, dim3(kTileRows), 0, on, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
                            w.K, ptr<int32_t>(w.class_counts), ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
         SP_HIP(hipGetLastError());
         return SP_OK;

@@ -216,10 +216,6 @@ Buf dev_alloc(size_t bytes, hipStream_t s) {
     return b;
 }
 
-int stream_wait(hipStream_t from, hipStream_t to) {
-    std::lock_guard<std::mutex> lk(pool().mu);
-    return pool().hand_over(from, to) ? SP_OK : fail(SP_ERR_HIP, "could not make one stream wait for another");
-}
 int pool_trim() { return pool().trim(); }
 int64_t pool_bytes() {
     std::lock_guard<std::mutex> lk(pool().mu);
@@ -341,6 +337,16 @@ void mail_release(MailSlot* slot) {
     else mp.free_slots.push_back(slot->index);
     slot->index = -1;
 }
+
+__global__ void mail_send_kernel(uint32_t* mail, uint32_t seq) {
+    __hip_atomic_store(mail + kMailSeqWord, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+void mail_send(MailSlot* slot, hipStream_t s) {
+    hipLaunchKernelGGL(mail_send_kernel, dim3(1), dim3(1), 0, s, slot->d, slot->seq);
+    slot->armed = true;
+    slot->stream = s;
+}
+bool mail_arrived(const MailSlot& slot) { return __atomic_load_n(slot.h + kMailSeqWord, __ATOMIC_ACQUIRE) == slot.seq; }
 
 int mail_wait(const MailSlot& slot, hipStream_t s) {
     volatile uint32_t* flag = slot.h + kMailSeqWord;

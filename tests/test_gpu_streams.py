@@ -209,3 +209,128 @@ def test_host_threads_with_their_own_streams(sp):
         th.join()
     torch.cuda.synchronize()
     assert not errors, errors
+
+
+# ---- what a map builds on its first use (the lists and the class order of a strided map's input side) --------------
+LAZY = [(32, 32, torch.float32), (128, 128, torch.bfloat16)]     # link lists; class order
+
+
+def lazy_case(sp, cin, cout, dt):
+    """A transposed strided map, features, weights, and what the convolution gives on a map of its own."""
+    c = sp.sp_coords_build(dev(spgen.coords_config(1, 0.4)), 1)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    kt, kt2 = (sp.sp_kmap_transpose(sp.sp_kmap_build(c, 3, 2, 1)[0]) for _ in range(2))
+    x = torch.randn((kt.n_in, cin), device="cuda", generator=g).to(dt)
+    w = torch.randn((27, cout, cin), device="cuda", generator=g).to(dt)
+    want = sp.sp_conv_fwd(kt2, x, w)
+    sp.sp_conv_fwd_noalloc(kt2, x, w, torch.empty_like(want))        # one-time set-up of the kernels
+    torch.cuda.synchronize()
+    return kt, x, w, want
+
+
+def busy(stream, n=60):
+    """Tens of milliseconds of work on the stream; returns the event behind it."""
+    with torch.cuda.stream(stream):
+        a = torch.ones((8192, 8192), device="cuda", dtype=torch.bfloat16)
+        for _ in range(n):
+            a @ a
+        ev = torch.cuda.Event()
+        ev.record(stream)
+    return ev
+
+
+def independent_streams():
+    """Two streams whose kernels really run side by side (streams share a few hardware queues)."""
+    first = torch.cuda.Stream()
+    for _ in range(8):
+        other = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        ev = busy(first)
+        with torch.cuda.stream(other):
+            torch.ones(16, device="cuda")
+        other.synchronize()
+        apart = not ev.query()
+        torch.cuda.synchronize()
+        if apart:
+            return first, other
+    pytest.skip("no two streams with hardware queues of their own")
+
+
+@pytest.mark.parametrize("cin,cout,dt", LAZY)
+def test_second_stream_does_not_wait_for_the_first_one(sp, cin, cout, dt):
+    kt, x, w, want = lazy_case(sp, cin, cout, dt)
+    a, b = independent_streams()
+    with torch.cuda.stream(a):
+        busy(a, 4)                                          # the build itself is still to come when b asks for it
+        ya = sp.sp_conv_fwd(kt, x, w)
+    with torch.cuda.stream(b):
+        yb = sp.sp_conv_fwd(kt, x, w)
+    b.synchronize()
+    assert torch.equal(yb, want)
+    ev = busy(a)                                            # work behind the build: none of b's business
+    with torch.cuda.stream(b):
+        yb = sp.sp_conv_fwd(kt, x, w)
+    b.synchronize()
+    assert not ev.query(), "the second stream waited for the first one's later work"
+    torch.cuda.synchronize()
+    assert torch.equal(ya, want) and torch.equal(yb, want)
+
+
+def node_count(graph):
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    n = ctypes.c_size_t()
+    rc = ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n))
+    assert rc == 0
+    return n.value
+
+
+@pytest.mark.parametrize("cin,cout,dt", LAZY)
+@pytest.mark.parametrize("warm", ["built", "building", "no"])
+def test_a_graph_holds_the_convolution_and_not_the_build(sp, cin, cout, dt, warm):
+    kt, x, w, want = lazy_case(sp, cin, cout, dt)
+    y = torch.empty_like(want)
+    if warm != "no":
+        if warm == "building":
+            busy(torch.cuda.current_stream(), 4)
+        sp.sp_conv_fwd(kt, x, w)
+    if warm == "built":
+        torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.stream(side):                           # (the capture context would synchronise first)
+        graph.capture_begin()
+        sp.sp_conv_fwd_noalloc(kt, x, w, y)
+        graph.capture_end()
+    nodes = node_count(graph)
+    assert nodes == (1 if dt == torch.bfloat16 else 2)      # weight copy and convolution
+    torch.cuda.synchronize()
+    graph.instantiate()
+    for _ in range(3):
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
+        assert torch.equal(sp.sp_conv_fwd(kt, x, w), want)
+
+
+def test_use_on_another_stream_while_the_building_one_is_captured(sp):
+    kt, x, w, want = lazy_case(sp, *LAZY[0])
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    y, ya = torch.empty_like(want), torch.empty_like(want)
+    with torch.cuda.stream(a):
+        busy(a, 4)
+        sp.sp_conv_fwd(kt, x, w)
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        graph.capture_begin(capture_error_mode="relaxed")
+        with torch.cuda.stream(b):
+            sp.sp_conv_fwd_noalloc(kt, x, w, y)             # runs now, on b
+        sp.sp_conv_fwd_noalloc(kt, x, w, ya)
+        graph.capture_end()
+    b.synchronize()
+    assert torch.equal(y, want)
+    assert node_count(graph) == 2
+    torch.cuda.synchronize()
+    graph.instantiate()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(ya, want)
