@@ -594,8 +594,8 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
     void* d_wf = scratch;
     if (!scratch) {
         wf = dev_alloc(copy, s);
-        if (!wf) return SP_ERR_ALLOC;
-        d_wf = wf->p;
+        if (!wf && (w_transposed || !tile_in_place_ok(t, cc))) return SP_ERR_ALLOC;  // the caller has another way
+        d_wf = wf ? wf->p : nullptr;
     } else if (copy > scratch_bytes) {
         d_wf = nullptr;
     }
@@ -672,7 +672,10 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         }
         return conv_gather_dense(side, kvol, d_f, w, d_g, cc, co, s);
     }
-    if (kind == 2) return conv_gather_tile(side, kvol, d_f, d_w, w_transposed, d_g, cc, co, dt, s, scratch, scratch_bytes);
+    if (kind == 2) {
+        const int rc = conv_gather_tile(side, kvol, d_f, d_w, w_transposed, d_g, cc, co, dt, s, scratch, scratch_bytes);
+        if (rc != SP_ERR_ALLOC) return rc;  // no memory for the weight copy: the plain kernel needs none
+    }
     if (kind == 1) {
         GatherArgs a;
         a.off = ptr<int32_t>(side.off);

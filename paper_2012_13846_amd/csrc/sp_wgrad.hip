@@ -652,20 +652,18 @@ int channel_block(int c) {
 }
 
 template <typename T>
-int wgrad_typed(const sp_kmap* m, const void* x, const void* dy, float* dw, int cin, int cout, hipStream_t s) {
+int wgrad_plain(const sp_kmap* m, const void* x, const void* dy, float* dw, int cin, int cout, hipStream_t s) {
+    hipLaunchKernelGGL(wgrad_plain_kernel<T>, dim3((cin * cout + 255) / 256, m->kvol), dim3(256), 0, s, ptr<int32_t>(m->pair_in),
+                       ptr<int32_t>(m->pair_out), ptr<int32_t>(m->d_counts), m->pair_stride, static_cast<const T*>(x),
+                       static_cast<const T*>(dy), cin, cout, dw);
+    SP_HIP(hipGetLastError());
+    return SP_OK;
+}
+
+template <typename T>
+int wgrad_staged(const sp_kmap* m, const void* x, const void* dy, float* dw, int cin, int cout, hipStream_t s) {
     constexpr int kN = 16 / (int)sizeof(T);
-    const int kvol = m->kvol;
     const int cin_row = (cin + kN - 1) / kN * kN, cout_row = (cout + kN - 1) / kN * kN;
-    const uint64_t lim = 0x7fffffffull;  // the staged kernel addresses its buffers with 32-bit offsets
-    const bool small = (uint64_t)m->n_in * cin_row * sizeof(T) < lim && (uint64_t)m->n_out * cout_row * sizeof(T) < lim &&
-                       (uint64_t)kvol * m->pair_stride * 4 < lim;
-    if (!small || m->total == 0 || kvol > 128) {
-        hipLaunchKernelGGL(wgrad_plain_kernel<T>, dim3((cin * cout + 255) / 256, kvol), dim3(256), 0, s,
-                           ptr<int32_t>(m->pair_in), ptr<int32_t>(m->pair_out), ptr<int32_t>(m->d_counts), m->pair_stride,
-                           static_cast<const T*>(x), static_cast<const T*>(dy), cin, cout, dw);
-        SP_HIP(hipGetLastError());
-        return SP_OK;
-    }
     // rows that are not whole 16-byte pieces: a padded copy
     Buf px, pdy;
     auto padded = [&](const void* p, int64_t n, int c, int cp, Buf& b) -> const void* {
@@ -720,6 +718,20 @@ int wgrad_typed(const sp_kmap* m, const void* x, const void* dy, float* dw, int 
 #undef SP_STAGED
 #undef SP_EXACT
     return fail(SP_ERR_UNSUPPORTED, "no weight-gradient kernel for %d x %d channels", cout, cin);
+}
+
+template <typename T>
+int wgrad_typed(const sp_kmap* m, const void* x, const void* dy, float* dw, int cin, int cout, hipStream_t s) {
+    constexpr int kN = 16 / (int)sizeof(T);
+    const int kvol = m->kvol, cin_row = (cin + kN - 1) / kN * kN, cout_row = (cout + kN - 1) / kN * kN;
+    const uint64_t lim = 0x7fffffffull;  // the staged kernel addresses its buffers with 32-bit offsets
+    const bool small = (uint64_t)m->n_in * cin_row * sizeof(T) < lim && (uint64_t)m->n_out * cout_row * sizeof(T) < lim &&
+                       (uint64_t)kvol * m->pair_stride * 4 < lim;
+    if (!small || m->total == 0 || kvol > 128) return wgrad_plain<T>(m, x, dy, dw, cin, cout, s);
+    const int rc = wgrad_staged<T>(m, x, dy, dw, cin, cout, s);
+    // no memory for padded rows or partial blocks: odd widths need none on the plain kernel
+    if (rc == SP_ERR_ALLOC && (cin % 16 || cout % 16)) return wgrad_plain<T>(m, x, dy, dw, cin, cout, s);
+    return rc;
 }
 
 }  // namespace

@@ -42,3 +42,28 @@ def test_features_beyond_32_bit_offsets(sp):  # noqa: F811
     at = torch.cat([torch.arange(0, n, 1009, device="cuda"), torch.arange(n - 200, n, device="cuda")])
     want = x[at].double() @ w[0].double().T
     assert float((y[at].double() - want).norm() / want.norm()) <= 1e-6
+
+
+@pytest.mark.parametrize("cin,cout,bf16", [(20, 24, False), (65, 40, True), (3, 128, False), (128, 100, False), (128, 128, False)])
+def test_without_memory_for_scratch(sp, cin, cout, bf16):  # noqa: F811
+    """An allocator that has nothing to give: convolutions need weight copies, padded rows and partial blocks only to be
+    fast.  (Layers of the other kernels report SP_ERR_ALLOC.)"""
+    c = sp.sp_coords_build(dev(random_coords(3, 300, 7)), 1)
+    km, _ = sp.sp_kmap_build(c, 3, 1, 1)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, dy = (torch.randn((c.n, ch), device="cuda", generator=g).to(dt) for ch in (cin, cout))
+    w = torch.randn((27, cout, cin), device="cuda", generator=g).to(dt)
+    calls = [lambda: sp.sp_conv_fwd(km, x, w), lambda: sp.sp_conv_bwd_data(km, dy, w)]
+    if cin % 16 or cout % 16:
+        calls.append(lambda: sp.sp_conv_bwd_weight(km, x, dy))
+    want = [f().float() for f in calls]
+    asked = []
+    sp.sp_set_allocator(lambda nbytes, stream: asked.append(nbytes) or 0, lambda ptr: None)
+    try:
+        got = [f().float() for f in calls]
+    finally:
+        sp.sp_set_allocator()
+    assert asked
+    for a, b in zip(got, want):   # sums of up to 3500 terms in another order; one rounding to bf16
+        assert float((a - b).norm() / b.norm()) <= (1e-2 if bf16 else 1e-5)
