@@ -4,8 +4,8 @@
 //
 // No host round trip.  (1) The searches: one thread per output row and column of offsets fills the neighbour table
 // and counts the links per (64-row sub-tile, offset); a workgroup is a tile of 1024 rows, so it also leaves the
-// tile's sum per offset.  (2) emit: every tile adds up the sums of the tiles before it (a few hundred numbers per
-// offset, cheaper than a prefix launch) and writes its stretch of every offset's list; the last tile delivers the
+// tile's sum per offset.  (2) emit: every tile adds up the sums of the tiles before it (up to kSumTiles of them; beyond
+// that a prefix launch does it once for all) and writes its stretch of every offset's list; the last tile delivers the
 // counts to device memory and to a mail slot, which the host reads when it first asks (kmap_resolve).  Row counts
 // that the host has not seen yet (the input set's N, the coarse set's N) are read from device memory by the kernels;
 // grids and allocations use upper bounds.  (A single-pass count + look-back + emit kernel was measured slower: the
@@ -42,8 +42,53 @@ __global__ __launch_bounds__(kThreads) void reset_kernel(int32_t* __restrict__ t
 struct Counts {
     int32_t* cnt;  // [tile][sub][kvol][half]
     int32_t* agg;  // [kvol][pitch]: a wavefront sums an offset's row of them
+    int32_t* pre;  // null, or [kvol][pitch + 1]: those sums (prefix_kernel)
     int64_t pitch;
 };
+
+// Up to this many tiles a workgroup adds up the tiles before its own by itself (no launch: 0.5 M rows, K = 1, 13 us against
+// 17), beyond it prefix_kernel does it once, or the work would grow with the square of the rows: K = 1 on 1 M rows 18 us
+// either way, 4.1 M 55 against 46, 16.8 M 346 against 182 (K = 3: 2560 against 2020).
+constexpr int64_t kSumTiles = 1024;
+
+// pre[row][t] = agg[row][0] + .. + agg[row][t - 1], t = 0 .. tiles.  A workgroup per row.  (Not in place: a build that is
+// repeated on another stream writes the same words to the same places, and readers of either find what they expect.)
+__global__ __launch_bounds__(kTileRows) void prefix_kernel(const int32_t* __restrict__ agg, int32_t* __restrict__ pre, int64_t pitch,
+                                                           Count n_rows) {
+    __shared__ int s_wave[2][kTileRows / 64];
+    const int64_t tiles = (get(n_rows) + kTileRows - 1) / kTileRows;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    agg += blockIdx.x * pitch;
+    pre += blockIdx.x * (pitch + 1);
+    int run = 0;
+    for (int64_t t0 = 0, turn = 0; t0 < tiles; t0 += 4 * kTileRows, ++turn) {
+        const int64_t t = t0 + 4 * tid;
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = t + i < tiles ? agg[t + i] : 0;
+        const int mine = (v[0] + v[1]) + (v[2] + v[3]);
+        int inc = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        int* sums = s_wave[turn & 1];  // the next turn's writes meet this turn's reads only beyond its barrier
+        if (lane == 63) sums[w] = inc;
+        __syncthreads();
+        int at = run + inc - mine;
+        for (int ww = 0; ww < kTileRows / 64; ++ww) {
+            if (ww < w) at += sums[ww];
+            run += sums[ww];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (t + i < tiles) pre[t + i] = at;
+            at += v[i];
+        }
+    }
+    if (tid == 0) pre[tiles] = run;
+}
 
 // A workgroup's share of the counts: offsets k(0) .. k(NO-1) of its tile, v[j] = this row's entry of the j-th.
 template <int NO, class Koff>
@@ -321,15 +366,19 @@ __global__ __launch_bounds__(kTileRows) void emit_kernel(EmitArgs a) {
     if (w < kChunk && k0 + w < kvol) {
         const int k = k0 + w;
         int sum = 0;
-        const int32_t* agg = a.counts.agg + k * a.counts.pitch;
-        for (int64_t t0 = lane; t0 < t; t0 += 256) {  // four loads at a time
-            int v4[4];
+        if (a.counts.pre) {
+            sum = a.counts.pre[k * (a.counts.pitch + 1) + t];
+        } else {
+            const int32_t* agg = a.counts.agg + k * a.counts.pitch;
+            for (int64_t t0 = lane; t0 < t; t0 += 256) {  // four loads at a time
+                int v4[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v4[i] = t0 + 64 * i < t ? agg[t0 + 64 * i] : 0;
-            sum += (v4[0] + v4[1]) + (v4[2] + v4[3]);
+                for (int i = 0; i < 4; ++i) v4[i] = t0 + 64 * i < t ? agg[t0 + 64 * i] : 0;
+                sum += (v4[0] + v4[1]) + (v4[2] + v4[3]);
+            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
         }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
         int2 c = {0, 0};
         if (ntiles && lane < kSubTiles) c = *reinterpret_cast<const int2*>(a.counts.cnt + ((t * kSubTiles + lane) * kvol + k) * kHalves);
         int inc = c.x + c.y;
@@ -383,7 +432,7 @@ __global__ __launch_bounds__(kTileRows) void emit_kernel(EmitArgs a) {
 
 // Rows per position class and tile.
 __global__ __launch_bounds__(kTileRows) void class_count_kernel(const int4* __restrict__ coords, int64_t n, int ts, int stride,
-                                                                int nclass, int32_t* __restrict__ agg) {
+                                                                int nclass, int32_t* __restrict__ agg, int64_t pitch) {
     __shared__ int s_cls[32][kSubTiles];
     const int64_t t = blockIdx.x, r = t * kTileRows + threadIdx.x;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -396,7 +445,7 @@ __global__ __launch_bounds__(kTileRows) void class_count_kernel(const int4* __re
     if ((int)threadIdx.x < nclass) {
         int sum = 0;
         for (int ww = 0; ww < kSubTiles; ++ww) sum += s_cls[threadIdx.x][ww];
-        agg[t * nclass + threadIdx.x] = sum;
+        agg[threadIdx.x * pitch + t] = sum;
     }
 }
 
@@ -407,6 +456,7 @@ __global__ __launch_bounds__(kTileRows) void class_count_kernel(const int4* __re
 // offset's displacement is congruent to r modulo the stride (output coordinates are multiples of the stride).
 __global__ __launch_bounds__(kTileRows) void class_emit_kernel(const int4* __restrict__ coords, int64_t n, int ts, int stride,
                                                                int nclass, int K, const int32_t* __restrict__ agg,
+                                                               const int32_t* __restrict__ pre, int64_t pitch,
                                                                int32_t* __restrict__ perm, uint32_t* __restrict__ mask) {
     __shared__ int s_cnt[32][kSubTiles];
     __shared__ int s_total[32], s_before[32], s_base[33];
@@ -423,15 +473,20 @@ __global__ __launch_bounds__(kTileRows) void class_emit_kernel(const int4* __res
     }
     for (int c = w; c < nclass; c += kSubTiles) {  // a wavefront per class: rows of the class before this tile, and in all
         int before = 0, all = 0;
-        for (int64_t tt = lane; tt < ntiles; tt += 64) {
-            const int v = agg[tt * nclass + c];
-            all += v;
-            before += tt < t ? v : 0;
-        }
+        if (pre) {
+            before = pre[c * (pitch + 1) + t];
+            all = pre[c * (pitch + 1) + ntiles];
+        } else {
+            for (int64_t tt = lane; tt < ntiles; tt += 64) {
+                const int v = agg[c * pitch + tt];
+                all += v;
+                before += tt < t ? v : 0;
+            }
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            before += __shfl_xor(before, d, 64);
-            all += __shfl_xor(all, d, 64);
+            for (int d = 32; d > 0; d >>= 1) {
+                before += __shfl_xor(before, d, 64);
+                all += __shfl_xor(all, d, 64);
+            }
         }
         if (lane == 0) {
             s_before[c] = before;
@@ -490,14 +545,25 @@ int reserve_lists(MapSide& side, int64_t n_ub, int64_t pitch, int kvol, hipStrea
     return side.off && side.src && side.dst ? SP_OK : SP_ERR_ALLOC;
 }
 
+// Sums of `width` things per tile, with room for their prefixes where prefix_kernel makes them.
+int64_t sum_words(int64_t nt, int width) { return nt * width + (nt > kSumTiles ? (nt + 1) * width : 0); }
+int32_t* prefixes_in(int32_t* agg, int64_t nt, int width) { return nt > kSumTiles ? agg + nt * width : nullptr; }
+
 size_t counts_bytes(int64_t n_ub, int kvol) {
     const int64_t nt = tiles_of(n_ub) ? tiles_of(n_ub) : 1;
-    return (size_t)nt * kvol * (kSubTiles * kHalves + 1) * 4;
+    return (size_t)(nt * kvol * kSubTiles * kHalves + sum_words(nt, kvol)) * 4;
 }
 Counts counts_in(const Buf& b, int64_t n_ub, int kvol) {
     const int64_t nt = tiles_of(n_ub) ? tiles_of(n_ub) : 1;
-    int32_t* p = ptr<int32_t>(b);
-    return Counts{p, p + nt * kvol * kSubTiles * kHalves, nt};
+    int32_t *p = ptr<int32_t>(b), *agg = p + nt * kvol * kSubTiles * kHalves;
+    return Counts{p, agg, prefixes_in(agg, nt, kvol), nt};
+}
+
+void launch_emit(const EmitArgs& a, int64_t n_ub, hipStream_t s) {
+    const int64_t nt = tiles_of(n_ub);
+    if (a.counts.pre)
+        hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)a.kvol), dim3(kTileRows), 0, s, a.counts.agg, a.counts.pre, a.counts.pitch, a.n_rows);
+    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt ? nt : 1), chunks_of(a.kvol)), dim3(kTileRows), 0, s, a);
 }
 
 EmitArgs emit_args(const MapSide& side, Count n_rows, int kvol, const Counts& counts) {
@@ -532,7 +598,7 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
         if (nclass && n_in_ub > 0) {
             si.perm = dev_alloc((size_t)n_in_ub * 4, s);
             si.tile_mask = dev_alloc((size_t)((n_in_ub + 255) / 256) * 16, s);
-            w.class_counts = dev_alloc((size_t)tiles_of(n_in_ub) * nclass * 4, s);
+            w.class_counts = dev_alloc((size_t)sum_words(tiles_of(n_in_ub), nclass) * 4, s);
             if (!si.perm || !si.tile_mask || !w.class_counts) return SP_ERR_ALLOC;
             w.coords = m->c_in->coords;
             w.ts = m->c_in->ts;
@@ -548,8 +614,7 @@ int finish_map(sp_kmap* m, bool symmetric, const Counts& counts, int64_t n_in_ub
     a.mail_seq = m->mail.seq;
     a.n_in = cn_in;
     a.n_out = cn_out;
-    const int64_t nt = tiles_of(n_out_ub);
-    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(nt ? nt : 1), chunks_of(kvol)), dim3(kTileRows), 0, s, a);
+    launch_emit(a, n_out_ub, s);
     m->mail.armed = mailed;
     m->mail.stream = s;
     m->pair_in = so.src;
@@ -632,7 +697,7 @@ int need_lists(const MapSide& side, int kvol, hipStream_t s) {
         const Counts c = counts_in(w.counts, side.n_rows, kvol);
         const dim3 grid((unsigned)tiles_of(side.n_rows), chunks_of(kvol));
         hipLaunchKernelGGL(count_kernel, grid, dim3(kTileRows), 0, on, ptr<int32_t>(side.nbr), n, kvol, c, (int32_t*)nullptr);
-        hipLaunchKernelGGL(emit_kernel, grid, dim3(kTileRows), 0, on, emit_args(side, n, kvol, c));
+        launch_emit(emit_args(side, n, kvol, c), side.n_rows, on);
         SP_HIP(hipGetLastError());
         return SP_OK;
     });
@@ -643,11 +708,15 @@ int need_classes(const MapSide& side, hipStream_t s) {
     SideWork& w = *side.work;
     std::lock_guard<std::mutex> lk(w.mu);
     return once(w.classes, s, [&](hipStream_t on) -> int {
-        const dim3 grid((unsigned)tiles_of(side.n_rows));
-        hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, on, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
-                           ptr<int32_t>(w.class_counts));
+        const int64_t nt = tiles_of(side.n_rows);
+        const dim3 grid((unsigned)nt);
+        int32_t *agg = ptr<int32_t>(w.class_counts), *pre = prefixes_in(agg, nt, w.nclass);
+        hipLaunchKernelGGL(class_count_kernel, grid, dim3(kTileRows), 0, on, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass, agg,
+                           nt);
+        if (pre)
+            hipLaunchKernelGGL(prefix_kernel, dim3((unsigned)w.nclass), dim3(kTileRows), 0, on, agg, pre, nt, Count{nullptr, side.n_rows});
         hipLaunchKernelGGL(class_emit_kernel, grid, dim3(kTileRows), 0, on, ptr<int4>(w.coords), side.n_rows, w.ts, w.stride, w.nclass,
-                           w.K, ptr<int32_t>(w.class_counts), ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
+                           w.K, agg, pre, nt, ptr<int32_t>(side.perm), ptr<uint32_t>(side.tile_mask));
         SP_HIP(hipGetLastError());
         return SP_OK;
     });

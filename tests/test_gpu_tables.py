@@ -97,3 +97,35 @@ def test_lists_of_the_input_side_under_capture(sp, cin, cout, bf16, warm):  # no
         torch.cuda.synchronize()
         assert torch.equal(y, want[i])
         assert torch.equal(sp.sp_conv_fwd(kt, xs[i], w), want[i])
+
+
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1, 2500000])
+def test_lists_and_classes_of_many_tiles(sp, n):  # noqa: F811
+    """Beyond 1024 tiles of 1024 rows the sums of earlier tiles come from a prefix launch: pair lists against the neighbour
+    table they compact (whole numbers), the lists and the class order of an input side through the convolutions that walk them."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    i = torch.randperm(3 << 20, device="cuda", generator=g)[:n].to(torch.int32)       # 5 of 6 sites, or a third of a lattice
+    raw = torch.stack([i >> 20, i >> 13 & 127, i >> 6 & 127, i & 63], dim=1).contiguous()
+    c = sp.sp_coords_build(raw, 1)
+    for K, stride in ((2, 1), (3, 2)):
+        km, _ = sp.sp_kmap_build(c, K, stride, 1)
+        nbr = km.table()[0]
+        pin, pout = km.pairs_strided()
+        for k in range(K ** 3):
+            dst = torch.nonzero(nbr[k] >= 0)[:, 0]
+            m = len(dst)
+            assert m == km.counts[k]
+            assert torch.equal(pout[k, :m].long(), dst) and torch.equal(pin[k, :m], nbr[k][dst])
+    kt = sp.sp_kmap_transpose(km)
+    tin, tout = kt.pairs_strided()
+    for ch, dt, tol in ((16, torch.float32, 1e-5), (128, torch.bfloat16, 1e-2)):       # link lists; class order
+        assert sp.sp_conv_kernel_name(kt, ch, ch, dt) == ("gather_wave_kernel" if ch == 16 else "gather_dense_kernel")
+        x = torch.randn((kt.n_in, ch), device="cuda", generator=g).to(dt)
+        w = torch.randn((27, ch, ch), device="cuda", generator=g).to(dt)
+        want = torch.zeros((kt.n_out, ch), device="cuda")
+        for k in range(27):
+            m = int(kt.counts[k])
+            want.index_add_(0, tout[k, :m], x[tin[k, :m].long()].float() @ w[k].float().T)
+        got = sp.sp_conv_fwd(kt, x, w).float()
+        assert float((got - want).norm() / want.norm()) <= tol
+        assert float((got - want).abs().max() / want.square().mean().sqrt()) <= 50 * tol
