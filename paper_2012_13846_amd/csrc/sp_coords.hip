@@ -559,14 +559,7 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     c->n_raw = n_src;
     c->ts = tensor_stride;
     c->stream = s;
-    // slots: room for every row at half load; small sets, whose builds and searches wait for the longest chain of
-    // collisions and not for memory, get an eighth
     const bool small = n_src <= kSmallRows;
-    uint32_t cap = 1024;
-    while ((int64_t)cap < (n_src <= kGridRows ? 8 : 2) * n_src) cap <<= 1;
-    if (small) cap = std::min<uint32_t>(cap, kSmallSlots);
-    c->tab.cap = cap;
-    for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
     // A grid: 32 bytes of dir per source row (128 cells of the box; 4 MB at least), whole scan blocks, and 64 bytes per
     // block that can be occupied.  Cell numbers have to fit 32 bits, places in cells 31.
     int64_t dir_words = 0;
@@ -574,6 +567,15 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
         dir_words = std::min<int64_t>((std::max<int64_t>(8 * n_src, 1 << 20) + kScanWords - 1) / kScanWords * kScanWords, (int64_t)1 << 28);
     const bool may_grid = dir_words > 0;
     c->tab.dir_words = dir_words;
+    // Slots, a power of two.  Builds and searches wait for the longest chain of collisions among a wavefront's rows, so
+    // room is time: eight per row for sets that take the hash form; where a grid is reserved (96 bytes a row) at least three,
+    // which take no more (262 k rows in a box too wide for a grid, coordinates + K = 3 map: two a row 232 us, three 169);
+    // the largest sets, and what is made from them, room for every row at half load.
+    uint32_t cap = 1024;
+    while ((int64_t)cap < (n_src <= kGridRows ? 8 : (may_grid ? 3 : 2)) * n_src) cap <<= 1;
+    if (small) cap = std::min<uint32_t>(cap, kSmallSlots);
+    c->tab.cap = cap;
+    for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
     const size_t grid_bytes = may_grid ? (size_t)dir_words * 4 + (size_t)n_src * 64 : 0;
     const int nthreads = n_src >= (1 << 20) ? kNumberThreads : (n_src >= (1 << 18) ? 512 : kThreads);
     const int block_rows = nthreads * kRowsPerThread;

@@ -29,11 +29,13 @@ CORNER = random_coords(12, 40000, 40, batches=2, lo=32728) + np.array([65534, 0,
 LOW = random_coords(13, 40000, 40, batches=2, lo=-32768)
 FAR = random_coords(14, 40000, 20000, batches=9, lo=-10000)           # a box too large for a grid
 PLANE = DENSE * np.array([1, 9, 1, 0], np.int32)
+WIDE = random_coords(15, 300000, 4000, batches=2, lo=-2000) // np.array([1, 1, 20, 100], np.int32)   # the same, all columns a thread
 CASES = [("grid", DENSE, 1, 3, 1, 1), ("grid_k5", DENSE, 1, 5, 1, 1), ("grid_k4", DENSE, 1, 4, 1, 1), ("grid_k2", DENSE, 1, 2, 1, 1),
          ("grid_d2", DENSE, 1, 3, 1, 2), ("grid_d5", DENSE, 1, 3, 1, 5), ("grid_k5_d7", DENSE, 1, 5, 1, 7),
          ("grid_s2", DENSE, 1, 3, 2, 1), ("grid_s3", DENSE, 1, 3, 3, 1), ("grid_k2s2", DENSE, 1, 2, 2, 1), ("grid_k4s2", DENSE, 1, 4, 2, 1),
          ("plane", PLANE, 1, 3, 1, 1), ("corner_d2", CORNER, 1, 3, 1, 2), ("corner_s2", CORNER, 1, 3, 2, 1), ("low_k5", LOW, 1, 5, 1, 1),
          ("low_s2", LOW, 1, 3, 2, 1), ("hash", FAR, 1, 3, 1, 1), ("hash_s2", FAR, 1, 3, 2, 1), ("hash_k2s2", FAR, 1, 2, 2, 1),
+         ("hash_wide", WIDE, 1, 3, 1, 1), ("hash_wide_d2", WIDE, 1, 3, 1, 2), ("hash_wide_s2", WIDE, 1, 3, 2, 1),
          ("ts4", scaled(DENSE, 4), 4, 3, 1, 1), ("ts4_s2", scaled(DENSE, 4), 4, 3, 2, 1), ("ts3_shifted", scaled(DENSE, 3, 1), 3, 3, 1, 1),
          ("ts2_shifted_s2", scaled(DENSE, 2, 1), 2, 3, 2, 1), ("off_lattice", DENSE, 2, 3, 1, 1), ("off_lattice_s2", DENSE, 2, 3, 2, 1)]
 
@@ -43,6 +45,11 @@ def test_forms_match_oracle(sp, case):  # noqa: F811
     if case[3:5] == (3, 1):
         check_set(sp, case[0], case[1])
     check_maps(sp, *case)
+
+
+def test_hash_of_more_than_a_million_rows_with_duplicates(sp):  # noqa: F811
+    """From 2^20 rows on the insertion looks at the slot before it spends an atomic."""
+    check_set(sp, "", WIDE[np.random.default_rng(16).integers(0, 200000, 1_100_000)])
 
 
 def test_out_of_range_row_among_many(sp):  # noqa: F811
