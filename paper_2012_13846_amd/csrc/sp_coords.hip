@@ -3,10 +3,10 @@
 //
 // No host round trip.  Up to kSmallRows one workgroup does everything in one launch, with the hash table in LDS.  Up to
 // kGridRows (where every launch counts): reset the hash table, insert every row (slot.first = smallest row carrying
-// the key), number, inverse.  Larger sets: the extent of the coordinates (a
-// coarser set takes its parent's), prepare (every workgroup derives the grid's box, or that a hash table is needed, and
-// clears that table), mark the occupied blocks (or insert into the hash table), number the blocks and clear their
-// cells, put the smallest row of each cell into it, number, inverse.
+// the key), number, inverse.  Larger sets: the extent of the coordinates (a coarser set takes its parent's), prepare
+// (every workgroup derives the grid's box, or that a hash table is needed, and clears that table), mark the occupied
+// blocks (or insert into the hash table), number the blocks and clear their cells, put the smallest row of each cell
+// into it, number, inverse.
 // number: in a single pass every block of rows counts its first occurrences, gets the count of all earlier blocks by
 // decoupled look-back, ranks its rows with ballots and writes coordinates + row numbers; the last block writes the
 // row count N to device memory for later kernels and to a mail slot for the host.  inverse: the row number of every
@@ -25,7 +25,10 @@ constexpr int kRowsPerThread = 4;
 constexpr int kNumberThreads = 1024;           // most threads of a numbering block
 constexpr int64_t kSmallRows = 8192;           // up to here one workgroup (8 rows a thread, keys and slots in LDS)
 constexpr int kSmallSlots = 16384;             // most slots of its table
-constexpr int64_t kGridRows = 32768;           // up to here a hash table: four launches instead of seven
+// Up to here a hash table: four launches instead of seven.  Coordinates / + K = 3 map / + 2 x 2 x 2 stride 2 map in us, hash
+// (eight slots a row) against grid: 46.7 k rows 25 / 46 / 67 against 37 / 52 / 86, 65 k 27 / 55 / 70 against 39 / 54 / 88,
+// 82 k 32 / 65 / 78 against 43 / 60 / 92, 130 k 38 / 81 / 92 against 48 / 70 / 102.
+constexpr int64_t kGridRows = 65536;
 constexpr int kBoxBlocks = 256;                // blocks of the extent kernel = threads of a prepare block
 constexpr int kBoxWords = 12;                  // min and max of b, x, y, z; out of range; off the lattice
 constexpr int kScanThreads = 1024;
@@ -418,11 +421,11 @@ __global__ __launch_bounds__(kScanThreads) void number_blocks_kernel(Build t) {
     for (int i = tid; i < total * 4; i += kScanThreads) cells[i] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
 }
 
-// Grid: at[i] becomes the row's place in cells (its complement for a row that is not the first of its cell), and the cell ends up with its smallest row.  A cell's value is one of its
-// rows and only ever decreases, so a row that reads one smaller than itself, however old the copy it reads, can stay
-// away: most duplicates spend no atomic.  (Plain stores followed by a pass of atomics for the rows that lost would
-// be faster still, but two XCDs that store different values to one word are left with an L2 copy each, and later
-// kernels have been seen to read both.)
+// Grid: at[i] becomes the row's place in cells (its complement for a row that is not the first of its cell), and the
+// cell ends up with its smallest row.  A cell's value is one of its rows and only ever decreases, so a row that reads
+// one smaller than itself, however old the copy it reads, can stay away: most duplicates spend no atomic.  (Plain
+// stores followed by a pass of atomics for the rows that lost would be faster still, but two XCDs that store different
+// values to one word are left with an L2 copy each, and later kernels have been seen to read both.)
 __global__ __launch_bounds__(kThreads) void place_kernel(Build t, int64_t n_host, const int32_t* __restrict__ d_n,
                                                          int32_t* __restrict__ at) {
     if (!is_grid(t)) return;

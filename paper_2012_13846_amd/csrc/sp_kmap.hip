@@ -845,8 +845,9 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
             hipLaunchKernelGGL(reset_kernel, dim3(blocks256((n_in_ub * (int64_t)kvol + 3) / 4)), dim3(kThreads), 0, s, ptr<int32_t>(si.nbr),
                                cn_in, kvol);
         const TableView tab = table_view(in);
-        // columns per thread: all K of one ax where the rows alone fill the chip, one where they do not
-        const bool few = n_out_ub < (1 << 17);
+        // Columns per thread: all K of one ax where the rows alone fill the chip, one where they do not (coordinates + map,
+        // one against three: 71 k rows 57 against 60 us, 130 k 71 against 75, 174 k 74 against 76, 255 k 82 against 83).
+        const bool few = n_out_ub < (1 << 18);
 #define SP_SEARCH(KS, NC)                                                                                                   \
     hipLaunchKernelGGL((search_kernel<KS, NC>), dim3(xcd_grid(nt), KS * KS / NC), dim3(kTileRows), 0, s, ptr<int4>(m->c_out->coords), cn_out, tab, \
                        dilation, symmetric ? 1 : 0, ptr<int32_t>(so.nbr), symmetric ? (int32_t*)nullptr : ptr<int32_t>(si.nbr), cn_in, \

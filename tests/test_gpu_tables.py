@@ -16,7 +16,7 @@ def scaled(raw, ts, shift=0):
     return raw * np.array([1, ts, ts, ts], np.int32) + np.array([0, shift, shift, shift], np.int32)
 
 
-@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 8191, 8192, 8193, 32768, 32769])
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 8191, 8192, 8193, 32768, 32769, 65535, 65536, 65537])
 def test_row_counts_at_which_the_table_changes(sp, n):  # noqa: F811
     raw = random_coords(n, n, 28, batches=2, lo=-14)
     check_set(sp, "", raw)
@@ -24,10 +24,11 @@ def test_row_counts_at_which_the_table_changes(sp, n):  # noqa: F811
     check_maps(sp, "", raw, 1, 3, 2, 1)
 
 
-DENSE = random_coords(11, 40000, 37, batches=3, lo=-19) + np.array([5, 0, 0, 0], np.int32)
-CORNER = random_coords(12, 40000, 40, batches=2, lo=32728) + np.array([65534, 0, 0, 0], np.int32)
-LOW = random_coords(13, 40000, 40, batches=2, lo=-32768)
-FAR = random_coords(14, 40000, 20000, batches=9, lo=-10000)           # a box too large for a grid
+N = 70000                                                             # more than the hash form takes for certain
+DENSE = random_coords(11, N, 37, batches=3, lo=-19) + np.array([5, 0, 0, 0], np.int32)
+CORNER = random_coords(12, N, 40, batches=2, lo=32728) + np.array([65534, 0, 0, 0], np.int32)
+LOW = random_coords(13, N, 40, batches=2, lo=-32768)
+FAR = random_coords(14, N, 20000, batches=9, lo=-10000)               # a box too large for a grid
 PLANE = DENSE * np.array([1, 9, 1, 0], np.int32)
 WIDE = random_coords(15, 300000, 4000, batches=2, lo=-2000) // np.array([1, 1, 20, 100], np.int32)   # the same, all columns a thread
 CASES = [("grid", DENSE, 1, 3, 1, 1), ("grid_k5", DENSE, 1, 5, 1, 1), ("grid_k4", DENSE, 1, 4, 1, 1), ("grid_k2", DENSE, 1, 2, 1, 1),
@@ -38,6 +39,10 @@ CASES = [("grid", DENSE, 1, 3, 1, 1), ("grid_k5", DENSE, 1, 5, 1, 1), ("grid_k4"
          ("hash_wide", WIDE, 1, 3, 1, 1), ("hash_wide_d2", WIDE, 1, 3, 1, 2), ("hash_wide_s2", WIDE, 1, 3, 2, 1),
          ("ts4", scaled(DENSE, 4), 4, 3, 1, 1), ("ts4_s2", scaled(DENSE, 4), 4, 3, 2, 1), ("ts3_shifted", scaled(DENSE, 3, 1), 3, 3, 1, 1),
          ("ts2_shifted_s2", scaled(DENSE, 2, 1), 2, 3, 2, 1), ("off_lattice", DENSE, 2, 3, 1, 1), ("off_lattice_s2", DENSE, 2, 3, 2, 1)]
+
+
+# the same sets with fewer rows, in the hash form of middle-sized sets
+CASES += [(c[0] + "_40000", c[1][:40000], *c[2:]) for c in CASES if len(c[1]) == N]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
