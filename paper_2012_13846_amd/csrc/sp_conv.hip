@@ -37,6 +37,7 @@ struct GatherArgs {
     int co_total;
     int flip;        // weight matrix of list k is kvol-1-k
     int lds_per_wave;  // bytes of LDS of one wavefront in gather_wave_kernel
+    int runs;          // sub-tiles are dealt to the XCDs in runs (xcd_run)
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
@@ -77,7 +78,12 @@ struct WaveCfg {
     static constexpr int kXStride = kRowBytes + 32;       // staged row + pad (b128 fragment reads at the full LDS rate)
     static constexpr int kXBytes = 16 * kXStride - 32;  // the last row needs no pad
     static constexpr int kXLoads = (16 * kPieces + 63) / 64;  // coalesced load instructions per 16-link block
-    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + ((kvol * 5 + 3) / 4) * 16; }  // 4 descriptors and a begin per offset
+    // Up to 4 blocks per offset.  A descriptor of 8 bytes holds the block's first link; one of 4 bytes leaves it to a table
+    // of the offsets' begins, i.e. to a second LDS trip.  The trip costs 64-byte rows 3-6 % (bf16 32 -> 64 on 0.6 M links 28.6
+    // against 27.8 us); the room costs wider ones a wavefront per CU (fp32 32 -> 64: 59 against 68 us).
+    static constexpr bool kWideDesc = kRowBytes == 64;
+    static constexpr bool kMayRun = kRowBytes == 64 || !kIsF32;  // see xcd_run; the others gain nothing from it
+    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + ((kvol * (kWideDesc ? 8 : 5) + 3) / 4) * 16; }
     // fragment-major weights: [kvol][co_total/COT][kNCT][kGroups][64 lanes][16 bytes]
     static constexpr size_t kWFragBytesPerOffsetTile = (size_t)kNCT * kGroups * 64 * 16;
 };
@@ -88,6 +94,14 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+
+// Workgroup -> sub-tile such that an XCD (workgroup id % 8) takes runs of kRun neighbours.  A sub-tile's stretch of an
+// offset's list is half a cache line or less: neighbours on one XCD fetch the line once.  Large launches only (kRunRows):
+// bf16 32 -> 32 on 0.37 M rows 56.2 -> 53.5 us, 0.62 M rows 103 -> 95, on 0.16 M rows equal; 64 -> 128 on 0.1 M rows,
+// which fill the chip once and a half, 61.5 -> 66.
+constexpr int kRun = 8;
+constexpr int64_t kRunRows = 1 << 17;
+__device__ __forceinline__ int64_t xcd_run(int64_t wg) { return wg / (8 * kRun) * (8 * kRun) + (wg & 7) * kRun + (wg >> 3) % kRun; }
 
 template <typename T, int CC, int COT>
 __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
@@ -118,14 +132,18 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     // of the grid half 1.  (Workgroups are dealt to the 8 XCDs round-robin: pairing (u,0),(u,1) on adjacent
     // indices would leave every other XCD with nothing but wavefronts that leave at once.)
     const int64_t nwt = (a.n_rows + 63) / 64;
-    const int half = blockIdx.x >= nwt ? 1 : 0;     // which 32-row half it takes if the sub-tile is split
-    const int64_t wt = (int64_t)blockIdx.x - (half ? nwt : 0);  // this wavefront's sub-tile
+    const bool runs = Cfg::kMayRun && a.runs;
+    const int half = !runs && blockIdx.x >= nwt ? 1 : 0;  // which 32-row half it takes if the sub-tile is split
+    const int64_t wt = runs ? xcd_run(blockIdx.x) : (int64_t)blockIdx.x - (half ? nwt : 0);  // this wavefront's sub-tile
+    if (Cfg::kMayRun && wt >= nwt) return;
     const int kvol = a.kvol;
     unsigned char* base = smem;
     float* acc = reinterpret_cast<float*>(base);
     unsigned char* xbuf = base + Cfg::kAccBytes;
+    constexpr bool kWideDesc = Cfg::kWideDesc;
     int* s_beg = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);  // per offset: where this wavefront's links begin
     int* s_blk = s_beg + kvol;
+    int2* s_blk2 = reinterpret_cast<int2*>(s_beg);             // kWideDesc: {descriptor, first link}
     const int n16 = lane & 15, g = lane >> 4;
 
     for (int i = lane; i < Cfg::kAccBytes / 16; i += 64) reinterpret_cast<f32x4*>(acc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -164,9 +182,12 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
             if (lane >= d) inc += t;
         }
         const int ex = nblk + inc - nb;
-        if (k < kvol) s_beg[k] = o0;
-        for (int i = 0; i < nb; ++i)
-            s_blk[ex + i] = k | ((min(16, cnt - 16 * i) - 1) << 7) | (i << 11);
+        if (!kWideDesc && k < kvol) s_beg[k] = o0;
+        for (int i = 0; i < nb; ++i) {
+            const int de = k | ((min(16, cnt - 16 * i) - 1) << 7) | (i << 11);
+            if (kWideDesc) s_blk2[ex + i] = int2{de, o0 + 16 * i};
+            else s_blk[ex + i] = de;
+        }
         nblk += __shfl(inc, 63, 64);
     }
     wave_sync();
@@ -212,9 +233,31 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     const int last = nblk - 1;
     // (Starting each wavefront at a block of its own, so that the wavefronts of a compute unit do not ask for
     // the same weight lines at the same moment, was measured and is slower: in step, they share the lines in L1.)
+    // bf16 rows of 128 bytes and more: the descriptors run ahead in registers (64 -> 128 on 2.4 M links 193 -> 190 us; fp32,
+    // whose turns are longer, loses 1 % by the registers)
+    int de_0 = 0, de_1 = 0, beg_0 = 0;
+    if (!kWideDesc && !kIsF32 && nblk > 0) {
+        de_0 = s_blk[0];
+        de_1 = s_blk[min(1, last)];
+        beg_0 = s_beg[de_0 & 127];
+    }
     auto load_entries = [&](Slot& sl, int b) __attribute__((always_inline)) {
-        sl.de = s_blk[min(b, last)];
-        const int cnt = ((sl.de >> 7) & 15) + 1, e0 = s_beg[sl.de & 127] + ((sl.de >> 11) << 4);
+        int e0;
+        if constexpr (kWideDesc) {
+            const int2 d = s_blk2[min(b, last)];
+            sl.de = d.x;
+            e0 = d.y;
+        } else if constexpr (!kIsF32) {  // blocks are asked for in order: b's descriptor was read two calls ago
+            sl.de = de_0;
+            e0 = beg_0 + ((sl.de >> 11) << 4);
+            de_0 = de_1;
+            beg_0 = s_beg[de_1 & 127];
+            de_1 = s_blk[min(b + 2, last)];
+        } else {
+            sl.de = s_blk[min(b, last)];
+            e0 = s_beg[sl.de & 127] + ((sl.de >> 11) << 4);
+        }
+        const int cnt = ((sl.de >> 7) & 15) + 1;
 #pragma unroll
         for (int t = 0; t < kXLoads; ++t)
             sl.esrc[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rSrc, (e0 + min((t * 64 + lane) / kPieces, cnt - 1)) * 4, 0, 0);
@@ -228,7 +271,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
             sl.x[t] = __builtin_amdgcn_raw_buffer_load_b128(rF, sl.esrc[t] * Cfg::kRowBytes + ((t * 64 + lane) % kPieces) * 16, 0, 0);
     };
     auto issue_weights = [&](WSlot& ws, int b, int ct0 = 0) __attribute__((always_inline)) {
-        load_weights(s_blk[min(b, last)] & 127, ws.w, ct0);
+        load_weights((kWideDesc ? s_blk2[min(b, last)].x : s_blk[min(b, last)]) & 127, ws.w, ct0);
     };
     auto stage = [&](const Slot& sl) __attribute__((always_inline)) {  // gathered rows -> LDS, row-major, padded
 #pragma unroll
@@ -455,8 +498,10 @@ int launch_wave(GatherArgs a, hipStream_t s) {
     // run in several rounds, where splitting would only add padding.
     const int64_t resident_tiles = 256 * (160 * 1024 / (int64_t)a.lds_per_wave);
     a.split_blocks = (nwt * (a.co_total / COT) * 5 / 4 <= resident_tiles) ? 48 : 0x7fffffff;
+    a.runs = Cfg::kMayRun && a.split_blocks == 0x7fffffff && a.n_rows >= kRunRows ? 1 : 0;
     // two wavefronts per sub-tile only where sub-tiles may be split (the second one leaves at once otherwise)
-    dim3 grid((unsigned)((a.split_blocks == 0x7fffffff ? 1 : 2) * nwt), (unsigned)(a.co_total / COT));
+    const int64_t wgs = a.runs ? (nwt + 8 * kRun - 1) / (8 * kRun) * (8 * kRun) : (a.split_blocks == 0x7fffffff ? 1 : 2) * nwt;
+    dim3 grid((unsigned)wgs, (unsigned)(a.co_total / COT));
     hipLaunchKernelGGL(kern, grid, dim3(64), lds, s, a);
     SP_HIP(hipGetLastError());
     return SP_OK;  // wf goes back to the pool; later users are ordered behind this launch on the stream
@@ -511,8 +556,8 @@ __global__ __launch_bounds__(256) void transpose_w_kernel(const T* __restrict__ 
 }
 
 // Narrow layers take the wavefront-private kernel, with the widest channel tile whose weight matrix fits in
-// 32 fragment registers (CC/group * COT/16 fragments of 4 registers each).  Returns that tile, or 0 when the
-// workgroup-cooperative kernel takes the layer.
+// 32 fragment registers (CC/group * COT/16 fragments of 4 registers each).  Returns that tile, or 0 when the tile
+// kernel takes the layer.
 int wave_tile(int cc, int co, bool is_f32) {
     const int groups = cc / (is_f32 ? 16 : 32);
     if (groups * 4 <= 16 && co % 64 == 0) return 64;  // more than 8 fragments per lane: the matrix is held in two halves

@@ -3,6 +3,7 @@ end: forward and both gradients against the fp64 oracle.  Tolerances are the par
 rounding to 8 bits, see util.py): channel counts change nothing about how a term is rounded."""
 import numpy as np
 import pytest
+import torch
 
 from test_gpu_parity import conv_case, full_cubes, random_coords, sp  # noqa: F401  (sp: the binding fixture)
 
@@ -34,3 +35,25 @@ def test_128_row_tiles_fp32(sp, cin, cout):  # noqa: F811
     # enough rows that the 128-row tiles are chosen; rows not a multiple of 64
     raw = np.unique(random_coords(77, 90000, 60, batches=3), axis=0)[:65601]
     conv_case(sp, raw[np.random.default_rng(2).permutation(len(raw))], 1, 3, 1, 1, cin, cout, False, seed=cin + cout)
+
+
+@pytest.mark.parametrize("n", [(1 << 17) - 1, 1 << 17, (1 << 17) + 64 * 73 + 1])
+@pytest.mark.parametrize("cin,cout,dt", [(16, 16, torch.float32), (32, 96, torch.bfloat16), (64, 64, torch.bfloat16)])
+def test_sub_tiles_dealt_in_runs(sp, n, cin, cout, dt):  # noqa: F811
+    """From 2^17 rows on the XCDs take runs of eight sub-tiles, the last group of runs may be short: every row is written."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    i = torch.randperm(1 << 20, device="cuda", generator=g)[:n].to(torch.int32)
+    c = sp.sp_coords_build(torch.stack([i >> 18, i >> 12 & 63, i >> 6 & 63, i & 63], dim=1).contiguous(), 1)
+    km, _ = sp.sp_kmap_build(c, 3, 1, 1)
+    assert sp.sp_conv_kernel_name(km, cin, cout, dt) == "gather_wave_kernel"
+    x = torch.randn((n, cin), device="cuda", generator=g).to(dt)
+    w = torch.randn((27, cout, cin), device="cuda", generator=g).to(dt)
+    pin, pout = km.pairs_strided()
+    want = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        m = int(km.counts[k])
+        want.index_add_(0, pout[k, :m], x[pin[k, :m].long()].float() @ w[k].float().T)
+    got = sp.sp_conv_fwd(km, x, w).float()
+    tol = 1e-5 if dt == torch.float32 else 1e-2
+    assert float((got - want).norm() / want.norm()) <= tol
+    assert float((got - want).abs().max() / want.square().mean().sqrt()) <= 10 * tol
