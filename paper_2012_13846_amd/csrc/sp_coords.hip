@@ -447,10 +447,11 @@ __global__ __launch_bounds__(kThreads) void place_kernel(Build t, int64_t n_host
 // takes itself for the first.)
 __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __restrict__ src, int64_t n_host,
                                                                 const int32_t* __restrict__ d_n, int32_t floor_step, Build t,
-                                                                const int32_t* __restrict__ at, Chain chain,
+                                                                const int32_t* __restrict__ at,
+                                                                unsigned long long* __restrict__ desc,
                                                                 int4* __restrict__ coords, uint32_t* __restrict__ mail,
                                                                 uint32_t mail_seq) {
-    __shared__ int s_own[1], s_excl[1], s_state[2];
+    __shared__ int s_own, s_before;  // first occurrences in this block, in all earlier ones
     __shared__ int s_row[kRowsPerThread * (kNumberThreads / 64)];  // first occurrences in earlier 64-row stretches of the block
     static_assert(kRowsPerThread * (kNumberThreads / 64) <= 64, "one wavefront scans them");
     const int nthreads = blockDim.x, nw = nthreads >> 6;
@@ -504,10 +505,14 @@ __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __re
             if (lane >= d) inc += u;
         }
         if (lane < kRowsPerThread * nw) s_row[lane] = inc - v;
-        if (lane == 63) s_own[0] = inc;
+        const int own = __shfl(inc, 63, 64), earlier = lookback(desc, b, own, meta + kMetaErr);
+        if (lane == 0) {
+            s_own = own;
+            s_before = earlier;
+        }
     }
-    chain_lookback(chain, b, s_own, s_excl, s_state, meta + kMetaErr);
-    const int before = s_excl[0];
+    __syncthreads();
+    const int before = s_before;
 #pragma unroll
     for (int j = 0; j < kRowsPerThread; ++j) {
         if (f[j]) {
@@ -518,7 +523,7 @@ __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __re
         }
     }
     if (b == nb - 1 && threadIdx.x == 0) {
-        const int run = before + s_own[0];
+        const int run = before + s_own;
         meta[kMetaN] = run;
         if (mail) {
             mail[0] = (uint32_t)run;
@@ -603,10 +608,6 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     t.dir_words = dir_words;
     t.meta = ptr<int32_t>(c->meta);
     t.ts = tensor_stride;
-    Chain chain;
-    chain.desc = desc;
-    chain.n_tiles = nb ? nb : 1;
-    chain.width = 1;
     const bool mailed = mail_acquire(&c->mail);
     const int4* src = reinterpret_cast<const int4*>(d_src);
     const dim3 rows(xcd_grid(blocks_for(n_src, kThreads))), threads(kThreads);
@@ -660,7 +661,7 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
         hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
     }
     hipLaunchKernelGGL(number_kernel, dim3((unsigned)nb), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at,
-                       chain, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
+                       desc, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
     hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, n_src, d_n_src, ptr<int32_t>(c->inverse));
     return hand_over();
 }

@@ -84,21 +84,6 @@ __device__ __forceinline__ int64_t hash_insert(HashSlot* __restrict__ tab, uint3
     return -1;
 }
 
-// Row number stored for `key`, or -1 when absent.  One 16-byte load per probed slot.
-__device__ __forceinline__ int32_t hash_find(const HashSlot* __restrict__ tab, uint32_t cap, int zshift, uint64_t key) {
-    uint32_t bucket, pos;
-    hash_home(key, cap, zshift, &bucket, &pos);
-    uint32_t slot = bucket * 4 + pos;
-    for (uint32_t probe = 0; probe < cap; ++probe) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(&tab[slot]);
-        const unsigned long long cur = ((unsigned long long)raw.y << 32) | raw.x;
-        if (cur == key) return (int32_t)raw.w;
-        if (cur == kEmptyKey) return -1;
-        slot = (slot + 1) & (cap - 1);
-    }
-    return -1;
-}
-
 // ---- grid ----------------------------------------------------------------------------------------------------
 struct TableView {
     const HashSlot* slots;  // hash form
