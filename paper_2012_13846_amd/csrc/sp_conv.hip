@@ -670,8 +670,16 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
 namespace {
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,
 // 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain.  The wavefront-private kernel keeps the whole
-// weight matrix of a narrow layer in registers and is 5-20 % faster there (fp32 64 -> 64 on 5 M links: 620-680 us
-// against 665-710); everything else, wide or not a multiple of its tiles, takes the tile kernel.
+// weight matrix of a narrow layer in registers; everything else, wide or not a multiple of its tiles, takes the tile kernel.
+// Forward in us, wavefront-private / tile kernel, on 1.5 k rows with 9 k links | 96 k, 0.61 M | 160 k, 0.66 M | 374 k, 2.4 M |
+// 613 k, 5.0 M:
+//   fp32 16 -> 16   16 / 14 | 23 / 38   | 27 / 51   | 55 / 115  | 88 / 206       bf16 32 -> 32   17 / 15 | 23 / 31 | 28 / 44  | 54 / 93   | 95 / 167
+//   fp32 32 -> 32   24 / 16 | 36 / 45   | 49 / 63   | 90 / 139  | 175 / 260      bf16 32 -> 64   21 / 16 | 28 / 38 | 48 / 51  | 78 / 103  | 142 / 192
+//   fp32 32 -> 64   34 / 19 | 56 / 62   | 89 / 84   | 153 / 195 | 310 / 376      bf16 64 -> 64   22 / 16 | 37 / 49 | 57 / 63  | 101 / 143 | (row-stationary)
+//   fp32 64 -> 32   35 / 22 | 57 / 87   | 92 / 123  | 160 / 292 | 324 / 554      bf16 64 -> 128  23 / 19 | 62 / 84 | 84 / 107 | 189 / 287 | (row-stationary)
+//   fp32 64 -> 64   54 / 27 | 114 / 100 | 166 / 134 | 305 / 341 | 604 / 664
+// So one rule for both types.  It gives away the smallest launches, which one tile's chain bounds, and fp32 64 -> 64 between
+// about 0.1 and 0.2 M rows, where the tile kernel's 128 rows fill the blocks of few links better.
 int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
     // Row-stationary kernel: it multiplies all kvol offsets of every row, the link-list kernels only the links
