@@ -55,17 +55,22 @@ typedef enum {
 
 typedef enum { SP_F32 = 0, SP_BF16 = 1 } sp_dtype; /* storage type of features/weights; accumulation is fp32 */
 
-typedef struct sp_coords sp_coords_t; /* distinct coordinates + their hash table + tensor stride   */
+typedef struct sp_coords sp_coords_t; /* distinct coordinates + the table that finds them + tensor stride */
 typedef struct sp_kmap sp_kmap_t;     /* kernel map of one (coords, kernel, stride, dilation)      */
 
 /* ---- step 0: the sparse tensor's coordinate set (Sec. III-B, sparse tensor definition) --------------
- * Hashes d_raw [n_raw][4] into an open-addressing table, merges duplicate rows and numbers the
- * distinct rows in first-occurrence order (unique row r = r-th distinct coordinate met walking the
- * rows in order).  tensor_stride (>= 1) is recorded, coordinates are expected on that lattice.
+ * Enters d_raw [n_raw][4] into a table (an open-addressing hash table, or for large sets in a bounded box a grid
+ * of cells), merges duplicate rows and numbers the distinct rows in first-occurrence order (unique row r = r-th
+ * distinct coordinate met walking the rows in order).  tensor_stride (>= 1) is recorded, coordinates are expected
+ * on that lattice.
  * Returns without waiting for the stream: d_raw must stay valid until the stream has passed the call.  A
  * coordinate outside the packable range is found on the device and reported (SP_ERR_RANGE) by the first later
  * call that needs this set's row count on the host (sp_coords_size, or any call on a map built from it).
- * n_raw may be 0.  *out receives a new handle (caller destroys). */
+ * n_raw may be 0.  *out receives a new handle (caller destroys).
+ * Device memory that the handle holds: 20 bytes per source row, and the table: 128 to 256 bytes per source row up to
+ * 65536 rows (256 KB at most up to 8192 of them), 96 (at least 64 and 4 MiB) below 2^26 rows, 32 to 64 beyond.  The build
+ * itself takes 4 bytes per row more.  Coarser sets made by sp_kmap_build are sized by the row bound of the set that they
+ * are made from. */
 int sp_coords_build(const int32_t* d_raw, int64_t n_raw, int32_t tensor_stride, void* stream, sp_coords_t** out);
 
 /* N and the tensor stride.  Asking for N waits (the first time) until the build's numbering kernel has delivered
@@ -86,7 +91,7 @@ int sp_coords_destroy(sp_coords_t* c);
  *   x,y,z to multiples of S = tensor_stride*s (true floor), merges duplicates in first-occurrence
  *   order, and the new tensor stride is S.
  * Step 2: M_k = {(i,o) : c_in[i] = c_out[o] + offset_k * dilation * tensor_stride, same batch index},
- *   found by probing the input set's hash table.
+ *   found by searching the input set's table.
  * Returns without waiting: where `in`'s N has not reached the host yet the kernels read it from device memory
  * and buffers are sized from `in`'s source row count (if that bound is wasteful - above 1 GiB of tables and
  * lists - the call waits for N first).
@@ -139,8 +144,14 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
  * (SP_BF16: 16-bit bfloat16, results rounded to nearest even once); accumulation is always fp32.
  * Outputs are overwritten (rows / offsets without pairs become zero).  No host synchronisation.
  * All feature / weight / gradient pointers must be 16-byte aligned (SP_ERR_INVALID_ARG otherwise).
- * Every channel count runs on the matrix cores; multiples of 16 (fp32) or 32 (bf16) without padding, 16-byte
- * multiples of a row without element-wise loads.
+ * Channel counts run on the matrix cores; multiples of 16 (fp32) or 32 (bf16) without padding, 16-byte multiples
+ * of a row without element-wise loads.  Plain kernels (one thread per result element: correct, slow) take
+ *   - forward / data gradient where source features or pair lists pass 4 GiB and a feature row is no whole number of
+ *     16-byte pieces, or where the padded weights pass 4 GiB;
+ *   - the weight gradient where an operand (its rows padded to 16 bytes) or the pair lists pass 2 GiB;
+ *   - layers whose scratch the allocator refuses, if they are of the kind that can do without (forward / data gradient
+ *     off the narrow layers' and the wide bf16 kernels, weight gradient of widths that are no multiple of 16); the
+ *     others return SP_ERR_ALLOC.
  *
  *   sp_conv_fwd:        y[o,:]  = sum_k sum_{(i,o) in M_k} W_k   x[i,:]      x [n_in][cin]   -> y  [n_out][cout]
  *   sp_conv_bwd_data:   dx[i,:] = sum_k sum_{(i,o) in M_k} W_k^T dy[o,:]     dy [n_out][cout] -> dx [n_in][cin]
@@ -154,14 +165,20 @@ int sp_conv_bwd_weight(const sp_kmap_t* m, const void* d_x, const void* d_dy, fl
                        int32_t cout, sp_dtype dt, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc): sp_conv_fwd with the same arguments, results and kernel choice, except that the
- * call allocates nothing (no hipMalloc / hipFree, no pool request).  Where sp_conv_fwd takes scratch from the
- * pool (the fragment-major copy of the weights that the link-list kernel reads), this call uses a 4 MiB
- * array in static device memory, which every GPU the library runs on holds until the process ends.
- * Weights larger than that on a shape that needs the copy give SP_ERR_UNSUPPORTED (kvol * cin * cout *
- * element size <= 4 MiB always fits).  All calls on one GPU share that array: calls that overlap in time on
- * one GPU (different streams) race; calls on one stream are ordered and safe.  The array's contents are
- * rewritten by every call, nothing in it needs to start at zero. */
+ * that forbid hipMalloc): sp_conv_fwd with the same arguments, except that the call allocates nothing (no
+ * hipMalloc / hipFree, no pool request).  Where sp_conv_fwd takes scratch from the pool (the fragment-major copy of
+ * the weights that the link-list kernels read), this call uses a 4 MiB array in static device memory, which every
+ * GPU the library runs on holds until the process ends.  While the copy fits, kernels and results are sp_conv_fwd's.
+ * A copy that does not fit (the tile kernel's is padded to whole channel tiles):
+ *   - narrow layers (gather_wave_kernel: cin 16 / 32 / 64 fp32, 32 / 64 / 128 bf16, cout to match): SP_ERR_UNSUPPORTED;
+ *     kvol * cin * cout * element size <= 4 MiB is never refused;
+ *   - other layers whose cin is whole slices of the tile kernel: the weights are read where they are stored; the same
+ *     results, slower;
+ *   - the rest run on the plain kernel: correct, slow, fp32 sums in another order than sp_conv_fwd's.
+ * All calls on one GPU share that array: calls that overlap in time on one GPU (different streams) race; calls on one
+ * stream are ordered and safe.  The array's contents are rewritten by every call, nothing in it needs to start at zero.
+ * Lists that the map makes on first use (the input side of strided maps and even kernels) and that do not exist yet
+ * when a call is captured are built outside the graph, on a stream of the library's own; the call waits for them. */
 int sp_conv_fwd_noalloc(const sp_kmap_t* m, const void* d_x, const void* d_w, void* d_y, int32_t cin, int32_t cout,
                         sp_dtype dt, void* stream);
 
