@@ -4,17 +4,17 @@
 One step = one pass of the whole path over one synthetic batch that is already resident in HBM:
   sp_coords_build (hash + merge duplicates) -> sp_kmap_build -> sp_conv_fwd -> sp_conv_bwd_data
   -> sp_conv_bwd_weight.
-Headline workload: benchmark configs[1] (8 clouds x 20k surface points on a 128^3 grid, 3x3x3 stride 1,
-Cin=32, Cout=64, fp32).
+Headline workload: 8 clouds x 20k surface points on a 128^3 grid, 3x3x3 stride 1, Cin=32, Cout=64, fp32.
 
-Prints ONE JSON line.  `value` is the effective TFLOP/s of the headline step: the active multiply-adds of
+Prints ONE JSON line on stdout.  `value` is the effective TFLOP/s of the headline step: the active multiply-adds of
 fwd + dgrad + wgrad (2 * 3 * pairs * Cin * Cout flops) divided by the time of the WHOLE step, map building
 included.  The same line carries
   - `roofline`: the dominant kernel of the headline step, timed live with events on the launch stream;
   - `cpu_baseline`: the CPU oracle on the headline workload, one thread and all cores (one process per cloud);
-  - `configs`: every other BASELINE config and the paper's sparsity-sweep batches, each with per-stage times,
-    the roof that binds each stage (matrix cores or HBM) and the achieved fraction of it; for the two
-    map-building stages the algorithmic bytes, achieved GB/s and the fraction of the HBM peak.
+  - `configs`: step time and rate of every other workload (the larger clouds, the stack, the paper's sparsity-sweep batches).
+The details of all of them go to stderr as one more JSON line: per-stage times, the roof that binds each stage (matrix
+cores or HBM) and the achieved fraction of it; for the two map-building stages the algorithmic bytes, achieved GB/s and
+the fraction of the HBM peak.
 `--workload NAME` makes another workload the headline; `--only-headline` skips `configs` (profiling runs).
 """
 from __future__ import annotations
@@ -345,7 +345,7 @@ def run_layer(name, steps, warmup, sp, spgen, torch, with_roofline):
 
 
 # ---------------------------------------------------------------------------------------------------------
-# the 8-conv stack of BASELINE config 3
+# the 8-conv stack on cfg 3's clouds
 # ---------------------------------------------------------------------------------------------------------
 STACK_CHANNELS = [32, 32, 64, 64, 128, 128, 256, 256, 256]  # input features, then the 8 convs' outputs
 STACK_STRIDES = [1, 1, 1, 2, 1, 2, 1, 1]                     # two stride-2 downsamples
@@ -575,7 +575,8 @@ def main():
             configs.append(e)
             sp.sp_pool_trim()
             torch.cuda.empty_cache()
-        out["configs"] = configs
+        print(json.dumps({"details": configs}), file=sys.stderr, flush=True)
+        out["configs"] = [{k: e[k] for k in ("workload", "ms_per_step", "tflops_step")} for e in configs]
     if cpu is not None:
         out["cpu_baseline"] = cpu
     print(json.dumps(out))

@@ -237,7 +237,7 @@ def coords_config(cfg: int, scale: float = 1.0) -> np.ndarray:
 
 
 def coords_literal(which: str) -> np.ndarray:
-    """The literal readings of two BASELINE configs whose text contradicts its own voxel count:
+    """The literal readings of two workloads whose text contradicts its own voxel count:
     "cfg2_2048pt": the config-0 generator with its 2048 points per cloud at a 256^3 grid, 8 clouds (latency datapoint);
     "cfg4_5cm": the room at 5 cm voxels (about a quarter of the ~1 M voxels the config names)."""
     if which == "cfg2_2048pt":

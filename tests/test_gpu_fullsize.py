@@ -1,4 +1,4 @@
-"""Parity at the full sizes of the BASELINE workloads, in the launch configuration bench.py times.
+"""Parity at the full sizes of the benchmark's workloads, in the launch configuration bench.py times.
 
   - coordinates (every level of the hierarchy): compared in full with the oracle's sort-based merge;
   - kernel maps: compared IN FULL with the oracle's map, as per-offset (in, out)-sorted pair lists, pair

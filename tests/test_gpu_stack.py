@@ -1,4 +1,4 @@
-"""The layers between the convolutions, and the ResNet-style stack of BASELINE config 3, on the GPU.
+"""The layers between the convolutions, and the ResNet-style stack on cfg 3's clouds, on the GPU.
 
 Per-op parity: batch norm (+ReLU), per-cloud average pooling, linear and softmax cross-entropy, forward and
 backward, against oracle/glue.py (float64 numpy) on generator inputs.
