@@ -68,7 +68,7 @@ typedef struct sp_kmap sp_kmap_t;     /* kernel map of one (coords, kernel, stri
  * call that needs this set's row count on the host (sp_coords_size, or any call on a map built from it).
  * n_raw may be 0.  *out receives a new handle (caller destroys).
  * Device memory that the handle holds: 20 bytes per source row, and the table: 128 to 256 bytes per source row up to
- * 65536 rows (256 KB at most up to 8192 of them), 96 (at least 64 and 4 MiB) below 2^26 rows, 32 to 64 beyond.  The build
+ * 65536 rows (256 KB at most up to 8192 of them), 96 to 128 up to 2^20 rows, 96 below 2^26, 32 to 64 beyond.  The build
  * itself takes 4 bytes per row more.  Coarser sets made by sp_kmap_build are sized by the row bound of the set that they
  * are made from. */
 int sp_coords_build(const int32_t* d_raw, int64_t n_raw, int32_t tensor_stride, void* stream, sp_coords_t** out);

@@ -576,11 +576,12 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     const bool may_grid = dir_words > 0;
     c->tab.dir_words = dir_words;
     // Slots, a power of two.  Builds and searches wait for the longest chain of collisions among a wavefront's rows, so
-    // room is time: eight per row for sets that take the hash form; where a grid is reserved (96 bytes a row) at least three,
-    // which take no more (262 k rows in a box too wide for a grid, coordinates + K = 3 map: two a row 232 us, three 169);
+    // room is time: eight per row for sets that take the hash form; where a grid is reserved (96 bytes a row) at least four
+    // up to 2^20 rows (at most 128 bytes), three beyond, which take no more (262 k rows in a box too wide for a grid,
+    // coordinates + K = 3 map: two a row 232 us, three 169; 160 k, 330 k: three 131, 225, four 119, 202, six 119, 202);
     // the largest sets, and what is made from them, room for every row at half load.
     uint32_t cap = 1024;
-    while ((int64_t)cap < (n_src <= kGridRows ? 8 : (may_grid ? 3 : 2)) * n_src) cap <<= 1;
+    while ((int64_t)cap < (n_src <= kGridRows ? 8 : (may_grid ? (n_src <= ((int64_t)1 << 20) ? 4 : 3) : 2)) * n_src) cap <<= 1;
     if (small) cap = std::min<uint32_t>(cap, kSmallSlots);
     c->tab.cap = cap;
     for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
