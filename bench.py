@@ -8,11 +8,12 @@ Headline workload: 8 clouds x 20k surface points on a 128^3 grid, 3x3x3 stride 1
 
 Prints ONE JSON line on stdout.  `value` is the effective TFLOP/s of the headline step: the active multiply-adds of
 fwd + dgrad + wgrad (2 * 3 * pairs * Cin * Cout flops) divided by the time of the WHOLE step, map building
-included.  The same line carries
+included.  The same line carries (`brief`)
+  - `stages`: ms of each;
   - `roofline`: the dominant kernel of the headline step, timed live with events on the launch stream;
   - `cpu_baseline`: the CPU oracle on the headline workload, one thread and all cores (one process per cloud);
-  - `configs`: step time and rate of every other workload (the larger clouds, the stack, the paper's sparsity-sweep batches).
-The details of all of them go to stderr as one more JSON line: per-stage times, the roof that binds each stage (matrix
+  - `configs`: [ms per step, TFLOP/s] of every other workload (the larger clouds, the stack, the paper's sparsity-sweep batches).
+All of it with its details goes to stderr as one more JSON line: per-stage times, the roof that binds each stage (matrix
 cores or HBM) and the achieved fraction of it; for the two map-building stages the algorithmic bytes, achieved GB/s and
 the fraction of the HBM peak.
 `--workload NAME` makes another workload the headline; `--only-headline` skips `configs` (profiling runs).
@@ -495,6 +496,24 @@ def run_stack(steps, warmup, sp, spgen, torch):
     return entry, roofline
 
 
+def brief(out):
+    """The line for stdout: everything that is one number, rounded, and of the rest what a reader of its end needs."""
+    def rounded(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+    b = dict(out)
+    b["stages"] = {k: v["ms"] if isinstance(v, dict) else v for k, v in out["stages"].items()}
+    b["roofline"] = {k: rounded(v) for k, v in out["roofline"].items() if k != "traffic_from"}
+    b["measured_roofs"] = {k: v for k, v in out["measured_roofs"].items() if "peak" not in k and k != "note"}
+    if "configs" in out:
+        b["configs"] = {e["workload"]: [e["ms_per_step"], e["tflops_step"]] for e in out["configs"]}
+    if "cpu_baseline" in out:
+        cpu = out["cpu_baseline"]
+        b["cpu_baseline"] = {k: rounded(cpu[k]) for k in ("value", "unit", "cores", "kind", "seconds") if k in cpu}
+        if "all_cores" in cpu:
+            b["cpu_baseline"]["all_cores"] = {k: rounded(cpu["all_cores"][k]) for k in ("value", "cores")}
+    return b
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -575,11 +594,11 @@ def main():
             configs.append(e)
             sp.sp_pool_trim()
             torch.cuda.empty_cache()
-        print(json.dumps({"details": configs}), file=sys.stderr, flush=True)
-        out["configs"] = [{k: e[k] for k in ("workload", "ms_per_step", "tflops_step")} for e in configs]
+        out["configs"] = configs
     if cpu is not None:
         out["cpu_baseline"] = cpu
-    print(json.dumps(out))
+    print(json.dumps({"details": out}), file=sys.stderr, flush=True)
+    print(json.dumps(brief(out)))
 
 
 if __name__ == "__main__":

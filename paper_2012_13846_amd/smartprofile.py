@@ -10,7 +10,7 @@ A layer = one convolution with its BatchNorm + ReLU; pooling, classifier and los
 The activation of a sparse layer is a sparse tensor: its coordinate matrix (16 bytes a row) travels with the
 feature matrix (Sec. III-B), so both count.
 
-Run on the GPU machine:  python -m paper_2012_13846_amd.smartprofile out.txt [--scale 1.0] [--warmup 50] [--iters 100]
+Run where the GPU is:  python -m paper_2012_13846_amd.smartprofile out.txt [--scale 1.0] [--warmup 50] [--iters 100]
 """
 from __future__ import annotations
 
