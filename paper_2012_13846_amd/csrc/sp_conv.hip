@@ -78,12 +78,18 @@ struct WaveCfg {
     static constexpr int kXStride = kRowBytes + 32;       // staged row + pad (b128 fragment reads at the full LDS rate)
     static constexpr int kXBytes = 16 * kXStride - 32;  // the last row needs no pad
     static constexpr int kXLoads = (16 * kPieces + 63) / 64;  // coalesced load instructions per 16-link block
-    // Up to 4 blocks per offset.  A descriptor of 8 bytes holds the block's first link; one of 4 bytes leaves it to a table
-    // of the offsets' begins, i.e. to a second LDS trip.  The trip costs 64-byte rows 3-6 % (bf16 32 -> 64 on 0.6 M links 28.6
-    // against 27.8 us); the room costs wider ones a wavefront per CU (fp32 32 -> 64: 59 against 68 us).
-    static constexpr bool kWideDesc = kRowBytes == 64;
+    // Up to 4 blocks per offset.  A descriptor says offset, links and which block of the offset it is, in 16 bits.  Where
+    // the block's first link is, a table of the offsets' begins says (a second LDS trip), or, wide descriptors, a word per
+    // block, read side by side with it.  The trip costs 64-byte rows 3-6 % (bf16 32 -> 64 on 0.6 M links 28.6 against 27.8 us);
+    // the room costs wider rows, and every row beyond 27 offsets, a wavefront per CU (fp32 32 -> 64: 59 against 68 us; bf16
+    // 32 -> 32, K = 5 on 0.37 M rows 140 against 172 us).  LDS is handed out in steps of 1280 bytes: wide descriptors of
+    // 8 bytes took bf16 32 -> 32 at K = 3 from nine steps to ten, from 14 wavefronts a CU to 12 (0.22 M rows, one round of
+    // wavefronts or two: 32 against 43 us), 4-byte descriptors fp32 32 -> 32 at K = 5 from 11 to 10 (0.37 M rows 303 against 334 us).
+    static constexpr bool kMayWide = kRowBytes == 64;
+    static bool wide(int kvol) { return kMayWide && kvol <= 27; }
+    static int desc_bytes(int kvol) { return (kvol * (wide(kvol) ? 24 : 12) + 15) / 16 * 16; }
     static constexpr bool kMayRun = kRowBytes == 64 || !kIsF32;  // see xcd_run; the others gain nothing from it
-    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + ((kvol * (kWideDesc ? 8 : 5) + 3) / 4) * 16; }
+    static int per_wave_bytes(int kvol) { return kAccBytes + kXBytes + desc_bytes(kvol); }
     // fragment-major weights: [kvol][co_total/COT][kNCT][kGroups][64 lanes][16 bytes]
     static constexpr size_t kWFragBytesPerOffsetTile = (size_t)kNCT * kGroups * 64 * 16;
 };
@@ -103,7 +109,7 @@ constexpr int kRun = 8;
 constexpr int64_t kRunRows = 1 << 17;
 __device__ __forceinline__ int64_t xcd_run(int64_t wg) { return wg / (8 * kRun) * (8 * kRun) + (wg & 7) * kRun + (wg >> 3) % kRun; }
 
-template <typename T, int CC, int COT>
+template <typename T, int CC, int COT, bool kWideDesc>
 __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     using Cfg = WaveCfg<T, CC, COT>;
     constexpr bool kIsF32 = Cfg::kIsF32;
@@ -140,10 +146,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     unsigned char* base = smem;
     float* acc = reinterpret_cast<float*>(base);
     unsigned char* xbuf = base + Cfg::kAccBytes;
-    constexpr bool kWideDesc = Cfg::kWideDesc;
-    int* s_beg = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);  // per offset: where this wavefront's links begin
-    int* s_blk = s_beg + kvol;
-    int2* s_blk2 = reinterpret_cast<int2*>(s_beg);             // kWideDesc: {descriptor, first link}
+    int* s_beg = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);  // where this wavefront's links begin, per offset; kWideDesc: per block
+    uint16_t* s_blk = reinterpret_cast<uint16_t*>(s_beg + (kWideDesc ? 4 : 1) * kvol);  // the blocks' descriptors
     const int n16 = lane & 15, g = lane >> 4;
 
     for (int i = lane; i < Cfg::kAccBytes / 16; i += 64) reinterpret_cast<f32x4*>(acc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -184,9 +188,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         const int ex = nblk + inc - nb;
         if (!kWideDesc && k < kvol) s_beg[k] = o0;
         for (int i = 0; i < nb; ++i) {
-            const int de = k | ((min(16, cnt - 16 * i) - 1) << 7) | (i << 11);
-            if (kWideDesc) s_blk2[ex + i] = int2{de, o0 + 16 * i};
-            else s_blk[ex + i] = de;
+            s_blk[ex + i] = (uint16_t)(k | ((min(16, cnt - 16 * i) - 1) << 7) | (i << 11));
+            if (kWideDesc) s_beg[ex + i] = o0 + 16 * i;
         }
         nblk += __shfl(inc, 63, 64);
     }
@@ -233,35 +236,39 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     const int last = nblk - 1;
     // (Starting each wavefront at a block of its own, so that the wavefronts of a compute unit do not ask for
     // the same weight lines at the same moment, was measured and is slower: in step, they share the lines in L1.)
-    // bf16 rows of 128 bytes and more: the descriptors run ahead in registers (64 -> 128 on 2.4 M links 193 -> 190 us; fp32,
-    // whose turns are longer, loses 1 % by the registers)
-    int de_0 = 0, de_1 = 0, beg_0 = 0;
-    if (!kWideDesc && !kIsF32 && nblk > 0) {
-        de_0 = s_blk[0];
-        de_1 = s_blk[min(1, last)];
-        beg_0 = s_beg[de_0 & 127];
-    }
-    auto load_entries = [&](Slot& sl, int b) __attribute__((always_inline)) {
-        int e0;
-        if constexpr (kWideDesc) {
-            const int2 d = s_blk2[min(b, last)];
-            sl.de = d.x;
-            e0 = d.y;
-        } else if constexpr (!kIsF32) {  // blocks are asked for in order: b's descriptor was read two calls ago
-            sl.de = de_0;
-            e0 = beg_0 + ((sl.de >> 11) << 4);
-            de_0 = de_1;
-            beg_0 = s_beg[de_1 & 127];
-            de_1 = s_blk[min(b + 2, last)];
-        } else {
-            sl.de = s_blk[min(b, last)];
-            e0 = s_beg[sl.de & 127] + ((sl.de >> 11) << 4);
-        }
-        const int cnt = ((sl.de >> 7) & 15) + 1;
+    auto request = [&](Slot& sl, int de, int e0) __attribute__((always_inline)) {
+        sl.de = de;
+        const int cnt = ((de >> 7) & 15) + 1;
 #pragma unroll
         for (int t = 0; t < kXLoads; ++t)
             sl.esrc[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rSrc, (e0 + min((t * 64 + lane) / kPieces, cnt - 1)) * 4, 0, 0);
         sl.erow = (int)__builtin_amdgcn_raw_buffer_load_b32(rRow, (e0 + min(n16, cnt - 1)) * 4, 0, 0);
+    };
+    auto look_up = [&](Slot& sl, int b) __attribute__((always_inline)) {
+        const int de = s_blk[min(b, last)];
+        request(sl, de, kWideDesc ? s_beg[min(b, last)] : s_beg[de & 127] + ((de >> 11) << 4));
+    };
+    // bf16 rows of 128 bytes and more: in the main loop, which asks for blocks in order, the descriptors run ahead in registers,
+    // b's was read two calls ago (64 -> 128 on 2.4 M links 193 -> 190 us; fp32, whose turns are longer, loses 1 % by the
+    // registers).  The first blocks are looked up directly: their trips overlap.
+    constexpr bool kAhead = !kWideDesc && !kIsF32;
+    int de_0 = 0, de_1 = 0, beg_0 = 0;
+    auto run_ahead = [&](int b) __attribute__((always_inline)) {
+        if constexpr (kAhead) {
+            de_0 = s_blk[min(b, last)];
+            de_1 = s_blk[min(b + 1, last)];
+            beg_0 = s_beg[de_0 & 127];
+        }
+    };
+    auto load_entries = [&](Slot& sl, int b) __attribute__((always_inline)) {
+        if constexpr (kAhead) {
+            request(sl, de_0, beg_0 + ((de_0 >> 11) << 4));
+            de_0 = de_1;
+            beg_0 = s_beg[de_1 & 127];
+            de_1 = s_blk[min(b + 2, last)];
+        } else {
+            look_up(sl, b);
+        }
     };
     auto issue_gather = [&](Slot& sl) __attribute__((always_inline)) {
         sl.dc = sl.de;
@@ -271,7 +278,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
             sl.x[t] = __builtin_amdgcn_raw_buffer_load_b128(rF, sl.esrc[t] * Cfg::kRowBytes + ((t * 64 + lane) % kPieces) * 16, 0, 0);
     };
     auto issue_weights = [&](WSlot& ws, int b, int ct0 = 0) __attribute__((always_inline)) {
-        load_weights((kWideDesc ? s_blk2[min(b, last)].x : s_blk[min(b, last)]) & 127, ws.w, ct0);
+        load_weights(s_blk[min(b, last)] & 127, ws.w, ct0);
     };
     auto stage = [&](const Slot& sl) __attribute__((always_inline)) {  // gathered rows -> LDS, row-major, padded
 #pragma unroll
@@ -290,7 +297,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         Slot xs[kDX] = {};
         WSlot ws[kDW] = {};
 #pragma unroll
-        for (int j = 0; j < kDX; ++j) load_entries(xs[j], j);
+        for (int j = 0; j < kDX; ++j) look_up(xs[j], j);
 #pragma unroll
         for (int j = 0; j < kDW; ++j) {
             if constexpr (kHalfW) issue_weights(ws[j], 0, j * kWT);  // both halves of block 0
@@ -299,7 +306,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
 #pragma unroll
         for (int j = 0; j < kDX; ++j) issue_gather(xs[j]);
 #pragma unroll
-        for (int j = 0; j < kDX; ++j) load_entries(xs[j], kDX + j);
+        for (int j = 0; j < kDX; ++j) look_up(xs[j], kDX + j);
+        run_ahead(2 * kDX);
         Frag xf_c[kGroups];
         stage(xs[0]);
         wave_sync();
@@ -458,10 +466,12 @@ __global__ __launch_bounds__(256) void weight_frag_kernel(const T* __restrict__ 
     wf[idx] = w[(size_t)k * co_total * CC + (size_t)co * s_co + (size_t)cc * s_cc];
 }
 
-template <typename T, int CC, int COT>
+template <typename T, int CC, int COT, bool kWideDesc>
 int launch_wave(GatherArgs a, hipStream_t s) {
     using Cfg = WaveCfg<T, CC, COT>;
-    auto kern = gather_wave_kernel<T, CC, COT>;
+    if constexpr (!kWideDesc && Cfg::kMayWide)
+        if (Cfg::wide(a.kvol)) return launch_wave<T, CC, COT, true>(a, s);
+    auto kern = gather_wave_kernel<T, CC, COT, kWideDesc>;
     a.lds_per_wave = Cfg::per_wave_bytes(a.kvol);
     a.w_bytes = (uint32_t)((size_t)a.kvol * a.co_total * CC * sizeof(T));
     const int lds = a.lds_per_wave;  // one wavefront per workgroup: they are independent, small groups place freely
@@ -571,11 +581,11 @@ int dispatch_co(const GatherArgs& a, hipStream_t s) {
     constexpr int kGroups = CC / (std::is_same<T, float>::value ? 16 : 32);
     const int cot = wave_tile(CC, a.co_total, std::is_same<T, float>::value);
     if constexpr (kGroups * 4 <= 16)
-        if (cot == 64) return launch_wave<T, CC, 64>(a, s);
+        if (cot == 64) return launch_wave<T, CC, 64, false>(a, s);
     if constexpr (kGroups * 2 <= 8)
-        if (cot == 32) return launch_wave<T, CC, 32>(a, s);
+        if (cot == 32) return launch_wave<T, CC, 32, false>(a, s);
     if constexpr (kGroups <= 2)
-        if (cot == 16) return launch_wave<T, CC, 16>(a, s);
+        if (cot == 16) return launch_wave<T, CC, 16, false>(a, s);
     return fail(SP_ERR_UNSUPPORTED, "internal: no wavefront kernel for %d -> %d channels", CC, a.co_total);
 }
 

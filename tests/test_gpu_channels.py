@@ -57,3 +57,26 @@ def test_sub_tiles_dealt_in_runs(sp, n, cin, cout, dt):  # noqa: F811
     tol = 1e-5 if dt == torch.float32 else 1e-2
     assert float((got - want).norm() / want.norm()) <= tol
     assert float((got - want).abs().max() / want.square().mean().sqrt()) <= 10 * tol
+
+
+@pytest.mark.parametrize("K", [2, 3, 4, 5])
+@pytest.mark.parametrize("cin,cout,dt", [(16, 16, torch.float32), (16, 64, torch.float32), (32, 32, torch.float32), (32, 32, torch.bfloat16),
+                                         (32, 64, torch.bfloat16), (64, 32, torch.bfloat16)])
+def test_sub_tiles_with_the_most_blocks(sp, K, cin, cout, dt):  # noqa: F811
+    """A full box of voxels: sub-tiles with four blocks of nearly every offset, the most there is room for, in a launch large
+    enough that none is split; 27 offsets and fewer keep a block's first link, more do not."""
+    n = 80 * 64 * 64
+    g = torch.Generator(device="cuda").manual_seed(K)
+    i = torch.randperm(n, device="cuda", generator=g).to(torch.int32)
+    c = sp.sp_coords_build(torch.stack([i * 0, i >> 12, i >> 6 & 63, i & 63], dim=1).contiguous(), 1)
+    km, _ = sp.sp_kmap_build(c, K, 1, 1)
+    assert sp.sp_conv_kernel_name(km, cin, cout, dt) == "gather_wave_kernel"
+    x = torch.randn((n, cin), device="cuda", generator=g).to(dt)
+    w = torch.randn((K ** 3, cout, cin), device="cuda", generator=g).to(dt)
+    pin, pout = km.pairs_strided()
+    want = torch.zeros((n, cout), device="cuda")
+    for k in range(K ** 3):
+        m = int(km.counts[k])
+        want.index_add_(0, pout[k, :m], x[pin[k, :m].long()].float() @ w[k].float().T)
+    got = sp.sp_conv_fwd(km, x, w).float()
+    assert float((got - want).norm() / want.norm()) <= (1e-5 if dt == torch.float32 else 1e-2)
