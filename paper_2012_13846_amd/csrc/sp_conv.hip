@@ -4,6 +4,7 @@
 // All of them are destination stationary: a destination row (output row for the forward pass, input row for the
 // data gradient) belongs to exactly one workgroup, its fp32 accumulator stays on the chip, links are added in a
 // fixed order without atomics (results are reproducible run to run), and the result is written once, rounded once.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -501,13 +502,14 @@ int launch_wave(GatherArgs a, hipStream_t s) {
     hipLaunchKernelGGL((weight_frag_kernel<T, CC, COT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                        static_cast<const T*>(a.w), d_wf, a.kvol, a.co_total, s_co, s_cc);
     a.w = d_wf;
-    const int64_t nwt = (a.n_rows + 63) / 64;
     // A launch whose sub-tiles fit the GPU's LDS at once runs as long as its longest wavefront: then long
-    // sub-tiles (48 blocks and more, against a typical 27-35; measured best of 32..64) are shared by two
-    // wavefronts.  Larger launches
-    // run in several rounds, where splitting would only add padding.
-    const int64_t resident_tiles = 256 * (160 * 1024 / (int64_t)a.lds_per_wave);
-    a.split_blocks = (nwt * (a.co_total / COT) * 5 / 4 <= resident_tiles) ? 48 : 0x7fffffff;
+    // sub-tiles (48 blocks and more at 27 offsets, against a typical 27-35; measured best of 32..64) are shared by two
+    // wavefronts.  More offsets have more blocks, all of them: sharing every sub-tile pays only if the halves fit at once too
+    // (K = 5, bf16 32 -> 32 on 0.15 M rows: 108-119 us with every sub-tile shared, 63 with none).  Larger launches run in
+    // several rounds, where splitting would only add padding.
+    const int64_t nwt = (a.n_rows + 63) / 64, waves = nwt * (a.co_total / COT);
+    const int64_t resident = 256 * (160 * 1024 / ((a.lds_per_wave + 1279) / 1280 * 1280));
+    a.split_blocks = 2 * waves <= resident ? 48 : (waves * 5 / 4 <= resident ? std::max(48, 48 * a.kvol / 27) : 0x7fffffff);
     a.runs = Cfg::kMayRun && a.split_blocks == 0x7fffffff && a.n_rows >= kRunRows ? 1 : 0;
     // two wavefronts per sub-tile only where sub-tiles may be split (the second one leaves at once otherwise)
     const int64_t wgs = a.runs ? (nwt + 8 * kRun - 1) / (8 * kRun) * (8 * kRun) : (a.split_blocks == 0x7fffffff ? 1 : 2) * nwt;
