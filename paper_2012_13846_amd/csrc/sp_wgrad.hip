@@ -637,9 +637,13 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
 
 // Channel tile of c channels: the widest of 128, 64, 48, 32, 16 that divides them, else the one of 64, 48, 32, 16
 // that pads least (a further tile gathers the other operand's rows again, worth about 8 padded channels).
-int channel_block(int c) {
+// few: little to contract, more workgroups with less to write out each are worth more than fewer gathers: 32 before 48
+// (bf16 96 -> 96 as tiles of 48 / 32: K = 3 on 9 k links 24.6 / 22.9 us, 47 k 27.7 / 23.7, 0.14 M 37.9 / 37.4, 0.22 M 49.0 / 58.1;
+// K = 2, stride 2 on 20 k links 22.5 / 15.4, 49 k 23.4 / 23.7, 77 k 29.5 / 31.9).
+constexpr int64_t kFewLinks = 1 << 16;
+int channel_block(int c, bool few) {
     for (int b : {128, 64, 48, 32, 16})
-        if (c % b == 0) return b;
+        if (c % b == 0 && !(few && b == 48 && c % 32 == 0)) return b;
     int best = 0, cost = 1 << 30;
     for (int b : {64, 48, 32, 16}) {
         const int t = (c + b - 1) / b, k = t * b + 8 * (t - 1);
@@ -677,7 +681,8 @@ int wgrad_staged(const sp_kmap* m, const void* x, const void* dy, float* dw, int
     x = padded(x, m->n_in, cin, cin_row, px);
     dy = padded(dy, m->n_out, cout, cout_row, pdy);
     if (!x || !dy) return SP_ERR_ALLOC;
-    int cob = channel_block(cout), cib = channel_block(cin);
+    const bool few = sizeof(T) == 2 && m->total < kFewLinks;
+    int cob = channel_block(cout, few), cib = channel_block(cin, few);
     if (cob == 128 && cib < 64) cob = 64;  // 128-wide tiles only in the combinations instantiated below
     if (cib == 128 && cob < 64) cib = 64;
     const bool pad = cin % cib != 0 || cout % cob != 0;

@@ -59,6 +59,21 @@ def test_sub_tiles_dealt_in_runs(sp, n, cin, cout, dt):  # noqa: F811
     assert float((got - want).abs().max() / want.square().mean().sqrt()) <= 10 * tol
 
 
+@pytest.mark.parametrize("n", [1, 65535, 65536])
+@pytest.mark.parametrize("cin,cout,dt", [(96, 96, torch.bfloat16), (96, 48, torch.bfloat16), (48, 288, torch.bfloat16), (96, 96, torch.float32)])
+def test_weight_gradient_tiles_of_few_links(sp, n, cin, cout, dt):  # noqa: F811
+    """96 channels are tiles of 32 below 2^16 links (bf16), of 48 from there on.  Sums of up to 65536 exact products in fp32
+    against fp64: the parity bound."""
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+    c = sp.sp_coords_build(torch.stack([i * 0, i >> 8, i & 255, i * 0], dim=1).contiguous(), 1)
+    km, _ = sp.sp_kmap_build(c, 1, 1, 1)
+    g = torch.Generator(device="cuda").manual_seed(n + cin)
+    x, dy = (torch.randn((n, ch), device="cuda", generator=g).to(dt) for ch in (cin, cout))
+    got = sp.sp_conv_bwd_weight(km, x, dy)[0].double()
+    want = dy.double().T @ x.double()
+    assert float((got - want).norm() / want.norm()) <= 1e-5
+
+
 @pytest.mark.parametrize("K", [2, 3, 4, 5])
 @pytest.mark.parametrize("cin,cout,dt", [(16, 16, torch.float32), (16, 64, torch.float32), (32, 32, torch.float32), (32, 32, torch.bfloat16),
                                          (32, 64, torch.bfloat16), (64, 32, torch.bfloat16)])
