@@ -250,8 +250,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         request(sl, de, kWideDesc ? s_beg[min(b, last)] : s_beg[de & 127] + ((de >> 11) << 4));
     };
     // bf16 rows of 128 bytes and more: in the main loop, which asks for blocks in order, the descriptors run ahead in registers,
-    // b's was read two calls ago (64 -> 128 on 2.4 M links 193 -> 190 us; fp32, whose turns are longer, loses 1 % by the
-    // registers).  The first blocks are looked up directly: their trips overlap.
+    // b's was read two calls ago (64 -> 128 on 2.4 M links 193 -> 188 us, 64 -> 32 on 0.22 M rows 53 -> 50; fp32, whose turns are
+    // longer, loses 1 % by the registers).  The first blocks are looked up directly: their trips overlap.
     constexpr bool kAhead = !kWideDesc && !kIsF32;
     int de_0 = 0, de_1 = 0, beg_0 = 0;
     auto run_ahead = [&](int b) __attribute__((always_inline)) {
