@@ -681,7 +681,7 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
 
 namespace {
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,
-// 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain.  The wavefront-private kernel keeps the whole
+// 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain, 4 few channels on one side (sp_conv_narrow.hip).  The wavefront-private kernel keeps the whole
 // weight matrix of a narrow layer in registers; everything else, wide or not a multiple of its tiles, takes the tile kernel.
 // Forward in us, wavefront-private / tile kernel, on 1.5 k rows with 9 k links | 96 k, 0.61 M | 160 k, 0.66 M | 374 k, 2.4 M |
 // 613 k, 5.0 M:
@@ -694,6 +694,7 @@ namespace {
 // about 0.1 and 0.2 M rows, where the tile kernel's 128 rows fill the blocks of few links better.
 int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
+    if (narrow_pays(cc, co, kvol)) return 4;
     // Row-stationary kernel: it multiplies all kvol offsets of every row, the link-list kernels only the links
     // that exist but pay per link for bookkeeping, weight re-reads and the accumulator update.  Measured, it is
     // the faster one from about 1 link in 20 row-offsets upwards on 128- and 256-channel inputs, from 1 in 4
@@ -722,6 +723,7 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
     const size_t elt = dt == SP_F32 ? 4 : 2;
     int kind = select_gather(side, kvol, total_links, cc, co, dt);
     if (scratch && kind == 2 && !tile_fits_scratch(side, cc, co, kvol, dt, scratch_bytes)) kind = 3;
+    if (kind == 4) return conv_narrow(side, kvol, d_f, d_w, w_transposed, d_g, cc, co, dt, s);
     if (kind == 1 || kind == 2) SP_TRY(need_lists(side, kvol, s));
     if (kind == 0) {
         SP_TRY(need_classes(side, s));
@@ -841,7 +843,7 @@ int sp_conv_bwd_data(const sp_kmap_t* m, const void* d_dy, const void* d_w, void
 
 const char* sp_conv_kernel_name(const sp_kmap_t* m, int32_t cin, int32_t cout, sp_dtype dt, int32_t direction) {
     static const char* const names[] = {"gather_dense_kernel", "gather_wave_kernel", "gather_tile_kernel",
-                                        "gather_plain_kernel"};
+                                        "gather_plain_kernel", "gather_narrow_kernel"};
     if (!m || cin < 1 || cout < 1 || (dt != SP_F32 && dt != SP_BF16) || kmap_resolve(m) != SP_OK) return "";
     return direction == 0 ? names[select_gather(m->out_side, m->kvol, m->total, cin, cout, dt)]
                           : names[select_gather(m->in_side, m->kvol, m->total, cout, cin, dt)];

@@ -219,6 +219,10 @@ bool dense_shape_ok(int cc, int co, sp_dtype dt);
 double dense_min_fill(int cc);
 int conv_gather_dense(const MapSide& side, int kvol, const void* d_f, const void* d_w, void* d_g, int cc, int co,
                       hipStream_t s);
+// few channels on one side (sp_conv_narrow.hip); needs neither link lists nor scratch memory
+bool narrow_pays(int cc, int co, int kvol);
+int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed, void* d_g, int cc, int co, sp_dtype dt,
+                hipStream_t s);
 // link lists, any channel counts (sp_conv_tile.h): kc-wide slices of the contraction, ncs * 16 channels and tr rows a workgroup
 struct TileArgs;
 int conv_tile_f32(const TileArgs& a, int kc, int ncs, int tr, hipStream_t s);
