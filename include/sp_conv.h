@@ -167,13 +167,15 @@ int sp_conv_bwd_weight(const sp_kmap_t* m, const void* d_x, const void* d_dy, fl
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): sp_conv_fwd with the same arguments, except that the call allocates nothing (no
  * hipMalloc / hipFree, no pool request).  Where sp_conv_fwd takes scratch from the pool (the fragment-major copy of
- * the weights that the link-list kernels read), this call uses a 4 MiB array in static device memory, which every
- * GPU the library runs on holds until the process ends.  While the copy fits, kernels and results are sp_conv_fwd's.
- * A copy that does not fit (the tile kernel's is padded to whole channel tiles):
+ * the weights that the link-list kernels read), this call uses a 6 MiB array in static device memory, which every
+ * GPU the library runs on holds until the process ends.  While the copy fits (4 MiB of weights as they are, or 6 MiB of
+ * the three bf16 pieces of fp32 weights, padded to whole channel tiles), kernels and results are sp_conv_fwd's.
+ * Pieces that do not fit: the kernels that take weights as they are, fp32 sums in another order than sp_conv_fwd's.
+ * A copy that does not fit either (the tile kernel's is padded to whole channel tiles):
  *   - narrow layers (gather_wave_kernel: cin 16 / 32 / 64 fp32, 32 / 64 / 128 bf16, cout to match): SP_ERR_UNSUPPORTED;
  *     kvol * cin * cout * element size <= 4 MiB is never refused;
- *   - other layers whose cin is whole slices of the tile kernel: the weights are read where they are stored; the same
- *     results, slower;
+ *   - other layers whose cin is whole slices of the tile kernel: the weights are read where they are stored; the
+ *     results of the tile kernel, slower;
  *   - the rest run on the plain kernel: correct, slow, fp32 sums in another order than sp_conv_fwd's.
  * All calls on one GPU share that array: calls that overlap in time on one GPU (different streams) race; calls on one
  * stream are ordered and safe.  The array's contents are rewritten by every call, nothing in it needs to start at zero.

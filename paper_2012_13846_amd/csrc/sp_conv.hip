@@ -612,6 +612,10 @@ bool wave_shape_ok(int cc, int co, sp_dtype dt) {
 }
 
 constexpr uint64_t kLim32 = 0xffffff00ull;
+// The allocation-free entry point's scratch: copies of weights as they are, and pieces of fp32 weights, which take half as
+// much again (what it refuses goes by the first).
+constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
+constexpr size_t kSplitScratchBytes = kStaticScratchBytes / 2 * 3;
 bool tile_big(const MapSide& side, int kvol, int cc, sp_dtype dt) {
     return (uint64_t)side.n_src * cc * (dt == SP_F32 ? 4 : 2) >= kLim32 || (uint64_t)side.pitch * kvol * 4 >= kLim32;
 }
@@ -680,8 +684,35 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
 }  // namespace
 
 namespace {
+// fp32: the split kernel against the one that has the layer otherwise (wave: the wavefront-private one).  Forward in us, before /
+// split, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 160 k, 0.66 M | 213 k, 2.4 M | 613 k, 5.0 M:
+//   wavefront-private  64 -> 64    56 / 26 | 66 / 38  | 124 / 85  | 180 / 115 | 345 / 250  | 681 / 530
+//                      32 -> 64    35 / 21 | 37 / 29  | 58 / 55   | 93 / 70   | 165 / 133  | 328 / 264
+//                      64 -> 128   56 / 31 | 96 / 47  | 200 / 143 | 280 / 195 | 602 / 451  | 1180 / 920
+//                      64 -> 32    36 / 28 | 39 / 39  | 64 / 73   | 100 / 97  | 194 / 227  | 373 / 418
+//                      32 -> 32    25 / 22 | 26 / 30  | 40 / 52   | 62 / 65   | 108 / 114  | 202 / 210
+//   tile               128 -> 128  66 / 52 | 130 / 78 | 362 / 264 | 446 / 343 | 1124 / 763 | 2484 / 1617
+//                      160 -> 64   67 / 74 | 94 / 106 | 265 / 211 | 358 / 278 | 839 / 596  | 1755 / 1220
+//                      96 -> 96    38 / 55 | 68 / 78  | 240 / 212 | 308 / 303 | 783 / 580  | 1743 / 1216
+//                      24 -> 40    19 / 23 | 23 / 27  | 55 / 49   | 73 / 64   | 158 / 113  | 298 / 225
+//                      48 -> 48    24 / 28 | 30 / 36  | 76 / 82   | 100 / 111 | 224 / 199  | 465 / 407
+// Channel tiles of 32 leave its wavefronts too little to do per row: small launches only.  What the tile kernel pads a third less
+// (48 channels, which are 64 here) only where many links share a read of the weights.
+bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bool wave) {
+    if (cc % 4 != 0 || cc <= 16 || co <= 16 || kvol > 125) return false;
+    const SplitShape t = split_shape(cc, co);
+    if (split_copy_bytes(t, kvol) >= kLim32) return false;
+    if (wave) return t.cot > 32 || side.n_rows < 16384;
+    if (side.n_rows < 1024) return false;
+    if (side.n_rows < 65536) return t.cot == 128;
+    const TileShape o = tile_shape(cc, co, true, false);
+    const bool dense = links * 128 >= (int64_t)32 * kvol * side.n_rows;
+    return dense || 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny <= 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
+}
+
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,
-// 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain, 4 few channels on one side (sp_conv_narrow.hip).  The wavefront-private kernel keeps the whole
+// 2 link lists with producer wavefronts (sp_conv_tile.h), 3 plain, 4 few channels on one side (sp_conv_narrow.hip),
+// 5 fp32 link lists on the bf16 matrix cores (sp_conv_split.hip).  The wavefront-private kernel keeps the whole
 // weight matrix of a narrow layer in registers; everything else, wide or not a multiple of its tiles, takes the tile kernel.
 // Forward in us, wavefront-private / tile kernel, on 1.5 k rows with 9 k links | 96 k, 0.61 M | 160 k, 0.66 M | 374 k, 2.4 M |
 // 613 k, 5.0 M:
@@ -692,7 +723,7 @@ namespace {
 //   fp32 64 -> 64   54 / 27 | 114 / 100 | 166 / 134 | 305 / 341 | 604 / 664
 // So one rule for both types.  It gives away the smallest launches, which one tile's chain bounds, and fp32 64 -> 64 between
 // about 0.1 and 0.2 M rows, where the tile kernel's 128 rows fill the blocks of few links better.
-int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt) {
+int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt, bool may_split = true) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
     if (narrow_pays(cc, co, kvol)) return 4;
     // Row-stationary kernel: it multiplies all kvol offsets of every row, the link-list kernels only the links
@@ -708,7 +739,9 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
     // the link-list kernels address their buffers with 32-bit offsets; the tile kernel takes larger features and lists
     // too if a row is whole 16-byte pieces
     const bool big = tile_big(side, kvol, cc, dt);
-    if (!big && wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32)) return 1;
+    const bool wave = !big && wave_shape_ok(cc, co, dt) && wave_tile(cc, co, dt == SP_F32);
+    if (may_split && dt == SP_F32 && !big && split_pays(side, kvol, total_links, cc, co, wave)) return 5;
+    if (wave) return 1;
     if ((big && cc * elt % 16) || tile_copy_bytes(tile_shape(cc, co, dt == SP_F32, big), kvol, (int)elt) >= kLim32) return 3;
     return 2;
 }
@@ -722,6 +755,23 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
     if (scratch && w_transposed) return fail(SP_ERR_UNSUPPORTED, "no allocation-free path for transposed weights");
     const size_t elt = dt == SP_F32 ? 4 : 2;
     int kind = select_gather(side, kvol, total_links, cc, co, dt);
+    if (kind == 5) {
+        const size_t bytes = split_copy_bytes(split_shape(cc, co), kvol);
+        Buf ws;
+        void* d_ws = scratch;
+        if (!scratch) {
+            ws = dev_alloc(bytes, s);
+            d_ws = ws ? ws->p : nullptr;
+        } else if (bytes > kSplitScratchBytes) {
+            d_ws = nullptr;
+        }
+        if (d_ws) {
+            SP_TRY(need_lists(side, kvol, s));
+            return conv_gather_split(side, kvol, total_links, static_cast<const float*>(d_f), static_cast<const float*>(d_w), w_transposed,
+                                     static_cast<float*>(d_g), cc, co, d_ws, s);
+        }
+        kind = select_gather(side, kvol, total_links, cc, co, dt, false);  // no room for the weights' pieces
+    }
     if (scratch && kind == 2 && !tile_fits_scratch(side, cc, co, kvol, dt, scratch_bytes)) kind = 3;
     if (kind == 4) return conv_narrow(side, kvol, d_f, d_w, w_transposed, d_g, cc, co, dt, s);
     if (kind == 1 || kind == 2) SP_TRY(need_lists(side, kvol, s));
@@ -786,8 +836,7 @@ using namespace sp;
 // pool.  One copy of the array exists on every GPU the library is loaded on, at its own address; host code
 // must not use the array's name as a pointer, only the address hipGetSymbolAddress reports for the current
 // device.
-constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kSplitScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -843,7 +892,7 @@ int sp_conv_bwd_data(const sp_kmap_t* m, const void* d_dy, const void* d_w, void
 
 const char* sp_conv_kernel_name(const sp_kmap_t* m, int32_t cin, int32_t cout, sp_dtype dt, int32_t direction) {
     static const char* const names[] = {"gather_dense_kernel", "gather_wave_kernel", "gather_tile_kernel",
-                                        "gather_plain_kernel", "gather_narrow_kernel"};
+                                        "gather_plain_kernel", "gather_narrow_kernel", "gather_split_kernel"};
     if (!m || cin < 1 || cout < 1 || (dt != SP_F32 && dt != SP_BF16) || kmap_resolve(m) != SP_OK) return "";
     return direction == 0 ? names[select_gather(m->out_side, m->kvol, m->total, cin, cout, dt)]
                           : names[select_gather(m->in_side, m->kvol, m->total, cout, cin, dt)];

@@ -1,0 +1,86 @@
+"""fp32 layers on the bf16 matrix cores (csrc/sp_conv_split.hip): row tiles of 64 and 128, steps of 32 and 48 links, slices and
+channel tiles that reach past the layer, values that bf16 cannot hold.  Against fp64: the parity bound, and no further off than
+fp32 matrix cores are (measured 1.1e-7 to 2e-7 of the rms for up to 125 * 64 products; 3e-7 allowed)."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import conv_case, full_cubes, random_coords, sp  # noqa: F401  (sp: the binding fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64), (32, 96), (64, 160), (32, 320)])
+def test_small_layers(sp, cin, cout):  # noqa: F811
+    conv_case(sp, random_coords(3 + cin, 1500, 12, batches=2, lo=-5), 1, 3, 1, 1, cin, cout, False, seed=7 * cin + cout)
+
+
+@pytest.mark.parametrize("K,stride,transposed", [(1, 1, False), (2, 2, False), (2, 2, True), (3, 2, False), (3, 2, True), (5, 1, False), (4, 1, False)])
+def test_other_maps(sp, K, stride, transposed):  # noqa: F811
+    conv_case(sp, full_cubes(9, 2), 1, K, stride, 1, 32, 64, False, seed=K, transposed=transposed)
+
+
+def cloud(sp, n, bits, seed):  # noqa: F811
+    """n voxels of 4 clouds of 2^bits cells per axis."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    i = torch.randperm(4 << 3 * bits, device="cuda", generator=g)[:n].to(torch.int32)
+    m = (1 << bits) - 1
+    c = sp.sp_coords_build(torch.stack([i >> 3 * bits, i >> 2 * bits & m, i >> bits & m, i & m], dim=1).contiguous(), 1)
+    return c, sp.sp_kmap_build(c, 3, 1, 1)[0], g
+
+
+def fwd64(km, x, w):
+    pin, pout = km.pairs_strided()
+    y = torch.zeros((km.n_out, w.shape[1]), device="cuda", dtype=torch.float64)
+    for k in range(w.shape[0]):
+        m = int(km.counts[k])
+        y.index_add_(0, pout[k, :m].long(), x[pin[k, :m].long()].double() @ w[k].double().T)
+    return y
+
+
+@pytest.mark.parametrize("n,bits,cin,cout", [(1, 2, 64, 64), (63, 3, 64, 64), (64, 2, 32, 64), (65, 2, 64, 128), (129, 3, 32, 64),   # 64-row tiles
+                                             (16257, 5, 64, 64), (16384, 6, 32, 64), (16513, 5, 64, 128),                          # .. 128-row tiles
+                                             (1100, 4, 128, 128), (20000, 5, 100, 128),                                            # slices past the last channel
+                                             (65536, 5, 96, 96), (65537, 6, 24, 40), (70000, 5, 48, 48), (70001, 5, 36, 100), (66000, 6, 128, 32)])
+def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
+    c, km, g = cloud(sp, n, bits, n + cin)
+    assert sp.sp_conv_kernel_name(km, cin, cout, torch.float32) == "gather_split_kernel"
+    x, w = torch.randn((n, cin), device="cuda", generator=g), torch.randn((27, cout, cin), device="cuda", generator=g)
+    for got, want in ((sp.sp_conv_fwd(km, x, w), fwd64(km, x, w)),
+                      (sp.sp_conv_bwd_data(km, x, w.transpose(1, 2).contiguous()), fwd64(km, x, w.flip(0)))):   # the input side: offsets reversed
+        err, rms = got.double() - want, want.square().mean().sqrt()
+        assert float(err.square().mean().sqrt() / rms) <= 3e-7
+        assert float(err.abs().max() / rms) <= 1e-5
+
+
+@pytest.mark.parametrize("cin,cout", [(64, 64), (32, 64), (128, 128)])
+def test_values_beyond_bf16(sp, cin, cout):  # noqa: F811
+    """Infinities, NaN and values that round to a bf16 infinity give what fp32 multiply-adds give, and only where they reach;
+    subnormal pieces keep their places."""
+    c, km, g = cloud(sp, 3000, 4, 5)
+    x, w = torch.randn((km.n_in, cin), device="cuda", generator=g), torch.randn((27, cout, cin), device="cuda", generator=g)
+    x[5, 3], x[100, 7], x[200, 1], x[300, 2], w[3, 5, 6] = float("inf"), float("nan"), 3.4e38, -float("inf"), 1e38
+    want = fwd64(km, x, w)
+    ok = want.abs() < 3.4e38
+    got = sp.sp_conv_fwd(km, x, w)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), ~ok & ~torch.isnan(want))
+    assert torch.allclose(got[ok].double(), want[ok], rtol=1e-4, atol=1e-3)
+    x = torch.randn((km.n_in, cin), device="cuda", generator=g) * 1e-33
+    w = torch.randn((27, cout, cin), device="cuda", generator=g)
+    want, got = fwd64(km, x, w), sp.sp_conv_fwd(km, x, w).double()
+    assert float((got - want).norm() / want.norm()) <= 3e-7
+
+
+def test_without_allocations(sp):  # noqa: F811
+    """Weights' pieces that fit the static scratch: the bits of sp_conv_fwd; pieces that do not, though the weights would: within
+    the parity bound."""
+    c, km, g = cloud(sp, 20000, 5, 9)
+    for cin, cout, same in ((64, 128, True), (128, 256, True), (64, 640, False)):
+        x, w = torch.randn((km.n_in, cin), device="cuda", generator=g), torch.randn((27, cout, cin), device="cuda", generator=g)
+        y = torch.full((km.n_out, cout), float("nan"), device="cuda")
+        if not same:
+            with pytest.raises(sp.SpError):       # a narrow layer whose copy does not fit either is refused, as ever
+                sp.sp_conv_fwd_noalloc(km, x, w, y)
+            continue
+        sp.sp_conv_fwd_noalloc(km, x, w, y)
+        assert torch.equal(y, sp.sp_conv_fwd(km, x, w))
