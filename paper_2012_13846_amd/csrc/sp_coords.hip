@@ -7,7 +7,10 @@
 // (every workgroup derives the grid's box, or that a hash table is needed, and clears that table), mark the occupied
 // blocks (or insert into the hash table), number the blocks and clear their cells, put the smallest row of each cell
 // into it, number, inverse.
-// number: in a single pass every block of rows counts its first occurrences, gets the count of all earlier blocks by
+// A set of half the resolution (floor step = twice the parent's lattice step) whose parent is a grid needs no atomics at all: a
+// block of the parent's grid holds two coarse cells whole, so one thread sees all rows of a cell (mark_coarse_kernel) and
+// knows the first of them; number and inverse read what it left.
+// number: from 65537 to 2^21 rows in two passes over tiles of rows (firsts_kernel, rank_kernel), otherwise in one: every block of rows counts its first occurrences, gets the count of all earlier blocks by
 // decoupled look-back, ranks its rows with ballots and writes coordinates + row numbers; the last block writes the
 // row count N to device memory for later kernels and to a mail slot for the host.  inverse: the row number of every
 // source row.  The host learns N when it first asks (coords_resolve).
@@ -22,7 +25,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kRowsPerThread = 4;
-constexpr int kNumberThreads = 1024;           // most threads of a numbering block
+constexpr int kNumberThreads = 1024;           // most threads of a numbering block; threads of the one that builds a small set
 constexpr int64_t kSmallRows = 8192;           // up to here one workgroup (8 rows a thread, keys and slots in LDS)
 constexpr int kSmallSlots = 16384;             // most slots of its table
 // Up to here a hash table: four launches instead of seven.  Coordinates / + K = 3 map / + 2 x 2 x 2 stride 2 map in us, hash
@@ -295,13 +298,16 @@ __global__ __launch_bounds__(kBoxBlocks) void prepare_kernel(Build t, int64_t n_
     }
     __syncthreads();
     int64_t ext[4], words = 1;
+    int low[4];
     bool ok = n > 0 && s_box[8] == 0 && s_box[9] == 0;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-        const int64_t cells = ((int64_t)s_box[4 + a] - s_box[a]) / (a == 0 ? 1 : t.ts) + 1;
-        ext[a] = a == 0 ? cells : (a == 3 ? (cells + 15) / 16 : (cells + 7) / 8);
-        ok = ok && cells >= 1 && cells <= 65536;
         ok = ok && s_box[a] >= (a == 0 ? 0 : -32768);
+        // the lower half of a cell of twice the size: cells of a coarser set are whole in the grid's blocks
+        low[a] = a > 0 && s_box[a] - floor_to_multiple(s_box[a], 2 * t.ts) >= t.ts ? s_box[a] - t.ts : s_box[a];
+        const int64_t cells = ((int64_t)s_box[4 + a] - low[a]) / (a == 0 ? 1 : t.ts) + 1;
+        ext[a] = a == 0 ? cells : (a == 3 ? (cells + 15) / 16 : (cells + 7) / 8);
+        ok = ok && cells >= 1 && cells <= 65537;
     }
     if (ok) words = ext[0] * ext[1] * ext[2] * ext[3] * 64;
     ok = ok && words <= t.dir_words;
@@ -312,7 +318,7 @@ __global__ __launch_bounds__(kBoxBlocks) void prepare_kernel(Build t, int64_t n_
         t.meta[kMetaGrid] = ok ? 1 : 0;
         t.meta[kMetaBlocks] = 0;
         for (int a = 0; a < 4; ++a) {
-            t.meta[kMetaLow + a] = s_box[a];
+            t.meta[kMetaLow + a] = low[a];
             t.meta[kMetaExt + a] = ok ? (int)ext[a] : 0;
         }
     }
@@ -367,6 +373,79 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const int4* __restrict__
     const uint32_t blk = grid_block(g, c.x - g.b0, qx, qy, qz >> 2);
     t.dir[blk] = 0;
     at[i] = (int32_t)(blk * 16u + (uint32_t)(grid_run(qx, qy) * 4 + (qz & 3)));
+}
+
+// What a set of half the resolution takes from its parent's grid.
+struct Halved {
+    const int32_t* meta;   // the parent's; null: not such a set
+    const int32_t* dir;
+    const int32_t* cells;
+    int ts;
+    int32_t* rank_of;      // [2 * blocks of the parent]: row number of a pair's coarse cell
+    int32_t* pair_of;      // [rows]: the pair a row came from
+};
+
+// The parent's grid, block by block: a block of 2 x 2 x 4 cells is two coarse cells, "pair" 2 * block + half.  at[row of the
+// parent] = its pair (its complement for a row that is not the first of its cell), and the coarse set's own block is occupied.
+// One coalesced pass over the parent's dir and a line per occupied block, where marking, placing and numbering the rows one by
+// one spent two scattered trips and an atomic each (0.5 M rows, 4 spheres: mark, place and number 43 us; this, firsts and rank 31).
+// A coarse set that is a hash table: insert_row, as mark_kernel.
+__global__ __launch_bounds__(kThreads) void mark_coarse_kernel(const int4* __restrict__ src, int64_t n_host, const int32_t* __restrict__ d_n,
+                                                               int32_t floor_step, Build t, Halved hv, int32_t* __restrict__ at, int always) {
+    const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x, stride = (int64_t)gridDim.x * kThreads;
+    if (!is_grid(t)) {
+        const int64_t n = row_count(n_host, d_n);
+        for (int64_t i = first; i < n; i += stride) insert_row(t, load_row(src, i, floor_step), i, always, at);
+        return;
+    }
+    const Grid pg = load_grid(hv.meta), g = load_grid(t.meta);  // a coarse set is a grid only if its parent is one
+    // four blocks in a row along z; each XCD takes a stretch of them, i.e. a few clouds, whose rows' at words are its own
+    const uint32_t quads = (uint32_t)pg.nb * pg.gx * pg.gy * pg.gz * 16u, per = (quads / 8 + 63) / 64 * 64 + 64;
+    const uint32_t lo = (blockIdx.x & 7) * per, hi = min(lo + per, quads);
+    for (uint32_t i = lo + (blockIdx.x >> 3) * kThreads + threadIdx.x; i < hi; i += gridDim.x / 8 * kThreads) {
+        const int4 d4 = reinterpret_cast<const int4*>(hv.dir)[i];
+        if ((d4.x & d4.y & d4.z & d4.w) < 0) continue;
+        uint32_t group = i >> 4;
+        const int bz0 = (int)(group % (uint32_t)pg.gz) * 4;
+        group /= (uint32_t)pg.gz;
+        const int by = (int)(group % (uint32_t)pg.gy) * 4 + (int)(i & 3u);
+        group /= (uint32_t)pg.gy;
+        const int bx = (int)(group % (uint32_t)pg.gx) * 4 + (int)(i >> 2 & 3u), qb = (int)(group / (uint32_t)pg.gx);
+        const int qx = (floor_to_multiple(pg.x0 + 2 * bx * hv.ts, t.ts) - g.x0) / t.ts;
+        const int qy = (floor_to_multiple(pg.y0 + 2 * by * hv.ts, t.ts) - g.y0) / t.ts;
+        const int qz0 = (floor_to_multiple(pg.z0 + 4 * bz0 * hv.ts, t.ts) - g.z0) / t.ts;
+        const int nums[4] = {d4.x, d4.y, d4.z, d4.w};
+        int4 c[4][4];  // the cells of all four, requested together
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const int4* runs = reinterpret_cast<const int4*>(hv.cells) + (int64_t)nums[z] * 4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                c[z][r] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
+                if (nums[z] >= 0) c[z][r] = runs[r];
+            }
+        }
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                int m[8];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    m[2 * r] = h ? c[z][r].z : c[z][r].x;
+                    m[2 * r + 1] = h ? c[z][r].w : c[z][r].y;
+                }
+                int lowest = m[0];
+#pragma unroll
+                for (int j = 1; j < 8; ++j) lowest = min(lowest, m[j]);
+                if (lowest == kNoRow) continue;
+                const int pair = 2 * nums[z] + h;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (m[j] != kNoRow) at[m[j]] = m[j] == lowest ? pair : ~pair;
+                t.dir[grid_block(g, pg.b0 + qb - g.b0, qx, qy, (qz0 + 2 * z + h) >> 2)] = 0;
+            }
+    }
 }
 
 // Grid: occupied blocks are numbered, their cells cleared.  16 words a thread.  The numbers need no order (nothing
@@ -440,6 +519,129 @@ __global__ __launch_bounds__(kThreads) void place_kernel(Build t, int64_t n_host
     at[i] = maybe ? p : ~p;
 }
 
+// kGridRows < rows <= kTiledRows: which rows are the first of their cell (or key), a bit per row and a sum per tile of kTile
+// rows.  Two launches, this and rank_kernel, since they may deal the rows to the XCDs in stretches, so that their scattered
+// trips meet lines of one or two clouds' tables in that XCD's L2, and nobody looks back; number_kernel has to take its blocks
+// in order.  us, number_kernel / these two: 0.16 M rows 13.0 / 12.3, 0.5 M 23.1 / 17.5, 1 M 24.6 / 20.3; a single cloud of
+// 4.6 M 52 / 73 (its table is in no L2 by the second launch), so the largest sets stay with one launch.
+constexpr int kTile = 1024;
+constexpr int kTileWords = kTile / 64;
+constexpr int64_t kTiledRows = 2 << 20;  // = 2048 tiles: each adds up the sums of those before it
+__global__ __launch_bounds__(kThreads) void firsts_kernel(Build t, int64_t n_host, const int32_t* __restrict__ d_n, const int32_t* __restrict__ at,
+                                                          int halved, unsigned long long* __restrict__ mask, int32_t* __restrict__ sums) {
+    __shared__ int s_sum[kThreads / 64];
+    const int64_t n = row_count(n_host, d_n);
+    const int64_t tile = xcd_tile(blockIdx.x, (n + kTile - 1) / kTile);
+    if (tile < 0) return;
+    const bool grid = is_grid(t);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int kPer = kTile / kThreads;
+    const int64_t base = tile * kTile + threadIdx.x;
+    int32_t s[kPer], first[kPer];
+    int sum = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t i = base + j * kThreads;
+        s[j] = i < n ? at[i] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        first[j] = -1;
+        if (s[j] >= 0) first[j] = !grid ? t.slots[s[j]].first : halved ? (int32_t)(base + j * kThreads) : t.cells[s[j]];
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t i = base + j * kThreads;
+        const unsigned long long m = __ballot(s[j] >= 0 && first[j] == (int32_t)i);
+        if (lane == 0 && i < n) mask[i >> 6] = m;
+        sum += __popcll(m);
+    }
+    if (lane == 0) s_sum[w] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kThreads / 64; ++i) sum += s_sum[i];
+        sums[tile] = sum;
+    }
+}
+
+// ... and their numbers: first rows of earlier tiles, of earlier 64-row stretches, of earlier lanes.  Writes the (floored)
+// coordinates at that rank and the rank into the table; the last tile delivers the total.  (Grid: the rank replaces the row
+// in the cell.)
+__global__ __launch_bounds__(kThreads) void rank_kernel(const int4* __restrict__ src, int64_t n_host, const int32_t* __restrict__ d_n,
+                                                        int32_t floor_step, Build t, const int32_t* __restrict__ at, Halved hv,
+                                                        const unsigned long long* __restrict__ mask, const int32_t* __restrict__ sums,
+                                                        int4* __restrict__ coords, uint32_t* __restrict__ mail, uint32_t mail_seq) {
+    __shared__ int s_red[kThreads / 64];
+    const int64_t n = row_count(n_host, d_n), tiles = (n + kTile - 1) / kTile;
+    const int64_t tile = xcd_tile(blockIdx.x, tiles);
+    if (tile < 0 && !(blockIdx.x == 0 && n == 0)) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int run = 0;
+    for (int64_t i0 = tid; i0 < tile; i0 += 4 * kThreads) {  // four loads at a time
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i0 + i * kThreads < tile ? sums[i0 + i * kThreads] : 0;
+        run += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) run += __shfl_xor(run, d, 64);
+    if (lane == 0) s_red[w] = run;
+    __syncthreads();
+    run = 0;
+    for (int i = 0; i < kThreads / 64; ++i) run += s_red[i];
+    const bool grid = is_grid(t), halved = grid && hv.meta;
+    const Grid g = load_grid(t.meta);
+    if (tile >= 0) {
+        constexpr int kPer = kTile / kThreads;
+        const int64_t base = tile * kTile;
+        // lane l: the bits of the tile's 64-row stretch l (16 of them), and how many there are before them
+        const unsigned long long mine = lane < kTileWords && base + 64 * lane < n ? mask[(base >> 6) + lane] : 0ull;
+        const int cnt = __popcll(mine);
+        int inc = cnt;
+#pragma unroll
+        for (int d = 1; d < kTileWords; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        const int total = __shfl(inc, kTileWords - 1, 64);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int word = j * (kThreads / 64) + w;
+            const unsigned long long m = ((unsigned long long)(unsigned)__shfl((int)(mine >> 32), word, 64) << 32) | (unsigned)__shfl((int)mine, word, 64);
+            const int before = __shfl(inc - cnt, word, 64);
+            if (!(m >> lane & 1ull)) continue;
+            const int64_t i = base + j * kThreads + tid;
+            const int32_t r = run + before + __popcll(m & ((1ull << lane) - 1ull)), s = at[i];
+            const int4 co = load_row(src, i, floor_step);
+            coords[r] = co;
+            if (halved) {
+                int qx, qy, qz;
+                lattice(co.y - g.x0, t.ts, &qx);
+                lattice(co.z - g.y0, t.ts, &qy);
+                lattice(co.w - g.z0, t.ts, &qz);
+                t.cells[(int64_t)t.dir[grid_block(g, co.x - g.b0, qx, qy, qz >> 2)] * 16 + grid_run(qx, qy) * 4 + (qz & 3)] = r;
+                hv.rank_of[s] = r;
+                hv.pair_of[r] = s;
+            } else if (grid) {
+                t.cells[s] = r;
+            } else {
+                t.slots[s].row = r;
+            }
+        }
+        run += total;
+    }
+    if (tile == tiles - 1 && tid == 0) {  // (no rows at all: tile -1 of 0)
+        t.meta[kMetaN] = run;
+        if (mail) {
+            mail[0] = (uint32_t)run;
+            mail[1] = (uint32_t)__hip_atomic_load(t.meta + kMetaErr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence_system();
+            __hip_atomic_store(mail + kMailSeqWord, mail_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
+// Middle-sized sets (always a hash table) and the largest, in one launch.
 // Block b numbers the first occurrences among its rows: rank = (first occurrences in earlier blocks, by look-back) +
 // (those before it in this block, row order).  Writes the (floored) coordinates at that rank and the rank into the
 // table.  The block holding the last rows delivers the total.
@@ -534,13 +736,13 @@ __global__ __launch_bounds__(kNumberThreads) void number_kernel(const int4* __re
     }
 }
 
-__global__ __launch_bounds__(kThreads) void inverse_kernel(Build t, const int32_t* __restrict__ at, int64_t n_host,
+__global__ __launch_bounds__(kThreads) void inverse_kernel(Build t, const int32_t* __restrict__ at, Halved hv, int64_t n_host,
                                                            const int32_t* __restrict__ d_n, int32_t* __restrict__ inverse) {
     const int64_t n = row_count(n_host, d_n);
     const int64_t tile = xcd_tile(blockIdx.x, (n + kThreads - 1) / kThreads), i = tile * kThreads + threadIdx.x;
     if (tile < 0 || i >= n) return;
     const int32_t s = at[i];
-    inverse[i] = is_grid(t) ? t.cells[s < 0 ? ~s : s] : (s < 0 ? -1 : t.slots[s].row);
+    inverse[i] = is_grid(t) ? (hv.meta ? hv.rank_of : t.cells)[s < 0 ? ~s : s] : (s < 0 ? -1 : t.slots[s].row);
 }
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -586,17 +788,26 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     c->tab.cap = cap;
     for (int t = tensor_stride; t > 1; t >>= 1) ++c->tab.zshift;
     const size_t grid_bytes = may_grid ? (size_t)dir_words * 4 + (size_t)n_src * 64 : 0;
-    const int nthreads = n_src >= (1 << 20) ? kNumberThreads : (n_src >= (1 << 18) ? 512 : kThreads);
+    const bool tiled = n_src > kGridRows && n_src <= kTiledRows;  // numbered by firsts_kernel and rank_kernel
+    const int nthreads = n_src > kTiledRows ? kNumberThreads : kThreads;
     const int block_rows = nthreads * kRowsPerThread;
-    const int64_t nb = (n_src + block_rows - 1) / block_rows;
+    const int64_t nb = tiled ? 0 : (n_src + block_rows - 1) / block_rows;
+    const int64_t tiles = tiled ? (n_src + kTile - 1) / kTile : 0;
     c->tab.mem = dev_alloc(std::max((size_t)cap * sizeof(HashSlot), grid_bytes), s);
     c->coords = dev_alloc((size_t)(n_src ? n_src : 1) * 16, s);
     c->inverse = dev_alloc((size_t)(n_src ? n_src : 1) * 4, s);
     c->meta = dev_alloc(kMetaWords * 4, s);
-    // scratch: a slot or cell per source row, the look-back words, the extents
-    const size_t at_bytes = ((size_t)(n_src ? n_src : 1) * 4 + 15) / 16 * 16;
+    // scratch: a slot or cell per source row; the look-back words; tiles: a bit per row and their sums; where a grid is possible: the
+    // extents; for a set of half the resolution the row number of each pair of the parent's blocks (no more blocks than rows)
+    const bool halved = tiled && may_grid && parent && floor_step == 2 * parent->ts;
+    const size_t at_bytes = ((size_t)(n_src ? n_src : 1) * 4 + 15) / 16 * 16, mask_bytes = tiled ? ((size_t)n_src + 63) / 64 * 8 : 0;
     const int64_t n_desc = nb ? nb : 1;
-    Buf scratch = small ? Buf() : dev_alloc(at_bytes + (size_t)n_desc * 8 + (may_grid ? kBoxBlocks * kBoxWords * 4 : 0), s);
+    Buf scratch = small ? Buf() : dev_alloc(at_bytes + (size_t)n_desc * 8 + mask_bytes + (size_t)tiles * 4 +
+                                                (may_grid ? kBoxBlocks * kBoxWords * 4 : 0) + (halved ? (size_t)n_src * 8 : 0), s);
+    if (halved) {
+        c->pairs = dev_alloc((size_t)n_src * 4, s);
+        if (!c->pairs) return SP_ERR_ALLOC;
+    }
     if (!c->tab.mem || !c->coords || !c->inverse || !c->meta || (!small && !scratch)) return SP_ERR_ALLOC;
     int32_t* at = ptr<int32_t>(scratch);
     unsigned long long* desc = small ? nullptr : reinterpret_cast<unsigned long long*>(ptr<unsigned char>(scratch) + at_bytes);
@@ -609,6 +820,18 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     t.dir_words = dir_words;
     t.meta = ptr<int32_t>(c->meta);
     t.ts = tensor_stride;
+    Halved hv{};
+    if (halved) {
+        hv.meta = ptr<int32_t>(parent->meta);
+        hv.dir = ptr<int32_t>(parent->tab.mem);
+        hv.cells = hv.dir + parent->tab.dir_words;
+        hv.ts = parent->ts;
+        hv.pair_of = ptr<int32_t>(c->pairs);
+    }
+    unsigned long long* mask = small ? nullptr : desc + n_desc;
+    int32_t* sums = small ? nullptr : reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(mask) + mask_bytes);
+    int32_t* part = small ? nullptr : sums + tiles;
+    if (halved) hv.rank_of = part + kBoxBlocks * kBoxWords;
     const bool mailed = mail_acquire(&c->mail);
     const int4* src = reinterpret_cast<const int4*>(d_src);
     const dim3 rows(xcd_grid(blocks_for(n_src, kThreads))), threads(kThreads);
@@ -645,25 +868,32 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
         return hand_over();
     }
     if (may_grid) {
-        int32_t* part = nullptr;
-        if (!parent) {
-            part = reinterpret_cast<int32_t*>(desc + n_desc);
-            hipLaunchKernelGGL(box_kernel, dim3(kBoxBlocks), threads, 0, s, src, n_src, d_n_src, tensor_stride, part);
-        }
+        if (!parent) hipLaunchKernelGGL(box_kernel, dim3(kBoxBlocks), threads, 0, s, src, n_src, d_n_src, tensor_stride, part);
         hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)std::min<int64_t>(2048, dir_words / 4 / kBoxBlocks)), dim3(kBoxBlocks), 0, s,
-                           t, n_src, d_n_src, part, parent ? ptr<int32_t>(parent->meta) : nullptr, parent ? parent->ts : 1, desc,
+                           t, n_src, d_n_src, parent ? (const int32_t*)nullptr : part, parent ? ptr<int32_t>(parent->meta) : nullptr, parent ? parent->ts : 1, desc,
                            n_desc);
-        hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
+        if (halved)
+            hipLaunchKernelGGL(mark_coarse_kernel, dim3(2048), threads, 0, s, src, n_src, d_n_src, floor_step, t, hv, at, always);
+        else
+            hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
         hipLaunchKernelGGL(number_blocks_kernel, dim3((unsigned)(dir_words / kScanWords)), dim3(kScanThreads), 0, s, t);
-        hipLaunchKernelGGL(place_kernel, rows, threads, 0, s, t, n_src, d_n_src, at);
+        if (!halved) hipLaunchKernelGGL(place_kernel, rows, threads, 0, s, t, n_src, d_n_src, at);
     } else {
         hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(std::max<int64_t>(cap, n_desc), kThreads)), threads, 0, s, t.slots, cap,
                            t.meta, desc, n_desc);
         hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
     }
-    hipLaunchKernelGGL(number_kernel, dim3((unsigned)nb), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at,
-                       desc, ptr<int4>(c->coords), mailed ? c->mail.d : (uint32_t*)nullptr, c->mail.seq);
-    hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, n_src, d_n_src, ptr<int32_t>(c->inverse));
+    uint32_t* mail = mailed ? c->mail.d : nullptr;
+    if (tiled) {
+        const dim3 tile_grid(xcd_grid(tiles));
+        hipLaunchKernelGGL(firsts_kernel, tile_grid, threads, 0, s, t, n_src, d_n_src, at, halved ? 1 : 0, mask, sums);
+        hipLaunchKernelGGL(rank_kernel, tile_grid, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, hv, mask, sums,
+                           ptr<int4>(c->coords), mail, c->mail.seq);
+    } else {
+        hipLaunchKernelGGL(number_kernel, dim3((unsigned)nb), dim3(nthreads), 0, s, src, n_src, d_n_src, floor_step, t, at, desc, ptr<int4>(c->coords),
+                           mail, c->mail.seq);
+    }
+    hipLaunchKernelGGL(inverse_kernel, rows, threads, 0, s, t, at, hv, n_src, d_n_src, ptr<int32_t>(c->inverse));
     return hand_over();
 }
 

@@ -121,6 +121,9 @@ struct sp_coords {
     sp::Buf inverse;  // int32 [n_raw]
     sp::Buf meta;     // int32 [kMetaWords]: the row count n, error bits, ...: what kernels of later builds read
     sp::CoordTab tab;
+    // A set of half the resolution of a parent with a grid: per row, the pair (2 * block + half) of the parent's grid that is its
+    // cell.  Written only if this set turned out a grid itself (kMetaGrid).
+    sp::Buf pairs;
     hipStream_t stream = nullptr;
     // the host's copy of n arrives through a mail slot and is read on first demand (coords_resolve)
     mutable std::mutex mu;

@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 import torch
 
-from test_gpu_parity import dev, random_coords, sp, test_coords_build_matches_oracle, test_kmap_matches_oracle  # noqa: F401
+from test_gpu_parity import check_map, dev, random_coords, sp, test_coords_build_matches_oracle, test_kmap_matches_oracle  # noqa: F401
+from util import oracle_steps
 
 pytestmark = pytest.mark.gpu
 check_set, check_maps = test_coords_build_matches_oracle, test_kmap_matches_oracle
@@ -57,6 +58,18 @@ def test_hash_of_more_than_a_million_rows_with_duplicates(sp):  # noqa: F811
     check_set(sp, "", WIDE[np.random.default_rng(16).integers(0, 200000, 1_100_000)])
 
 
+@pytest.mark.parametrize("n", [N, (1 << 21) - 1, 1 << 21, (1 << 21) + 1])
+def test_numbering_of_tiles_and_of_one_launch(sp, n):  # noqa: F811
+    """Up to 2^21 rows numbered by tiles, beyond in one launch: both forms of table, tiles without a first row (all rows of the
+    second half are repeats), the next set's likewise."""
+    for some in (random_coords(17, n // 2 + 1, 180, batches=2, lo=-90), random_coords(17, n // 2 + 1, 30000, batches=2, lo=-9000)):
+        raw = np.concatenate([some, some[::-1]])[:n]
+        check_set(sp, "", raw)
+        km, c = sp.sp_kmap_build(sp.sp_coords_build(dev(raw), 1), 2, 2, 1)
+        want = oracle_steps(np.unique(raw, axis=0), 2, 2, 1, 1)
+        assert c.n == len(want["c_out"]) and np.array_equal(np.sort(km.counts), np.sort(want["counts"]))
+
+
 def test_out_of_range_row_among_many(sp):  # noqa: F811
     for bad in ([0, 32768, 0, 0], [0, 0, -32769, 0], [65536, 0, 0, 0], [-1, 0, 0, 0]):
         raw = DENSE.copy()
@@ -78,6 +91,46 @@ def test_two_levels_built_without_waiting(sp):  # noqa: F811
     top = {tuple(r) for r in v(u, 4)}
     links = sum((b, x + 4 * i, y + 4 * j, z + 4 * k) in top for b, x, y, z in top for i in (-1, 0, 1) for j in (-1, 0, 1) for k in (-1, 0, 1))
     assert k3.total == links and k1.n_out == c1.n and k2.n_in == c1.n
+
+
+FULL = np.unique(random_coords(21, 260000, 52, batches=3, lo=-27), axis=0)    # enough rows that the coarse sets are grids too
+
+
+@pytest.mark.parametrize("resolved", [True, False])
+@pytest.mark.parametrize("K,ts,shift", [(2, 1, 0), (3, 1, 0), (2, 2, 1), (2, 3, 2), (3, 4, 0)])
+def test_sets_of_half_the_resolution(sp, K, ts, shift, resolved):  # noqa: F811
+    """Coarse sets out of the blocks of their parent's grid, level by level: rows, parents, pairs and tables against the oracle's,
+    with lowest coordinates odd and even, lattices off zero, row counts known to the host and not."""
+    raw = scaled(FULL[np.random.default_rng(ts).permutation(len(FULL))], ts, shift) + np.array([0, 0, ts, 0], np.int32)
+    c = sp.sp_coords_build(dev(np.concatenate([raw, raw[:5000]])), ts)
+    rows, step = raw, ts
+    for _ in range(3):
+        if resolved:
+            assert c.n == len(rows)
+        km, co = sp.sp_kmap_build(c, K, 2, 1)
+        want = oracle_steps(rows, K, 2, 1, step)
+        assert co.n == len(want["c_out"])
+        assert np.array_equal(co.coords().cpu().numpy(), want["c_out"])
+        assert np.array_equal(co.inverse().cpu().numpy(), want["parent"])
+        if K == 2 and shift:                                           # off the lattice of zero: each row at one place of its cell
+            nbr_out, nbr_in = (t.cpu().numpy() for t in km.table()[:2])
+            k, o = np.nonzero(nbr_out >= 0)
+            assert len(k) == len(rows) and np.array_equal(nbr_in[k, nbr_out[k, o]], o) and np.array_equal(want["parent"][nbr_out[k, o]], o)
+            assert np.count_nonzero(nbr_in >= 0) == len(rows) == km.total
+            c, rows, step = co, want["c_out"], 2 * step
+            shift = 0
+            continue
+        check_map(sp, km, want, len(rows), len(want["c_out"]))
+        for side, i, o, n in ((0, want["pair_in"], want["pair_out"], km.n_out), (1, want["pair_out"], want["pair_in"], km.n_in)):
+            table, base = np.full((K ** 3, n), -1, np.int32), 0
+            for k, cnt in enumerate(want["counts"]):
+                table[k, o[base:base + cnt]] = i[base:base + cnt]
+                base += cnt
+            assert np.array_equal(km.table()[side].cpu().numpy(), table)
+        if K == 3:                                                     # the coarse set's own table is searched
+            k1, _ = sp.sp_kmap_build(co, 3, 1, 1)
+            assert np.array_equal(k1.counts, oracle_steps(want["c_out"], 3, 1, 1, 2 * step)["counts"])
+        c, rows, step = co, want["c_out"], 2 * step
 
 
 @pytest.mark.parametrize("cin,cout,bf16", [(32, 32, False), (128, 128, True), (20, 24, False)])
