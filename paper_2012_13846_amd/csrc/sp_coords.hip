@@ -36,6 +36,7 @@ constexpr int kBoxBlocks = 256;                // blocks of the extent kernel = 
 constexpr int kBoxWords = 12;                  // min and max of b, x, y, z; out of range; off the lattice
 constexpr int kScanThreads = 1024;
 constexpr int kScanWords = 16 * kScanThreads;  // dir words numbered by one block
+constexpr int64_t kFewScanWords = 2 << 20;     // up to here blocks of a quarter of that
 
 __device__ __forceinline__ int32_t floor_to_multiple(int32_t v, int32_t s) {
     int32_t q = v / s;
@@ -256,6 +257,7 @@ __global__ __launch_bounds__(kThreads) void box_kernel(const int4* __restrict__ 
 }
 
 // Every block derives the box and the form of the table for itself and clears its share of it; block 0 writes meta.
+// (512 blocks: 0.5 and 1 M rows 10.4 and 12.1 us with up to 2048, which all reduce the extents first, 5.6 and 8.8 so.)
 // part: the extents box_kernel left, or null: the parent's box (parent_meta, lattice step parent_ts), floored to t.ts.
 __global__ __launch_bounds__(kBoxBlocks) void prepare_kernel(Build t, int64_t n_host, const int32_t* __restrict__ d_n,
                                                              const int32_t* __restrict__ part,
@@ -450,42 +452,58 @@ __global__ __launch_bounds__(kThreads) void mark_coarse_kernel(const int4* __res
 
 // Grid: occupied blocks are numbered, their cells cleared.  16 words a thread.  The numbers need no order (nothing
 // that the build returns depends on them), so a workgroup takes as many as it needs from a counter: 12 ns per
-// workgroup, where a look-back made the launch wait 8 us.
+// workgroup, where a look-back made the launch wait 8 us.  Scans stay inside the wavefronts but for one: 0.15, 0.5 and 1 M rows
+// 7.7, 9.8 and 15.8 us with a scan of the whole workgroup for every four words, 6.2, 9.0 and 13.4 so; small sets in blocks of
+// a quarter, which else fill 77 CUs.
 __global__ __launch_bounds__(kScanThreads) void number_blocks_kernel(Build t) {
     __shared__ int s_base;
     __shared__ int s_wave[kScanThreads / 64];
     if (!is_grid(t)) return;
     const Grid g = load_grid(t.meta);
     const int64_t words = (int64_t)g.nb * g.gx * g.gy * g.gz * 64;
-    if ((int64_t)blockIdx.x * kScanWords >= words) return;
+    const int nthreads = blockDim.x;
+    if ((int64_t)blockIdx.x * 16 * nthreads >= words) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // thread t takes quads t, t + 1024, ...: coalesced; numbers follow quad by quad
-    int4* q = reinterpret_cast<int4*>(t.dir + (int64_t)blockIdx.x * kScanWords);
+    // a wavefront takes 256 quads in a row, 64 at a time; its numbers follow quad by quad
+    int4* q = reinterpret_cast<int4*>(t.dir + (int64_t)blockIdx.x * 16 * nthreads) + w * 256 + lane;
     int4 v[4];
-    int pos[4], total = 0;
+    int pos[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = q[j * kScanThreads + tid];
+    for (int j = 0; j < 4; ++j) v[j] = q[j * 64];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pos[j] = (v[j].x == 0) + (v[j].y == 0) + (v[j].z == 0) + (v[j].w == 0);
+    int mine[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mine[j] = pos[j];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int u = __shfl_up(pos[j], d, 64);
+            if (lane >= d) pos[j] += u;
+        }
+    int total = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int mine = (v[j].x == 0) + (v[j].y == 0) + (v[j].z == 0) + (v[j].w == 0);
-        int inc = mine;
+        const int all = __shfl(pos[j], 63, 64);
+        pos[j] += total - mine[j];
+        total += all;
+    }
+    if (lane == 0) s_wave[w] = total;
+    __syncthreads();
+    if (w == 0) {
+        const int nw = nthreads / 64, own = lane < nw ? s_wave[lane] : 0;
+        int inc = own;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
+        for (int d = 1; d < kScanThreads / 64; d <<= 1) {
             const int u = __shfl_up(inc, d, 64);
             if (lane >= d) inc += u;
         }
-        if (lane == 63) s_wave[w] = inc;
-        __syncthreads();
-        pos[j] = total + inc - mine;
-        for (int ww = 0; ww < kScanThreads / 64; ++ww) {
-            if (ww < w) pos[j] += s_wave[ww];
-            total += s_wave[ww];
-        }
-        __syncthreads();
+        if (lane < nw) s_wave[lane] = inc - own;
+        if (lane == nw - 1) s_base = inc ? atomicAdd(t.meta + kMetaBlocks, inc) : 0;
     }
-    if (tid == 0) s_base = total ? atomicAdd(t.meta + kMetaBlocks, total) : 0;
     __syncthreads();
-    const int base = s_base;
+    const int base = s_base + s_wave[w];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         int r = base + pos[j];
@@ -494,10 +512,10 @@ __global__ __launch_bounds__(kScanThreads) void number_blocks_kernel(Build t) {
         if (v[j].y == 0) v[j].y = r++;
         if (v[j].z == 0) v[j].z = r++;
         if (v[j].w == 0) v[j].w = r++;
-        q[j * kScanThreads + tid] = v[j];
+        q[j * 64] = v[j];
     }
-    int4* cells = reinterpret_cast<int4*>(t.cells) + (int64_t)base * 4;
-    for (int i = tid; i < total * 4; i += kScanThreads) cells[i] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
+    int4* cells = reinterpret_cast<int4*>(t.cells) + (int64_t)base * 4;  // each wavefront clears its own
+    for (int i = lane; i < total * 4; i += 64) cells[i] = int4{kNoRow, kNoRow, kNoRow, kNoRow};
 }
 
 // Grid: at[i] becomes the row's place in cells (its complement for a row that is not the first of its cell), and the
@@ -869,14 +887,15 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     }
     if (may_grid) {
         if (!parent) hipLaunchKernelGGL(box_kernel, dim3(kBoxBlocks), threads, 0, s, src, n_src, d_n_src, tensor_stride, part);
-        hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)std::min<int64_t>(2048, dir_words / 4 / kBoxBlocks)), dim3(kBoxBlocks), 0, s,
+        hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)std::min<int64_t>(512, dir_words / 4 / kBoxBlocks)), dim3(kBoxBlocks), 0, s,
                            t, n_src, d_n_src, parent ? (const int32_t*)nullptr : part, parent ? ptr<int32_t>(parent->meta) : nullptr, parent ? parent->ts : 1, desc,
                            n_desc);
         if (halved)
             hipLaunchKernelGGL(mark_coarse_kernel, dim3(2048), threads, 0, s, src, n_src, d_n_src, floor_step, t, hv, at, always);
         else
             hipLaunchKernelGGL(mark_kernel, rows, threads, 0, s, src, n_src, d_n_src, floor_step, t, at, always);
-        hipLaunchKernelGGL(number_blocks_kernel, dim3((unsigned)(dir_words / kScanWords)), dim3(kScanThreads), 0, s, t);
+        const int scan = dir_words <= kFewScanWords ? kScanThreads / 4 : kScanThreads;
+        hipLaunchKernelGGL(number_blocks_kernel, dim3((unsigned)(dir_words / (16 * scan))), dim3(scan), 0, s, t);
         if (!halved) hipLaunchKernelGGL(place_kernel, rows, threads, 0, s, t, n_src, d_n_src, at);
     } else {
         hipLaunchKernelGGL(reset_kernel, dim3(blocks_for(std::max<int64_t>(cap, n_desc), kThreads)), threads, 0, s, t.slots, cap,
