@@ -173,7 +173,8 @@ int sp_conv_bwd_weight(const sp_kmap_t* m, const void* d_x, const void* d_dy, fl
  * Pieces that do not fit: the kernels that take weights as they are, fp32 sums in another order than sp_conv_fwd's.
  * A copy that does not fit either (the tile kernel's is padded to whole channel tiles):
  *   - narrow layers (gather_wave_kernel: cin 16 / 32 / 64 fp32, 32 / 64 / 128 bf16, cout to match): SP_ERR_UNSUPPORTED;
- *     kvol * cin * cout * element size <= 4 MiB is never refused;
+ *     kvol * cin * cout * element size <= 4 MiB is never refused, nor a layer that larger maps of the same density run on
+ *     gather_dense_kernel (the weights are read where they are stored, same results);
  *   - other layers whose cin is whole slices of the tile kernel: the weights are read where they are stored; the
  *     results of the tile kernel, slower;
  *   - the rest run on the plain kernel: correct, slow, fp32 sums in another order than sp_conv_fwd's.

@@ -41,6 +41,7 @@ struct GatherArgs {
     int runs;          // sub-tiles are dealt to the XCDs in runs (xcd_run)
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
+    int in_place;      // host-side only: the weights are read where they are stored
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
@@ -50,6 +51,7 @@ struct GatherArgs {
 // Narrow-channel variant: every wavefront owns 64 destination rows (one sub-tile) and all COT channels of a
 // channel tile, and runs on its own: no workgroup barrier anywhere.
 //
+//  (Small launches: four wavefronts share a sub-tile, kWaveShare, and meet once, at the end.)
 //  - The wavefront first cuts its links into blocks of up to 16 links of one offset and writes one packed
 //    descriptor per block into LDS, so that block b+n is addressable without walking a cursor.
 //  - Everything a block needs is requested well ahead of its use and kept in registers: link entries
@@ -110,8 +112,11 @@ constexpr int kRun = 8;
 constexpr int64_t kRunRows = 1 << 17;
 __device__ __forceinline__ int64_t xcd_run(int64_t wg) { return wg / (8 * kRun) * (8 * kRun) + (wg & 7) * kRun + (wg >> 3) % kRun; }
 
-template <typename T, int CC, int COT, bool kWideDesc>
-__global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
+// kShare wavefronts share a sub-tile, each a stretch of its blocks with an accumulator of its own; the accumulators are added at
+// the end.  For launches whose length is one sub-tile's chain of blocks (share_fits).
+// kStored: the weights are read as they are stored, [kvol][co_total][CC], instead of from the fragment-major copy.
+template <typename T, int CC, int COT, bool kWideDesc, int kShare, bool kStored>
+__global__ __launch_bounds__(64 * kShare) void gather_wave_kernel(GatherArgs a) {
     using Cfg = WaveCfg<T, CC, COT>;
     constexpr bool kIsF32 = Cfg::kIsF32;
     constexpr int kGroups = Cfg::kGroups, kNCT = Cfg::kNCT, kPieces = Cfg::kPieces, kXLoads = Cfg::kXLoads;
@@ -135,6 +140,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
 
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
+    const int wave = kShare == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // grid.x = 2 * sub-tiles: the first half of the grid takes half 0 (or the whole sub-tile), the second half
     // of the grid half 1.  (Workgroups are dealt to the 8 XCDs round-robin: pairing (u,0),(u,1) on adjacent
     // indices would leave every other XCD with nothing but wavefronts that leave at once.)
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     const int64_t wt = runs ? xcd_run(blockIdx.x) : (int64_t)blockIdx.x - (half ? nwt : 0);  // this wavefront's sub-tile
     if (Cfg::kMayRun && wt >= nwt) return;
     const int kvol = a.kvol;
-    unsigned char* base = smem;
+    unsigned char* base = smem + wave * a.lds_per_wave;
     float* acc = reinterpret_cast<float*>(base);
     unsigned char* xbuf = base + Cfg::kAccBytes;
     int* s_beg = reinterpret_cast<int*>(xbuf + Cfg::kXBytes);  // where this wavefront's links begin, per offset; kWideDesc: per block
@@ -195,6 +201,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         nblk += __shfl(inc, 63, 64);
     }
     wave_sync();
+    // this wavefront's blocks: all, or its share of them
+    const int b0 = kShare == 1 ? 0 : nblk * wave / kShare, b1 = kShare == 1 ? nblk : nblk * (wave + 1) / kShare;
 
     // Buffer addressing: a 32-bit byte offset per lane against a descriptor in scalar registers costs one
     // integer multiply-add per load instead of 64-bit pointer arithmetic, and reads past the end return 0.
@@ -205,7 +213,8 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.src), 0, (int)a.list_bytes, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rRow =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.dst), 0, (int)a.list_bytes, kRsrcFlags);
-    const uint32_t w_tile_off = (uint32_t)(blockIdx.y * Cfg::kWFragBytesPerOffsetTile);
+    const uint32_t w_tile_off = (uint32_t)(blockIdx.y * Cfg::kWFragBytesPerOffsetTile);  // (the same in both layouts)
+    const int w_lane = kStored ? n16 * Cfg::kRowBytes + g * 16 : lane * 16;
     const uint32_t w_offset_stride = (uint32_t)((a.co_total / COT) * Cfg::kWFragBytesPerOffsetTile);
 
     auto load_weights = [&](int k, Frag (&wf)[kWT][kGroups], int ct0) __attribute__((always_inline)) {
@@ -217,7 +226,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
 #pragma unroll
             for (int s = 0; s < kGroups; ++s)
                 wf[ct][s] = __builtin_bit_cast(
-                    Frag, __builtin_amdgcn_raw_buffer_load_b128(rW, lane * 16 + ((ct0 + ct) * kGroups + s) * 1024, soff, 0));
+                    Frag, __builtin_amdgcn_raw_buffer_load_b128(rW, w_lane + (kStored ? (ct0 + ct) * 16 * Cfg::kRowBytes + s * 64 : ((ct0 + ct) * kGroups + s) * 1024), soff, 0));
     };
 
     // The main loop is straight-line code with the same loads in every turn (blocks past the end are
@@ -234,7 +243,7 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
     struct WSlot {
         Frag w[kWT][kGroups];     // a block's weight matrix (kHalfW: one half of it)
     };
-    const int last = nblk - 1;
+    const int last = b1 - 1;
     // (Starting each wavefront at a block of its own, so that the wavefronts of a compute unit do not ask for
     // the same weight lines at the same moment, was measured and is slower: in step, they share the lines in L1.)
     auto request = [&](Slot& sl, int de, int e0) __attribute__((always_inline)) {
@@ -294,21 +303,21 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
             xf[s] = *reinterpret_cast<const Frag*>(xbuf + n16 * Cfg::kXStride + s * 64 + g * 16);
     };
 
-    if (nblk > 0) {
+    if (b1 > b0) {
         Slot xs[kDX] = {};
         WSlot ws[kDW] = {};
 #pragma unroll
-        for (int j = 0; j < kDX; ++j) look_up(xs[j], j);
+        for (int j = 0; j < kDX; ++j) look_up(xs[j], b0 + j);
 #pragma unroll
         for (int j = 0; j < kDW; ++j) {
-            if constexpr (kHalfW) issue_weights(ws[j], 0, j * kWT);  // both halves of block 0
-            else issue_weights(ws[j], j);
+            if constexpr (kHalfW) issue_weights(ws[j], b0, j * kWT);  // both halves of the first block
+            else issue_weights(ws[j], b0 + j);
         }
 #pragma unroll
         for (int j = 0; j < kDX; ++j) issue_gather(xs[j]);
 #pragma unroll
-        for (int j = 0; j < kDX; ++j) look_up(xs[j], kDX + j);
-        run_ahead(2 * kDX);
+        for (int j = 0; j < kDX; ++j) look_up(xs[j], b0 + kDX + j);
+        run_ahead(b0 + 2 * kDX);
         Frag xf_c[kGroups];
         stage(xs[0]);
         wave_sync();
@@ -407,30 +416,33 @@ __global__ __launch_bounds__(64) void gather_wave_kernel(GatherArgs a) {
                 }
             }
         };
-        int done = 0;  // number of blocks computed; the last one's result is still to be added
-        for (int b = 0; b < nblk; b += kTurn) {
+        int done = b0;  // blocks computed, the ones before b0 counted; the last one's result is still to be added
+        for (int b = b0; b < b1; b += kTurn) {
             bool stop = false;
 #pragma unroll
             for (int j = 0; j < kTurn; ++j) {
                 if (!stop) {
                     body(b + j, xs[j % kDX], xs[(j + 1) % kDX], ws[kHalfW ? 0 : j % kDW], ws[1], res[j % 2], res[(j + 1) % 2]);
                     done = b + j + 1;
-                    stop = b + j + 1 >= nblk;
+                    stop = b + j + 1 >= b1;
                 }
             }
         }
         f32x4 av[kNCT];
-        if ((done + 1) % 2 == 0) { flush_read(res[0], av); flush_write(res[0], av); }  // the set of block done-1
+        if ((done - b0 + 1) % 2 == 0) { flush_read(res[0], av); flush_write(res[0], av); }  // the set of block done-1
         else { flush_read(res[1], av); flush_write(res[1], av); }
     }
-    wave_sync();
+    if constexpr (kShare == 1) wave_sync();
+    else __syncthreads();
     const int co0 = blockIdx.y * COT;
     constexpr int kQuads = COT / 4;
-    for (int idx = lane; idx < row_count * kQuads; idx += 64) {
+    for (int idx = threadIdx.x; idx < row_count * kQuads; idx += 64 * kShare) {
         const int r = idx / kQuads, c4 = (idx % kQuads) * 4;
         const int64_t row = wt * 64 + row_base + r;
         if (row >= a.n_rows) break;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(acc + r * Cfg::kStride + c4);
+        f32x4 v = *reinterpret_cast<const f32x4*>(smem + (r * Cfg::kStride + c4) * 4);
+#pragma unroll
+        for (int w = 1; w < kShare; ++w) v += *reinterpret_cast<const f32x4*>(smem + w * a.lds_per_wave + (r * Cfg::kStride + c4) * 4);
         if constexpr (kIsF32) {
             *reinterpret_cast<f32x4*>(static_cast<float*>(a.g) + row * a.co_total + co0 + c4) = v;
         } else {
@@ -467,15 +479,10 @@ __global__ __launch_bounds__(256) void weight_frag_kernel(const T* __restrict__ 
     wf[idx] = w[(size_t)k * co_total * CC + (size_t)co * s_co + (size_t)cc * s_cc];
 }
 
-template <typename T, int CC, int COT, bool kWideDesc>
-int launch_wave(GatherArgs a, hipStream_t s) {
-    using Cfg = WaveCfg<T, CC, COT>;
-    if constexpr (!kWideDesc && Cfg::kMayWide)
-        if (Cfg::wide(a.kvol)) return launch_wave<T, CC, COT, true>(a, s);
-    auto kern = gather_wave_kernel<T, CC, COT, kWideDesc>;
-    a.lds_per_wave = Cfg::per_wave_bytes(a.kvol);
-    a.w_bytes = (uint32_t)((size_t)a.kvol * a.co_total * CC * sizeof(T));
-    const int lds = a.lds_per_wave;  // one wavefront per workgroup: they are independent, small groups place freely
+template <typename T, int CC, int COT, bool kWideDesc, int kShare, bool kStored>
+int run_wave(const GatherArgs& a, dim3 grid, hipStream_t s) {
+    auto kern = gather_wave_kernel<T, CC, COT, kWideDesc, kShare, kStored>;
+    const int lds = a.lds_per_wave * kShare;
     {
         static std::mutex mu;
         static int attr_lds = 0;  // largest dynamic LDS size opted into so far
@@ -485,38 +492,75 @@ int launch_wave(GatherArgs a, hipStream_t s) {
             attr_lds = lds;
         }
     }
-    // fragment-major copy of the weights (also undoes the data gradient's transposition)
+    hipLaunchKernelGGL(kern, grid, dim3(64 * kShare), lds, s, a);
+    SP_HIP(hipGetLastError());
+    return SP_OK;
+}
+
+// LDS is handed out in steps of 1280 bytes: workgroups of a launch that the GPU's 256 CUs hold at once
+inline int64_t resident_wgs(int64_t lds) { return 256 * (160 * 1024 / ((lds + 1279) / 1280 * 1280)); }
+
+// Four wavefronts per sub-tile where all sub-tiles then still fit the GPU at once: such a launch is as long as one sub-tile's
+// chain of 27 and more blocks, each behind the one before it.  Forward in us, one wavefront / four (host included, 10 us at
+// least), K = 3 on 1.5 k rows with 4.6 k links | 16 k, 67 k | 32 k, 0.22 M:
+//   fp32 16 -> 16   15.1 / 9.9  | 15.0 / 9.8  | 17.5 / 10.5     bf16 32 -> 32   15.9 / 10.4 | 16.3 / 9.8  | 18.5 / 11.0
+//   fp32 32 -> 32   18 / 11.8   | 21.9 / 11.8 | 27.7 / 16.4     bf16 64 -> 64   20.4 / 11.7 | 20.8 / 12.3 | 30 / 18.1
+// Where they do not fit the blocks of all sub-tiles matter and not the longest chain: bf16 32 -> 32 on 64 k rows, 0.83 M links 23.3
+// / 26.5, fp32 64 -> 32 63 / 75.  Eight wavefronts gain nothing over four.
+constexpr int kWaveShare = 4;
+inline int64_t wave_lds(int cc, int cot, int elt, int kvol) {
+    return 64 * (cot + 4) * 4 + 16 * (cc * elt + 32) - 32 + (kvol * (cc * elt == 64 && kvol <= 27 ? 24 : 12) + 15) / 16 * 16;
+}
+inline bool share_fits(int64_t waves, int64_t lds_per_wave) { return waves <= resident_wgs(kWaveShare * lds_per_wave); }
+
+template <typename T, int CC, int COT, bool kWideDesc>
+int launch_wave(GatherArgs a, hipStream_t s) {
+    using Cfg = WaveCfg<T, CC, COT>;
+    if constexpr (!kWideDesc && Cfg::kMayWide)
+        if (Cfg::wide(a.kvol)) return launch_wave<T, CC, COT, true>(a, s);
+    a.lds_per_wave = Cfg::per_wave_bytes(a.kvol);
+    a.w_bytes = (uint32_t)((size_t)a.kvol * a.co_total * CC * sizeof(T));
+    const int64_t nwt = (a.n_rows + 63) / 64, waves = nwt * (a.co_total / COT);
+    const bool share = share_fits(waves, a.lds_per_wave);
+    // A shared sub-tile's wavefronts read few matrices each: small ones are read as they are stored, 16 stretches of 64 bytes a load
+    // instead of 1 KB, which saves the copy's launch (fp32 16 -> 16 on 1.5 k rows 9.9 -> 8.4 us, 32 -> 32 11.8 -> 9.7; 32 -> 32 on
+    // 32 k rows 16.4 -> 17.9, bf16 64 -> 64 on 1.5 k 11.7 -> 14.4).
+    constexpr int kMatrix = CC * COT * (int)sizeof(T);
+    const bool stored = !a.w_transposed && ((share && (kMatrix <= 2048 || (kMatrix <= 4096 && waves <= 256))) || a.in_place);
     const int64_t n = (int64_t)a.kvol * a.co_total * CC;
+    if (a.scratch && !a.in_place && (size_t)n * sizeof(T) > a.scratch_bytes)  // the same layers at every size of the map
+        return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch",
+                    (long long)(n * sizeof(T)), a.scratch_bytes);
     Buf wf;
-    T* d_wf = static_cast<T*>(a.scratch);
-    if (d_wf) {
-        if ((size_t)n * sizeof(T) > a.scratch_bytes)
-            return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch",
-                        (long long)(n * sizeof(T)), a.scratch_bytes);
-    } else {
-        wf = dev_alloc((size_t)n * sizeof(T), s);
-        if (!wf) return SP_ERR_ALLOC;
-        d_wf = ptr<T>(wf);
+    if (!stored) {  // fragment-major copy of the weights (also undoes the data gradient's transposition)
+        T* d_wf = static_cast<T*>(a.scratch);
+        if (!d_wf) {
+            wf = dev_alloc((size_t)n * sizeof(T), s);
+            if (!wf) return SP_ERR_ALLOC;
+            d_wf = ptr<T>(wf);
+        }
+        const int s_co = a.w_transposed ? 1 : CC, s_cc = a.w_transposed ? a.co_total : 1;
+        hipLaunchKernelGGL((weight_frag_kernel<T, CC, COT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           static_cast<const T*>(a.w), d_wf, a.kvol, a.co_total, s_co, s_cc);
+        a.w = d_wf;
     }
-    const int s_co = a.w_transposed ? 1 : CC, s_cc = a.w_transposed ? a.co_total : 1;
-    hipLaunchKernelGGL((weight_frag_kernel<T, CC, COT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       static_cast<const T*>(a.w), d_wf, a.kvol, a.co_total, s_co, s_cc);
-    a.w = d_wf;
     // A launch whose sub-tiles fit the GPU's LDS at once runs as long as its longest wavefront: then long
     // sub-tiles (48 blocks and more at 27 offsets, against a typical 27-35; measured best of 32..64) are shared by two
     // wavefronts.  More offsets have more blocks, all of them: sharing every sub-tile pays only if the halves fit at once too
     // (K = 5, bf16 32 -> 32 on 0.15 M rows: 108-119 us with every sub-tile shared, 63 with none).  Larger launches run in
     // several rounds, where splitting would only add padding.
-    const int64_t nwt = (a.n_rows + 63) / 64, waves = nwt * (a.co_total / COT);
-    const int64_t resident = 256 * (160 * 1024 / ((a.lds_per_wave + 1279) / 1280 * 1280));
+    const int64_t resident = resident_wgs(a.lds_per_wave);
     a.split_blocks = 2 * waves <= resident ? 48 : (waves * 5 / 4 <= resident ? std::max(48, 48 * a.kvol / 27) : 0x7fffffff);
     a.runs = Cfg::kMayRun && a.split_blocks == 0x7fffffff && a.n_rows >= kRunRows ? 1 : 0;
     // two wavefronts per sub-tile only where sub-tiles may be split (the second one leaves at once otherwise)
     const int64_t wgs = a.runs ? (nwt + 8 * kRun - 1) / (8 * kRun) * (8 * kRun) : (a.split_blocks == 0x7fffffff ? 1 : 2) * nwt;
-    dim3 grid((unsigned)wgs, (unsigned)(a.co_total / COT));
-    hipLaunchKernelGGL(kern, grid, dim3(64), lds, s, a);
-    SP_HIP(hipGetLastError());
-    return SP_OK;  // wf goes back to the pool; later users are ordered behind this launch on the stream
+    const dim3 grid((unsigned)wgs, (unsigned)(a.co_total / COT));
+    // (the copy goes back to the pool; later users are ordered behind this launch on the stream)
+    if constexpr (kMatrix <= 4096 || (!Cfg::kIsF32 && CC >= 64))
+        if (share && stored) return run_wave<T, CC, COT, kWideDesc, kWaveShare, true>(a, grid, s);
+    if constexpr (!Cfg::kIsF32 && CC >= 64)
+        if (stored) return run_wave<T, CC, COT, kWideDesc, 1, true>(a, grid, s);
+    return share ? run_wave<T, CC, COT, kWideDesc, kWaveShare, false>(a, grid, s) : run_wave<T, CC, COT, kWideDesc, 1, false>(a, grid, s);
 }
 
 // Plain kernel for what the other kernels' 32-bit buffer offsets cannot address: one thread per (row, channel),
@@ -686,6 +730,8 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
 namespace {
 // fp32: the split kernel against the one that has the layer otherwise (wave: the wavefront-private one).  Forward in us, before /
 // split, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 160 k, 0.66 M | 213 k, 2.4 M | 613 k, 5.0 M:
+// (wavefront-private: one wavefront a sub-tile; where four share one, 64 -> 64 takes 20 us on 1.5 k and 22 on 16 k rows, 32 -> 64
+// 14 and 15, 32 k rows 24, the split kernel 25, 29, 20, 24 and 30: share_fits is the line.)
 //   wavefront-private  64 -> 64    56 / 26 | 66 / 38  | 124 / 85  | 180 / 115 | 345 / 250  | 681 / 530
 //                      32 -> 64    35 / 21 | 37 / 29  | 58 / 55   | 93 / 70   | 165 / 133  | 328 / 264
 //                      64 -> 128   56 / 31 | 96 / 47  | 200 / 143 | 280 / 195 | 602 / 451  | 1180 / 920
@@ -702,12 +748,33 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
     if (cc % 4 != 0 || cc <= 16 || co <= 16 || kvol > 125) return false;
     const SplitShape t = split_shape(cc, co);
     if (split_copy_bytes(t, kvol) >= kLim32) return false;
-    if (wave) return t.cot > 32 || side.n_rows < 16384;
+    if (wave) return t.cot > 32 && !share_fits((side.n_rows + 63) / 64 * (co / wave_tile(cc, co, true)), wave_lds(cc, wave_tile(cc, co, true), 4, kvol));
     if (side.n_rows < 1024) return false;
     if (side.n_rows < 65536) return t.cot == 128;
     const TileShape o = tile_shape(cc, co, true, false);
     const bool dense = links * 128 >= (int64_t)32 * kvol * side.n_rows;
     return dense || 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny <= 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
+}
+
+bool dense_pays(const MapSide& side, int kvol, int64_t links, int cc) {
+    return side.tile_mask || (double)links >= dense_min_fill(cc) * (double)side.n_rows * kvol;
+}
+
+// Small launches of layers that have a row-stationary kernel: its length is one tile's chain of kvol steps, whatever the number of
+// rows, and few CUs have one; the wavefront-private kernel's follows the blocks.  Line: sub-tiles times channel tiles, times
+// the blocks of 16 links an offset has in one on average (estimated).  Forward in us, row-stationary / wavefront-private, K = 3 on
+// 1 k rows with 11 k links | 16 k, 67 k | 16 k, 0.39 M | 32 k, 0.22 M | 48 k, 0.48 M (- : the link-list kernel before, too):
+//   64 -> 64    29 / 12 | - | 29 / 20 | 30 / 18 | 32 / 27       128 -> 64   44 / 14 | 45 / 16 | 50 / 34 | 47 / 35 | 48 / 45
+//   64 -> 128   37 / 12 | - | 38 / 33 | 40 / 32 | 42 / 47       128 -> 128  60 / 15 | 61 / 29 | 65 / 47 | 64 / 43 | 64 / 77
+//   64 -> 256   49 / 13 | - | 52 / 48 | 53 / 44 | 55 / 78       128 -> 256  76 / 17 | 80 / 38 | 82 / 107 | 82 / 85 | 85 / 154
+// Not on a side with position classes, whose row-stationary steps are few.  bf16 sums are fp32 and rounded once in both.
+bool small_wave(const MapSide& side, int kvol, int64_t links, int cc, int co, sp_dtype dt) {
+    if (side.tile_mask || tile_big(side, kvol, cc, dt) || !wave_shape_ok(cc, co, dt)) return false;
+    const int cot = wave_tile(cc, co, dt == SP_F32);
+    if (!cot) return false;
+    const int64_t nwt = (side.n_rows + 63) / 64;
+    const double per = (double)links * 64 / ((double)side.n_rows * kvol), blocks = std::max(1.0, per / 16 + 0.5);
+    return (double)(nwt * (co / cot)) * blocks <= 2100.0;
 }
 
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,
@@ -721,8 +788,9 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
 //   fp32 32 -> 64   34 / 19 | 56 / 62   | 89 / 84   | 153 / 195 | 310 / 376      bf16 64 -> 64   22 / 16 | 37 / 49 | 57 / 63  | 101 / 143 | (row-stationary)
 //   fp32 64 -> 32   35 / 22 | 57 / 87   | 92 / 123  | 160 / 292 | 324 / 554      bf16 64 -> 128  23 / 19 | 62 / 84 | 84 / 107 | 189 / 287 | (row-stationary)
 //   fp32 64 -> 64   54 / 27 | 114 / 100 | 166 / 134 | 305 / 341 | 604 / 664
-// So one rule for both types.  It gives away the smallest launches, which one tile's chain bounds, and fp32 64 -> 64 between
-// about 0.1 and 0.2 M rows, where the tile kernel's 128 rows fill the blocks of few links better.
+// So one rule for both types (the smallest launches, which one sub-tile's chain bounds, are four wavefronts a sub-tile since: 10
+// to 12 us, fp32 64 -> 64 20).  It gives away fp32 64 -> 64 between about 0.1 and 0.2 M rows where the split kernel has not taken
+// it, since the tile kernel's 128 rows fill the blocks of few links better.
 int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt, bool may_split = true) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
     if (narrow_pays(cc, co, kvol)) return 4;
@@ -732,8 +800,7 @@ int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, in
     // on 64-channel inputs.
     // (A side with position classes skips the offsets its tiles cannot have: its cost follows the links.)
     const uint64_t lim = 0x7fffffffull;
-    if (dense_shape_ok(cc, co, dt) &&
-        (side.tile_mask || (double)total_links >= dense_min_fill(cc) * (double)side.n_rows * kvol) &&
+    if (dense_shape_ok(cc, co, dt) && dense_pays(side, kvol, total_links, cc) && !small_wave(side, kvol, total_links, cc, co, dt) &&
         (uint64_t)side.n_src * cc * elt < lim && (uint64_t)side.n_rows * kvol * 4 < lim && (uint64_t)kvol * cc * co * elt < lim)
         return 0;
     // the link-list kernels address their buffers with 32-bit offsets; the tile kernel takes larger features and lists
@@ -802,6 +869,9 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         a.w = d_w;
         a.w_transposed = w_transposed ? 1 : 0;
         a.scratch = scratch;
+        // a copy that does not fit refuses the layer, unless the row-stationary kernel, which needs none, has it on larger maps
+        a.in_place = scratch && (size_t)kvol * cc * co * elt > scratch_bytes && dense_shape_ok(cc, co, dt) &&
+                             dense_pays(side, kvol, total_links, cc) ? 1 : 0;
         a.scratch_bytes = scratch_bytes;
         const uint64_t fb = (uint64_t)side.n_src * cc * elt;
         a.f_bytes = (uint32_t)fb;

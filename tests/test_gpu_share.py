@@ -1,0 +1,50 @@
+"""Small launches of the wavefront-private kernel (csrc/sp_conv.hip): four wavefronts a sub-tile with weights read as they are
+stored and from the copy, one wavefront a sub-tile, and where the row-stationary and the split kernel begin.  Against fp64: fp32
+sums of up to 27 * 128 products (bound 1e-6 of the rms, measured up to 4e-7), bf16 results rounded once (2^-9 of the value, and
+the sums' error)."""
+import pytest
+import torch
+
+from test_gpu_parity import sp  # noqa: F401  (the binding fixture)
+from test_gpu_split import cloud, fwd64
+
+pytestmark = pytest.mark.gpu
+F, B = torch.float32, torch.bfloat16
+
+
+@pytest.mark.parametrize("n,bits,cin,cout,dt,kernel", [
+    (1, 2, 16, 16, F, "wave"), (63, 2, 32, 32, B, "wave"), (65, 3, 64, 64, B, "wave"), (100, 2, 64, 64, F, "wave"),     # full and nearly empty sub-tiles
+    (1500, 4, 16, 48, F, "wave"), (1500, 6, 32, 64, F, "wave"), (4096, 4, 64, 128, B, "wave"), (3000, 4, 128, 256, B, "wave"),
+    (16384, 4, 64, 128, B, "wave"), (16385, 5, 128, 64, B, "wave"),                                                        # as many as fit at once, one more
+    (16384, 5, 64, 64, F, "wave"), (16385, 5, 64, 64, F, "split"), (32768, 6, 32, 64, F, "wave"), (32769, 6, 32, 64, F, "split"),
+    (49152, 5, 32, 32, F, "wave"), (49153, 5, 32, 32, F, "wave"), (81984, 6, 16, 16, F, "wave"),
+    (24000, 5, 128, 256, B, "wave"), (16384, 4, 128, 256, B, "dense"), (64000, 5, 64, 64, B, "dense")])
+def test_launch_sizes(sp, n, bits, cin, cout, dt, kernel):  # noqa: F811
+    c, km, g = cloud(sp, n, bits, n + cin)
+    assert sp.sp_conv_kernel_name(km, cin, cout, dt) == "gather_%s_kernel" % kernel
+    x, w = torch.randn((n, cin), device="cuda", generator=g).to(dt), torch.randn((27, cout, cin), device="cuda", generator=g).to(dt)
+    y = torch.full((n, cout), float("nan"), device="cuda", dtype=dt)
+    got = sp.sp_conv_fwd(km, x, w)
+    sp.sp_conv_fwd_noalloc(km, x, w, y)
+    assert torch.equal(y, got)
+    for got, want in ((got, fwd64(km, x, w)), (sp.sp_conv_bwd_data(km, x, w.transpose(1, 2).contiguous()), fwd64(km, x, w.flip(0)))):
+        err, rms = (got.double() - want).abs(), want.square().mean().sqrt()
+        if dt == B:
+            assert bool((err <= want.abs() * 2.0 ** -8 + rms * 1e-5).all())
+        else:
+            assert float(err.square().mean().sqrt() / rms) <= 1e-6
+
+
+def test_weights_beyond_the_static_scratch(sp):  # noqa: F811
+    """K = 5, 64 -> 512 and 128 -> 320 in bf16: 8 and 10 MB of weights, read where they are stored by the allocation-free call."""
+    for n, cin, cout in ((500, 64, 512), (500, 128, 320), (20000, 128, 256)):
+        c, _, g = cloud(sp, n, 5, n)
+        km, _ = sp.sp_kmap_build(c, 5, 1, 1)
+        x, w = torch.randn((n, cin), device="cuda", generator=g).to(B), torch.randn((125, cout, cin), device="cuda", generator=g).to(B)
+        y = torch.full((n, cout), float("nan"), device="cuda", dtype=B)
+        if sp.sp_conv_kernel_name(km, cin, cout, B) == "gather_wave_kernel" and km.total < n * 125 * (0.06 if cin == 128 else 0.25):
+            with pytest.raises(sp.SpError):                   # a map whose layer the row-stationary kernel would not have had
+                sp.sp_conv_fwd_noalloc(km, x, w, y)
+            continue
+        sp.sp_conv_fwd_noalloc(km, x, w, y)
+        assert torch.equal(y, sp.sp_conv_fwd(km, x, w))

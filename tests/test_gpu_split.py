@@ -38,9 +38,9 @@ def fwd64(km, x, w):
     return y
 
 
-@pytest.mark.parametrize("n,bits,cin,cout", [(1, 2, 64, 64), (63, 3, 64, 64), (64, 2, 32, 64), (65, 2, 64, 128), (129, 3, 32, 64),   # 64-row tiles
-                                             (16257, 5, 64, 64), (16384, 6, 32, 64), (16513, 5, 64, 128),                          # .. 128-row tiles
-                                             (1100, 4, 128, 128), (20000, 5, 100, 128),                                            # slices past the last channel
+@pytest.mark.parametrize("n,bits,cin,cout", [(8193, 5, 64, 128), (16257, 5, 64, 128), (1100, 4, 128, 128), (1217, 4, 100, 128),        # 64-row tiles
+                                             (16449, 5, 64, 64), (32769, 6, 32, 64), (16513, 5, 64, 128),                          # .. 128-row tiles
+                                             (20000, 5, 100, 128),                                                                 # slices past the last channel
                                              (65536, 5, 96, 96), (65537, 6, 24, 40), (70000, 5, 48, 48), (70001, 5, 36, 100), (66000, 6, 128, 32)])
 def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
     c, km, g = cloud(sp, n, bits, n + cin)
@@ -57,7 +57,7 @@ def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
 def test_values_beyond_bf16(sp, cin, cout):  # noqa: F811
     """Infinities, NaN and values that round to a bf16 infinity give what fp32 multiply-adds give, and only where they reach;
     subnormal pieces keep their places."""
-    c, km, g = cloud(sp, 3000, 4, 5)
+    c, km, g = cloud(sp, 40000, 5, 5)
     x, w = torch.randn((km.n_in, cin), device="cuda", generator=g), torch.randn((27, cout, cin), device="cuda", generator=g)
     x[5, 3], x[100, 7], x[200, 1], x[300, 2], w[3, 5, 6] = float("inf"), float("nan"), 3.4e38, -float("inf"), 1e38
     want = fwd64(km, x, w)
