@@ -101,43 +101,60 @@ __device__ __forceinline__ StripPlan strip_plan(const PlanArgs& pa, int s, int c
     return sp;
 }
 
-// dW[k][e] = sum of offset k's partial blocks, strip by strip, in a fixed order: 16 interleaved running sums
-// per element, each over every 16th block, then added in order 0..15.  grid (per/64, kvol); block = 16 lanes
-// x 4 elements each x 16 block slices.
+// dW[k][e] = sum of offset k's partial blocks, strip by strip, in a fixed order: G interleaved running sums per element, each
+// over every G-th block, then added in order 0..G-1.  grid (per * G / 1024, kvol); block = 256 / G lanes x 4 elements each x G
+// block slices; a thread's loads are requested four at a time.  G = 16 where an offset has many blocks, 4 where it has
+// few: 256 -> 256 bf16 at 55 k rows, 17 blocks an offset of 256 KB, 40 us with G = 16 and a load at a time, 21 so.
 // P: type of the partial blocks and of the sums (double on the fp32 path, see wgrad_staged_kernel).
 // first / count [S8][kvol]: number of offset k's first partial block in strip s and how many it has (written by
 // the staged kernel).  A block is cout_p x cin_p (per elements), the real cout x cin channels of it are written.
-template <typename P>
+template <typename P, int G>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const P* __restrict__ part,
                                                            const int32_t* __restrict__ first,
                                                            const int32_t* __restrict__ count, int S8, int kvol, int per,
                                                            int cin_p, int cin, int cout, float* __restrict__ dw) {
     typedef P Px4 __attribute__((ext_vector_type(4)));
-    constexpr int kMaxStrips = 64;
-    __shared__ int s_first[kMaxStrips], s_count[kMaxStrips];
-    __shared__ Px4 red[16][16];
+    constexpr int kMaxStrips = 64, kLanes = 256 / G, kU = 4;
+    __shared__ int s_base[kMaxStrips], s_end[kMaxStrips];  // block j of the offset is block s_base + j of the strip with j < s_end
+    __shared__ Px4 red[G][kLanes];
     const int k = blockIdx.y;
-    const int el = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const int e = (blockIdx.x * 16 + el) * 4;
-    for (int s = threadIdx.x; s < S8; s += 256) {
-        s_first[s] = first[s * kvol + k];
-        s_count[s] = count[s * kvol + k];
+    const int el = threadIdx.x % kLanes, grp = threadIdx.x / kLanes;
+    const int e = (blockIdx.x * kLanes + el) * 4;
+    if (threadIdx.x < 64) {
+        const int s = threadIdx.x, c = s < S8 ? count[s * kvol + k] : 0;
+        int inc = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(inc, d, 64);
+            if (s >= d) inc += t;
+        }
+        s_base[s] = (s < S8 ? first[s * kvol + k] : 0) - (inc - c);
+        s_end[s] = inc;
     }
     __syncthreads();
+    const int n = s_end[S8 - 1];
     Px4 sum = {0, 0, 0, 0};
-    int n = 0;
-    for (int s = 0; s < S8; ++s) {
-        const int f = s_first[s], c = s_count[s];
-        for (int j = (grp - n) & 15; j < c; j += 16)
-            sum += *reinterpret_cast<const Px4*>(part + (size_t)(f + j) * per + e);
-        n += c;
+    int s = 0;
+    for (int j0 = grp; j0 < n; j0 += kU * G) {
+        Px4 v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int j = j0 + u * G;
+            v[u] = Px4{0, 0, 0, 0};
+            if (j < n) {
+                while (j >= s_end[s]) ++s;
+                v[u] = *reinterpret_cast<const Px4*>(part + (size_t)(s_base[s] + j) * per + e);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) sum += v[u];
     }
     red[grp][el] = sum;
     __syncthreads();
     if (grp == 0) {
         Px4 t = red[0][el];
 #pragma unroll
-        for (int i = 1; i < 16; ++i) t += red[i][el];
+        for (int i = 1; i < G; ++i) t += red[i][el];
         // 4 elements of one row: padded rows are whole multiples of 16 channels
         const int co = e / cin_p, ci = e - co * cin_p;
         float* out = dw + (size_t)k * cin * cout + (size_t)co * cin + ci;
@@ -625,12 +642,10 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
     a.pair_bytes = (uint32_t)((uint64_t)kvol * m->pair_stride * 4);
     const int64_t wgs = (int64_t)pa.S8 * nc * pa.tiles;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(Cfg::kThreads), Cfg::kLds, s, a);
-    if constexpr (Cfg::kIsF32)
-        hipLaunchKernelGGL(wgrad_reduce_kernel<double>, dim3(per / 64, kvol), dim3(256), 0, s, ptr<double>(part), a.first,
-                           a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
-    else
-        hipLaunchKernelGGL(wgrad_reduce_kernel<float>, dim3(per / 64, kvol), dim3(256), 0, s, ptr<float>(part), a.first,
-                           a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
+    typedef typename std::conditional<Cfg::kIsF32, double, float>::type P;
+    const bool few = slots <= 32 * kvol;  // at most 32 blocks an offset on average
+    hipLaunchKernelGGL((few ? wgrad_reduce_kernel<P, 4> : wgrad_reduce_kernel<P, 16>), dim3(per / (few ? 256 : 64), kvol), dim3(256), 0, s,
+                       ptr<P>(part), a.first, a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
     SP_HIP(hipGetLastError());
     return SP_OK;
 }
