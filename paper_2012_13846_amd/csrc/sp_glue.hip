@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void column_sums_kernel(const T* __restri
 }
 
 // Adds the block partials in double, in a fixed order: 32 interleaved running sums per channel (block b goes
-// to sum b % 32), then added 0..31.  Block = 32 channels x 32 slices.
+// to sum b % 32), then added 0..31.  Block = 32 channels x 32 slices.  (The loads one by one: 7 us for 512 blocks, 4.7 so.)
 // MODE 0: mean / rstd (the partials are sums of deviations from `shift[ch]`).  MODE 1: dbeta (sum 0) /
 // dgamma (sum 1).
 template <int MODE, typename T>
@@ -91,11 +91,26 @@ __global__ __launch_bounds__(1024) void column_sums_final_kernel(const float* __
     const int cx = threadIdx.x & 31, slice = threadIdx.x >> 5;
     const int ch = blockIdx.x * 32 + cx;
     double s0 = 0.0, s1 = 0.0;
-    if (ch < c)
-        for (int64_t b = slice; b < nblk; b += 32) {
-            s0 += (double)partial[((size_t)b * 2 + 0) * c + ch];
-            s1 += (double)partial[((size_t)b * 2 + 1) * c + ch];
+    if (ch < c) {
+        // the loads of eight blocks at a time, without a condition: 512 blocks are two trips
+        const float* p = partial + ch;
+        const int last = (int)nblk - 1;
+        for (int b0 = slice; b0 <= last; b0 += 32 * 8) {
+            float v0[8], v1[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const size_t at = (size_t)min(b0 + 32 * i, last) * 2 * c;
+                v0[i] = p[at];
+                v1[i] = p[at + c];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const bool in = b0 + 32 * i <= last;
+                s0 += in ? (double)v0[i] : 0.0;
+                s1 += in ? (double)v1[i] : 0.0;
+            }
         }
+    }
     red[0][slice][cx] = s0;
     red[1][slice][cx] = s1;
     __syncthreads();
@@ -159,13 +174,15 @@ __device__ __forceinline__ Vec<T> load_vec(const T* p, size_t elem) {
 // Same sums as column_sums_kernel.  Thread = (row lane, 16-byte channel group); tpr = c / kN threads cover a
 // row, 256 / tpr rows are read per pass (tpr need not divide 256: the spare threads idle).  The block's rows
 // are rows [blockIdx.x * rows_per_block, ...).  Row lanes are added in lane order.
+// MODE 1 with relu leaves a byte per 16-byte group, which of its elements have y > 0, so that the pass behind it need not read
+// y again (7 passes over the rows become 6 and an eighth).
 template <typename T, int MODE>
 __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __restrict__ x, const T* __restrict__ y,
                                                                    const T* __restrict__ dy, int64_t n, int c,
                                                                    int64_t rows_per_block,
                                                                    const float* __restrict__ mean,
                                                                    const float* __restrict__ rstd, int relu,
-                                                                   float* __restrict__ partial) {
+                                                                   float* __restrict__ partial, uint8_t* __restrict__ live) {
     constexpr int kN = Vec<T>::kN;
     extern __shared__ float red[];  // [2][row lanes][c]
     const int tpr = c / kN, lanes = kThreads / tpr;
@@ -190,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __re
             }
         }
         auto raw = [&](const T* p, size_t e) { return *reinterpret_cast<const u32x4*>(p + e); };
-        auto add_row = [&](const u32x4& rx, const u32x4& rg, const u32x4& ry) __attribute__((always_inline)) {
+        auto add_row = [&](const u32x4& rx, const u32x4& rg, const u32x4& ry, size_t e) __attribute__((always_inline)) {
             Vec<T> xv, gv, yv;
             unpack(rx, xv);
             if (MODE == 0) {
@@ -203,13 +220,16 @@ __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __re
             } else {
                 unpack(rg, gv);
                 unpack(ry, yv);
+                uint32_t bits = 0;
 #pragma unroll
                 for (int i = 0; i < kN; ++i) {
                     float g = gv.v[i];
                     if (relu && !(yv.v[i] > 0.f)) g = 0.f;
+                    else bits |= 1u << i;
                     s0[i] += g;
                     s1[i] += g * (xv.v[i] - m[i]) * rs[i];
                 }
+                if (relu) live[e / kN] = (uint8_t)bits;
             }
         };
         // 4 rows' loads are requested before the first is used (the rows are still added in row order)
@@ -228,14 +248,14 @@ __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __re
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add_row(rx[u], rg[u], ry[u]);
+            for (int u = 0; u < 4; ++u) add_row(rx[u], rg[u], ry[u], (size_t)(r + u * lanes) * c + (size_t)cg * kN);
         }
         for (; r < row_end; r += lanes) {
             const size_t e = (size_t)r * c + (size_t)cg * kN;
             const u32x4 rx = raw(x, e);
             const u32x4 rg = MODE == 1 ? raw(dy, e) : rx;
             const u32x4 ry = MODE == 1 && relu ? raw(y, e) : rg;
-            add_row(rx, rg, ry);
+            add_row(rx, rg, ry, e);
         }
 #pragma unroll
         for (int i = 0; i < kN; ++i) {
@@ -273,21 +293,30 @@ __global__ __launch_bounds__(kThreads) void bn_apply_vec_kernel(const T* __restr
         g[j] = gamma[ch + j];
         b[j] = beta[ch + j];
     }
-    for (int64_t i = i0; i < chunks; i += stride) {
-        const Vec<T> xv = load_vec(x, (size_t)i * kN);
-        Vec<T> o;
+    constexpr int kU = 4;  // groups requested at a time
+    for (int64_t i = i0; i < chunks; i += kU * stride) {
+        u32x4 rx[kU];
 #pragma unroll
-        for (int j = 0; j < kN; ++j) {
-            float v = (xv.v[j] - m[j]) * k[j] * g[j] + b[j];
-            if (relu) v = fmaxf(v, 0.f);
-            o.v[j] = v;
+        for (int u = 0; u < kU; ++u)
+            if (i + u * stride < chunks) rx[u] = *reinterpret_cast<const u32x4*>(x + (size_t)(i + u * stride) * kN);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (i + u * stride >= chunks) break;
+            Vec<T> xv, o;
+            unpack(rx[u], xv);
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {
+                float v = (xv.v[j] - m[j]) * k[j] * g[j] + b[j];
+                if (relu) v = fmaxf(v, 0.f);
+                o.v[j] = v;
+            }
+            *reinterpret_cast<u32x4*>(y + (size_t)(i + u * stride) * kN) = pack(o);
         }
-        *reinterpret_cast<u32x4*>(y + (size_t)i * kN) = pack(o);
     }
 }
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __restrict__ x, const T* __restrict__ y,
+__global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __restrict__ x, const uint8_t* __restrict__ live,
                                                                     const T* __restrict__ dy, T* __restrict__ dx,
                                                                     int64_t n, int c, const float* __restrict__ gamma,
                                                                     const float* __restrict__ mean,
@@ -311,20 +340,32 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __r
         dg[j] = dgamma[ch + j];
         db[j] = dbeta[ch + j];
     }
-    for (int64_t i = i0; i < chunks; i += stride) {
-        const size_t e = (size_t)i * kN;
-        const Vec<T> xv = load_vec(x, e), gv = load_vec(dy, e);
-        Vec<T> yv = gv;
-        if (relu) yv = load_vec(y, e);
-        Vec<T> o;
+    constexpr int kU = 4;  // groups requested at a time
+    for (int64_t i = i0; i < chunks; i += kU * stride) {
+        u32x4 rx[kU], rg[kU];
+        uint32_t bits[kU];
 #pragma unroll
-        for (int j = 0; j < kN; ++j) {
-            float g = gv.v[j];
-            if (relu && !(yv.v[j] > 0.f)) g = 0.f;
-            const float xhat = (xv.v[j] - m[j]) * k[j];
-            o.v[j] = ga[j] * k[j] * (g - (db[j] + xhat * dg[j]) * inv_n);
+        for (int u = 0; u < kU; ++u) {
+            const int64_t q = i + u * stride;
+            if (q >= chunks) continue;
+            rx[u] = *reinterpret_cast<const u32x4*>(x + (size_t)q * kN);
+            rg[u] = *reinterpret_cast<const u32x4*>(dy + (size_t)q * kN);
+            bits[u] = relu ? live[q] : 0xffu;
         }
-        *reinterpret_cast<u32x4*>(dx + (size_t)i * kN) = pack(o);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (i + u * stride >= chunks) break;
+            Vec<T> xv, gv, o;
+            unpack(rx[u], xv);
+            unpack(rg[u], gv);
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {
+                const float g = bits[u] >> j & 1u ? gv.v[j] : 0.f;
+                const float xhat = (xv.v[j] - m[j]) * k[j];
+                o.v[j] = ga[j] * k[j] * (g - (db[j] + xhat * dg[j]) * inv_n);
+            }
+            *reinterpret_cast<u32x4*>(dx + (size_t)(i + u * stride) * kN) = pack(o);
+        }
     }
 }
 
@@ -615,6 +656,10 @@ inline unsigned stream_blocks(int64_t total) {
     return (unsigned)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
 }
 
+// Normalisation passes: a thread keeps its channels' 32 to 40 parameters, 160 bytes, for several 16-byte groups (a group a thread
+// and y read again: 25 us a layer of the 8-layer stack's backward pass, 21 so; both passes run at 5.0-5.6 TB/s).
+inline unsigned apply_blocks(int64_t total) { return std::min(stream_blocks(total), 2048u); }
+
 // vector kernels: whole 16-byte groups per row, at most 256 of them, 16-byte aligned base pointers
 template <typename T>
 bool vec_ok(int c, const void* p0, const void* p1, const void* p2, const void* p3) {
@@ -642,7 +687,7 @@ int bn_fwd_typed(const void* x, int64_t n, int c, const float* gamma, const floa
             hipLaunchKernelGGL((column_sums_vec_kernel<T, 0>), dim3((unsigned)nblk), dim3(kThreads),
                                (size_t)2 * lanes * c * 4, s, static_cast<const T*>(x), (const T*)nullptr,
                                (const T*)nullptr, n, c, rpb, (const float*)nullptr, (const float*)nullptr, 0,
-                               ptr<float>(partial));
+                               ptr<float>(partial), (uint8_t*)nullptr);
         } else {
             hipLaunchKernelGGL((column_sums_kernel<T, 0>), dim3((unsigned)nblk), dim3(kThreads), 0, s,
                                static_cast<const T*>(x), (const T*)nullptr, (const T*)nullptr, n, c,
@@ -653,7 +698,7 @@ int bn_fwd_typed(const void* x, int64_t n, int c, const float* gamma, const floa
                        nblk, n, c, eps, static_cast<const T*>(x), mean, rstd);
     if (n > 0) {
         if (vec)
-            hipLaunchKernelGGL(bn_apply_vec_kernel<T>, dim3(stream_blocks(n * c / (16 / (int64_t)sizeof(T)))),
+            hipLaunchKernelGGL(bn_apply_vec_kernel<T>, dim3(apply_blocks(n * c / (16 / (int64_t)sizeof(T)))),
                                dim3(kThreads), 0, s, static_cast<const T*>(x), static_cast<T*>(y),
                                n * c / (16 / (int64_t)sizeof(T)), c, gamma, beta, mean, rstd, relu);
         else
@@ -670,14 +715,16 @@ int bn_bwd_typed(const void* x, const void* y, const void* dy, int64_t n, int c,
     const bool vec = vec_ok<T>(c, x, y, dy, dx);
     const int64_t rpb = vec ? vec_rows_per_block(n) : kSlabRows;
     const int64_t nblk = (n + rpb - 1) / rpb;
-    Buf partial = dev_alloc((size_t)(nblk ? nblk : 1) * 2 * c * 4, s);
+    const size_t sum_bytes = (size_t)(nblk ? nblk : 1) * 2 * c * 4;
+    Buf partial = dev_alloc(sum_bytes + (vec && relu ? (size_t)n * c / (16 / sizeof(T)) : 0), s);
     if (!partial) return SP_ERR_ALLOC;
+    uint8_t* live = ptr<uint8_t>(partial) + sum_bytes;
     if (nblk > 0) {
         if (vec) {
             const int lanes = kThreads / (c / (16 / (int)sizeof(T)));
             hipLaunchKernelGGL((column_sums_vec_kernel<T, 1>), dim3((unsigned)nblk), dim3(kThreads),
                                (size_t)2 * lanes * c * 4, s, static_cast<const T*>(x), static_cast<const T*>(y),
-                               static_cast<const T*>(dy), n, c, rpb, mean, rstd, relu, ptr<float>(partial));
+                               static_cast<const T*>(dy), n, c, rpb, mean, rstd, relu, ptr<float>(partial), live);
         } else {
             hipLaunchKernelGGL((column_sums_kernel<T, 1>), dim3((unsigned)nblk), dim3(kThreads), 0, s,
                                static_cast<const T*>(x), static_cast<const T*>(y), static_cast<const T*>(dy), n, c, mean,
@@ -688,8 +735,8 @@ int bn_bwd_typed(const void* x, const void* y, const void* dy, int64_t n, int c,
                        nblk, n, c, 0.f, (const T*)nullptr, dbeta, dgamma);
     if (n > 0) {
         if (vec)
-            hipLaunchKernelGGL(bn_bwd_apply_vec_kernel<T>, dim3(stream_blocks(n * c / (16 / (int64_t)sizeof(T)))),
-                               dim3(kThreads), 0, s, static_cast<const T*>(x), static_cast<const T*>(y),
+            hipLaunchKernelGGL(bn_bwd_apply_vec_kernel<T>, dim3(apply_blocks(n * c / (16 / (int64_t)sizeof(T)))),
+                               dim3(kThreads), 0, s, static_cast<const T*>(x), live,
                                static_cast<const T*>(dy), static_cast<T*>(dx), n, c, gamma, mean, rstd, dgamma, dbeta,
                                relu);
         else

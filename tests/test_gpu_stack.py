@@ -219,3 +219,28 @@ def test_stack_free_running_loss_close_to_oracle(sp):
     loss, _ = sp.sp_softmax_ce(sp.sp_linear_fwd(pooled, dev(w_fc), dev(np.zeros(40, np.float32))), dev(labels))
     print("free-running loss", float(loss.item()), "oracle", LOSS)
     assert abs(float(loss.item()) - LOSS) <= 0.03 * abs(LOSS)
+
+
+@pytest.mark.parametrize("n,c", [(1, 8), (255, 24), (257, 64), (1025, 2048), (4099, 136), (33000, 512)])
+@pytest.mark.parametrize("dt,relu", [(torch.bfloat16, True), (torch.bfloat16, False), (torch.float32, True)])
+def test_normalisation_of_whole_groups(sp, n, c, dt, relu):
+    """Rows, groups of 16 bytes and blocks of partial sums around what a thread takes at a time, y kept as a bit per element by the
+    backward pass; against fp64 on the same rounded inputs (one rounding of bf16, fp32 sums of up to 33000 rows)."""
+    g = torch.Generator(device="cuda").manual_seed(n + c)
+    x, dy = (torch.randn((n, c), device="cuda", generator=g).to(dt) for _ in range(2))
+    gamma, beta = 1 + 0.1 * torch.randn(c, device="cuda", generator=g), 0.1 * torch.randn(c, device="cuda", generator=g)
+    y, mean, rstd = sp.sp_bn_relu_fwd(x, gamma, beta, 1e-5, relu)
+    dx, dgamma, dbeta = sp.sp_bn_relu_bwd(x, y, dy, gamma, mean, rstd, relu)
+    X = x.double()
+    m, r = X.mean(0), 1 / (X.var(0, unbiased=False) + 1e-5).sqrt()
+    xhat = (X - m) * r
+    want = xhat * gamma.double() + beta.double()
+    want = want.clamp_min(0) if relu else want
+    tol = dict(rtol=2.0 ** -8, atol=1e-5) if dt == torch.bfloat16 else dict(rtol=1e-5, atol=1e-5)
+    assert torch.allclose(y.double(), want, **tol)
+    G = torch.where(y > 0, dy, torch.zeros_like(dy)).double() if relu else dy.double()
+    scale = float(n) ** 0.5
+    assert torch.allclose(dbeta.double(), G.sum(0), rtol=1e-5, atol=1e-5 * scale)
+    assert torch.allclose(dgamma.double(), (G * xhat).sum(0), rtol=1e-5, atol=1e-5 * scale)
+    want = gamma.double() * r * (G - (G.sum(0) + xhat * (G * xhat).sum(0)) / n)
+    assert torch.allclose(dx.double(), want, rtol=tol["rtol"], atol=1e-4 if n > 1 else 1e-2)
