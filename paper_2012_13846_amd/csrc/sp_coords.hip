@@ -10,10 +10,11 @@
 // A set of half the resolution (floor step = twice the parent's lattice step) whose parent is a grid needs no atomics at all: a
 // block of the parent's grid holds two coarse cells whole, so one thread sees all rows of a cell (mark_coarse_kernel) and
 // knows the first of them; number and inverse read what it left.
-// number: from 65537 to 2^21 rows in two passes over tiles of rows (firsts_kernel, rank_kernel), otherwise in one: every block of rows counts its first occurrences, gets the count of all earlier blocks by
-// decoupled look-back, ranks its rows with ballots and writes coordinates + row numbers; the last block writes the
-// row count N to device memory for later kernels and to a mail slot for the host.  inverse: the row number of every
-// source row.  The host learns N when it first asks (coords_resolve).
+// number: from 65537 to 2^21 rows in two passes over tiles of rows (firsts_kernel, rank_kernel), otherwise in one: every block of
+// rows counts its first occurrences, gets the count of all earlier blocks by decoupled look-back, ranks its rows with ballots
+// and writes coordinates + row numbers; the last block writes the row count N to device memory for later kernels and to a
+// mail slot for the host.  inverse: the row number of every source row.  The host learns N when it first asks
+// (coords_resolve).
 #include <algorithm>
 
 #include "sp_hash.h"

@@ -31,7 +31,7 @@ __device__ __forceinline__ float load_f32(const bf16_t* p) { return __uint_as_fl
 
 // Work decomposition.  Offset k's links are sorted by row on one side, so the j-th fraction of every
 // offset's list covers about the same rows (and, on the other side, their spatial neighbours).  The lists are
-// cut into S8 "strips" (the host uses 8, one per XCD): strip s is, for every offset in turn, the s-th 1/S8 of
+// cut into S8 "strips" (the host uses 8, one per XCD, fewer for short lists): strip s is, for every offset in turn, the s-th 1/S8 of
 // its list; the concatenation of these stretches is the strip's link sequence.  Workgroup i runs on XCD i % 8,
 // so a strip's rows, touched by up to 27 offsets, are fetched by one XCD.  A strip's sequence is cut into nc
 // chunks of C links, one workgroup each (times the channel tiles): equal work whatever the offsets'
@@ -228,10 +228,10 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK) void wgrad_staged_kernel(Stage
     constexpr int kLoadsA = Cfg::kLoadsA, kLoadsB = Cfg::kLoadsB, kThreads = Cfg::kThreads;
     extern __shared__ __align__(16) unsigned char smem[];
 
-    // workgroup -> (strip, chunk, channel tile): XCD = id % 8 takes strips XCD, XCD + 8, ... in that order
+    // workgroup -> (strip, chunk, channel tile): with 8 strips and one tile XCD = id % 8 takes strip XCD
     const PlanArgs& pa = a.plan;
     const int tile = blockIdx.x % pa.tiles, q0 = blockIdx.x / pa.tiles;
-    const int q = q0 >> 3, strip = (q0 & 7) + 8 * (q / pa.nc), chunk = q % pa.nc;
+    const int strip = q0 % pa.S8, chunk = q0 / pa.S8;
     const int cb = chunk * pa.C, ce = cb + pa.C;  // this chunk's positions in the strip's link sequence
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wk = wave % WK, wci = (wave / WK) % WCI, wco = wave / (WK * WCI);
@@ -609,7 +609,10 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
     // Strips: one per XCD.  (More strips, sized so that a strip's rows fit an XCD's L2, were measured slower on
     // every workload, 4-19 %: each strip adds one partial block per offset, and the rows' L2 hits did not pay for
     // that traffic.  Fewer than one per XCD, with the chunks dealt to the XCDs in turn, were 1-12 % slower too.)
-    pa.S8 = 8;
+    // Short lists: fewer, so that an offset's stretch is not shorter than a step.  Every stretch is a piece of its own, with a pipeline to
+    // fill and a block to write (whole call, fp32 16 -> 16 on 0.8 k, 4.6 k and 13 k links 52, 24 and 17 us with 8 strips, 18, 11
+    // and 12 so; bf16 64 -> 64 58, 23 and 19, 16, 12 and 16).
+    for (pa.S8 = 8; pa.S8 > 1 && m->total < (int64_t)pa.S8 * kvol * Cfg::kS;) pa.S8 /= 2;
     // Chunks (one workgroup each): exactly as many as workgroups are resident together, so the launch is one
     // round of equal chunks whatever the size of the map.  A chunk costs a partial block (per * 4 or 8 bytes written
     // and read again) and a pipeline fill; shorter chunks in several rounds were measured slower throughout
@@ -643,7 +646,12 @@ int launch_staged(const sp_kmap* m, const void* x, const void* dy, int cin, int 
     const int64_t wgs = (int64_t)pa.S8 * nc * pa.tiles;
     hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(Cfg::kThreads), Cfg::kLds, s, a);
     typedef typename std::conditional<Cfg::kIsF32, double, float>::type P;
-    const bool few = slots <= 32 * kvol;  // at most 32 blocks an offset on average
+    // Few blocks, and enough elements to fill the chip with a quarter of the threads (blocks of an offset: its links' chunks, and one
+    // or two more per strip; the centre of a sparse map has most of them: fp32 32 -> 64 on 64 k rows with 0.16 M links 12.3 us with 4
+    // slices, 7.3 with 16).
+    int64_t most = 0;
+    for (int k = 0; k < kvol; ++k) most = std::max<int64_t>(most, m->koff[k + 1] - m->koff[k]);
+    const bool few = per >= 256 * 256 || (per >= 128 * 128 && most / C + 2 * pa.S8 <= 64);
     hipLaunchKernelGGL((few ? wgrad_reduce_kernel<P, 4> : wgrad_reduce_kernel<P, 16>), dim3(per / (few ? 256 : 64), kvol), dim3(256), 0, s,
                        ptr<P>(part), a.first, a.count, pa.S8, kvol, per, cin_p, cin, cout, dw);
     SP_HIP(hipGetLastError());

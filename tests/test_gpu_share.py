@@ -35,6 +35,20 @@ def test_launch_sizes(sp, n, bits, cin, cout, dt, kernel):  # noqa: F811
             assert float(err.square().mean().sqrt() / rms) <= 1e-6
 
 
+@pytest.mark.parametrize("n,bits", [(1, 1), (100, 2), (600, 5), (1500, 4), (3000, 4), (20000, 5)])
+@pytest.mark.parametrize("cin,cout,dt", [(16, 16, F), (64, 64, F), (20, 24, F), (64, 64, B), (256, 256, B)])
+def test_weight_gradient_of_short_lists(sp, n, bits, cin, cout, dt):  # noqa: F811
+    """Lists cut into 1, 2, 4 and 8 strips, partial blocks added in 4 and in 16 slices; fp32 sums (double totals in fp32) of up to n
+    products against fp64."""
+    c, km, g = cloud(sp, n, bits, n)
+    x, dy = torch.randn((n, cin), device="cuda", generator=g).to(dt), torch.randn((n, cout), device="cuda", generator=g).to(dt)
+    dw, (pin, pout) = sp.sp_conv_bwd_weight(km, x, dy), km.pairs_strided()
+    for k in range(27):
+        m = int(km.counts[k])
+        want = dy[pout[k, :m].long()].double().T @ x[pin[k, :m].long()].double()
+        assert float((dw[k].double() - want).norm()) <= 1e-6 * float(want.norm()) + 1e-6 * m ** 0.5
+
+
 def test_weights_beyond_the_static_scratch(sp):  # noqa: F811
     """K = 5, 64 -> 512 and 128 -> 320 in bf16: 8 and 10 MB of weights, read where they are stored by the allocation-free call."""
     for n, cin, cout in ((500, 64, 512), (500, 128, 320), (20000, 128, 256)):
