@@ -787,6 +787,7 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     std::unique_ptr<sp_coords> c(new sp_coords);
     c->n_raw = n_src;
     c->ts = tensor_stride;
+    c->on_lattice = floor_step % tensor_stride == 0;
     c->stream = s;
     const bool small = n_src <= kSmallRows;
     // A grid: 32 bytes of dir per source row (128 cells of the box; 4 MB at least), whole scan blocks, and 64 bytes per

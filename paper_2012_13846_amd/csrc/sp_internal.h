@@ -117,6 +117,7 @@ struct sp_coords {
     std::atomic<int> ref{1};
     int64_t n_raw = 0;   // source rows (an upper bound of them when the set was derived from an unresolved one)
     int32_t ts = 1;
+    bool on_lattice = false;  // coordinates are multiples of ts for certain (a caller's rows are only expected to be)
     sp::Buf coords;   // int32 [n][4] (allocated for n_raw rows)
     sp::Buf inverse;  // int32 [n_raw]
     sp::Buf meta;     // int32 [kMetaWords]: the row count n, error bits, ...: what kernels of later builds read

@@ -310,6 +310,8 @@ __device__ __forceinline__ int32_t find_row(const TableView& t, int b, int x, in
 // Output side of a 2 x 2 x 2 stride-2 map whose input set may be a grid: a coarse row's eight children are one half of a block,
 // 32 bytes apart from its pair number (c_out's pairs, valid if c_out is a grid itself), written and counted in one pass over the
 // coarse rows: no table preset, no scattered stores, no counting of the table (0.5 M rows: with child_map_kernel 18 us, now 13).
+// Only for rows that are multiples of the tensor stride for certain: a child is then at its cell's corner plus 0 or one stride per
+// axis, which is what child_map_kernel goes by for the input side.
 __global__ __launch_bounds__(kTileRows) void child_rows_kernel(const int4* __restrict__ c_out, Count cn_out, const int32_t* __restrict__ meta_out,
                                                                const int32_t* __restrict__ pairs, TableView t, int32_t* __restrict__ nbr_out,
                                                                Counts counts, int32_t* __restrict__ done) {
@@ -329,22 +331,6 @@ __global__ __launch_bounds__(kTileRows) void child_rows_kernel(const int4* __res
                 const int2 two = runs[2 * r];
                 v[2 * r] = two.x == kNoRow ? -1 : two.x;
                 v[2 * r + 1] = two.y == kNoRow ? -1 : two.y;
-            }
-            // (Coordinates that are no multiples of the tensor stride: cell_class counts positions towards zero.)
-            const Grid g = load_grid(t.meta);
-            if (t.ts > 1 && (g.x0 % t.ts != 0 || g.y0 % t.ts != 0 || g.z0 % t.ts != 0)) {
-                const int4 c = c_out[o];
-                const int flip = (c.y < 0 && g.x0 % t.ts ? 4 : 0) | (c.z < 0 && g.y0 % t.ts ? 2 : 0) | (c.w < 0 && g.z0 % t.ts ? 1 : 0);
-#pragma unroll
-                for (int bit = 1; bit < 8; bit *= 2)
-                    if (flip & bit)
-#pragma unroll
-                        for (int k = 0; k < 8; ++k)
-                            if (!(k & bit)) {
-                                const int32_t u = v[k];
-                                v[k] = v[k | bit];
-                                v[k | bit] = u;
-                            }
             }
         } else {
             const int4 c = c_out[o];
@@ -908,7 +894,8 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
     const Counts counts = counts_in(work, n_out_ub, kvol);
     int32_t* done = ptr<int32_t>(m->d_counts) + kvol;
     const unsigned nt = (unsigned)(tiles_of(n_out_ub) ? tiles_of(n_out_ub) : 1);
-    if (stride == 2 && kernel_size == 2 && m->c_out->pairs) {
+    // (Rows off the lattice, which a caller may have, are found by their place in the cell on both sides.)
+    if (stride == 2 && kernel_size == 2 && in->on_lattice && m->c_out->pairs) {
         hipLaunchKernelGGL(child_map_kernel, dim3(blocks256(n_in_ub)), dim3(kThreads), 0, s, ptr<int4>(in->coords), cn_in, in->ts, stride,
                            ptr<int32_t>(m->c_out->inverse), cn_out, kvol, (int32_t*)nullptr, ptr<int32_t>(si.nbr));
         hipLaunchKernelGGL(child_rows_kernel, dim3(nt), dim3(kTileRows), 0, s, ptr<int4>(m->c_out->coords), cn_out, ptr<int32_t>(m->c_out->meta),
@@ -980,6 +967,7 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
     SP_HIP(hipGetLastError());
     sp_coords* fine = nullptr;
     SP_TRY(coords_build_impl(ptr<int32_t>(cand), n_cand, nullptr, 1, ts_out, nullptr, s, &fine));
+    fine->on_lattice = in->on_lattice;
 
     // the stride-s convolution's map from the fine rows (inputs) to the coarse rows (outputs) ...
     std::unique_ptr<sp_kmap, int (*)(sp_kmap*)> m(new sp_kmap, sp_kmap_destroy);

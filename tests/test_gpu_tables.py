@@ -133,6 +133,33 @@ def test_sets_of_half_the_resolution(sp, K, ts, shift, resolved):  # noqa: F811
         c, rows, step = co, want["c_out"], 2 * step
 
 
+@pytest.mark.parametrize("ts,shift", [(1, 0), (2, 0), (2, 1), (3, -1), (3, 2)])
+@pytest.mark.parametrize("box", ["wide", "grid, then wide", "grid"])
+def test_both_sides_of_a_cell_map_agree_off_the_lattice(sp, ts, shift, box):  # noqa: F811
+    """2 x 2 x 2, stride 2 on sets whose coordinates are no multiples of the tensor stride: a row's place in its cell decides on both
+    sides, whatever the form of the two tables (boxes too wide for a grid; a parent with a grid under a coarse set without)."""
+    rng = np.random.default_rng(5)
+    some = FULL[:90000] if box == "grid" else FAR[:40000]
+    if box == "grid, then wide":
+        some = np.stack([rng.integers(0, hi, 70000) for hi in (4, 320, 320, 656)], 1).astype(np.int32)
+    near = some + rng.integers(0, 2, (len(some), 4)).astype(np.int32) * np.array([0, 1, 1, 1], np.int32)
+    rows = scaled(np.concatenate([some, near]), ts, shift)
+    rows = rows[np.sort(np.unique(rows, axis=0, return_index=True)[1])]
+    assert len(rows) > 65536
+    # many repeats: room for a grid in the parent's table, none in that of a set made from its distinct rows
+    c = sp.sp_coords_build(dev(np.tile(rows, (24, 1)) if box == "grid, then wide" else rows), ts)
+    assert c.n == len(rows)
+    km, co = sp.sp_kmap_build(c, 2, 2, 1)
+    want = oracle_steps(rows, 2, 2, 1, ts)
+    assert np.array_equal(co.coords().cpu().numpy(), want["c_out"]) and np.array_equal(co.inverse().cpu().numpy(), want["parent"])
+    nbr_out, nbr_in = (t.cpu().numpy() for t in km.table()[:2])
+    k, o = np.nonzero(nbr_out >= 0)
+    assert len(k) == len(rows) == km.total == np.count_nonzero(nbr_in >= 0)
+    assert np.array_equal(nbr_in[k, nbr_out[k, o]], o) and np.array_equal(want["parent"][nbr_out[k, o]], o)
+    if shift == 0:
+        check_map(sp, km, want, len(rows), len(want["c_out"]))
+
+
 @pytest.mark.parametrize("cin,cout,bf16", [(32, 32, False), (128, 128, True), (20, 24, False)])
 @pytest.mark.parametrize("warm", [True, False])
 def test_lists_of_the_input_side_under_capture(sp, cin, cout, bf16, warm):  # noqa: F811
