@@ -1,15 +1,16 @@
 // Link-list gather-GEMM (Eq. 2 and its input gradient) for fp32 layers on the bf16 matrix cores, without giving up fp32
-// precision: every value is the exact sum of three bf16 numbers (8 + 8 + 8 significant bits, the exponent range is the
-// same), and a product of two values is the six partial products that matter,
+// precision: every value, taken 2^24 times, is the exact sum of three bf16 numbers (8 + 8 + 8 significant bits; the exponent range
+// is the same, so without the factor values below 2^-110 would lose bits, and with it a subnormal's last bit, 2^-149, becomes
+// 2^-125, a normal bf16 number), and a product of two values is the six partial products that matter,
 //   x w = x0 w0 + (x0 w1 + x1 w0) + (x1 w1 + x0 w2 + x2 w0)   (+ terms below 2^-24 of it),
 // added smallest first in the matrix cores' fp32 accumulator.  Six bf16 MFMAs of 32 contraction channels take 96
 // cycles where fp32 MFMAs take 256, and leave the vector pipe free meanwhile.
 // Error against fp64 (one MI355X, normal inputs, 27 links of 64 channels, over the result's rms): 1.1e-7 rms, 8.7e-7
 // largest; fp32 MFMAs 1.75e-7 and 1.0e-6 (32 channels 1.1e-7 / 9.8e-7 against 1.4e-7 / 9.3e-7, 128 1.2e-7 / 9.3e-7 against
 // 2.3e-7 / 1.2e-6): a chain of 64 channels is rounded 12 times instead of 64.
-// An infinity, a NaN or a value that rounds to a bf16 infinity makes its link's products NaN.  A workgroup that finds a
-// value that is not finite among its results therefore computes its rows again with fp32 MFMAs (redo below), and what it
-// writes is what those give.
+// An infinity, a NaN or a value of 2^104 and more makes its link's products NaN, and sums of 2^80 (1e24) overflow.  A workgroup
+// that finds a value that is not finite among its sums therefore computes its rows again with fp32 MFMAs (redo below), and what
+// it writes is what those give.
 #include <mutex>
 
 #include "sp_internal.h"
@@ -40,11 +41,18 @@ struct SplitArgs {
     uint32_t f_bytes, w_bytes, list_bytes;
 };
 
-// The three bf16 pieces of two values, nearest even: each remainder is exact in fp32.
+// 2^24, of rows and of weights.  (Two more instructions for every eleven of a pair's split: a layer's three passes and its maps at
+// 0.6 M rows, 64 -> 64, 1427 -> 1449 us.  Without it the error is 2.7e-6 of values around 1e-35 and 2.7e-4 around 1e-37.)
+constexpr float kScale = 16777216.f;
+constexpr float kUnscale = 1.f / kScale / kScale;
+
+// The three bf16 pieces of two values, kScale times, nearest even: each remainder is exact in fp32.
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 __device__ __forceinline__ void split_two(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+    a *= kScale;
+    b *= kScale;
     h = bf16_pair(a, b);
     a -= __uint_as_float(h << 16);
     b -= __uint_as_float(h & 0xffff0000u);
@@ -355,8 +363,8 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
     }
     __syncthreads();
 
-    // whole rows; is any value not finite?
-    auto write = [&]() __attribute__((always_inline)) {
+    // whole rows; is any sum not finite?
+    auto write = [&](float unscale) __attribute__((always_inline)) {
         constexpr int kQuads = Cfg::kCOT / 4;
         const bool whole = a.co % 4 == 0;
         bool bad = false;
@@ -365,7 +373,10 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
             const int64_t row = row0 + r;
             if (row >= a.n_rows) break;
             if (c >= a.co) continue;
-            const f32x4 v = *reinterpret_cast<const f32x4*>(acc + r * Cfg::kStride + (idx % kQuads) * 4);
+            f32x4 v = *reinterpret_cast<const f32x4*>(acc + r * Cfg::kStride + (idx % kQuads) * 4);
+            const float z = (v[0] - v[0]) + (v[1] - v[1]) + (v[2] - v[2]) + (v[3] - v[3]);  // 0, or NaN
+            bad = bad || !(z == 0.f);
+            v *= unscale;
             float* out = a.g + row * a.co + c;
             if (whole) {
                 *reinterpret_cast<f32x4*>(out) = v;
@@ -374,12 +385,10 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
                 for (int i = 0; i < 4; ++i)
                     if (c + i < a.co) out[i] = v[i];
             }
-            const float z = (v[0] - v[0]) + (v[1] - v[1]) + (v[2] - v[2]) + (v[3] - v[3]);  // 0, or NaN
-            bad = bad || !(z == 0.f);
         }
         return bad;
     };
-    if (!__syncthreads_or(write() ? 1 : 0)) return;
+    if (!__syncthreads_or(write(kUnscale) ? 1 : 0)) return;
 
     // ---- redo: the same rows with fp32 MFMAs, one block at a time, each wavefront its own channels
     clear(tid, kThreads);
@@ -407,7 +416,7 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
         }
     }
     __syncthreads();
-    write();
+    write(1.f);
 }
 
 // Weights as stored (element (k, co, cc) at w[k*co*cc + co*s_co + cc*s_cc]) -> their pieces, fragment-major:

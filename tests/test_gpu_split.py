@@ -71,6 +71,21 @@ def test_values_beyond_bf16(sp, cin, cout):  # noqa: F811
     assert float((got - want).norm() / want.norm()) <= 3e-7
 
 
+@pytest.mark.parametrize("size_x,size_w", [(1e-33, 1.0), (1e-35, 1.0), (1e-37, 1e4), (1e-40, 1e30), (1.0, 1e-36), (1e10, 1e-38), (1e30, 1e-37),
+                                           (1e-18, 1e-18), (1e-22, 1e18), (1e30, 1.0), (1e10, 1e14), (1e25, 1e10), (1.0, 1e33)])
+def test_magnitudes(sp, size_x, size_w):  # noqa: F811
+    """Any finite size of either operand: fp32 products and sums carry 24 bits, down to values that are themselves subnormal, as long
+    as the results are normal numbers (fp32 matrix cores, to which the largest results fall back: 2.5e-7 of the rms)."""
+    c, km, g = cloud(sp, 40000, 5, 5)
+    x, w = torch.randn((km.n_in, 64), device="cuda", generator=g) * size_x, torch.randn((27, 64, 64), device="cuda", generator=g) * size_w
+    assert sp.sp_conv_kernel_name(km, 64, 64, torch.float32) == "gather_split_kernel"
+    for got, want in ((sp.sp_conv_fwd(km, x, w), fwd64(km, x, w)), (sp.sp_conv_bwd_data(km, x, w), fwd64(km, x, w.flip(0).transpose(1, 2)))):
+        err, rms = got.double() - want, want.square().mean().sqrt()
+        print("rms error", float(err.square().mean().sqrt() / rms), "largest", float(err.abs().max() / rms))
+        assert float(err.square().mean().sqrt() / rms) <= 3e-7
+        assert float(err.abs().max() / rms) <= 1e-5
+
+
 def test_without_allocations(sp):  # noqa: F811
     """Weights' pieces that fit the static scratch: the bits of sp_conv_fwd; pieces that do not, though the weights would: within
     the parity bound."""
