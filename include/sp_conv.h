@@ -156,7 +156,7 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
  *   - the weight gradient where an operand (its rows padded to 16 bytes) or the pair lists pass 2 GiB;
  *   - layers whose scratch the allocator refuses, if they are of the kind that can do without (forward / data gradient
  *     off the narrow layers' and the wide bf16 kernels, weight gradient of widths that are no multiple of 16); the
- *     others return SP_ERR_ALLOC.
+ *     others return SP_ERR_ALLOC, but for the forward pass of the wide bf16 kernels, which needs no memory.
  *
  *   sp_conv_fwd:        y[o,:]  = sum_k sum_{(i,o) in M_k} W_k   x[i,:]      x [n_in][cin]   -> y  [n_out][cout]
  *   sp_conv_bwd_data:   dx[i,:] = sum_k sum_{(i,o) in M_k} W_k^T dy[o,:]     dy [n_out][cout] -> dx [n_in][cin]

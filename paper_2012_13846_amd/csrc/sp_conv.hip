@@ -42,6 +42,7 @@ struct GatherArgs {
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
     int in_place;      // host-side only: the weights are read where they are stored
+    int may_in_place;  // host-side only: ... if there is no memory for the copy
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
@@ -526,19 +527,19 @@ int launch_wave(GatherArgs a, hipStream_t s) {
     // instead of 1 KB, which saves the copy's launch (fp32 16 -> 16 on 1.5 k rows 9.9 -> 8.4 us, 32 -> 32 11.8 -> 9.7; 32 -> 32 on
     // 32 k rows 16.4 -> 17.9, bf16 64 -> 64 on 1.5 k 11.7 -> 14.4).
     constexpr int kMatrix = CC * COT * (int)sizeof(T);
-    const bool stored = !a.w_transposed && ((share && (kMatrix <= 2048 || (kMatrix <= 4096 && waves <= 256))) || a.in_place);
+    bool stored = !a.w_transposed && ((share && (kMatrix <= 2048 || (kMatrix <= 4096 && waves <= 256))) || a.in_place);
     const int64_t n = (int64_t)a.kvol * a.co_total * CC;
     if (a.scratch && !a.in_place && (size_t)n * sizeof(T) > a.scratch_bytes)  // the same layers at every size of the map
         return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch",
                     (long long)(n * sizeof(T)), a.scratch_bytes);
     Buf wf;
+    if (!stored && !a.scratch) {
+        wf = dev_alloc((size_t)n * sizeof(T), s);
+        stored = !wf && !a.w_transposed && a.may_in_place;
+        if (!wf && !stored) return SP_ERR_ALLOC;
+    }
     if (!stored) {  // fragment-major copy of the weights (also undoes the data gradient's transposition)
-        T* d_wf = static_cast<T*>(a.scratch);
-        if (!d_wf) {
-            wf = dev_alloc((size_t)n * sizeof(T), s);
-            if (!wf) return SP_ERR_ALLOC;
-            d_wf = ptr<T>(wf);
-        }
+        T* d_wf = a.scratch ? static_cast<T*>(a.scratch) : ptr<T>(wf);
         const int s_co = a.w_transposed ? 1 : CC, s_cc = a.w_transposed ? a.co_total : 1;
         hipLaunchKernelGGL((weight_frag_kernel<T, CC, COT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                            static_cast<const T*>(a.w), d_wf, a.kvol, a.co_total, s_co, s_cc);
@@ -870,8 +871,8 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         a.w_transposed = w_transposed ? 1 : 0;
         a.scratch = scratch;
         // a copy that does not fit refuses the layer, unless the row-stationary kernel, which needs none, has it on larger maps
-        a.in_place = scratch && (size_t)kvol * cc * co * elt > scratch_bytes && dense_shape_ok(cc, co, dt) &&
-                             dense_pays(side, kvol, total_links, cc) ? 1 : 0;
+        a.may_in_place = dense_shape_ok(cc, co, dt) && dense_pays(side, kvol, total_links, cc) ? 1 : 0;
+        a.in_place = a.may_in_place && scratch && (size_t)kvol * cc * co * elt > scratch_bytes ? 1 : 0;
         a.scratch_bytes = scratch_bytes;
         const uint64_t fb = (uint64_t)side.n_src * cc * elt;
         a.f_bytes = (uint32_t)fb;

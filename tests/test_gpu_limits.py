@@ -98,3 +98,22 @@ def test_without_memory_for_scratch(sp, cin, cout, bf16):  # noqa: F811
     assert asked
     for a, b in zip(got, want):   # sums of up to 3500 terms in another order; one rounding to bf16
         assert float((a - b).norm() / b.norm()) <= (1e-2 if bf16 else 1e-5)
+
+
+@pytest.mark.parametrize("cin,cout,K", [(64, 64, 3), (64, 128, 3), (128, 64, 3), (128, 256, 3), (64, 192, 5)])
+def test_forward_of_row_stationary_layers_without_memory(sp, cin, cout, K):  # noqa: F811
+    """bf16 layers that the row-stationary kernel, which needs no weight copy, has on larger maps: the forward pass needs no memory
+    on small ones either, and gives the same bits."""
+    c = sp.sp_coords_build(dev(random_coords(3, 900, 7)), 1)
+    km, _ = sp.sp_kmap_build(c, K, 1, 1)
+    assert km.total >= 0.25 * K ** 3 * c.n
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((c.n, cin), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((K ** 3, cout, cin), device="cuda", generator=g).to(torch.bfloat16)
+    want = sp.sp_conv_fwd(km, x, w)
+    sp.sp_set_allocator(lambda nbytes, stream: 0, lambda ptr: None)
+    try:
+        got = sp.sp_conv_fwd(km, x, w)
+    finally:
+        sp.sp_set_allocator()
+    assert torch.equal(got, want)
