@@ -184,7 +184,7 @@ int sp_conv_bwd_weight(const sp_kmap_t* m, const void* d_x, const void* d_dy, fl
  *     results of the tile kernel, slower;
  *   - the rest run on the plain kernel: correct, slow, fp32 sums in another order than sp_conv_fwd's.
  * All calls on one GPU share that array: calls that overlap in time on one GPU (different streams) race; calls on one
- * stream are ordered and safe.  The array's contents are rewritten by every call, nothing in it needs to start at zero.
+ * stream are ordered and safe.  (bf16 layers that gather_dense_kernel has at any size of the map do not touch it.)  The array's contents are rewritten by every call, nothing in it needs to start at zero.
  * Lists that the map makes on first use (the input side of strided maps and even kernels) and that do not exist yet
  * when a call is captured are built outside the graph, on a stream of the library's own; the call waits for them. */
 int sp_conv_fwd_noalloc(const sp_kmap_t* m, const void* d_x, const void* d_w, void* d_y, int32_t cin, int32_t cout,

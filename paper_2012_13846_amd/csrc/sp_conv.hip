@@ -41,8 +41,7 @@ struct GatherArgs {
     int runs;          // sub-tiles are dealt to the XCDs in runs (xcd_run)
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
-    int in_place;      // host-side only: the weights are read where they are stored
-    int may_in_place;  // host-side only: ... if there is no memory for the copy
+    int may_in_place;  // host-side only: ... instead of a copy into `scratch`, or if there is no memory for one
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
@@ -527,9 +526,9 @@ int launch_wave(GatherArgs a, hipStream_t s) {
     // instead of 1 KB, which saves the copy's launch (fp32 16 -> 16 on 1.5 k rows 9.9 -> 8.4 us, 32 -> 32 11.8 -> 9.7; 32 -> 32 on
     // 32 k rows 16.4 -> 17.9, bf16 64 -> 64 on 1.5 k 11.7 -> 14.4).
     constexpr int kMatrix = CC * COT * (int)sizeof(T);
-    bool stored = !a.w_transposed && ((share && (kMatrix <= 2048 || (kMatrix <= 4096 && waves <= 256))) || a.in_place);
+    bool stored = !a.w_transposed && ((share && (kMatrix <= 2048 || (kMatrix <= 4096 && waves <= 256))) || (a.scratch && a.may_in_place));
     const int64_t n = (int64_t)a.kvol * a.co_total * CC;
-    if (a.scratch && !a.in_place && (size_t)n * sizeof(T) > a.scratch_bytes)  // the same layers at every size of the map
+    if (a.scratch && !a.may_in_place && (size_t)n * sizeof(T) > a.scratch_bytes)  // the same layers at every size of the map
         return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch",
                     (long long)(n * sizeof(T)), a.scratch_bytes);
     Buf wf;
@@ -870,9 +869,10 @@ int conv_gather(const MapSide& side, int kvol, int64_t total_links, const void* 
         a.w = d_w;
         a.w_transposed = w_transposed ? 1 : 0;
         a.scratch = scratch;
-        // a copy that does not fit refuses the layer, unless the row-stationary kernel, which needs none, has it on larger maps
+        // Layers that the row-stationary kernel has on larger maps: it copies no weights, so the allocation-free entry point never
+        // touches its static array for them, and calls on two streams at once do not meet there.  (bf16 64 -> 64 on 1.5 k rows
+        // 14.4 us, 11.7 with a copy, 29 row-stationary.)
         a.may_in_place = dense_shape_ok(cc, co, dt) && dense_pays(side, kvol, total_links, cc) ? 1 : 0;
-        a.in_place = a.may_in_place && scratch && (size_t)kvol * cc * co * elt > scratch_bytes ? 1 : 0;
         a.scratch_bytes = scratch_bytes;
         const uint64_t fb = (uint64_t)side.n_src * cc * elt;
         a.f_bytes = (uint32_t)fb;

@@ -244,3 +244,32 @@ def test_normalisation_of_whole_groups(sp, n, c, dt, relu):
     assert torch.allclose(dgamma.double(), (G * xhat).sum(0), rtol=1e-5, atol=1e-5 * scale)
     want = gamma.double() * r * (G - (G.sum(0) + xhat * (G * xhat).sum(0)) / n)
     assert torch.allclose(dx.double(), want, rtol=tol["rtol"], atol=1e-4 if n > 1 else 1e-2)
+
+
+@pytest.mark.parametrize("n,c,dt", [(4099, 64, torch.bfloat16), (1000, 20, torch.float32)])
+def test_normalisation_with_little_memory(sp, n, c, dt):
+    """The backward pass keeps a bit per element only if it gets the memory; with room for the blocks' sums alone it reads y again:
+    the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x, dy = (torch.randn((n, c), device="cuda", generator=g).to(dt) for _ in range(2))
+    gamma, beta = 1 + 0.1 * torch.randn(c, device="cuda", generator=g), 0.1 * torch.randn(c, device="cuda", generator=g)
+    y, mean, rstd = sp.sp_bn_relu_fwd(x, gamma, beta, 1e-5, True)
+    want = sp.sp_bn_relu_bwd(x, y, dy, gamma, mean, rstd, True)
+    sums, refused, store = [], [], torch.empty(8 << 20, dtype=torch.uint8, device="cuda")
+
+    def alloc(nbytes, stream):
+        if sums and nbytes > sums[0]:
+            refused.append(nbytes)
+            return 0
+        sums.append(nbytes)
+        return store.data_ptr()
+
+    sp.sp_set_allocator(alloc, lambda ptr: None)
+    try:
+        sp.sp_bn_relu_bwd(x, y, dy, gamma, mean, rstd, False)       # what the blocks' sums take
+        got = sp.sp_bn_relu_bwd(x, y, dy, gamma, mean, rstd, True)
+    finally:
+        sp.sp_set_allocator()
+    assert refused
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
