@@ -219,7 +219,7 @@ int sp_pool_bwd(const sp_kmap_t* m, const void* d_dy, const uint8_t* d_arg, void
  *   d_mean / d_rstd [c] are outputs (the backward pass needs them).
  * sp_bn_relu_bwd: with dyh = dy (masked where y <= 0 if relu), xhat = (x - mean) * rstd:
  *   dbeta = sum dyh, dgamma = sum dyh * xhat, dx = gamma * rstd / n * (n * dyh - dbeta - xhat * dgamma).
- *   d_y (the forward output) is only read when relu != 0. */
+ *   d_y (the forward output) is only read when relu != 0: once, if there is memory for a bit per element, else twice. */
 int sp_bn_relu_fwd(const void* d_x, int64_t n, int32_t c, const float* d_gamma, const float* d_beta, float eps,
                    int32_t relu, void* d_y, float* d_mean, float* d_rstd, sp_dtype dt, void* stream);
 int sp_bn_relu_bwd(const void* d_x, const void* d_y, const void* d_dy, int64_t n, int32_t c, const float* d_gamma,

@@ -174,8 +174,8 @@ __device__ __forceinline__ Vec<T> load_vec(const T* p, size_t elem) {
 // Same sums as column_sums_kernel.  Thread = (row lane, 16-byte channel group); tpr = c / kN threads cover a
 // row, 256 / tpr rows are read per pass (tpr need not divide 256: the spare threads idle).  The block's rows
 // are rows [blockIdx.x * rows_per_block, ...).  Row lanes are added in lane order.
-// MODE 1 with relu leaves a byte per 16-byte group, which of its elements have y > 0, so that the pass behind it need not read
-// y again (7 passes over the rows become 6 and an eighth).
+// MODE 1 with relu leaves a byte per 16-byte group (live, if there is memory for them), which of its elements have y > 0, so
+// that the pass behind it need not read y again (7 passes over the rows become 6 and an eighth).
 template <typename T, int MODE>
 __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __restrict__ x, const T* __restrict__ y,
                                                                    const T* __restrict__ dy, int64_t n, int c,
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __re
                     s0[i] += g;
                     s1[i] += g * (xv.v[i] - m[i]) * rs[i];
                 }
-                if (relu) live[e / kN] = (uint8_t)bits;
+                if (live) live[e / kN] = (uint8_t)bits;
             }
         };
         // 4 rows' loads are requested before the first is used (the rows are still added in row order)
@@ -315,8 +315,10 @@ __global__ __launch_bounds__(kThreads) void bn_apply_vec_kernel(const T* __restr
     }
 }
 
+// (y is read only where relu finds no live bits.)
 template <typename T>
-__global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __restrict__ x, const uint8_t* __restrict__ live,
+__global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __restrict__ x, const T* __restrict__ y,
+                                                                    const uint8_t* __restrict__ live,
                                                                     const T* __restrict__ dy, T* __restrict__ dx,
                                                                     int64_t n, int c, const float* __restrict__ gamma,
                                                                     const float* __restrict__ mean,
@@ -350,7 +352,13 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_vec_kernel(const T* __r
             if (q >= chunks) continue;
             rx[u] = *reinterpret_cast<const u32x4*>(x + (size_t)q * kN);
             rg[u] = *reinterpret_cast<const u32x4*>(dy + (size_t)q * kN);
-            bits[u] = relu ? live[q] : 0xffu;
+            bits[u] = live ? live[q] : 0xffu;
+            if (relu && !live) {
+                const Vec<T> yv = load_vec(y, (size_t)q * kN);
+                bits[u] = 0;
+#pragma unroll
+                for (int j = 0; j < kN; ++j) bits[u] |= yv.v[j] > 0.f ? 1u << j : 0u;
+            }
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -716,9 +724,10 @@ int bn_bwd_typed(const void* x, const void* y, const void* dy, int64_t n, int c,
     const int64_t rpb = vec ? vec_rows_per_block(n) : kSlabRows;
     const int64_t nblk = (n + rpb - 1) / rpb;
     const size_t sum_bytes = (size_t)(nblk ? nblk : 1) * 2 * c * 4;
-    Buf partial = dev_alloc(sum_bytes + (vec && relu ? (size_t)n * c / (16 / sizeof(T)) : 0), s);
+    Buf partial = vec && relu ? dev_alloc(sum_bytes + (size_t)n * c / (16 / sizeof(T)), s) : Buf();
+    uint8_t* live = partial ? ptr<uint8_t>(partial) + sum_bytes : nullptr;
+    if (!partial) partial = dev_alloc(sum_bytes, s);  // the least it takes: y is read twice then
     if (!partial) return SP_ERR_ALLOC;
-    uint8_t* live = ptr<uint8_t>(partial) + sum_bytes;
     if (nblk > 0) {
         if (vec) {
             const int lanes = kThreads / (c / (16 / (int)sizeof(T)));
@@ -736,7 +745,7 @@ int bn_bwd_typed(const void* x, const void* y, const void* dy, int64_t n, int c,
     if (n > 0) {
         if (vec)
             hipLaunchKernelGGL(bn_bwd_apply_vec_kernel<T>, dim3(apply_blocks(n * c / (16 / (int64_t)sizeof(T)))),
-                               dim3(kThreads), 0, s, static_cast<const T*>(x), live,
+                               dim3(kThreads), 0, s, static_cast<const T*>(x), static_cast<const T*>(y), live,
                                static_cast<const T*>(dy), static_cast<T*>(dx), n, c, gamma, mean, rstd, dgamma, dbeta,
                                relu);
         else
