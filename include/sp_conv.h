@@ -69,8 +69,9 @@ typedef struct sp_kmap sp_kmap_t;     /* kernel map of one (coords, kernel, stri
  * n_raw may be 0.  *out receives a new handle (caller destroys).
  * Device memory that the handle holds: 20 bytes per source row, and the table: 128 to 256 bytes per source row up to
  * 65536 rows (256 KB at most up to 8192 of them), 96 to 128 up to 2^20 rows, 96 below 2^26, 32 to 64 beyond.  The build
- * itself takes 4 bytes per row more.  Coarser sets made by sp_kmap_build are sized by the row bound of the set that they
- * are made from. */
+ * itself takes 4 bytes per row more, and a bit from 65537 to 2^21 rows.  Coarser sets made by sp_kmap_build are sized by the
+ * row bound of the set that they are made from; those of half its resolution take, in that range, 8 bytes per source row more
+ * while they are built, and 12 with a 2 x 2 x 2 map. */
 int sp_coords_build(const int32_t* d_raw, int64_t n_raw, int32_t tensor_stride, void* stream, sp_coords_t** out);
 
 /* N and the tensor stride.  Asking for N waits (the first time) until the build's numbering kernel has delivered

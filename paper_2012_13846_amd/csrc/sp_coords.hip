@@ -385,7 +385,7 @@ struct Halved {
     const int32_t* cells;
     int ts;
     int32_t* rank_of;      // [2 * blocks of the parent]: row number of a pair's coarse cell
-    int32_t* pair_of;      // [rows]: the pair a row came from
+    int32_t* pair_of;      // [rows]: the pair a row came from; or null
 };
 
 // The parent's grid, block by block: a block of 2 x 2 x 4 cells is two coarse cells, "pair" 2 * block + half.  at[row of the
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(kThreads) void rank_kernel(const int4* __restrict__
                 lattice(co.w - g.z0, t.ts, &qz);
                 t.cells[(int64_t)t.dir[grid_block(g, co.x - g.b0, qx, qy, qz >> 2)] * 16 + grid_run(qx, qy) * 4 + (qz & 3)] = r;
                 hv.rank_of[s] = r;
-                hv.pair_of[r] = s;
+                if (hv.pair_of) hv.pair_of[r] = s;
             } else if (grid) {
                 t.cells[s] = r;
             } else {
@@ -782,7 +782,7 @@ TableView table_view(const sp_coords* c) {
 }
 
 int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_src, int32_t floor_step,
-                      int32_t tensor_stride, const sp_coords* parent, hipStream_t s, sp_coords_t** out) {
+                      int32_t tensor_stride, const sp_coords* parent, bool want_pairs, hipStream_t s, sp_coords_t** out) {
     if (n_src >= (int64_t)1 << 30) return fail(SP_ERR_INVALID_ARG, "too many rows (%lld)", (long long)n_src);
     std::unique_ptr<sp_coords> c(new sp_coords);
     c->n_raw = n_src;
@@ -824,7 +824,7 @@ int coords_build_impl(const int32_t* d_src, int64_t n_src, const int32_t* d_n_sr
     const int64_t n_desc = nb ? nb : 1;
     Buf scratch = small ? Buf() : dev_alloc(at_bytes + (size_t)n_desc * 8 + mask_bytes + (size_t)tiles * 4 +
                                                 (may_grid ? kBoxBlocks * kBoxWords * 4 : 0) + (halved ? (size_t)n_src * 8 : 0), s);
-    if (halved) {
+    if (halved && want_pairs) {
         c->pairs = dev_alloc((size_t)n_src * 4, s);
         if (!c->pairs) return SP_ERR_ALLOC;
     }
@@ -954,7 +954,7 @@ int sp_coords_build(const int32_t* d_raw, int64_t n_raw, int32_t tensor_stride, 
     if (n_raw > 0 && !d_raw) return sp::fail(SP_ERR_INVALID_ARG, "d_raw is NULL");
     if (tensor_stride < 1) return sp::fail(SP_ERR_INVALID_ARG, "tensor_stride < 1");
     if (((uintptr_t)d_raw & 15) != 0) return sp::fail(SP_ERR_INVALID_ARG, "d_raw must be 16-byte aligned");
-    return sp::coords_build_impl(d_raw, n_raw, nullptr, 1, tensor_stride, nullptr, (hipStream_t)stream, out);
+    return sp::coords_build_impl(d_raw, n_raw, nullptr, 1, tensor_stride, nullptr, false, (hipStream_t)stream, out);
 }
 
 int sp_coords_size(const sp_coords_t* c, int64_t* n, int32_t* tensor_stride) {

@@ -94,9 +94,10 @@ struct CoordTab {
 // Builds a coordinate set from d_src rows; floor_step > 1 floors x,y,z to multiples of it first.  n_src_ub is an
 // upper bound of the row count (sizes every allocation and grid); d_n_src, if not null, points at the true count
 // in device memory (a count that the host has not seen yet), else the count is n_src_ub.  Does not wait.
-// parent: the set whose coordinates d_src are, or null (then their extent is looked up first).
+// parent: the set whose coordinates d_src are, or null (then their extent is looked up first).  want_pairs: the caller's map
+// reads sp_coords::pairs, if this set can have them, and drops them.
 int coords_build_impl(const int32_t* d_src, int64_t n_src_ub, const int32_t* d_n_src, int32_t floor_step,
-                      int32_t tensor_stride, const sp_coords* parent, hipStream_t s, sp_coords_t** out);
+                      int32_t tensor_stride, const sp_coords* parent, bool want_pairs, hipStream_t s, sp_coords_t** out);
 // Waits (first call only) until the handle's row count has come back; reports device-detected errors.
 int coords_resolve(const sp_coords_t* c);
 struct TableView;
@@ -122,8 +123,8 @@ struct sp_coords {
     sp::Buf inverse;  // int32 [n_raw]
     sp::Buf meta;     // int32 [kMetaWords]: the row count n, error bits, ...: what kernels of later builds read
     sp::CoordTab tab;
-    // A set of half the resolution of a parent with a grid: per row, the pair (2 * block + half) of the parent's grid that is its
-    // cell.  Written only if this set turned out a grid itself (kMetaGrid).
+    // A set of half the resolution of a parent with a grid, while the 2 x 2 x 2 map that made it is being built: per row, the pair
+    // (2 * block + half) of the parent's grid that is its cell.  Written only if this set turned out a grid itself (kMetaGrid).
     sp::Buf pairs;
     hipStream_t stream = nullptr;
     // the host's copy of n arrives through a mail slot and is read on first demand (coords_resolve)

@@ -860,6 +860,8 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
     m->stride = stride;
     m->dilation = dilation;
     m->stream = s;
+    // (Rows off the lattice, which a caller may have, are found by their place in the cell on both sides: child_map_kernel.)
+    const bool child_rows = stride == 2 && kernel_size == 2 && in->on_lattice;
     sp_coords* cin = const_cast<sp_coords*>(in);
     cin->ref.fetch_add(1);
     m->c_in = cin;
@@ -870,7 +872,7 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
         m->c_out = cin;
     } else {
         sp_coords* co = nullptr;
-        SP_TRY(coords_build_impl(ptr<int32_t>(in->coords), n_in_ub, cn_in.d, in->ts * stride, in->ts * stride, in, s, &co));
+        SP_TRY(coords_build_impl(ptr<int32_t>(in->coords), n_in_ub, cn_in.d, in->ts * stride, in->ts * stride, in, child_rows, s, &co));
         cin->ref.fetch_add(1);
         co->src_of = cin;  // its inverse array has one entry per row of `in`
         m->c_out = co;
@@ -894,12 +896,12 @@ int sp_kmap_build(const sp_coords_t* in, int32_t kernel_size, int32_t stride, in
     const Counts counts = counts_in(work, n_out_ub, kvol);
     int32_t* done = ptr<int32_t>(m->d_counts) + kvol;
     const unsigned nt = (unsigned)(tiles_of(n_out_ub) ? tiles_of(n_out_ub) : 1);
-    // (Rows off the lattice, which a caller may have, are found by their place in the cell on both sides.)
-    if (stride == 2 && kernel_size == 2 && in->on_lattice && m->c_out->pairs) {
+    if (child_rows && m->c_out->pairs) {
         hipLaunchKernelGGL(child_map_kernel, dim3(blocks256(n_in_ub)), dim3(kThreads), 0, s, ptr<int4>(in->coords), cn_in, in->ts, stride,
                            ptr<int32_t>(m->c_out->inverse), cn_out, kvol, (int32_t*)nullptr, ptr<int32_t>(si.nbr));
         hipLaunchKernelGGL(child_rows_kernel, dim3(nt), dim3(kTileRows), 0, s, ptr<int4>(m->c_out->coords), cn_out, ptr<int32_t>(m->c_out->meta),
                            ptr<int32_t>(m->c_out->pairs), table_view(in), ptr<int32_t>(so.nbr), counts, done);
+        m->c_out->pairs.reset();  // (later users of the memory are ordered behind this launch on the stream)
     } else if (stride > 1 && kernel_size == stride && kernel_size % 2 == 0) {
         if (n_out_ub > 0) {
             hipLaunchKernelGGL(reset_kernel, dim3(blocks256((n_out_ub * (int64_t)kvol + 3) / 4)), dim3(kThreads), 0, s, ptr<int32_t>(so.nbr),
@@ -966,7 +968,7 @@ int sp_kmap_build_generative(const sp_coords_t* in, int32_t kernel_size, int32_t
                            n_coarse, kernel_size, ts_out, ptr<int4>(cand));
     SP_HIP(hipGetLastError());
     sp_coords* fine = nullptr;
-    SP_TRY(coords_build_impl(ptr<int32_t>(cand), n_cand, nullptr, 1, ts_out, nullptr, s, &fine));
+    SP_TRY(coords_build_impl(ptr<int32_t>(cand), n_cand, nullptr, 1, ts_out, nullptr, false, s, &fine));
     fine->on_lattice = in->on_lattice;
 
     // the stride-s convolution's map from the fine rows (inputs) to the coarse rows (outputs) ...

@@ -160,6 +160,34 @@ def test_both_sides_of_a_cell_map_agree_off_the_lattice(sp, ts, shift, box):  # 
         check_map(sp, km, want, len(rows), len(want["c_out"]))
 
 
+def test_memory_of_coarse_sets(sp):  # noqa: F811
+    """A set of half the resolution holds what other coarse sets of the same parent hold, once its map is built."""
+    c = sp.sp_coords_build(dev(FULL), 1)
+    live, held = {}, []
+
+    def alloc(nbytes, stream):
+        p = torch.cuda.caching_allocator_alloc(max(nbytes, 512), stream=stream)
+        live[p] = nbytes
+        return p
+
+    def free(p):
+        del live[p]
+        torch.cuda.caching_allocator_delete(p)
+
+    sp.sp_set_allocator(alloc, free)
+    try:
+        for K, stride in ((3, 3), (3, 2), (2, 2)):
+            before = sum(live.values())
+            km, co = sp.sp_kmap_build(c, K, stride, 1)
+            km.close()
+            held.append((sum(live.values()) - before, co))
+    finally:
+        sp.sp_set_allocator()
+    assert held[0][0] == held[1][0] == held[2][0] > 0
+    for _, co in held:
+        co.close()
+
+
 @pytest.mark.parametrize("cin,cout,bf16", [(32, 32, False), (128, 128, True), (20, 24, False)])
 @pytest.mark.parametrize("warm", [True, False])
 def test_lists_of_the_input_side_under_capture(sp, cin, cout, bf16, warm):  # noqa: F811
