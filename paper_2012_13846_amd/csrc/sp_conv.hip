@@ -793,7 +793,8 @@ bool small_wave(const MapSide& side, int kvol, int64_t links, int cc, int co, sp
 // it, since the tile kernel's 128 rows fill the blocks of few links better.
 int select_gather(const MapSide& side, int kvol, int64_t total_links, int cc, int co, sp_dtype dt, bool may_split = true) {
     const size_t elt = dt == SP_F32 ? 4 : 2;
-    if (narrow_pays(cc, co, kvol)) return 4;
+    // (features and lists beyond 32-bit offsets, which the tile kernel takes slowly or not at all, are nothing special to kind 4)
+    if (narrow_pays(cc, co, kvol, side.n_rows, total_links, dt) || (narrow_ok(cc, co, kvol) && tile_big(side, kvol, cc, dt))) return 4;
     // Row-stationary kernel: it multiplies all kvol offsets of every row, the link-list kernels only the links
     // that exist but pay per link for bookkeeping, weight re-reads and the accumulator update.  Measured, it is
     // the faster one from about 1 link in 20 row-offsets upwards on 128- and 256-channel inputs, from 1 in 4

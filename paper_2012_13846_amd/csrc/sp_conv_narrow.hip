@@ -4,10 +4,12 @@
 // added in offset order, each one's dot product first: fixed order, rounded once.  (Only links that exist are multiplied: an
 // infinite weight does not reach rows it is not linked to.)
 // What bounds it: one trip through the address unit per row and offset, live or not, and the multiply-adds of an offset
-// that any of a wavefront's rows has (nearly all).  Times against the tile kernel's at narrow_pays.
+// that any of a wavefront's rows has (nearly all).  Times against the tile kernel's at narrow_us.
 #include <algorithm>
+#include <cmath>
 
 #include "sp_internal.h"
+#include "sp_tile_shape.h"
 
 namespace sp {
 namespace {
@@ -198,21 +200,79 @@ bool pow2(int v) { return (v & (v - 1)) == 0; }
 }  // namespace
 
 namespace {
-bool narrow_in_ok(int cc, int co, int kvol) { return cc <= 8 && co <= 64 && (size_t)kvol * cc * ((co + 7) / 8 * 8) * 4 <= (size_t)kMaxLds; }
+bool narrow_in_ok(int cc, int co, int kvol) { return cc <= 8 && cc * co <= 128 && co <= 64 && (size_t)kvol * cc * ((co + 7) / 8 * 8) * 4 <= (size_t)kMaxLds; }
 bool narrow_out_ok(int cc, int co, int kvol) {
     return co <= 8 && cc >= 8 && cc <= 256 && pow2(cc) && (size_t)kvol * co * cc * 4 <= (size_t)kMaxLds;
 }
+// Destination channels per thread: twice the threads where 8 would leave the chip half empty (3 -> 32 on 23 k rows 13.7 against
+// 11.3 us, 96 k 31.7 against 36.6).
+int narrow_in_channels(int64_t rows, int co) { return co > 4 && rows * ((co + 7) / 8) >= 131072 ? 8 : 4; }
 }  // namespace
 
-// us per launch, this kernel / the tile kernel, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 213 k, 2.4 M:
-//   few destinations  fp32 32 -> 3  10 / 17 | 11 / 20 | 27 / 62  | 57 / 170    bf16 32 -> 3  11 / 14 | 11 / 15 | 25 / 36 | 54 / 90
-//                     fp32 64 -> 6  14 / 23 | 21 / 44 | 56 / 129 | 125 / 382   bf16 64 -> 6  15 / 16 | 19 / 18 | 56 / 58 | 125 / 159
-//   few sources       fp32 3 -> 16  13 / 16 | 9 / 19  | 17 / 45  | 41 / 112    bf16 3 -> 16  13 / 20 | 9 / 22  | 17 / 54 | 40 / 151
-//                     fp32 3 -> 32  10 / 18 | 11 / 20 | 32 / 42  | 62 / 113    bf16 3 -> 32  14 / 25 | 11 / 27 | 28 / 54 | 58 / 153
-//                     fp32 4 -> 64  13 / 16 | 22 / 19 | 70 / 44  | 147 / 121   bf16 4 -> 64  13 / 18 | 19 / 21 | 63 / 44 | 140 / 120
-//                     fp32 8 -> 32  16 / 15 | 25 / 16 | 63 / 34  | 121 / 89
-// Few destinations always; few sources while the products of a link are few.
-bool narrow_pays(int cc, int co, int kvol) { return narrow_out_ok(cc, co, kvol) || (narrow_in_ok(cc, co, kvol) && cc * co <= 128); }
+// Microseconds of a launch: this kernel's, and the tile kernel's on the same rows.  Fitted to 13000 pairs of times each (300 to
+// 613 k rows with 1 to 34 links each, K = 1 to 5, strides 1 and 2, both directions); off by 13 % rms, the tile kernel's on few fp32
+// destinations by 22 %.  This kernel pays for every offset of a row, 27 at a time, and for the products of an offset that any row of
+// a wavefront has (live); the tile kernel for the blocks of 16 links that a tile of rows has of each offset.
+// this kernel / the tile kernel in us, fp32 | bf16:
+//   few destinations, K = 3   64 -> 3, 96 k rows, 0.61 M links 46 / 130 | 43 / 58    32 -> 3  26 / 61 | 25 / 36    16 -> 6  19 / 38 | 17 / 36
+//                             64 -> 6, 29 k rows, 52 k links   17 / 39  | 17 / 17    32 -> 6  12 / 18 | 12 / 14    8 -> 8   18 / 14 | 18 / 14
+//                             64 -> 8, 213 k rows, 2.4 M links 200 / 356 | 207 / 154 32 -> 8  91 / 164 | 94 / 87   16 -> 8  54 / 93 | 54 / 86
+//                      K = 5   8 -> 3, 1.9 k rows, 8 k links    33 / 25  | 37 / 23    8 -> 8   71 / 24 | 76 / 23
+//   few sources, K = 3        3 -> 16, 148 k rows, 0.37 M links 27 / 54 | 24 / 68     3 -> 32 41 / 51 | 38 / 68     4 -> 32 48 / 42 | 43 / 47
+//                             7 -> 16                           40 / 54 | 41 / 74     2 -> 64 58 / 44 | 47 / 39     3 -> 40 48 / 40 | 47 / 52
+//                             4 -> 32, 1.9 k rows, 4 k links    8 / 13  | 9 / 16      2 -> 64 7 / 17 | 7 / 17       8 -> 16 13 / 13 | 13 / 13
+//                      K = 5   4 -> 32, 56 k rows, 0.28 M links  66 / 42 | 65 / 43
+namespace {
+struct Layer {
+    double rows, links, k, cc, co;
+    bool f32;
+};
+double live(const Layer& l, double rows_of_a_wave) { return 1.0 - std::pow(1.0 - std::min(1.0, l.links / (l.rows * l.k)), rows_of_a_wave); }
+double blocks_of_a_tile(const Layer& l, double tile_rows) {
+    const double per = l.links * tile_rows / (l.rows * l.k);
+    return l.k * (1.0 - std::exp(-per) + per / 16.0);
+}
+double narrow_us(const Layer& l, bool few_out) {
+    const double walked = std::ceil(l.k / kAhead) * kAhead, weights = l.k * l.cc * l.co / 1000.0;
+    if (few_out) {
+        const double tpr = l.cc / 8.0, turns = l.rows * tpr / 65536.0;   // 65536: a wavefront per SIMD
+        const double chain = l.f32 ? 0.080 * walked + 0.044 * l.k * l.co * live(l, 64.0 / tpr) : 0.091 * walked + 0.047 * l.k * l.co * live(l, 64.0 / tpr);
+        const double resident = std::min(8.0, std::floor(160.0 * 1024.0 / (l.k * l.co * l.cc * 4.0 + 1.0)));  // workgroups a CU, by LDS
+        const double full = chain * std::max(1.0, (l.f32 ? 0.45 : 0.48) * turns * std::max(1.0, 2.7 / resident));
+        return l.f32 ? 4.3 + 0.26 * weights + full + 0.029 * turns * walked + 0.22e-6 * l.links * l.cc
+                     : 3.8 + 0.29 * weights + full + 0.0056 * turns * walked + 0.19e-6 * l.links * l.cc;
+    }
+    const int oc = narrow_in_channels((int64_t)l.rows, (int)l.co);
+    const double tpr = std::ceil(l.co / oc), turns = l.rows * tpr / 65536.0;
+    const double chain = 0.050 * walked + 0.008 * l.k * l.cc * oc * live(l, 64.0 / tpr);
+    const double full = chain * std::max(1.0, 0.53 * turns);
+    return l.f32 ? 4.9 + 0.40 * weights + full + 0.014 * turns * walked + 1.5e-6 * l.rows * l.co
+                 : 4.7 + 0.47 * weights + full + 0.011 * turns * walked + 0.51e-6 * l.rows * l.co;
+}
+double tile_us(const Layer& l, bool few_out) {
+    const TileShape t = tile_shape((int)l.cc, (int)l.co, l.f32, false);
+    if (few_out) {
+        const double unit = (l.f32 ? 0.0054 : 0.0030) * t.kc * t.nsl * blocks_of_a_tile(l, 64.0), tiles = l.rows / 64.0;
+        return l.f32 ? 8.7 + (1.3 + unit) * std::max(1.0, tiles / 240.0) : 7.3 + (2.4 + unit) * std::max(1.0, tiles / 350.0);
+    }
+    const double tr = t.ncs >= 3 && l.rows / 128.0 * t.ny >= 512.0 ? 128.0 : 64.0, tiles = l.rows / tr * t.ny;
+    const int row_bytes = (int)l.cc * (l.f32 ? 4 : 2);   // rows that are no whole 16-byte pieces are loaded in smaller ones
+    const double loads = 1.0 + (row_bytes % 16 ? (l.f32 ? 0.36 : 0.30) : 0.0) + (row_bytes % 4 ? 0.98 : 0.0);
+    const double unit = ((l.f32 ? 0.11 : 0.10) + (l.f32 ? 0.011 : 0.010) * t.ncs * tr / 64.0) * loads * blocks_of_a_tile(l, tr);
+    return l.f32 ? 6.9 + (2.7 + unit) * std::max(1.0, tiles / 450.0) : 7.0 + (3.4 + unit) * std::max(1.0, tiles / 490.0);
+}
+}  // namespace
+
+bool narrow_ok(int cc, int co, int kvol) { return narrow_out_ok(cc, co, kvol) || narrow_in_ok(cc, co, kvol); }
+
+// A tenth between the two estimates.  Of 10000 launches that the fit had not seen, 63 are slower than on the tile kernel by more than
+// 10 % (935 if channels alone decide) and 157 left to it would be more than 20 % faster here.
+bool narrow_pays(int cc, int co, int kvol, int64_t rows, int64_t links, sp_dtype dt) {
+    const bool few_out = narrow_out_ok(cc, co, kvol);
+    if (!few_out && !narrow_in_ok(cc, co, kvol)) return false;
+    const Layer l{(double)rows, (double)links, (double)kvol, (double)cc, (double)co, dt == SP_F32};
+    return 1.1 * narrow_us(l, few_out) < tile_us(l, few_out);
+}
 
 int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed, void* d_g, int cc, int co, sp_dtype dt,
                 hipStream_t s) {
@@ -246,9 +306,7 @@ int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w,
 #undef SP_OUT
     }
     if (narrow_in_ok(cc, co, kvol)) {
-        // channels per thread: twice the threads where 8 would leave the chip half empty (3 -> 32 on 23 k rows 13.7 against 11.3 us,
-        // 96 k 31.7 against 36.6)
-        const int oc = co > 4 && a.n_rows * ((co + 7) / 8) >= 131072 ? 8 : 4;
+        const int oc = narrow_in_channels(a.n_rows, co);
         const int cop = (co + oc - 1) / oc * oc, rows = kThreads / (cop / oc);
         const size_t lds = (size_t)kvol * cc * cop * 4;
 #define SP_IN_OC(CC, OC) \

@@ -225,7 +225,8 @@ double dense_min_fill(int cc);
 int conv_gather_dense(const MapSide& side, int kvol, const void* d_f, const void* d_w, void* d_g, int cc, int co,
                       hipStream_t s);
 // few channels on one side (sp_conv_narrow.hip); needs neither link lists nor scratch memory
-bool narrow_pays(int cc, int co, int kvol);
+bool narrow_ok(int cc, int co, int kvol);                                                          // it can take them
+bool narrow_pays(int cc, int co, int kvol, int64_t rows, int64_t links, sp_dtype dt);             // and is faster than the tile kernel
 int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed, void* d_g, int cc, int co, sp_dtype dt,
                 hipStream_t s);
 // fp32 link lists on the bf16 matrix cores (sp_conv_split.hip): slices and channel tiles, bytes of the weights' pieces (d_ws)
