@@ -742,18 +742,32 @@ namespace {
 //                      96 -> 96    38 / 55 | 68 / 78  | 240 / 212 | 308 / 303 | 783 / 580  | 1743 / 1216
 //                      24 -> 40    19 / 23 | 23 / 27  | 55 / 49   | 73 / 64   | 158 / 113  | 298 / 225
 //                      48 -> 48    24 / 28 | 30 / 36  | 76 / 82   | 100 / 111 | 224 / 199  | 465 / 407
-// Channel tiles of 32 leave its wavefronts too little to do per row: small launches only.  What the tile kernel pads a third less
-// (48 channels, which are 64 here) only where many links share a read of the weights.
+// Channel tiles of 32 leave its wavefronts too little to do per row: not in place of the wavefront-private kernel, and of the tile
+// kernel only on large sets.  What the tile kernel pads a third less (48 channels, which are 64 here) only where many links share a
+// read of the weights.  A read serves the links of one offset in a tile, padded to steps of 32 or 48: where a tile of 128 rows has few
+// of an offset (per), the tile kernel's blocks of 16 are less work.  us, before / split, per and rows in front:
+//   K = 3, stride 2, input side  per 10, 68 k rows   24 -> 40 26 / 34    64 -> 40 49 / 60    96 -> 96 106 / 125  72 -> 56 74 / 71    128 -> 64 92 / 88
+//   K = 5                        per 11, 68 k        24 -> 40 106 / 109  64 -> 40 158 / 216  96 -> 96 413 / 519  72 -> 56 280 / 379  128 -> 64 439 / 355
+//   K = 3                        per 37, 99 k                            64 -> 40 119 / 86   96 -> 96 294 / 221
+//   128 -> 128                   K = 5, per 1.4, 16 k 71 / 94   K = 3, per 5.3, 16 k 39 / 45   K = 4, per 6.7, 20 k 188 / 104
+//   36 -> 100 (padded)           K = 3, per 14, 12 k 26 / 29, per 18, 20 k 48 / 35
+// Of the wavefront-private kernel's layers it leaves K = 1 (64 -> 128 on 374 k rows 106 / 132, 32 -> 128 69 / 94), and 32 -> 128 channels on
+// many rows with few links (K = 2, stride 2, input side, one link a row: 374 k rows 97 / 117, 30 k rows 21 / 17).
 bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bool wave) {
     if (cc % 4 != 0 || cc <= 16 || co <= 16 || kvol > 125) return false;
     const SplitShape t = split_shape(cc, co);
     if (split_copy_bytes(t, kvol) >= kLim32) return false;
-    if (wave) return t.cot > 32 && !share_fits((side.n_rows + 63) / 64 * (co / wave_tile(cc, co, true)), wave_lds(cc, wave_tile(cc, co, true), 4, kvol));
+    if (wave) {
+        if (t.cot <= 32 || kvol == 1 || (kvol <= 8 && cc <= 32 && t.cot == 128 && side.n_rows >= 32768 && links < 5 * side.n_rows)) return false;
+        return !share_fits((side.n_rows + 63) / 64 * (co / wave_tile(cc, co, true)), wave_lds(cc, wave_tile(cc, co, true), 4, kvol));
+    }
     if (side.n_rows < 1024) return false;
-    if (side.n_rows < 65536) return t.cot == 128;
     const TileShape o = tile_shape(cc, co, true, false);
-    const bool dense = links * 128 >= (int64_t)32 * kvol * side.n_rows;
-    return dense || 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny <= 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
+    const double per = (double)links * 128.0 / ((double)side.n_rows * kvol);
+    const bool padded = 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny > 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
+    if (padded && (per < 32.0 || kvol == 1) && (side.n_rows <= 16384 || side.n_rows >= 65536)) return false;
+    if (side.n_rows < 65536) return t.cot == 128 && per >= 6.0;
+    return per >= (t.cot == 48 ? 20.0 : t.cot == 64 && t.cc == 32 ? 14.0 : 6.0);
 }
 
 bool dense_pays(const MapSide& side, int kvol, int64_t links, int cc) {

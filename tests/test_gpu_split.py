@@ -41,7 +41,7 @@ def fwd64(km, x, w):
 @pytest.mark.parametrize("n,bits,cin,cout", [(8193, 5, 64, 128), (16257, 5, 64, 128), (1100, 4, 128, 128), (1217, 4, 100, 128),        # 64-row tiles
                                              (16449, 5, 64, 64), (32769, 6, 32, 64), (16513, 5, 64, 128),                          # .. 128-row tiles
                                              (20000, 5, 100, 128),                                                                 # slices past the last channel
-                                             (65536, 5, 96, 96), (65537, 6, 24, 40), (70000, 5, 48, 48), (70001, 5, 36, 100), (66000, 6, 128, 32)])
+                                             (65536, 5, 96, 96), (65537, 5, 24, 40), (70000, 5, 48, 48), (70001, 5, 36, 100), (66000, 6, 128, 32)])
 def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
     c, km, g = cloud(sp, n, bits, n + cin)
     assert sp.sp_conv_kernel_name(km, cin, cout, torch.float32) == "gather_split_kernel"
@@ -51,6 +51,23 @@ def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
         err, rms = got.double() - want, want.square().mean().sqrt()
         assert float(err.square().mean().sqrt() / rms) <= 3e-7
         assert float(err.abs().max() / rms) <= 1e-5
+
+
+@pytest.mark.parametrize("n,bits,K,cin,cout,kernel", [
+    (40000, 5, 1, 64, 128, "wave"), (40000, 5, 2, 64, 128, "split"), (40000, 6, 2, 32, 128, "wave"), (30000, 6, 2, 32, 128, "split"),      # in place of wave
+    (16385, 8, 3, 128, 128, "tile"), (16385, 6, 3, 128, 128, "split"), (12000, 6, 3, 36, 100, "tile"), (20000, 6, 3, 36, 100, "split"),    # of tile, under 64 k rows
+    (66000, 6, 3, 64, 40, "tile"), (66000, 5, 3, 64, 40, "split"), (66000, 6, 3, 128, 64, "split"), (66000, 6, 3, 72, 56, "tile"),         # .. from there on
+    (66000, 6, 5, 96, 96, "tile"), (66000, 5, 3, 24, 40, "split"), (66000, 6, 3, 128, 32, "split")])
+def test_links_of_a_tile_and_offset(sp, n, bits, K, cin, cout, kernel):  # noqa: F811
+    """Both sides of the lines that the links of an offset in a tile of rows draw; the results on each against fp64 (1e-6 of the rms
+    for the other kernels' sums of up to 125 * 128 products)."""
+    c, _, g = cloud(sp, n, bits, n + cin)
+    km, _ = sp.sp_kmap_build(c, K, 1, 1)
+    assert sp.sp_conv_kernel_name(km, cin, cout, torch.float32) == "gather_%s_kernel" % kernel
+    x, w = torch.randn((n, cin), device="cuda", generator=g), torch.randn((K ** 3, cout, cin), device="cuda", generator=g)
+    want = fwd64(km, x, w)
+    err, rms = sp.sp_conv_fwd(km, x, w).double() - want, want.square().mean().sqrt()
+    assert float(err.square().mean().sqrt() / rms) <= (3e-7 if kernel == "split" else 1e-6)
 
 
 @pytest.mark.parametrize("cin,cout", [(64, 64), (32, 64), (128, 128)])
