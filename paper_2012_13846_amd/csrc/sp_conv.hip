@@ -781,6 +781,9 @@ bool dense_pays(const MapSide& side, int kvol, int64_t links, int cc) {
 //   64 -> 64    29 / 12 | - | 29 / 20 | 30 / 18 | 32 / 27       128 -> 64   44 / 14 | 45 / 16 | 50 / 34 | 47 / 35 | 48 / 45
 //   64 -> 128   37 / 12 | - | 38 / 33 | 40 / 32 | 42 / 47       128 -> 128  60 / 15 | 61 / 29 | 65 / 47 | 64 / 43 | 64 / 77
 //   64 -> 256   49 / 13 | - | 52 / 48 | 53 / 44 | 55 / 78       128 -> 256  76 / 17 | 80 / 38 | 82 / 107 | 82 / 85 | 85 / 154
+// Few offsets are few steps, and channel counts that are no multiples of 128 have the cheaper ones (row-stationary / wavefront-private
+// in us): K = 1, 64 -> 64 on 13 k rows 8.4 / 9.4, 128 -> 128 on 3 k 13 / 10, on 8 k 13 / 17; K = 2 64 -> 64 on 12 k rows 14.1 / 12.2, on 42 k
+// 14.1 / 19, 64 -> 192 on 14 k 14.3 / 22, 128 -> 128 on 34 k 26.6 / 26.6; K = 3 128 -> 64 on 50 k rows 49 / 57, 64 -> 192 on 12 k 30 / 36.
 // Not on a side with position classes, whose row-stationary steps are few.  bf16 sums are fp32 and rounded once in both.
 bool small_wave(const MapSide& side, int kvol, int64_t links, int cc, int co, sp_dtype dt) {
     if (side.tile_mask || tile_big(side, kvol, cc, dt) || !wave_shape_ok(cc, co, dt)) return false;
@@ -788,7 +791,9 @@ bool small_wave(const MapSide& side, int kvol, int64_t links, int cc, int co, sp
     if (!cot) return false;
     const int64_t nwt = (side.n_rows + 63) / 64;
     const double per = (double)links * 64 / ((double)side.n_rows * kvol), blocks = std::max(1.0, per / 16 + 0.5);
-    return (double)(nwt * (co / cot)) * blocks <= 2100.0;
+    const double line = co % 128 == 0 ? (kvol == 1 ? 800.0 : kvol <= 8 ? 1900.0 : 2100.0)
+                                      : (kvol == 1 ? 0.0 : kvol <= 8 ? 600.0 : kvol > 27 && cc == 128 ? 1900.0 : 1400.0);
+    return (double)(nwt * (co / cot)) * blocks <= line;
 }
 
 // Which gather kernel a layer takes: 0 row-stationary (sp_conv_dense.hip), 1 wavefront-private link lists,

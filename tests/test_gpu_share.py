@@ -35,6 +35,21 @@ def test_launch_sizes(sp, n, bits, cin, cout, dt, kernel):  # noqa: F811
             assert float(err.square().mean().sqrt() / rms) <= 1e-6
 
 
+@pytest.mark.parametrize("n,bits,K,cin,cout,kernel", [
+    (8000, 5, 1, 64, 64, "dense"), (3000, 5, 1, 128, 128, "wave"), (30000, 5, 1, 128, 128, "dense"), (8000, 5, 2, 64, 64, "wave"),
+    (60000, 5, 2, 64, 64, "dense"), (12000, 4, 2, 64, 192, "dense"), (12000, 4, 2, 128, 128, "wave"), (12000, 4, 3, 64, 64, "wave"),
+    (60000, 5, 3, 128, 64, "dense"), (30000, 5, 4, 128, 64, "wave"), (12000, 4, 3, 64, 192, "dense")])
+def test_launch_sizes_by_offsets(sp, n, bits, K, cin, cout, kernel):  # noqa: F811
+    """Where the row-stationary kernel begins for few offsets and for channels that are no multiples of 128; bf16 results rounded once."""
+    c, _, g = cloud(sp, n, bits, n + cin)
+    km, _ = sp.sp_kmap_build(c, K, 1, 1)
+    assert sp.sp_conv_kernel_name(km, cin, cout, B) == "gather_%s_kernel" % kernel
+    x, w = torch.randn((n, cin), device="cuda", generator=g).to(B), torch.randn((K ** 3, cout, cin), device="cuda", generator=g).to(B)
+    want = fwd64(km, x, w)
+    err, rms = (sp.sp_conv_fwd(km, x, w).double() - want).abs(), want.square().mean().sqrt()
+    assert bool((err <= want.abs() * 2.0 ** -8 + rms * 1e-5).all())
+
+
 @pytest.mark.parametrize("n,bits", [(1, 1), (100, 2), (600, 5), (1500, 4), (3000, 4), (20000, 5)])
 @pytest.mark.parametrize("cin,cout,dt", [(16, 16, F), (64, 64, F), (20, 24, F), (64, 64, B), (256, 256, B)])
 def test_weight_gradient_of_short_lists(sp, n, bits, cin, cout, dt):  # noqa: F811
