@@ -174,9 +174,10 @@ __device__ __forceinline__ Vec<T> load_vec(const T* p, size_t elem) {
 // Same sums as column_sums_kernel.  Thread = (row lane, 16-byte channel group); tpr = c / kN threads cover a
 // row, 256 / tpr rows are read per pass (tpr need not divide 256: the spare threads idle).  The block's rows
 // are rows [blockIdx.x * rows_per_block, ...).  Row lanes are added in lane order.
-// MODE 1 with relu leaves a byte per 16-byte group (live, if there is memory for them), which of its elements have y > 0, so
-// that the pass behind it need not read y again (7 passes over the rows become 6 and an eighth).
-template <typename T, int MODE>
+// MODE 1, kLive (relu, and memory for them): leaves a byte per 16-byte group, which of its elements have y > 0, so that the pass
+// behind it need not read y again (7 passes over the rows become 6 and an eighth).  (Decided in the kernel: 256 channels on 1.5 k rows
+// 16.1 us for these sums, 12.5 so.)
+template <typename T, int MODE, bool kLive>
 __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __restrict__ x, const T* __restrict__ y,
                                                                    const T* __restrict__ dy, int64_t n, int c,
                                                                    int64_t rows_per_block,
@@ -220,16 +221,17 @@ __global__ __launch_bounds__(kThreads) void column_sums_vec_kernel(const T* __re
             } else {
                 unpack(rg, gv);
                 unpack(ry, yv);
-                uint32_t bits = 0;
+                [[maybe_unused]] uint32_t bits = 0;
 #pragma unroll
                 for (int i = 0; i < kN; ++i) {
                     float g = gv.v[i];
-                    if (relu && !(yv.v[i] > 0.f)) g = 0.f;
-                    else bits |= 1u << i;
+                    const bool dead = (kLive || relu) && !(yv.v[i] > 0.f);
+                    g = dead ? 0.f : g;
+                    if constexpr (kLive) bits |= dead ? 0u : 1u << i;
                     s0[i] += g;
                     s1[i] += g * (xv.v[i] - m[i]) * rs[i];
                 }
-                if (live) live[e / kN] = (uint8_t)bits;
+                if constexpr (kLive) live[e / kN] = (uint8_t)bits;
             }
         };
         // 4 rows' loads are requested before the first is used (the rows are still added in row order)
@@ -664,9 +666,13 @@ inline unsigned stream_blocks(int64_t total) {
     return (unsigned)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
 }
 
-// Normalisation passes: a thread keeps its channels' 32 to 40 parameters, 160 bytes, for several 16-byte groups (a group a thread
-// and y read again: 25 us a layer of the 8-layer stack's backward pass, 21 so; both passes run at 5.0-5.6 TB/s).
-inline unsigned apply_blocks(int64_t total) { return std::min(stream_blocks(total), 2048u); }
+// Normalisation passes: a thread keeps its channels' 32 to 40 parameters, 160 bytes, for four 16-byte groups, one round of its loop;
+// more where 2048 blocks, the chip's fill, are enough for the rows.  Forward in us with 2048 blocks / 16384 / a group a thread, in
+// bf16: 256 channels on 60 k rows 24 / 27 / 27, on 0.37 M 107 / 99 / 110, 512 channels on 0.61 M rows 426 / 364 / 351; with this rule
+// 25, 97 and 346.
+inline unsigned apply_blocks(int64_t total) {
+    return std::min(stream_blocks(total), (unsigned)std::min<int64_t>(65536, std::max<int64_t>(2048, (total + 4 * kThreads - 1) / (4 * kThreads))));
+}
 
 // vector kernels: whole 16-byte groups per row, at most 256 of them, 16-byte aligned base pointers
 template <typename T>
@@ -692,7 +698,7 @@ int bn_fwd_typed(const void* x, int64_t n, int c, const float* gamma, const floa
     if (nblk > 0) {
         if (vec) {
             const int lanes = kThreads / (c / (16 / (int)sizeof(T)));
-            hipLaunchKernelGGL((column_sums_vec_kernel<T, 0>), dim3((unsigned)nblk), dim3(kThreads),
+            hipLaunchKernelGGL((column_sums_vec_kernel<T, 0, false>), dim3((unsigned)nblk), dim3(kThreads),
                                (size_t)2 * lanes * c * 4, s, static_cast<const T*>(x), (const T*)nullptr,
                                (const T*)nullptr, n, c, rpb, (const float*)nullptr, (const float*)nullptr, 0,
                                ptr<float>(partial), (uint8_t*)nullptr);
@@ -731,7 +737,7 @@ int bn_bwd_typed(const void* x, const void* y, const void* dy, int64_t n, int c,
     if (nblk > 0) {
         if (vec) {
             const int lanes = kThreads / (c / (16 / (int)sizeof(T)));
-            hipLaunchKernelGGL((column_sums_vec_kernel<T, 1>), dim3((unsigned)nblk), dim3(kThreads),
+            hipLaunchKernelGGL((live ? column_sums_vec_kernel<T, 1, true> : column_sums_vec_kernel<T, 1, false>), dim3((unsigned)nblk), dim3(kThreads),
                                (size_t)2 * lanes * c * 4, s, static_cast<const T*>(x), static_cast<const T*>(y),
                                static_cast<const T*>(dy), n, c, rpb, mean, rstd, relu, ptr<float>(partial), live);
         } else {
