@@ -750,7 +750,8 @@ namespace {
 //   K = 5                        per 11, 68 k        24 -> 40 106 / 109  64 -> 40 158 / 216  96 -> 96 413 / 519  72 -> 56 280 / 379  128 -> 64 439 / 355
 //   K = 3                        per 37, 99 k                            64 -> 40 119 / 86   96 -> 96 294 / 221
 //   128 -> 128                   K = 5, per 1.4, 16 k 71 / 94   K = 3, per 5.3, 16 k 39 / 45   K = 4, per 6.7, 20 k 188 / 104
-//   36 -> 100 (padded)           K = 3, per 14, 12 k 26 / 29, per 18, 20 k 48 / 35
+//   padded                       36 -> 100, K = 3, per 14, 12 k 26 / 29, per 33, 8 k 32 / 36, per 84, 12 k 55 / 47, per 18, 20 k 48 / 35
+//                                40 -> 24, K = 3, per 53, 146 k 139 / 158
 // Of the wavefront-private kernel's layers it leaves K = 1 (64 -> 128 on 374 k rows 106 / 132, 32 -> 128 69 / 94), and 32 -> 128 channels on
 // many rows with few links (K = 2, stride 2, input side, one link a row: 374 k rows 97 / 117, 30 k rows 21 / 17).
 bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bool wave) {
@@ -765,7 +766,7 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
     const TileShape o = tile_shape(cc, co, true, false);
     const double per = (double)links * 128.0 / ((double)side.n_rows * kvol);
     const bool padded = 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny > 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
-    if (padded && (per < 32.0 || kvol == 1) && (side.n_rows <= 16384 || side.n_rows >= 65536)) return false;
+    if (padded && (t.cot == 32 || ((per < (side.n_rows <= 16384 ? 40.0 : 32.0) || kvol == 1) && (side.n_rows <= 16384 || side.n_rows >= 65536)))) return false;
     if (side.n_rows < 65536) return t.cot == 128 && per >= 6.0;
     return per >= (t.cot == 48 ? 20.0 : t.cot == 64 && t.cc == 32 ? 14.0 : 6.0);
 }

@@ -5,19 +5,44 @@ import numpy as np
 import pytest
 import torch
 
-from test_gpu_parity import conv_case, full_cubes, random_coords, sp  # noqa: F401  (sp: the binding fixture)
+from test_gpu_parity import conv_case, dev, full_cubes, sp  # noqa: F401  (sp: the binding fixture)
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64), (32, 96), (64, 160), (32, 320)])
+@pytest.mark.parametrize("cin,cout", [(128, 128), (100, 128), (64, 128), (128, 384), (192, 128)])
 def test_small_layers(sp, cin, cout):  # noqa: F811
-    conv_case(sp, random_coords(3 + cin, 1500, 12, batches=2, lo=-5), 1, 3, 1, 1, cin, cout, False, seed=7 * cin + cout)
+    """Against the oracle, all three passes; the forward pass on this kernel, and the data gradient of 100 and 128 channels."""
+    raw = full_cubes(12, 5)
+    km, _ = sp.sp_kmap_build(sp.sp_coords_build(dev(raw), 1), 3, 1, 1)
+    assert sp.sp_conv_kernel_name(km, cin, cout, torch.float32) == "gather_split_kernel"
+    conv_case(sp, raw, 1, 3, 1, 1, cin, cout, False, seed=7 * cin + cout)
 
 
-@pytest.mark.parametrize("K,stride,transposed", [(1, 1, False), (2, 2, False), (2, 2, True), (3, 2, False), (3, 2, True), (5, 1, False), (4, 1, False)])
-def test_other_maps(sp, K, stride, transposed):  # noqa: F811
-    conv_case(sp, full_cubes(9, 2), 1, K, stride, 1, 32, 64, False, seed=K, transposed=transposed)
+@pytest.mark.parametrize("K,stride,dil,transposed", [(2, 1, 1, False), (2, 2, 1, False), (2, 2, 1, True), (3, 2, 1, False), (3, 2, 1, True),
+                                                     (3, 1, 2, False), (4, 1, 1, False), (4, 2, 1, False), (4, 2, 1, True), (5, 1, 1, False), (5, 2, 1, True), (1, 1, 1, False)])
+def test_other_maps(sp, K, stride, dil, transposed):  # noqa: F811
+    """64, 27, 8 and 125 offsets (two rounds of 64 in a tile's first wavefront), strided and transposed maps, dilation, both directions;
+    against fp64 (an error of sums in fp32: it grows with the square root of the links that are added)."""
+    cin = cout = 128
+    km, _ = sp.sp_kmap_build(sp.sp_coords_build(dev(full_cubes(26, 1)), 1), K, stride, dil)
+    if transposed:
+        km = sp.sp_kmap_transpose(km)
+    assert [sp.sp_conv_kernel_name(km, cin, cout, torch.float32, d) for d in (0, 1)] == ["gather_split_kernel"] * 2
+    g = torch.Generator(device="cuda").manual_seed(K)
+    x, dy = torch.randn((km.n_in, cin), device="cuda", generator=g), torch.randn((km.n_out, cout), device="cuda", generator=g)
+    w = torch.randn((K ** 3, cout, cin), device="cuda", generator=g)
+    pin, pout = km.pairs()
+    at = np.concatenate([[0], np.cumsum(km.counts)])
+    y, dx = torch.zeros((km.n_out, cout), device="cuda", dtype=torch.float64), torch.zeros((km.n_in, cin), device="cuda", dtype=torch.float64)
+    for k in range(K ** 3):
+        i, o = pin[at[k]:at[k + 1]].long(), pout[at[k]:at[k + 1]].long()
+        y.index_add_(0, o, x[i].double() @ w[k].double().T)
+        dx.index_add_(0, i, dy[o].double() @ w[k].double())
+    for got, want in ((sp.sp_conv_fwd(km, x, w), y), (sp.sp_conv_bwd_data(km, dy, w), dx)):
+        err, rms = got.double() - want, want.square().mean().sqrt()
+        assert float(err.square().mean().sqrt() / rms) <= 3e-7 * max(1.0, K ** 3 / 27.0) ** 0.5
+        assert float(err.abs().max() / rms) <= 1e-5
 
 
 def cloud(sp, n, bits, seed):  # noqa: F811
@@ -107,6 +132,12 @@ def test_without_allocations(sp):  # noqa: F811
     """Weights' pieces that fit the static scratch: the bits of sp_conv_fwd; pieces that do not, though the weights would: within
     the parity bound."""
     c, km, g = cloud(sp, 20000, 5, 9)
+    x, w = torch.randn((km.n_in, 100), device="cuda", generator=g), torch.randn((27, 384, 100), device="cuda", generator=g)
+    y = torch.full((km.n_out, 384), float("nan"), device="cuda")
+    assert sp.sp_conv_kernel_name(km, 100, 384, torch.float32) == "gather_split_kernel"     # 4.0 MB of weights, 8 MB of padded pieces
+    sp.sp_conv_fwd_noalloc(km, x, w, y)
+    want = fwd64(km, x, w)
+    assert not torch.equal(y, sp.sp_conv_fwd(km, x, w)) and float((y.double() - want).norm() / want.norm()) <= 1e-6
     for cin, cout, same in ((64, 128, True), (128, 256, True), (64, 640, False)):
         x, w = torch.randn((km.n_in, cin), device="cuda", generator=g), torch.randn((27, cout, cin), device="cuda", generator=g)
         y = torch.full((km.n_out, cout), float("nan"), device="cuda")
