@@ -764,6 +764,8 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
     }
     if (side.n_rows < 1024) return false;
     const TileShape o = tile_shape(cc, co, true, false);
+    // More slices are more roundings: 80 -> 24 in three of 32 is 1.18e-7 of the rms off, 1.10e-7 in the tile kernel's two of 48.
+    if (t.cot == 32 && t.nsl > o.nsl) return false;
     const double per = (double)links * 128.0 / ((double)side.n_rows * kvol);
     const bool padded = 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny > 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
     if (padded && (t.cot == 32 || ((per < (side.n_rows <= 16384 ? 40.0 : 32.0) || kvol == 1) && (side.n_rows <= 16384 || side.n_rows >= 65536)))) return false;

@@ -82,7 +82,8 @@ def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
     (40000, 5, 1, 64, 128, "wave"), (40000, 5, 2, 64, 128, "split"), (40000, 6, 2, 32, 128, "wave"), (30000, 6, 2, 32, 128, "split"),      # in place of wave
     (16385, 8, 3, 128, 128, "tile"), (16385, 6, 3, 128, 128, "split"), (12000, 6, 3, 36, 100, "tile"), (20000, 6, 3, 36, 100, "split"),    # of tile, under 64 k rows
     (66000, 6, 3, 64, 40, "tile"), (66000, 5, 3, 64, 40, "split"), (66000, 6, 3, 128, 64, "split"), (66000, 6, 3, 72, 56, "tile"),         # .. from there on
-    (66000, 6, 5, 96, 96, "tile"), (66000, 5, 3, 24, 40, "split"), (66000, 6, 3, 128, 32, "split")])
+    (66000, 6, 5, 96, 96, "tile"), (66000, 5, 3, 24, 40, "split"), (66000, 6, 3, 128, 32, "split"),
+    (66000, 5, 3, 80, 24, "tile"), (66000, 5, 3, 96, 96, "split")])
 def test_links_of_a_tile_and_offset(sp, n, bits, K, cin, cout, kernel):  # noqa: F811
     """Both sides of the lines that the links of an offset in a tile of rows draw; the results on each against fp64 (1e-6 of the rms
     for the other kernels' sums of up to 125 * 128 products)."""
