@@ -1,7 +1,8 @@
 // Step 3 of the generalized sparse convolution (Eq. 2) and its input gradient for layers with few channels on one side (the
 // first layer of a network: 3 to 6 values a point): plain multiply-adds, a few threads per destination row, all weights in
 // LDS, a row's neighbours requested together.  The matrix cores multiply four fifths of padding there.  A row's links are
-// added in offset order, each one's dot product first: fixed order, rounded once.  (Only links that exist are multiplied: an
+// added in offset order, each one's dot product first, nine offsets before the total: fixed order, rounded once (one sum of all
+// links was up to 10 % further from fp64 than the tile kernel is).  (Only links that exist are multiplied: an
 // infinite weight does not reach rows it is not linked to.)
 // What bounds it: one trip through the address unit per row and offset, live or not, and the multiply-adds of an offset
 // that any of a wavefront's rows has (nearly all).  Times against the tile kernel's at narrow_us.
@@ -85,20 +86,26 @@ __global__ __launch_bounds__(kThreads) void narrow_in_kernel(NarrowArgs a, int c
 #pragma unroll
                     for (int c = 0; c < CC; ++c) x[i][c] = load_f32(v + c);
                 }
+                float part[OC];
+#pragma unroll
+                for (int j = 0; j < OC; ++j) part[j] = 0.f;
 #pragma unroll
                 for (int i = 0; i < kN; ++i) {
                     if (src[i0 + i] < 0) continue;
                     const float* wk = s_w + (k0 + i0 + i) * CC * cop + o0;
-                    float dot[OC];
+                    constexpr int kHalf = CC > 4 ? (CC + 1) / 2 : CC;
+                    float dot[2][OC];  // more than four products in two chains: fewer roundings of large sums
 #pragma unroll
-                    for (int j = 0; j < OC; ++j) dot[j] = 0.f;
+                    for (int j = 0; j < OC; ++j) dot[0][j] = dot[1][j] = 0.f;
 #pragma unroll
                     for (int c = 0; c < CC; ++c)
 #pragma unroll
-                        for (int j = 0; j < OC; ++j) dot[j] = fmaf(wk[c * cop + j], x[i][c], dot[j]);
+                        for (int j = 0; j < OC; ++j) dot[c / kHalf][j] = fmaf(wk[c * cop + j], x[i][c], dot[c / kHalf][j]);
 #pragma unroll
-                    for (int j = 0; j < OC; ++j) acc[j] += dot[j];
+                    for (int j = 0; j < OC; ++j) part[j] += CC > 4 ? dot[0][j] + dot[1][j] : dot[0][j];
                 }
+#pragma unroll
+                for (int j = 0; j < OC; ++j) acc[j] += part[j];
             }
         }
         T* out = static_cast<T*>(a.g) + row * a.co + o0;
@@ -109,9 +116,10 @@ __global__ __launch_bounds__(kThreads) void narrow_in_kernel(NarrowArgs a, int c
 }
 
 // OM destination channels: a thread sums the part of them that 8 source channels make, cc / 8 threads per row (a power of
-// two), which add their parts at the end.  LDS: weights [offset][OM][cc].
+// two), which add their parts at the end.  LDS: weights [offset][OM][cc].  (Three wavefronts a SIMD: 170 registers would be two,
+// 64 -> 6 on 2.4 M links 220 us against 126.)
 template <typename T, int OM>
-__global__ __launch_bounds__(kThreads) void narrow_out_kernel(NarrowArgs a) {
+__global__ __launch_bounds__(kThreads, 3) void narrow_out_kernel(NarrowArgs a) {
     extern __shared__ __align__(16) float s_w[];
     const T* __restrict__ w = static_cast<const T*>(a.w);
     const T* __restrict__ f = static_cast<const T*>(a.f);
@@ -149,6 +157,9 @@ __global__ __launch_bounds__(kThreads) void narrow_out_kernel(NarrowArgs a) {
 #pragma unroll
                     for (int v = 0; v < kV; ++v) x[i][v] = p[v];
                 }
+                float part[OM];
+#pragma unroll
+                for (int j = 0; j < OM; ++j) part[j] = 0.f;
 #pragma unroll
                 for (int i = 0; i < kN; ++i) {
                     if (src[i0 + i] < 0) continue;
@@ -162,14 +173,16 @@ __global__ __launch_bounds__(kThreads) void narrow_out_kernel(NarrowArgs a) {
 #pragma unroll
                     for (int j = 0; j < OM; ++j) {
                         const f32x4 lo = *reinterpret_cast<const f32x4*>(wk + j * a.cc), hi = *reinterpret_cast<const f32x4*>(wk + j * a.cc + 4);
-                        float dot = 0.f;
+                        float dot[2] = {0.f, 0.f};
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) dot = fmaf(lo[c], xv[c], dot);
+                        for (int c = 0; c < 4; ++c) dot[0] = fmaf(lo[c], xv[c], dot[0]);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) dot = fmaf(hi[c], xv[4 + c], dot);
-                        acc[j] += dot;
+                        for (int c = 0; c < 4; ++c) dot[1] = fmaf(hi[c], xv[4 + c], dot[1]);
+                        part[j] += dot[0] + dot[1];
                     }
                 }
+#pragma unroll
+                for (int j = 0; j < OM; ++j) acc[j] += part[j];
             }
         }
 #pragma unroll
@@ -200,7 +213,7 @@ bool pow2(int v) { return (v & (v - 1)) == 0; }
 }  // namespace
 
 namespace {
-bool narrow_in_ok(int cc, int co, int kvol) { return cc <= 8 && cc * co <= 128 && co <= 64 && (size_t)kvol * cc * ((co + 7) / 8 * 8) * 4 <= (size_t)kMaxLds; }
+bool narrow_in_ok(int cc, int co, int kvol) { return cc <= 7 && cc * co <= 128 && co <= 64 && (size_t)kvol * cc * ((co + 7) / 8 * 8) * 4 <= (size_t)kMaxLds; }
 bool narrow_out_ok(int cc, int co, int kvol) {
     return co <= 8 && cc >= 8 && cc <= 256 && pow2(cc) && (size_t)kvol * co * cc * 4 <= (size_t)kMaxLds;
 }
@@ -220,7 +233,7 @@ int narrow_in_channels(int64_t rows, int co) { return co > 4 && rows * ((co + 7)
 //                      K = 5   8 -> 3, 1.9 k rows, 8 k links    33 / 25  | 37 / 23    8 -> 8   71 / 24 | 76 / 23
 //   few sources, K = 3        3 -> 16, 148 k rows, 0.37 M links 27 / 54 | 24 / 68     3 -> 32 41 / 51 | 38 / 68     4 -> 32 48 / 42 | 43 / 47
 //                             7 -> 16                           40 / 54 | 41 / 74     2 -> 64 58 / 44 | 47 / 39     3 -> 40 48 / 40 | 47 / 52
-//                             4 -> 32, 1.9 k rows, 4 k links    8 / 13  | 9 / 16      2 -> 64 7 / 17 | 7 / 17       8 -> 16 13 / 13 | 13 / 13
+//                             4 -> 32, 1.9 k rows, 4 k links    8 / 13  | 9 / 16      2 -> 64 7 / 17 | 7 / 17
 //                      K = 5   4 -> 32, 56 k rows, 0.28 M links  66 / 42 | 65 / 43
 namespace {
 struct Layer {
@@ -323,7 +336,6 @@ int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w,
             SP_IN(5);
             SP_IN(6);
             SP_IN(7);
-            SP_IN(8);
         }
 #undef SP_IN
 #undef SP_IN_OC
