@@ -41,7 +41,7 @@ struct GatherArgs {
     int runs;          // sub-tiles are dealt to the XCDs in runs (xcd_run)
     int split_blocks;  // sub-tiles with at least this many 16-link blocks are shared by two wavefronts
     uint32_t f_bytes, w_bytes, list_bytes;  // sizes of f / w / src and dst for buffer addressing (< 4 GiB)
-    int may_in_place;  // host-side only: ... instead of a copy into `scratch`, or if there is no memory for one
+    int may_in_place;  // host-side only: ... instead of a copy into `scratch`, under capture, or if there is no memory for one
     int w_transposed;  // host-side only: the stored weights are [k][cc][co] (data gradient) instead of [k][co][cc]
     void* scratch;     // host-side only: if set, device memory for the weight copy instead of a pool allocation
     size_t scratch_bytes;
@@ -532,6 +532,11 @@ int launch_wave(GatherArgs a, hipStream_t s) {
         return fail(SP_ERR_UNSUPPORTED, "weights of %lld bytes exceed the %zu bytes of static scratch",
                     (long long)(n * sizeof(T)), a.scratch_bytes);
     Buf wf;
+    if (!stored && !a.scratch && !a.w_transposed && a.may_in_place) {  // a graph must not hold on to a block of the pool
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+        stored = cap != hipStreamCaptureStatusNone;
+    }
     if (!stored && !a.scratch) {
         wf = dev_alloc((size_t)n * sizeof(T), s);
         stored = !wf && !a.w_transposed && a.may_in_place;

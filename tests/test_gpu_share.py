@@ -99,3 +99,27 @@ def test_allocation_free_calls_of_two_streams(sp):  # noqa: F811
         torch.cuda.synchronize()
         for outs, ref in zip(ys, want):
             assert all(torch.equal(y, ref) for y in outs)
+
+
+def test_a_captured_forward_pass_of_a_row_stationary_layer_holds_no_pool_memory(sp):  # noqa: F811
+    """sp_conv_fwd itself, whose weight copy would be another call's memory by the time of a replay: one node, right on every replay."""
+    from test_gpu_streams import node_count
+    c, km, g = cloud(sp, 1500, 3, 5)
+    x = torch.randn((1500, 64), device="cuda", generator=g).to(B)
+    ws = [torch.randn((27, 64, 64), device="cuda", generator=g).to(B) for _ in range(2)]
+    want = sp.sp_conv_fwd(km, x, ws[0])
+    y = torch.empty_like(want)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        sp.sp_conv_fwd(km, x, ws[0], y)
+        graph.capture_end()
+    assert node_count(graph) == 1
+    graph.instantiate()
+    for _ in range(3):
+        y.fill_(float("nan"))
+        sp.sp_conv_fwd(km, x, ws[1])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
