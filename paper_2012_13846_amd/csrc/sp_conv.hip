@@ -799,8 +799,9 @@ bool small_wave(const MapSide& side, int kvol, int64_t links, int cc, int co, sp
     if (!cot) return false;
     const int64_t nwt = (side.n_rows + 63) / 64;
     const double per = (double)links * 64 / ((double)side.n_rows * kvol), blocks = std::max(1.0, per / 16 + 0.5);
+    // (64 -> 64 at K = 3 is level between 1400 and 2100: 32 / 33 on 49 k rows, 32 / 33 on 59 k.)
     const double line = co % 128 == 0 ? (kvol == 1 ? 800.0 : kvol <= 8 ? 1900.0 : 2100.0)
-                                      : (kvol == 1 ? 0.0 : kvol <= 8 ? 600.0 : kvol > 27 && cc == 128 ? 1900.0 : 1400.0);
+                                      : (kvol == 1 ? 0.0 : kvol <= 8 ? 600.0 : cc * co == 4096 ? 2100.0 : kvol > 27 && cc == 128 ? 1900.0 : 1400.0);
     return (double)(nwt * (co / cot)) * blocks <= line;
 }
 
