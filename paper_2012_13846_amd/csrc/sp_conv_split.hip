@@ -93,7 +93,7 @@ struct SplitCfg {
 //   - splits its share of the next step's rows, which it asked for kR steps ago, and stores the pieces to LDS;
 //   - multiplies this step's blocks and adds a block's sums to the accumulator while the next one is multiplied.
 // One barrier a step; every wavefront has the same number of blocks, so none waits long, and two or more workgroups share a CU.
-// What bounds it (64 -> 64, 0.6 M rows, 5 M links, 514 us, before 672 on fp32 MFMAs): the L1's data return is busy 70 % of the
+// What bounds it (64 -> 64, 0.6 M rows, 5 M links, 514 us, before 672 on fp32 MFMAs; 2.4 % more with kScale): the L1's data return is busy 70 % of the
 // time (half of it the weights, 24 KB a step), the LDS 41 %, the vector pipes 35 %, the matrix pipes 25 %; two wavefronts
 // per SIMD issue in order and wait a third of their time.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64
 // channels and meets no barrier (weights in 96 or 192 registers, everything dealt out between the MFMAs): 555 us, since a single
