@@ -69,8 +69,8 @@ struct DenseCfg {
     // makes the compiler spill, and a reload inside the loop waits for every gather in flight (loads return in
     // order), which undoes the rows' second register stage.
     static constexpr int kWF = (kWaves > 4 && CC == 256) ? 2 : 3;
-    static constexpr int kOutPitch = COT * 2 + 16;   // output staging row (bf16)
-    static constexpr int kLds = 2 * kBuf > kTR * kOutPitch ? 2 * kBuf : kTR * kOutPitch;
+    static constexpr int kOutPitch = 128 + 16;       // output staging row: 64 channels, a pad
+    static constexpr int kLds = 2 * kBuf > kWaves * 64 * kOutPitch ? 2 * kBuf : kWaves * 64 * kOutPitch;
     static constexpr int kMI = 4;                    // 16-row groups per wavefront: 64 rows
     static constexpr int kNI = COT == 64 ? 4 : 8;    // 16-channel tiles per wavefront: 64 or 128 channels
     static_assert(CC % kKS == 0, "whole slices");
@@ -80,12 +80,20 @@ struct DenseCfg {
 };
 
 // Staged rows have no pad; the 16-byte piece p of row r sits in slot p ^ f(r), f(r) = (r >> 1) & 7 for 128-byte
-// rows and (r >> 2) & 3 for 64-byte rows (rows that share a bank range get different slots).  With this swizzle
+// rows and -(r >> 2) & 3 for 64-byte rows (rows that share a bank range get different slots).  With this swizzle
 // the b128 fragment reads (16 rows x 4 k-groups per wavefront) run at the full LDS rate, like a 32-byte pad
-// would, and the buffers stay small enough for 8 wavefronts' worth of tile.
+// would, and the buffers stay small enough for 8 wavefronts' worth of tile.  (The LDS serves such a read in groups of
+// lanes like 0-3, 12-15, 20-27: rows 4-11 of the second k-group beside rows 0-3 and 12-15 of the first.  (r >> 2) & 3 puts
+// those on the same banks: counted conflicts were a third of the LDS time, 128 -> 128 on 0.18 M rows.)
 template <int P>
 __device__ __forceinline__ int swz(int row, int piece) {
-    return (P == 8 ? (piece ^ ((row >> 1) & 7)) : (piece ^ ((row >> 2) & 3))) * 16;
+    return (P == 8 ? (piece ^ ((row >> 1) & 7)) : (piece ^ (-(row >> 2) & 3))) * 16;
+}
+
+// LDS traffic of one wavefront is processed in order; this only stops the compiler from moving accesses across.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <int COT>
@@ -109,6 +117,8 @@ __global__ __launch_bounds__(kDenseThreads<COT>, (KS == 32 ? 2 : 1)) void gather
     if (row0 >= a.n_rows) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n16 = lane & 15, g = lane >> 4;
+    __shared__ int s_rows[Cfg::kTR];  // the tile's destination rows, -1 past the end (read behind the main loop's barriers)
+    if (tid < Cfg::kTR) s_rows[tid] = row0 + tid < a.n_rows ? (a.perm ? a.perm[row0 + tid] : (int)(row0 + tid)) : -1;
     const int rq = wave & 3, ch = wave >> 2;  // this wavefront: tile rows rq*64 .. +63, slice channels ch*128 .. (+127 | +63)
 
     constexpr int kRsrcFlags = 0x00020000;
@@ -128,27 +138,23 @@ __global__ __launch_bounds__(kDenseThreads<COT>, (KS == 32 ? 2 : 1)) void gather
     struct Where {
         uint32_t x[kXLoads], w;
     };
-    // destination rows this thread gathers for: entry row0 + lrow + kRP j of the tile, -1 past the end
-    int my_row[kXLoads];
-#pragma unroll
-    for (int j = 0; j < kXLoads; ++j) {
-        const int64_t e = row0 + lrow + kRP * j;
-        my_row[j] = e < a.n_rows ? (a.perm ? a.perm[e] : (int)e) : -1;
-    }
-    auto load_nbr = [&](int k, int (&raw)[kXLoads]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < kXLoads; ++j) {
-            const bool live = my_row[j] >= 0 && k < a.kvol;
-            // past the table the load returns 0, which would name row 0: such entries are masked in locate()
-            raw[j] = (int)__builtin_amdgcn_raw_buffer_load_b32(
-                rN, live ? (uint32_t)(((int64_t)k * a.n_rows + my_row[j]) * 4) : kOutside, 0, 0);
-        }
+    // A wavefront's threads gather for kXLoads stretches of 64 / kP rows; lane l holds the entry of the l-th of those rows, so that
+    // one request brings all of an offset's entries (a request occupies the addresser for 16 cycles however little it asks
+    // for), and each thread takes its own from there.  -1 past the end.
+    constexpr int kRW = 64 / kP;
+    static_assert(kRW * kXLoads <= 64, "a lane per row");
+    const int64_t my_entry = row0 + wave * kRW + lane % kRW + kRP * (lane / kRW);
+    const int my_row = lane < kRW * kXLoads && my_entry < a.n_rows ? (a.perm ? a.perm[my_entry] : (int)my_entry) : -1;
+    auto load_nbr = [&](int k) __attribute__((always_inline)) {
+        return (int)__builtin_amdgcn_raw_buffer_load_b32(
+            rN, my_row >= 0 && k < a.kvol ? (uint32_t)(((int64_t)k * a.n_rows + my_row) * 4) : kOutside, 0, 0);
     };
-    auto locate = [&](int k, const int (&raw)[kXLoads], Where& wh) __attribute__((always_inline)) {
+    auto locate = [&](int k, int raw, Where& wh) __attribute__((always_inline)) {
+        const int mine = my_row >= 0 && k < a.kvol ? raw : -1;  // (past the table the load returned 0, which would name row 0)
 #pragma unroll
         for (int j = 0; j < kXLoads; ++j) {
-            const bool live = my_row[j] >= 0 && k < a.kvol && raw[j] >= 0;
-            wh.x[j] = live ? (uint32_t)raw[j] * (CC * 2) + piece * 16 : kOutside;
+            const int r = __shfl(mine, j * kRW + lane / kP, 64);
+            wh.x[j] = r >= 0 ? (uint32_t)r * (CC * 2) + piece * 16 : kOutside;
         }
         const int wk = a.flip ? a.kvol - 1 - k : k;
         wh.w = k < a.kvol ? ((uint32_t)wk * a.co_total + co0 + lrow) * (CC * 2) + piece * 16 : kOutside;
@@ -249,25 +255,25 @@ __global__ __launch_bounds__(kDenseThreads<COT>, (KS == 32 ? 2 : 1)) void gather
     };
     Where cur[kOPR], nxt[kOPR];  // the offsets of this turn and of the next
     int k_cur[kOPR];             // this turn's offsets (kvol: none left)
-    int raw[kOPR][kXLoads];      // neighbour entries of the turn after that, in flight
+    int raw[kOPR];               // neighbour entries of the turn after that, in flight
     int k_raw[kOPR];
 #pragma unroll
     for (int o = 0; o < kOPR; ++o) {
         k_cur[o] = next_offset();
-        load_nbr(k_cur[o], raw[o]);
+        raw[o] = load_nbr(k_cur[o]);
         locate(k_cur[o], raw[o], cur[o]);
     }
     int k_nxt[kOPR];
 #pragma unroll
     for (int o = 0; o < kOPR; ++o) {
         k_nxt[o] = next_offset();
-        load_nbr(k_nxt[o], raw[o]);
+        raw[o] = load_nbr(k_nxt[o]);
         locate(k_nxt[o], raw[o], nxt[o]);
     }
 #pragma unroll
     for (int o = 0; o < kOPR; ++o) {
         k_raw[o] = next_offset();
-        load_nbr(k_raw[o], raw[o]);
+        raw[o] = load_nbr(k_raw[o]);
     }
     // step j of this turn (j < kRS) or of the next (j >= kRS): its offset's addresses and its slice
     auto where_of = [&](int j) -> const Where& { return j < kRS ? cur[j / kSPO] : nxt[(j - kRS) / kSPO]; };
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(kDenseThreads<COT>, (KS == 32 ? 2 : 1)) void gather
             k_nxt[o] = k_raw[o];
             locate(k_nxt[o], raw[o], nxt[o]);
             k_raw[o] = next_offset();
-            load_nbr(k_raw[o], raw[o]);
+            raw[o] = load_nbr(k_raw[o]);
         }
     };
     u32x4 sx[2][kXLoads], sw[kWDepth][kWLoads];
@@ -324,26 +330,30 @@ __global__ __launch_bounds__(kDenseThreads<COT>, (KS == 32 ? 2 : 1)) void gather
     // the accumulators are read below by ordinary instructions: the MFMAs were written as opaque instructions,
     // so the wait states between the last of them and the first read are put in by hand (18 are required)
     asm volatile("s_nop 15\n s_nop 15" ::: "memory");
-    // one rounding to bf16, stage the tile in LDS, write whole rows
-    unsigned char* out = smem;  // all staging reads are behind the last barrier
+    // One rounding to bf16; a wavefront stages its rows 64 channels at a time in LDS of its own and writes pieces of 128 bytes.
+    // (The rows' numbers are in LDS already: read from memory here, one after the other, they took 5 of a tile's 26 us.)
+    unsigned char* out = smem + wave * 64 * Cfg::kOutPitch;  // all staging reads are behind the last barrier
 #pragma unroll
-    for (int ni = 0; ni < kNI; ++ni)
+    for (int h = 0; h < kNI / 4; ++h) {
 #pragma unroll
-        for (int mi = 0; mi < kMI; ++mi) {
-            const f32x4 v = acc[ni][mi];
-            u32x2 p;
-            p[0] = bf16_bits(v[0]) | (bf16_bits(v[1]) << 16);
-            p[1] = bf16_bits(v[2]) | (bf16_bits(v[3]) << 16);
-            *reinterpret_cast<u32x2*>(out + (rq * 64 + mi * 16 + n16) * Cfg::kOutPitch + (ch * 128 + ni * 16 + 4 * g) * 2) = p;
+        for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < kMI; ++mi) {
+                const f32x4 v = acc[h * 4 + ni][mi];
+                u32x2 p;
+                p[0] = bf16_bits(v[0]) | (bf16_bits(v[1]) << 16);
+                p[1] = bf16_bits(v[2]) | (bf16_bits(v[3]) << 16);
+                *reinterpret_cast<u32x2*>(out + (mi * 16 + n16) * Cfg::kOutPitch + (ni * 16 + 4 * g) * 2) = p;
+            }
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = i * 8 + (lane >> 3), row = s_rows[rq * 64 + r];
+            const u32x4 v = *reinterpret_cast<const u32x4*>(out + r * Cfg::kOutPitch + (lane & 7) * 16);
+            if (row >= 0)
+                *reinterpret_cast<u32x4*>(static_cast<unsigned char*>(a.g) + ((size_t)row * a.co_total + co0 + ch * 128 + h * 64) * 2 + (lane & 7) * 16) = v;
         }
-    __syncthreads();
-    constexpr int kRowPieces = COT * 2 / 16;
-    for (int idx = tid; idx < Cfg::kTR * kRowPieces; idx += Cfg::kThreads) {
-        const int r = idx / kRowPieces, pc = idx % kRowPieces;
-        if (row0 + r >= a.n_rows) break;
-        const int64_t row = a.perm ? a.perm[row0 + r] : row0 + r;
-        *reinterpret_cast<u32x4*>(static_cast<unsigned char*>(a.g) + ((size_t)row * a.co_total + co0) * 2 + pc * 16) =
-            *reinterpret_cast<const u32x4*>(out + r * Cfg::kOutPitch + pc * 16);
+        wave_sync();
     }
 }
 
