@@ -737,16 +737,19 @@ namespace {
 // split, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 160 k, 0.66 M | 213 k, 2.4 M | 613 k, 5.0 M:
 // (wavefront-private: one wavefront a sub-tile; where four share one, 64 -> 64 takes 20 us on 1.5 k and 22 on 16 k rows, 32 -> 64
 // 14 and 15, 32 k rows 24, the split kernel 25, 29, 20, 24 and 30: share_fits is the line.)
-//   wavefront-private  64 -> 64    56 / 26 | 66 / 38  | 124 / 85  | 180 / 115 | 345 / 250  | 681 / 530
-//                      32 -> 64    35 / 21 | 37 / 29  | 58 / 55   | 93 / 70   | 165 / 133  | 328 / 264
-//                      64 -> 128   56 / 31 | 96 / 47  | 200 / 143 | 280 / 195 | 602 / 451  | 1180 / 920
+//   wavefront-private  64 -> 64    56 / 26 | 66 / 38  | 124 / 81  | 180 / 104 | 345 / 250  | 681 / 503
+//                      32 -> 64    35 / 21 | 37 / 29  | 58 / 50   | 93 / 70   | 165 / 133  | 328 / 264
+//                      64 -> 128   56 / 31 | 96 / 47  | 200 / 143 | 280 / 195 | 602 / 451  | 1180 / 853
 //                      64 -> 32    36 / 28 | 39 / 39  | 64 / 73   | 100 / 97  | 194 / 227  | 373 / 418
 //                      32 -> 32    25 / 22 | 26 / 30  | 40 / 52   | 62 / 65   | 108 / 114  | 202 / 210
-//   tile               128 -> 128  66 / 52 | 130 / 78 | 362 / 264 | 446 / 343 | 1124 / 763 | 2484 / 1617
+//   tile               128 -> 128  66 / 50 | 130 / 78 | 362 / 264 | 446 / 322 | 1124 / 763 | 2484 / 1617
 //                      160 -> 64   67 / 74 | 94 / 106 | 265 / 211 | 358 / 278 | 839 / 596  | 1755 / 1220
 //                      96 -> 96    38 / 55 | 68 / 78  | 240 / 212 | 308 / 303 | 783 / 580  | 1743 / 1216
 //                      24 -> 40    19 / 23 | 23 / 27  | 55 / 49   | 73 / 64   | 158 / 113  | 298 / 225
-//                      48 -> 48    24 / 28 | 30 / 36  | 76 / 82   | 100 / 111 | 224 / 199  | 465 / 407
+//                      48 -> 48    24 / 28 | 30 / 36  | 77 / 73   | 100 / 109 | 224 / 199  | 465 / 407
+// The line between few and many rows (links of an offset in 128 rows: per):  50 k rows, per 49: 48 -> 48 76 / 65, 128 -> 64 213 / 129,
+// 24 -> 40 47 / 48; 55 k, per 63: 48 -> 48 84 / 77, 80 -> 48 146 / 129, 128 -> 32 195 / 100, 24 -> 40 51 / 53; 48 -> 48, 96 k rows, per 30:
+// 77 / 73, per 19: 105 / 109.
 // Channel tiles of 32 leave its wavefronts too little to do per row: not in place of the wavefront-private kernel, and of the tile
 // kernel only on large sets.  What the tile kernel pads a third less (48 channels, which are 64 here) only where many links share a
 // read of the weights.  A read serves the links of one offset in a tile, padded to steps of 32 or 48: where a tile of 128 rows has few
@@ -773,8 +776,9 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
     if (t.cot == 32 && t.nsl > o.nsl) return false;
     const double per = (double)links * 128.0 / ((double)side.n_rows * kvol);
     const bool padded = 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny > 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
-    if (padded && (t.cot == 32 || ((per < (side.n_rows <= 16384 ? 40.0 : 32.0) || kvol == 1) && (side.n_rows <= 16384 || side.n_rows >= 65536)))) return false;
-    if (side.n_rows < 65536) return t.cot == 128 && per >= 6.0;
+    const bool many_rows = side.n_rows >= (t.cc == 32 ? 65536 : 49152);
+    if (padded && (t.cot == 32 || ((per < (many_rows ? 26.0 : 40.0) || kvol == 1) && (side.n_rows <= 16384 || many_rows)))) return false;
+    if (!many_rows) return t.cot == 128 && per >= 6.0;
     return per >= (t.cot == 48 ? 20.0 : t.cot == 64 && t.cc == 32 ? 14.0 : 6.0);
 }
 

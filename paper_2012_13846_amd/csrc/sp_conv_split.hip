@@ -11,6 +11,7 @@
 // An infinity, a NaN or a value of 2^104 and more makes its link's products NaN, and sums of 2^80 (1e24) overflow.  A workgroup
 // that finds a value that is not finite among its sums therefore computes its rows again with fp32 MFMAs (redo below), and what
 // it writes is what those give.
+#include <algorithm>
 #include <mutex>
 
 #include "sp_internal.h"
@@ -78,32 +79,37 @@ struct SplitCfg {
     static constexpr int kPieces = CC / 4;               // 16-byte pieces of a row's slice
     static constexpr int kLoads = (kLinks * kPieces + kThreads - 1) / kThreads;  // per thread and step
     static constexpr int kPlane = CC * 2;                // one of the three pieces of a staged row
-    static constexpr int kPitch = 3 * kPlane + 32;       // staged row + pad: an odd multiple of 32 bytes, b128 fragment reads at the full LDS rate
+    static constexpr int kPitch = 3 * kPlane;            // staged row
+    // Place of 16-byte piece p in a plane of staged row `link`: the fragment reads and the stores meet no bank twice (the LDS serves a
+    // read of 16 bytes a lane in groups of lanes like 0-3, 12-15, 20-27).  A pad of 32 bytes instead left the stores conflicts and
+    // took room: 32 -> 128 on 0.6 M links 107 us, one workgroup a CU, 86 so with two.
+    static __device__ __forceinline__ int place(int link, int p) { return (CC == 64 ? p ^ (link >> 1 & 7) : p ^ (-(link >> 2) & 3)) * 16; }
     static constexpr int kBuf = kLinks * kPitch;
     static constexpr int kW = 3 * kK;                    // weight fragments of a step and wavefront
     static constexpr int kWBytes = kW * NW * 1024;       // split weights of one offset, slice and channel tile
+    static int max_steps(int halves, int kvol) { return kvol * ((halves * 32 + 16 * G - 1) / (16 * G)); }
     static int acc_bytes(int halves) { return (halves * 32 + 1) * kStride * 4; }  // one spare row for links that do not exist
     static int lds(int halves, int max_steps) { return acc_bytes(halves) + 2 * kBuf + 2 * kLinks * 4 + max_steps * 8; }
 };
 
 // A workgroup owns `halves` x 32 destination rows and 16 NW channels and accumulates in LDS.  Its links of one offset (and one
 // slice of the contraction) are cut into steps of up to 16 G.  In a step every wavefront
-//   - asks for its 16 channels of the next step's weights, which then serve all links of that step: a tile of 128 rows
-//     has two to four blocks of 16 links per offset;
+//   - asks for its 16 channels of the next step's weights, which then serve all links of that step;
 //   - splits its share of the next step's rows, which it asked for kR steps ago, and stores the pieces to LDS;
 //   - multiplies this step's blocks and adds a block's sums to the accumulator while the next one is multiplied.
 // One barrier a step; every wavefront has the same number of blocks, so none waits long, and two or more workgroups share a CU.
-// What bounds it (64 -> 64, 0.6 M rows, 5 M links, 514 us, before 672 on fp32 MFMAs; 2.4 % more with kScale): the L1's data return is busy 70 % of the
-// time (half of it the weights, 24 KB a step), the LDS 41 %, the vector pipes 35 %, the matrix pipes 25 %; two wavefronts
-// per SIMD issue in order and wait a third of their time.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64
-// channels and meets no barrier (weights in 96 or 192 registers, everything dealt out between the MFMAs): 555 us, since a single
-// wavefront issues one instruction in four cycles of whatever kind.  Requests in front of the blocks instead of between their
-// MFMAs, and fragments read when they are due: 542 us.
+// What bounds it (64 -> 64, 0.6 M rows, 5 M links, 503 us; 547 with rows asked for four steps ahead, padded rows in LDS and tiles of
+// 128, 672 on fp32 MFMAs): the L1's data return is busy most of the time (half of it the weights, 24 KB a step), the LDS half, the
+// vector pipes 44 %, the matrix pipes 30 %; two or three wavefronts per SIMD issue in order and wait a third of their time, so what
+// lets a third workgroup in pays.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64 channels and meets no barrier
+// (weights in 96 or 192 registers, everything dealt out between the MFMAs): 555 against 514 us, since a single wavefront issues one
+// instruction in four cycles of whatever kind.  Requests in front of the blocks instead of between their MFMAs, and fragments read
+// when they are due: 542.
 template <int CC, int NW, int G>
 __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
     using Cfg = SplitCfg<CC, NW, G>;
     constexpr int kK = Cfg::kK, kThreads = Cfg::kThreads, kPieces = Cfg::kPieces, kLoads = Cfg::kLoads, kLinks = Cfg::kLinks;
-    constexpr int kR = 4;  // steps whose rows are in flight or being stored (even: the weights alternate between two sets)
+    constexpr int kR = 2;  // steps whose rows are in flight or being stored (even: the weights alternate between two sets); 4 take a third workgroup's registers
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_steps;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -214,7 +220,7 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
         uint32_t lo[3], hi[3];
         split_two(v[0], v[1], lo[0], lo[1], lo[2]);
         split_two(v[2], v[3], hi[0], hi[1], hi[2]);
-        unsigned char* b = xbuf + par * Cfg::kBuf + my_piece * 8 + link * Cfg::kPitch;
+        unsigned char* b = xbuf + par * Cfg::kBuf + Cfg::place(link, my_piece >> 1) + (my_piece & 1) * 8 + link * Cfg::kPitch;
         if (kLinks * kPieces % kThreads == 0 || link < kLinks)
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(b + q * Cfg::kPlane) = u32x2{lo[q], hi[q]};
@@ -240,13 +246,13 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
         int row;
     };
     float* const my_acc = acc + wave * 16 + g * 4;
-    const unsigned char* const my_frag = xbuf + n16 * Cfg::kPitch + g * 16;
+    const unsigned char* const my_frag[2] = {xbuf + n16 * Cfg::kPitch + Cfg::place(n16, g), xbuf + n16 * Cfg::kPitch + Cfg::place(n16, (4 + g) % (CC / 8))};
     auto read_frags = [&](Frags& f, int par, int block) __attribute__((always_inline)) {
-        const unsigned char* b = my_frag + par * Cfg::kBuf + block * 16 * Cfg::kPitch;
+        const int b = par * Cfg::kBuf + block * 16 * Cfg::kPitch;
 #pragma unroll
         for (int q = 0; q < 3; ++q)
 #pragma unroll
-            for (int t = 0; t < kK; ++t) f.x[q][t] = *reinterpret_cast<const bf16x8*>(b + q * Cfg::kPlane + t * 64);
+            for (int t = 0; t < kK; ++t) f.x[q][t] = *reinterpret_cast<const bf16x8*>(my_frag[t] + b + q * Cfg::kPlane);
         f.row = s_row[par * kLinks + block * 16 + n16];
     };
     // A block: its MFMAs, product by product, and between them the previous block's sums go to the accumulator and
@@ -351,11 +357,11 @@ __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
         for (int left = total;; left -= 4) {
             body(0, xs[0], xs[1], ws[0], ws[1], ents[0], ents[3]);
             if (left <= 1) break;
-            body(1, xs[1], xs[2], ws[1], ws[0], ents[1], ents[0]);
+            body(1, xs[1], xs[0], ws[1], ws[0], ents[1], ents[0]);
             if (left <= 2) break;
-            body(0, xs[2], xs[3], ws[0], ws[1], ents[2], ents[1]);
+            body(0, xs[0], xs[1], ws[0], ws[1], ents[2], ents[1]);
             if (left <= 3) break;
-            body(1, xs[3], xs[0], ws[1], ws[0], ents[3], ents[2]);
+            body(1, xs[1], xs[0], ws[1], ws[0], ents[3], ents[2]);
             if (left <= 4) break;
         }
         f32x4* p = reinterpret_cast<f32x4*>(res.dst);
@@ -451,14 +457,45 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float* __restr
     for (int q = 0; q < 3; ++q) ws[base + (size_t)(q * steps + t) * 64 + lane] = p[q];
 }
 
+// 32-row halves of a tile.  More rows are fewer reads of the weights and fuller blocks; fewer let more workgroups share a CU and fill
+// its last round better.  The tiles of the fullest CU cost their rows, for every offset its weights (as much as 12 links of 64
+// or 128 channels, 7 of fewer; per: links of an offset in 128 rows) and 0.6 halves more, and each of a CU's resident wavefronts hides
+// what the others wait for.  Over 123 launches of the shapes below (17 k to 0.6 M rows, per 8 to 90) this takes 1 % longer than the
+// best of H = 2 .. 7, tiles of 128 rows (of 64 where those are fewer than 128) 17 % longer; 96 k rows with per 89, 3 - 5 %
+// shorter with those and steps of 48 links, are what it gets wrong most.  H = halves, us:
+//   64 -> 64     21 k rows, per 23, H = 2, 3, 4: 37, 32, 34; 36 k, 36: 48, 45, 56; 66 k, 63: 95, 87, 114;
+//                0.16 M, per 23, H = 3 .. 6: 103, 100, 88, 97; 0.6 M, per 14: 348, 311, 268, 250; 0.6 M, per 75: 804, 869, 819, 843
+//   32 -> 64     96 k, per 30, H = 2, 3, 4: 61, 50, 55; 0.6 M, per 14, H = 3 .. 6: 199, 181, 184, 172; per 75: 477, 513, 522, 519
+//   64 -> 128    96 k, per 16, H = 3 .. 7: 115, 94, 98, 78, 80; 0.6 M, per 14: 711, 576, 504, 472, 430; per 75: 1427, 1486, 1369, 1390, 1352
+//   32 -> 128    0.6 M, per 14, H = 3 .. 7: 382, 319, 371, 344, 311; per 75: 799, 814, 900, 944, 905
+//   48 -> 48     0.24 M, per 32, H = 3 .. 7: 194, 168, 146, 144, 243        96 -> 96   0.6 M, per 75, H = 2 .. 6: 2024, 2171, 2066, 1902, 2290
+//   128 -> 32    0.6 M, per 75, H = 3 .. 7: 1018, 1178, 1079, 1361, 1318; 66 k, per 12: 72, 71, 72, 74, 76
 template <int CC, int NW, int G>
-int launch_split(SplitArgs a, int ny, hipStream_t s) {
+int tile_halves(int64_t n_rows, int ny, int kvol, int64_t links) {
+    using Cfg = SplitCfg<CC, NW, G>;
+    const double per = std::max(1.0, (double)links * 128.0 / ((double)n_rows * kvol));
+    constexpr int kFit = std::max(1, 4 * (CC == 32 ? 4 : NW >= 4 ? 3 : 2) / NW);  // workgroups of a CU that find registers
+    int best = 0;
+    double least = 0.0;
+    for (int h = 2; h <= 7; ++h) {
+        const int64_t tiles = (n_rows + h * 32 - 1) / (h * 32) * ny, cu = (tiles + 255) / 256;
+        const int room = 163840 / (Cfg::lds(h, Cfg::max_steps(h, kvol)) + 1024);
+        const int waves = NW * (int)std::min<int64_t>(cu, std::max(1, std::min(kFit, room)));
+        const double cost = (double)cu * (h + 0.6 + (CC == 64 || NW == 8 ? 50.0 : 30.0) / per) * (1.0 + 7.0 / waves);
+        if (best == 0 || cost < least) {
+            least = cost;
+            best = h;
+        }
+    }
+    return best;
+}
+
+template <int CC, int NW, int G>
+int launch_split(SplitArgs a, int ny, int64_t links, hipStream_t s) {
     using Cfg = SplitCfg<CC, NW, G>;
     auto kern = gather_split_kernel<CC, NW, G>;
-    // Tiles of 128 rows: half the reads of the weights per link, and fuller blocks.  Of 64 where those are too few for the
-    // chip (64 -> 64, 128 -> 128 on 1.5 k rows 26 against 36, 52 against 70 us; on 23 k rows 37 against 38, 109 against 80).
-    a.halves = (a.n_rows + 127) / 128 * ny < 128 ? 2 : 4;
-    const int max_steps = a.kvol * ((a.halves * 32 + 16 * G - 1) / (16 * G));
+    a.halves = tile_halves<CC, NW, G>(a.n_rows, ny, a.kvol, links);
+    const int max_steps = Cfg::max_steps(a.halves, a.kvol);
     const int lds = Cfg::lds(a.halves, max_steps);
     {
         static std::mutex mu;
@@ -527,23 +564,17 @@ int conv_gather_split(const MapSide& side, int kvol, int64_t links, const float*
     const int threads = t.ny * kvol * t.nsl * (t.cc / 32) * (t.cot / 16) * 64;
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, d_w, static_cast<u32x4*>(d_ws), kvol,
                        co, cc, a.s_co, a.s_cc, t.ny, t.nsl, t.cc / 32, t.cot / 16);
-    // Links of a step: 48 where a tile of 128 rows has more than 32 of an offset on average, 32 where it has fewer (64 -> 64 with
-    // 38 a tile and offset 530 against 550 us, with 19 117 against 115; 128 -> 128 with 19 375 against 343).  Tiles of 48
-    // channels: always 48 (96 -> 96 212 against 250 us), 32 source channels and 64 destinations: always 32 (264 against 306).
-    const bool many = t.cot == 48 || (links * 128 >= (int64_t)32 * kvol * side.n_rows && !(t.cc == 32 && t.cot <= 64));
-#define SP_SPLIT(CC, NW) \
-    if (t.cc == CC && t.cot == 16 * NW) return many ? launch_split<CC, NW, 3>(a, t.ny, s) : launch_split<CC, NW, 2>(a, t.ny, s)
-#define SP_SPLIT_G(CC, NW, G) \
-    if (t.cc == CC && t.cot == 16 * NW) return launch_split<CC, NW, G>(a, t.ny, s)
-    SP_SPLIT(64, 8);
-    SP_SPLIT(64, 4);
-    SP_SPLIT_G(64, 3, 3);
-    SP_SPLIT(64, 2);
-    SP_SPLIT(32, 8);
-    SP_SPLIT_G(32, 4, 2);
-    SP_SPLIT_G(32, 3, 3);
-    SP_SPLIT_G(32, 2, 2);
-#undef SP_SPLIT_G
+    // Links of a step: 32, and 48 for channel tiles of 48 (96 -> 96 212 against 250 us).
+#define SP_SPLIT(CC, NW, G) \
+    if (t.cc == CC && t.cot == 16 * NW) return launch_split<CC, NW, G>(a, t.ny, links, s)
+    SP_SPLIT(64, 8, 2);
+    SP_SPLIT(64, 4, 2);
+    SP_SPLIT(64, 3, 3);
+    SP_SPLIT(64, 2, 2);
+    SP_SPLIT(32, 8, 2);
+    SP_SPLIT(32, 4, 2);
+    SP_SPLIT(32, 3, 3);
+    SP_SPLIT(32, 2, 2);
 #undef SP_SPLIT
     return fail(SP_ERR_UNSUPPORTED, "internal: no split kernel for %d -> %d channels", cc, co);
 }
