@@ -470,14 +470,18 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float* __restr
 //   32 -> 128    0.6 M, per 14, H = 3 .. 7: 382, 319, 371, 344, 311; per 75: 799, 814, 900, 944, 905
 //   48 -> 48     0.24 M, per 32, H = 3 .. 7: 194, 168, 146, 144, 243        96 -> 96   0.6 M, per 75, H = 2 .. 6: 2024, 2171, 2066, 1902, 2290
 //   128 -> 32    0.6 M, per 75, H = 3 .. 7: 1018, 1178, 1079, 1361, 1318; 66 k, per 12: 72, 71, 72, 74, 76
+// Surfaces in sampling order fill their tiles less evenly than those random clouds and are best in lower ones (32 -> 64 on 101 k rows,
+// per 28, H = 2 .. 7: 66, 60, 61, 62, 70, 76; 0.37 M rows, H = 3 .. 7: 169, 174, 194, 191, 191; 64 -> 64 254, 267, 258, 250, 351):
+// no height that leaves one workgroup of four wavefronts a CU, and 128 rows at most for 32 -> 64.
 template <int CC, int NW, int G>
 int tile_halves(int64_t n_rows, int ny, int kvol, int64_t links) {
     using Cfg = SplitCfg<CC, NW, G>;
     const double per = std::max(1.0, (double)links * 128.0 / ((double)n_rows * kvol));
     constexpr int kFit = std::max(1, 4 * (CC == 32 ? 4 : NW >= 4 ? 3 : 2) / NW);  // workgroups of a CU that find registers
+    constexpr int kMost = NW == 8 ? 7 : NW == 4 && CC == 32 ? 4 : 6;
     int best = 0;
     double least = 0.0;
-    for (int h = 2; h <= 7; ++h) {
+    for (int h = 2; h <= kMost; ++h) {
         const int64_t tiles = (n_rows + h * 32 - 1) / (h * 32) * ny, cu = (tiles + 255) / 256;
         const int room = 163840 / (Cfg::lds(h, Cfg::max_steps(h, kvol)) + 1024);
         const int waves = NW * (int)std::min<int64_t>(cu, std::max(1, std::min(kFit, room)));
