@@ -10,6 +10,7 @@
 
 #include "sp_conv_tile.h"
 #include "sp_internal.h"
+#include "sp_split_shape.h"
 
 namespace sp {
 namespace {

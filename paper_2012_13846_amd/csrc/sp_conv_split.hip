@@ -11,10 +11,10 @@
 // An infinity, a NaN or a value of 2^104 and more makes its link's products NaN, and sums of 2^80 (1e24) overflow.  A workgroup
 // that finds a value that is not finite among its sums therefore computes its rows again with fp32 MFMAs (redo below), and what
 // it writes is what those give.
-#include <algorithm>
 #include <mutex>
 
 #include "sp_internal.h"
+#include "sp_split_shape.h"
 
 namespace sp {
 namespace {
@@ -38,7 +38,7 @@ struct SplitArgs {
     int kvol, co, cc, flip;
     int s_co, s_cc;
     int nsl;             // slices of CC contraction channels
-    int halves;          // 32-row halves of sub-tiles per workgroup
+    int halves;          // 32-row halves of sub-tiles per workgroup (split_tile)
     uint32_t f_bytes, w_bytes, list_bytes;
 };
 
@@ -87,21 +87,20 @@ struct SplitCfg {
     static constexpr int kBuf = kLinks * kPitch;
     static constexpr int kW = 3 * kK;                    // weight fragments of a step and wavefront
     static constexpr int kWBytes = kW * NW * 1024;       // split weights of one offset, slice and channel tile
-    static int max_steps(int halves, int kvol) { return kvol * ((halves * 32 + 16 * G - 1) / (16 * G)); }
-    static int acc_bytes(int halves) { return (halves * 32 + 1) * kStride * 4; }  // one spare row for links that do not exist
-    static int lds(int halves, int max_steps) { return acc_bytes(halves) + 2 * kBuf + 2 * kLinks * 4 + max_steps * 8; }
+    static_assert(split_lds(CC, NW, G, 2, 1) == 65 * kStride * 4 + 2 * kBuf + 2 * kLinks * 4 + (64 + kLinks - 1) / kLinks * 8, "the kernel's carving of smem");
 };
 
 // A workgroup owns `halves` x 32 destination rows and 16 NW channels and accumulates in LDS.  Its links of one offset (and one
 // slice of the contraction) are cut into steps of up to 16 G.  In a step every wavefront
 //   - asks for its 16 channels of the next step's weights, which then serve all links of that step;
-//   - splits its share of the next step's rows, which it asked for kR steps ago, and stores the pieces to LDS;
+//   - splits its share of the next step's rows, which it asked for a step ago, and stores the pieces to LDS;
 //   - multiplies this step's blocks and adds a block's sums to the accumulator while the next one is multiplied.
-// One barrier a step; every wavefront has the same number of blocks, so none waits long, and two or more workgroups share a CU.
-// What bounds it (64 -> 64, 0.6 M rows, 5 M links, 503 us; 547 with rows asked for four steps ahead, padded rows in LDS and tiles of
-// 128, 672 on fp32 MFMAs): the L1's data return is busy most of the time (half of it the weights, 24 KB a step), the LDS half, the
-// vector pipes 44 %, the matrix pipes 30 %; two or three wavefronts per SIMD issue in order and wait a third of their time, so what
-// lets a third workgroup in pays.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64 channels and meets no barrier
+// One barrier a step; every wavefront has the same number of blocks, so none waits long, and where registers and LDS allow it two or more
+// workgroups share a CU (tiles of 128 channels: one; two of 32 -> 128).
+// What bounds it (64 -> 64, 0.6 M rows, 4.8 M links: 425 us alone with the chip cool, 618 on fp32 MFMAs): the L1's data return is
+// busy most of the time (half of it the weights, 24 KB a step), the LDS half, the vector pipes 44 %, the matrix pipes 30 %; two or
+// three wavefronts per SIMD issue in order and wait a third of their time, so what lets a third workgroup in pays: rows asked for two
+// steps ahead instead of four, no padded rows in LDS.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64 channels and meets no barrier
 // (weights in 96 or 192 registers, everything dealt out between the MFMAs): 555 against 514 us, since a single wavefront issues one
 // instruction in four cycles of whatever kind.  Requests in front of the blocks instead of between their MFMAs, and fragments read
 // when they are due: 542.
@@ -109,7 +108,7 @@ template <int CC, int NW, int G>
 __global__ __launch_bounds__(64 * NW) void gather_split_kernel(SplitArgs a) {
     using Cfg = SplitCfg<CC, NW, G>;
     constexpr int kK = Cfg::kK, kThreads = Cfg::kThreads, kPieces = Cfg::kPieces, kLoads = Cfg::kLoads, kLinks = Cfg::kLinks;
-    constexpr int kR = 2;  // steps whose rows are in flight or being stored (even: the weights alternate between two sets); 4 take a third workgroup's registers
+    constexpr int kR = 2;  // steps whose rows are in flight or being stored (even: the weights alternate between two sets)
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_steps;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -457,50 +456,11 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float* __restr
     for (int q = 0; q < 3; ++q) ws[base + (size_t)(q * steps + t) * 64 + lane] = p[q];
 }
 
-// 32-row halves of a tile.  More rows are fewer reads of the weights and fuller blocks; fewer let more workgroups share a CU and fill
-// its last round better.  The tiles of the fullest CU cost their rows, for every offset its weights (as much as 12 links of 64
-// or 128 channels, 7 of fewer; per: links of an offset in 128 rows) and 0.6 halves more, and each of a CU's resident wavefronts hides
-// what the others wait for.  Over 123 launches of the shapes below (17 k to 0.6 M rows, per 8 to 90) this takes 1 % longer than the
-// best of H = 2 .. 7, tiles of 128 rows (of 64 where those are fewer than 128) 17 % longer; 96 k rows with per 89, 3 - 5 %
-// shorter with those and steps of 48 links, are what it gets wrong most.  H = halves, us:
-//   64 -> 64     21 k rows, per 23, H = 2, 3, 4: 37, 32, 34; 36 k, 36: 48, 45, 56; 66 k, 63: 95, 87, 114;
-//                0.16 M, per 23, H = 3 .. 6: 103, 100, 88, 97; 0.6 M, per 14: 348, 311, 268, 250; 0.6 M, per 75: 804, 869, 819, 843
-//   32 -> 64     96 k, per 30, H = 2, 3, 4: 61, 50, 55; 0.6 M, per 14, H = 3 .. 6: 199, 181, 184, 172; per 75: 477, 513, 522, 519
-//   64 -> 128    96 k, per 16, H = 3 .. 7: 115, 94, 98, 78, 80; 0.6 M, per 14: 711, 576, 504, 472, 430; per 75: 1427, 1486, 1369, 1390, 1352
-//   32 -> 128    0.6 M, per 14, H = 3 .. 7: 382, 319, 371, 344, 311; per 75: 799, 814, 900, 944, 905
-//   48 -> 48     0.24 M, per 32, H = 3 .. 7: 194, 168, 146, 144, 243        96 -> 96   0.6 M, per 75, H = 2 .. 6: 2024, 2171, 2066, 1902, 2290
-//   128 -> 32    0.6 M, per 75, H = 3 .. 7: 1018, 1178, 1079, 1361, 1318; 66 k, per 12: 72, 71, 72, 74, 76
-// Surfaces in sampling order fill their tiles less evenly than those random clouds and are best in lower ones (32 -> 64 on 101 k rows,
-// per 28, H = 2 .. 7: 66, 60, 61, 62, 70, 76; 0.37 M rows, H = 3 .. 7: 169, 174, 194, 191, 191; 64 -> 64 254, 267, 258, 250, 351):
-// no height that leaves one workgroup of four wavefronts a CU, and 128 rows at most for 32 -> 64.
 template <int CC, int NW, int G>
-int tile_halves(int64_t n_rows, int ny, int kvol, int64_t links) {
-    using Cfg = SplitCfg<CC, NW, G>;
-    const double per = std::max(1.0, (double)links * 128.0 / ((double)n_rows * kvol));
-    constexpr int kFit = std::max(1, 4 * (CC == 32 ? 4 : NW >= 4 ? 3 : 2) / NW);  // workgroups of a CU that find registers
-    constexpr int kMost = NW == 8 ? 7 : NW == 4 && CC == 32 ? 4 : 6;
-    int best = 0;
-    double least = 0.0;
-    for (int h = 2; h <= kMost; ++h) {
-        const int64_t tiles = (n_rows + h * 32 - 1) / (h * 32) * ny, cu = (tiles + 255) / 256;
-        const int room = 163840 / (Cfg::lds(h, Cfg::max_steps(h, kvol)) + 1024);
-        const int waves = NW * (int)std::min<int64_t>(cu, std::max(1, std::min(kFit, room)));
-        const double cost = (double)cu * (h + 0.6 + (CC == 64 || NW == 8 ? 50.0 : 30.0) / per) * (1.0 + 7.0 / waves);
-        if (best == 0 || cost < least) {
-            least = cost;
-            best = h;
-        }
-    }
-    return best;
-}
-
-template <int CC, int NW, int G>
-int launch_split(SplitArgs a, int ny, int64_t links, hipStream_t s) {
+int launch_split(const SplitArgs& a, int ny, hipStream_t s) {
     using Cfg = SplitCfg<CC, NW, G>;
     auto kern = gather_split_kernel<CC, NW, G>;
-    a.halves = tile_halves<CC, NW, G>(a.n_rows, ny, a.kvol, links);
-    const int max_steps = Cfg::max_steps(a.halves, a.kvol);
-    const int lds = Cfg::lds(a.halves, max_steps);
+    const int lds = split_lds(CC, NW, G, a.halves, a.kvol);
     {
         static std::mutex mu;
         static int attr_lds = 0;  // largest dynamic LDS size opted into so far
@@ -517,31 +477,6 @@ int launch_split(SplitArgs a, int ny, int64_t links, hipStream_t s) {
 }
 
 }  // namespace
-
-// Slices and channel tiles of a layer: the cut with the least padding.
-SplitShape split_shape(int cc, int co) {
-    SplitShape t{};
-    int best = 1 << 30;
-    for (int c : {64, 32}) {
-        const int n = (cc + c - 1) / c, cost = n * c + 8 * (n - 1);
-        if (cost < best) {
-            best = cost;
-            t.cc = c;
-            t.nsl = n;
-        }
-    }
-    best = 1 << 30;
-    for (int c : {128, 64, 48, 32}) {
-        const int n = (co + c - 1) / c, cost = n * c + 8 * (n - 1);
-        if (cost < best) {
-            best = cost;
-            t.cot = c;
-            t.ny = n;
-        }
-    }
-    return t;
-}
-size_t split_copy_bytes(const SplitShape& t, int kvol) { return (size_t)kvol * t.nsl * t.cc * t.ny * t.cot * 6; }
 
 int conv_gather_split(const MapSide& side, int kvol, int64_t links, const float* d_f, const float* d_w, bool w_transposed, float* d_g, int cc, int co,
                       void* d_ws, hipStream_t s) {
@@ -568,11 +503,14 @@ int conv_gather_split(const MapSide& side, int kvol, int64_t links, const float*
     const int threads = t.ny * kvol * t.nsl * (t.cc / 32) * (t.cot / 16) * 64;
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, d_w, static_cast<u32x4*>(d_ws), kvol,
                        co, cc, a.s_co, a.s_cc, t.ny, t.nsl, t.cc / 32, t.cot / 16);
-    // Links of a step: 32, and 48 for channel tiles of 48 (96 -> 96 212 against 250 us).
+    const SplitTile tile = split_tile(t, side.n_rows, kvol, links);
+    a.halves = tile.halves;
 #define SP_SPLIT(CC, NW, G) \
-    if (t.cc == CC && t.cot == 16 * NW) return launch_split<CC, NW, G>(a, t.ny, links, s)
+    if (t.cc == CC && t.cot == 16 * NW && tile.g == G) return launch_split<CC, NW, G>(a, t.ny, s)
     SP_SPLIT(64, 8, 2);
+    SP_SPLIT(64, 8, 3);
     SP_SPLIT(64, 4, 2);
+    SP_SPLIT(64, 4, 3);
     SP_SPLIT(64, 3, 3);
     SP_SPLIT(64, 2, 2);
     SP_SPLIT(32, 8, 2);

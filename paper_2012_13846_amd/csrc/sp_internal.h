@@ -229,12 +229,7 @@ bool narrow_ok(int cc, int co, int kvol);                                       
 bool narrow_pays(int cc, int co, int kvol, int64_t rows, int64_t links, sp_dtype dt);             // and is faster than the tile kernel
 int conv_narrow(const MapSide& side, int kvol, const void* d_f, const void* d_w, bool w_transposed, void* d_g, int cc, int co, sp_dtype dt,
                 hipStream_t s);
-// fp32 link lists on the bf16 matrix cores (sp_conv_split.hip): slices and channel tiles, bytes of the weights' pieces (d_ws)
-struct SplitShape {
-    int cc, nsl, cot, ny;
-};
-SplitShape split_shape(int cc, int co);
-size_t split_copy_bytes(const SplitShape& t, int kvol);
+// fp32 link lists on the bf16 matrix cores (sp_conv_split.hip); d_ws: split_copy_bytes (sp_split_shape.h) for the weights' pieces
 int conv_gather_split(const MapSide& side, int kvol, int64_t links, const float* d_f, const float* d_w, bool w_transposed, float* d_g,
                       int cc, int co, void* d_ws, hipStream_t s);
 // link lists, any channel counts (sp_conv_tile.h): kc-wide slices of the contraction, ncs * 16 channels and tr rows a workgroup

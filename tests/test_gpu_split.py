@@ -1,4 +1,4 @@
-"""fp32 layers on the bf16 matrix cores (csrc/sp_conv_split.hip): row tiles of 64 and 128, steps of 32 and 48 links, slices and
+"""fp32 layers on the bf16 matrix cores (csrc/sp_conv_split.hip): few and many rows (tiles of every height are test_gpu_split_tiles.py), slices and
 channel tiles that reach past the layer, values that bf16 cannot hold.  Against fp64: the parity bound, and no further off than
 fp32 matrix cores are (measured 1.1e-7 to 2e-7 of the rms for up to 125 * 64 products; 3e-7 allowed)."""
 import numpy as np
@@ -63,8 +63,8 @@ def fwd64(km, x, w):
     return y
 
 
-@pytest.mark.parametrize("n,bits,cin,cout", [(8193, 5, 64, 128), (16257, 5, 64, 128), (1100, 4, 128, 128), (1217, 4, 100, 128),        # 64-row tiles
-                                             (16449, 5, 64, 64), (32769, 6, 32, 64), (16513, 5, 64, 128),                          # .. 128-row tiles
+@pytest.mark.parametrize("n,bits,cin,cout", [(8193, 5, 64, 128), (16257, 5, 64, 128), (1100, 4, 128, 128), (1217, 4, 100, 128),
+                                             (16449, 5, 64, 64), (32769, 6, 32, 64), (16513, 5, 64, 128),
                                              (20000, 5, 100, 128),                                                                 # slices past the last channel
                                              (65536, 5, 96, 96), (65537, 5, 24, 40), (70000, 5, 48, 48), (70001, 5, 36, 100), (66000, 6, 128, 32)])
 def test_rows_slices_and_channel_tiles(sp, n, bits, cin, cout):  # noqa: F811
