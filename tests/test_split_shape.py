@@ -3,6 +3,7 @@ itself uses: every cut has a kernel, its LDS is there, and the heights and steps
 import ctypes
 import functools
 import os
+import re
 import subprocess
 import tempfile
 
@@ -15,9 +16,10 @@ using namespace sp;
 extern "C" void cut(int cc, int co, int64_t n_rows, int kvol, int64_t links, int* out) {
     const SplitShape t = split_shape(cc, co);
     const SplitTile x = split_tile(t, n_rows, kvol, links);
-    const int v[] = {x.halves, x.g, t.cc, t.nsl, t.cot, t.ny, split_lds(t.cc, t.cot / 16, x.g, x.halves, kvol), split_simd_waves(t.cc, t.cot / 16, x.g)};
-    for (int i = 0; i < 8; ++i) out[i] = v[i];
+    const int v[] = {x.halves, x.g, t.cc, t.nsl, t.cot, t.ny, split_lds(t.cc, t.cot / 16, x.g, x.halves, kvol)};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
+extern "C" int waves_of_a_simd(int cc, int nw, int g) { return split_simd_waves(cc, nw, g); }
 """
 KERNELS = {(64, 128, 2), (64, 128, 3), (64, 64, 2), (64, 64, 3), (64, 48, 3), (64, 32, 2), (32, 128, 2), (32, 64, 2), (32, 48, 3), (32, 32, 2)}
 
@@ -35,10 +37,14 @@ def _lib():
 
 
 def cut(cc, co, n_rows, kvol, links):
-    """(halves of 32 rows, blocks of 16 links a step, slice, slices, channel tile, channel tiles, LDS bytes, wavefronts of a SIMD)"""
-    out = (ctypes.c_int * 8)()
+    """(halves of 32 rows, blocks of 16 links a step, slice, slices, channel tile, channel tiles, LDS bytes)"""
+    out = (ctypes.c_int * 7)()
     _lib().cut(cc, co, n_rows, kvol, links, out)
     return tuple(out)
+
+
+def waves_of_a_simd(cc, nw, g):
+    return _lib().waves_of_a_simd(cc, nw, g)
 
 
 def test_every_cut_has_a_kernel_and_fits():
@@ -48,7 +54,7 @@ def test_every_cut_has_a_kernel_and_fits():
             for kvol in (1, 8, 27, 64, 125):
                 for n in (1, 31, 1000, 4097, 16384, 16385, 50000, 131073, 613402, 5000000):
                     for per in (0.2, 1.0, 5.0, 12.0, 33.0, 63.9, 64.0, 128.0):
-                        h, g, c, nsl, cot, ny, lds, _ = cut(cc, co, n, kvol, int(n * kvol * per / 128))
+                        h, g, c, nsl, cot, ny, lds = cut(cc, co, n, kvol, int(n * kvol * per / 128))
                         assert 2 <= h <= 7 and (c, cot, g) in KERNELS
                         assert c * nsl >= cc and cot * ny >= co
                         assert lds <= 163840 - 256        # static LDS beside it: a few words
@@ -65,3 +71,29 @@ def test_measured_choices(cc, co, n, kvol, per, want):
     """Launches whose times stand at split_tile, or that a rule which counts an offset's weights once a tile made 5 to 15 % slower."""
     assert cut(cc, co, n, kvol, round(n * kvol * per / 128))[:2] == want
 
+
+
+def test_registers_leave_the_workgroups_that_the_rule_counts_on():
+    """The built kernels' vector registers (512 a SIMD lane, handed out in eights) and spills, from the metadata of their object file."""
+    obj = os.path.join(os.path.dirname(CSRC), "_build", "sp_conv_split.o")
+    llvm = "/opt/rocm/llvm/bin/"
+    if not os.path.exists(obj) or not os.path.exists(llvm + "llvm-readelf"):
+        pytest.skip("needs the object file of the build and ROCm's binary tools")
+    with tempfile.TemporaryDirectory() as d:
+        fat, code = os.path.join(d, "fat"), os.path.join(d, "code")
+        subprocess.check_call([llvm + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, obj, os.path.join(d, "copy")])
+        subprocess.check_call([llvm + "clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                               "--input=" + fat, "--output=" + code])
+        notes = subprocess.check_output([llvm + "llvm-readelf", "--notes", code], text=True)
+    seen = set()
+    for kernel in notes.split(".agpr_count:")[1:]:
+        m = re.search(r"gather_split_kernelILi(\d+)ELi(\d+)ELi(\d+)E", kernel)
+        if not m:
+            continue
+        cc, nw, g = map(int, m.groups())
+        seen.add((cc, 16 * nw, g))
+        regs = int(kernel.split()[0]) + int(re.search(r"\.vgpr_count: +(\d+)", kernel).group(1))
+        waves = waves_of_a_simd(cc, nw, g)
+        assert (regs + 7) // 8 * 8 * waves <= 512, (cc, nw, g, regs, waves)
+        assert re.search(r"\.vgpr_spill_count: +0\b", kernel)
+    assert seen == KERNELS
