@@ -735,7 +735,8 @@ int conv_gather_tile(const MapSide& side, int kvol, const void* d_f, const void*
 
 namespace {
 // fp32: the split kernel against the one that has the layer otherwise (wave: the wavefront-private one).  Forward in us, before /
-// split, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 160 k, 0.66 M | 213 k, 2.4 M | 613 k, 5.0 M:
+// split, on 1.5 k rows with 9 k links | 23 k, 0.14 M | 96 k, 0.61 M | 160 k, 0.66 M | 213 k, 2.4 M | 613 k, 5.0 M (one kernel's launches
+// back to back, which takes the clock down: with pauses 64 -> 64 on the last takes 618 / 425):
 // (wavefront-private: one wavefront a sub-tile; where four share one, 64 -> 64 takes 20 us on 1.5 k and 22 on 16 k rows, 32 -> 64
 // 14 and 15, 32 k rows 24, the split kernel 25, 29, 20, 24 and 30: share_fits is the line.)
 //   wavefront-private  64 -> 64    56 / 26 | 66 / 38  | 124 / 81  | 180 / 104 | 345 / 250  | 681 / 503

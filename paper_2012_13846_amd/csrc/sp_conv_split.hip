@@ -97,10 +97,11 @@ struct SplitCfg {
 //   - multiplies this step's blocks and adds a block's sums to the accumulator while the next one is multiplied.
 // One barrier a step; every wavefront has the same number of blocks, so none waits long, and where registers and LDS allow it two or more
 // workgroups share a CU (tiles of 128 channels: one; two of 32 -> 128).
-// What bounds it (64 -> 64, 0.6 M rows, 4.8 M links: 425 us alone with the chip cool, 618 on fp32 MFMAs): the L1's data return is
-// busy most of the time (half of it the weights, 24 KB a step), the LDS half, the vector pipes 44 %, the matrix pipes 30 %; two or
-// three wavefronts per SIMD issue in order and wait a third of their time, so what lets a third workgroup in pays: rows asked for two
-// steps ahead instead of four, no padded rows in LDS.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64 channels and meets no barrier
+// What bounds it (64 -> 64, 0.6 M rows, 5 M links: 425 us with pauses between launches, 496 between the other kernels of a training pass,
+// where the clock is lower; 467 with rows asked for four steps ahead, padded rows in LDS and tiles of 128, 618 on fp32 MFMAs): the L1's data
+// return is busy 98 % of the cycles (half of it the weights, 24 KB a step), its addresser 81 %, the LDS 57 %, the vector pipes 51 %, the
+// matrix pipes 35 %; two or three wavefronts per SIMD issue in order and wait a third of their time, so what lets a third workgroup in
+// pays.  Built and dropped: one wavefront per SIMD that owns 128 rows and 64 channels and meets no barrier
 // (weights in 96 or 192 registers, everything dealt out between the MFMAs): 555 against 514 us, since a single wavefront issues one
 // instruction in four cycles of whatever kind.  Requests in front of the blocks instead of between their MFMAs, and fragments read
 // when they are due: 542.
