@@ -58,15 +58,16 @@ struct SplitTile {
 // workgroups share a CU and fill its last round better.  A tile costs, for every offset with mu links in it, its steps (their weights are
 // read again in each; as much as 6 blocks, 7.4 with rows for 48 links) and its blocks of 16, each 0.7 more than mu alone would fill, and
 // little for its rows.  The tiles of the fullest CU add up (some of the last round's start early), and a round of those that share
-// it takes `hide` / wavefronts of a tile more, which more wavefronts hide; of equals the lower one, since surfaces fill tall tiles unevenly
-// (1.5 % a half; 32 -> 64 none above 128 rows: on 0.1 M rows of objects, per 28, H = 2 .. 7: 58, 53, 53, 54, 62, 67).
+// it takes `hide` / wavefronts of a tile more, which more wavefronts hide.  Of equals the lower one, since surfaces fill tall tiles unevenly
+// (1.5 % a half; 32 -> 64 none above 128 rows: on 0.1 M rows of objects, per 28, H = 2 .. 7: 58, 53, 53, 54, 62, 67), and 20 % on tall tiles
+// of several steps an offset that all start together: nothing balances heavy ones that meet on a CU (64 -> 64, 86 k rows of
+// objects, per 27, two tiles a CU: H = 6 90 us, H = 3 66).
 // Steps of 48 links save weights where an offset has more than 32 in a tile, and their rows take registers: 64 -> 64 has two such
 // workgroups on a CU against three.  Tiles of 128 channels lose no workgroup by them, but time where few links fill the step, and gain
 // from about 64 links of an offset in 128 rows (per) on: 96 k rows, per 89, 128 -> 128 467 / 431 us, 64 -> 128 241 / 225; per 12 0.83 times as fast.
 // Over 1571 launches (objects, spheres, rooms in sampling order, random clouds, full cubes; K = 2, 3, 5, strides 1 and 2; 14 k to 0.6 M rows,
-// per 5 to 120) this takes 1.8 % longer than the best of all heights and both steps (32 -> 128 5 %: no steps of 48), tiles of 128 rows (64
-// where those were fewer than 128) with steps of 32 or 48 by per 18 %, a rule that counted an offset's weights once a tile 2.6 %.  What it
-// gets most wrong are few tall tiles whose heavy ones meet on a CU (64 -> 64, 86 k rows, per 27: H = 6, 90 us, with H = 3 66).
+// per 5 to 120) this takes 1.7 % longer than the best of all heights and both steps (32 -> 128 5 %: no steps of 48), tiles of 128 rows (64
+// where those were fewer than 128) with steps of 32 or 48 by per 18 %, a rule that counted an offset's weights once a tile 2.6 %.
 // H = halves of 32 rows, us, steps of 32 / 48:
 //   64 -> 64     0.61 M rows of objects, per 39, H = 2 .. 6: 486, 425, 476, 464, 451 / 638, 489, 441, 628, 624
 //                0.14 M, per 38: 121, 109, 125, 119, 131 / 152, 121, 116, 160, 157;   96 k, random, per 89: 150, 150, 151, 182, 142 / 140, 146, 140, 225, 170
@@ -94,7 +95,8 @@ inline SplitTile split_tile(const SplitShape& t, int64_t n_rows, int kvol, int64
             const double one = (double)t.nsl * kvol * ((g == 2 ? 6.0 : 7.4) * steps + blocks) + h;
             const double cu = std::max(1.0, 0.7 * (double)fullest + 0.3 * ((double)tiles / 256.0 + 0.5)), share = cu / there;
             const double rounds = share > 2.0 ? share : 0.7 * (double)((fullest + there - 1) / there) + 0.3 * std::max(1.0, share);
-            const double cost = one * (cu + hide / nw * rounds) * (1.0 + 0.015 * h);
+            const double uneven = g == 2 && nw < 8 && h >= 5 && mu > 32.0 && fullest <= there ? 1.2 : 1.0;
+            const double cost = one * (cu + hide / nw * rounds) * (1.0 + 0.015 * h) * uneven;
             if (best.g == 0 || cost < least) {
                 least = cost;
                 best = SplitTile{h, g};

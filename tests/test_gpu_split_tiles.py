@@ -21,9 +21,9 @@ def near(got, want, kvol=27):
 HEIGHTS = {
     (64, 128): [(12033, 5, 2, 2), (16417, 5, 3, 2), (114721, 5, 3, 3), (24577, 5, 4, 2), (32801, 5, 5, 2), (69761, 5, 5, 3), (41089, 5, 6, 2),
                 (81985, 5, 6, 3), (49281, 5, 7, 2), (98337, 5, 7, 3)],
-    (64, 192): [(16321, 5, 2, 2), (12001, 5, 3, 2), (16385, 5, 4, 2), (40961, 5, 4, 3), (24641, 5, 5, 2), (27265, 5, 6, 2)],
+    (64, 192): [(16321, 5, 2, 2), (12001, 5, 3, 2), (16385, 5, 4, 2), (40961, 5, 4, 3), (24641, 5, 5, 2), (13633, 6, 6, 2)],
     (20, 128): [(1473, 4, 2, 2), (16417, 5, 3, 2), (24577, 6, 4, 2), (32801, 6, 5, 2), (41089, 6, 6, 2), (49281, 5, 7, 2)],
-    (64, 64): [(34049, 5, 2, 2), (65569, 5, 3, 2), (49153, 6, 4, 2), (49153, 5, 4, 3), (73761, 5, 5, 2), (41089, 6, 6, 2), (49281, 7, 7, 2)],
+    (64, 64): [(34049, 5, 2, 2), (65569, 5, 3, 2), (49153, 6, 4, 2), (49153, 5, 4, 3), (34081, 6, 5, 2), (41089, 6, 6, 2), (49281, 7, 7, 2)],
     (32, 64): [(34049, 5, 2, 2), (65569, 5, 3, 2), (49153, 6, 4, 2)],
     (128, 32): [(49153, 5, 2, 2), (65569, 5, 3, 2), (49153, 6, 4, 2), (98401, 6, 5, 2)],
     (48, 48): [(98305, 5, 3, 3), (49153, 5, 4, 3), (65601, 5, 5, 3), (81985, 5, 6, 3)],
@@ -41,7 +41,7 @@ def test_heights(sp, cin, cout, n, bits, halves, g):  # noqa: F811
     assert near(sp.sp_conv_bwd_data(km, x, w.transpose(1, 2).contiguous()), fwd64(km, x, w.flip(0)))
 
 
-@pytest.mark.parametrize("n,bits,K,stride,cin,cout,direction", [(50000, 5, 5, 1, 64, 128, 0), (100000, 6, 5, 1, 64, 128, 0), (96000, 6, 2, 1, 64, 64, 0),
+@pytest.mark.parametrize("n,bits,K,stride,cin,cout,direction", [(50000, 5, 5, 1, 64, 128, 0), (100000, 6, 5, 1, 64, 128, 0), (96000, 6, 2, 1, 64, 128, 0),
     (90000, 6, 4, 1, 128, 128, 0), (90000, 6, 4, 2, 64, 64, 1), (100000, 6, 3, 2, 128, 128, 0), (100000, 6, 3, 2, 64, 64, 1), (160000, 7, 2, 2, 128, 128, 1)])
 def test_tall_tiles_of_other_maps(sp, n, bits, K, stride, cin, cout, direction):  # noqa: F811
     """160 rows and more with 8, 64 and 125 offsets and on both sides of strided maps; a row with an infinity makes the tiles it reaches
