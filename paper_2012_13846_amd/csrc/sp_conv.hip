@@ -751,8 +751,9 @@ namespace {
 //                      48 -> 48    24 / 28 | 30 / 36  | 77 / 73   | 100 / 109 | 224 / 199  | 465 / 407
 // The line between few and many rows (links of an offset in 128 rows: per):  50 k rows, per 49: 48 -> 48 76 / 65, 128 -> 64 213 / 129,
 // 24 -> 40 47 / 48; 55 k, per 63: 48 -> 48 84 / 77, 128 -> 32 195 / 100, 24 -> 40 51 / 53; 48 -> 48, 96 k rows, per 30: 77 / 73, per 19:
-// 105 / 109.  Padded ones of two channel tiles not yet there (48 -> 80, 50 k, per 49: 111 / 116, 64 k, per 61: 136 / 142); tiles of 128 channels
-// gain on both sides of it with few links too (48 -> 128, 50 k, per 10: 91 / 61; 60 k, per 12: 91 / 60, 36 -> 100 the same).
+// 105 / 109.  Padded ones of two channel tiles with more links (48 -> 80, 50 k to 62 k rows, split over tile kernel: per 25 0.93, per 28 0.96,
+// per 31 0.98 to 1.04, per 46 to 69 0.97 to 1.12); tiles of 128 channels gain on both sides of it with few links too (48 -> 128, 50 k,
+// per 10: 91 / 61; 60 k, per 12: 91 / 60, 36 -> 100 the same).
 // Channel tiles of 32 leave its wavefronts too little to do per row: not in place of the wavefront-private kernel, and of the tile
 // kernel only on large sets.  What the tile kernel pads a third less (48 channels, which are 64 here) only where many links share a
 // read of the weights.  A read serves the links of one offset in a tile, padded to steps of 32 or 48: where a tile of 128 rows has few
@@ -779,8 +780,9 @@ bool split_pays(const MapSide& side, int kvol, int64_t links, int cc, int co, bo
     if (t.cot == 32 && t.nsl > o.nsl) return false;
     const double per = (double)links * 128.0 / ((double)side.n_rows * kvol);
     const bool padded = 10 * (int64_t)t.cc * t.nsl * t.cot * t.ny > 13 * (int64_t)o.kc * o.nsl * 16 * o.ncs * o.ny;
-    const bool many_rows = side.n_rows >= (t.cc == 32 || t.cot == 128 || (padded && t.ny > 1) ? 65536 : 49152);
-    if (padded && (t.cot == 32 || ((per < (many_rows ? 26.0 : 40.0) || kvol == 1) && (side.n_rows <= 16384 || many_rows)))) return false;
+    const bool many_rows = side.n_rows >= (t.cc == 32 || t.cot == 128 ? 65536 : 49152);
+    const double enough = !many_rows ? 40.0 : t.ny > 1 && side.n_rows < 65536 ? 31.0 : 26.0;
+    if (padded && (t.cot == 32 || ((per < enough || kvol == 1) && (side.n_rows <= 16384 || many_rows)))) return false;
     if (!many_rows) return t.cot == 128 && per >= 6.0;
     return per >= (t.cot == 48 ? 20.0 : t.cot == 64 && t.cc == 32 ? 14.0 : 6.0);
 }

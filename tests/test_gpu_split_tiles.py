@@ -76,8 +76,8 @@ def test_tall_tiles_of_other_maps(sp, n, bits, K, stride, cin, cout, direction):
 @pytest.mark.parametrize("n,bits,cin,cout,kernel", [(49151, 5, 48, 48, "tile"), (49152, 5, 48, 48, "split"), (56000, 5, 24, 40, "tile"),
                                                     (60000, 5, 40, 24, "tile"), (50000, 5, 128, 32, "split"), (100000, 6, 48, 48, "tile"),
                                                     (200000, 6, 48, 48, "split"), (49152, 6, 48, 128, "split"), (60000, 6, 36, 100, "split"),
-                                                    (65535, 6, 40, 256, "split"), (65536, 6, 48, 128, "tile"), (65535, 5, 48, 80, "tile"),
-                                                    (65536, 5, 48, 80, "split")])
+                                                    (65535, 6, 40, 256, "split"), (65536, 6, 48, 128, "tile"), (49151, 5, 48, 80, "tile"),
+                                                    (49152, 5, 48, 80, "split"), (60000, 6, 48, 80, "tile"), (65536, 5, 48, 80, "split")])
 def test_lines(sp, n, bits, cin, cout, kernel):  # noqa: F811
     """Both sides of the lines between this kernel and the tile kernel: rows, and links of an offset a tile (16 and 27); layers that it
     pads, of one and two channel tiles and of tiles of 128 channels, which have the line of 64 k rows."""
