@@ -41,10 +41,10 @@ def test_heights(sp, cin, cout, n, bits, halves, g):  # noqa: F811
     assert near(sp.sp_conv_bwd_data(km, x, w.transpose(1, 2).contiguous()), fwd64(km, x, w.flip(0)))
 
 
-@pytest.mark.parametrize("n,bits,K,stride,cin,cout,direction", [(50000, 5, 5, 1, 64, 128, 0), (100000, 6, 5, 1, 64, 128, 0), (96000, 6, 2, 1, 64, 128, 0),
+@pytest.mark.parametrize("n,bits,K,stride,cin,cout,direction", [(50000, 5, 5, 1, 64, 128, 0), (98337, 5, 5, 1, 64, 128, 0), (100000, 6, 5, 1, 64, 128, 0), (96000, 6, 2, 1, 64, 128, 0),
     (90000, 6, 4, 1, 128, 128, 0), (90000, 6, 4, 2, 64, 64, 1), (100000, 6, 3, 2, 128, 128, 0), (100000, 6, 3, 2, 64, 64, 1), (160000, 7, 2, 2, 128, 128, 1)])
 def test_tall_tiles_of_other_maps(sp, n, bits, K, stride, cin, cout, direction):  # noqa: F811
-    """160 rows and more with 8, 64 and 125 offsets and on both sides of strided maps; a row with an infinity makes the tiles it reaches
+    """160 rows and more with 8, 64 and 125 offsets (the second case: 161 048 bytes of LDS, the most there are) and on both sides of strided maps; a row with an infinity makes the tiles it reaches
     compute theirs again."""
     c, _, gen = cloud(sp, n, bits, n + K)
     km, _ = sp.sp_kmap_build(c, K, stride, 1)
